@@ -1,4 +1,5 @@
-"""Builds libogq.so (HIP kernels + C ABI) for gfx950 with hipcc.  Run: python -m paper_2002_11082_amd.build
+"""Builds libogq.so (HIP kernels + C ABI) for gfx950 with hipcc, and _marshal.so (the extension module that hands torch
+tensors to it) with g++.  Run: python -m paper_2002_11082_amd.build
 
 The library is compiled as several object files in parallel (the random-rounding kernels once per bucket
 capacity) and linked into one shared library.
@@ -10,12 +11,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libogq.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17",
@@ -41,7 +44,17 @@ def _run(cmd, verbose):
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed: " + " ".join(cmd))
+        raise RuntimeError("compiler failed: " + " ".join(cmd))
+
+
+def _marshal_command():
+    import torch
+    at = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
+            "-isystem", os.path.join(at, "include"), "-I" + sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "torch_marshal.cpp"), "-o", MARSHAL, "-L" + os.path.join(at, "lib"), "-ltorch_python",
+            "-ltorch_cpu", "-lc10"]
 
 
 def build(verbose: bool = False, jobs: int = 0) -> str:
@@ -56,6 +69,7 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
             out = os.path.join(OBJ, obj)
             objects.append(out)
             futures.append(pool.submit(_run, [hipcc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", out], verbose))
+        futures.append(pool.submit(_run, _marshal_command(), verbose))
         for f in futures:
             f.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objects, "-o", LIB], verbose)
