@@ -145,9 +145,10 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t x, uint32_t lane)
 
 // Gradient clipping of a register-resident bucket (Section 5): v <- sign(v) * min(|v|, c * sigma) with
 // sigma^2 the population variance about the bucket mean, both in fp64.  valid(j) tells whether
-// register j of this lane holds a bucket element; bucket_sum(x) adds x over all lanes that hold the bucket.
+// register j of this lane holds a bucket element; bucket_sum(x) adds x over all lanes that hold the bucket.  Returns
+// the threshold.
 template <int N, class ValidFn, class SumFn>
-__device__ __forceinline__ void clip_in_registers(float (&v)[N], uint32_t len, float c, ValidFn valid, SumFn bucket_sum)
+__device__ __forceinline__ float clip_in_registers(float (&v)[N], uint32_t len, float c, ValidFn valid, SumFn bucket_sum)
 {
     double part = 0.0;
 #pragma unroll
@@ -163,12 +164,13 @@ __device__ __forceinline__ void clip_in_registers(float (&v)[N], uint32_t len, f
     const float limit = (float)((double)c * sigma);
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j] = fminf(fmaxf(v[j], -limit), limit);
+    return limit;
 }
 
 template <int N, class ValidFn>
-__device__ __forceinline__ void clip_in_registers(float (&v)[N], uint32_t len, float c, ValidFn valid)
+__device__ __forceinline__ float clip_in_registers(float (&v)[N], uint32_t len, float c, ValidFn valid)
 {
-    clip_in_registers<N>(v, len, c, valid, [](double x) { return wave_sum(x); });
+    return clip_in_registers<N>(v, len, c, valid, [](double x) { return wave_sum(x); });
 }
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }

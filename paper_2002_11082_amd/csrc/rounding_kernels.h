@@ -36,6 +36,35 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     r[0] = c0; r[1] = c1; r[2] = c2; r[3] = c3;
 }
 
+// The same where c1 is wave-uniform: the first two rounds are then partly scalar (one product and one exclusive or of
+// each; written out because the compiler takes the scalar product for a vector one).
+__device__ __forceinline__ void philox4x32_10_uniform_c1(uint32_t c0, uint32_t c1, uint32_t k0, uint32_t k1, uint32_t (&r)[4])
+{
+    constexpr uint32_t kMulA = 0xD2511F53u, kMulB = 0xCD9E8D57u, kWeylA = 0x9E3779B9u, kWeylB = 0xBB67AE85u;
+    const uint64_t pa = (uint64_t)kMulA * c0;                    // round 1: c2 = c3 = 0
+    const uint64_t qa = (uint64_t)kMulA * uniform_u32(c1 ^ k0);  // round 2, the product of the uniform word
+    const uint64_t qb = (uint64_t)kMulB * ((uint32_t)(pa >> 32) ^ k1);
+    uint32_t x0 = (uint32_t)(qb >> 32) ^ (k0 + kWeylA), x1 = (uint32_t)qb;
+    uint32_t x2 = (uint32_t)pa ^ uniform_u32((uint32_t)(qa >> 32) ^ (k1 + kWeylB)), x3 = uniform_u32((uint32_t)qa);
+    k0 += 2u * kWeylA;
+    k1 += 2u * kWeylB;
+#pragma unroll
+    for (int round = 2; round < 10; ++round) {
+        const uint64_t ra = (uint64_t)kMulA * x0, rb = (uint64_t)kMulB * x2;
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(rb >> 32), x1, k0, 0x96);
+        // (round 2: x3 and the key are both uniform)
+        const uint32_t n2 = round == 2 ? (uint32_t)(ra >> 32) ^ uniform_u32(x3 ^ k1)
+                                       : __builtin_amdgcn_bitop3_b32((uint32_t)(ra >> 32), x3, k1, 0x96);
+        x1 = (uint32_t)rb;
+        x3 = (uint32_t)ra;
+        x0 = n0;
+        x2 = n2;
+        k0 += kWeylA;
+        k1 += kWeylB;
+    }
+    r[0] = x0; r[1] = x1; r[2] = x2; r[3] = x3;
+}
+
 // ----------------------------------------------------------------------------------------------
 // ORQ quantize.  One wavefront (= one workgroup) owns one bucket.  Lane l holds, for chunk c, the
 // four consecutive bucket elements 256*c + 4*l + {0,1,2,3} (one 16-byte load), which are also the
@@ -648,86 +677,276 @@ __device__ __forceinline__ void for_each_chunk(uint32_t len, F f)
 }
 
 // ---- encode (random rounding, Section 3.1) + pack ------------------------------------------------
-// v: the 256*C elements a wavefront holds (lane l, chunk c: elements 256c + 4l + {0..3} of the range that
-// starts at global element `begin` and has `len` valid elements; FULL: len == 256*C); lv: the levels.
-template <int C, int S, int BITS, bool FULL>
-__device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
-                                           uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32)
+// Interval of an element among S levels: the last level not above it, at most S - 2.  base = that level, width = the next
+// one minus it (fp32, one rounding), bit[p] = lanes whose interval index has bit p set.  Up to four levels one compare per
+// interior level; from five levels on a binary search, whose compare masks are the index bits: with eight levels 13
+// vector instructions per element instead of the 18 of one compare and two selects per interior level, with nine 14
+// instead of 21.
+template <int S>
+struct Interval {
+    static constexpr int kIndexBits = S == 2 ? 0 : S == 3 ? 1 : S <= 5 ? 2 : 3;
+    float base, width;
+    uint64_t bit[3];
+};
+
+template <int S>
+__device__ __forceinline__ Interval<S> find_interval(float x, const float (&lv)[S], const float (&width)[S - 1])
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    // Per element only the level compares, the selects of (level below, interval width) and the rounding
-    // test run on the vector unit; the level index is assembled from the compare masks on the scalar unit
-    // (the masks are a thermometer code of the interval, to which the rounding bit is added with carry).
-    float width[S - 1];
+    static_assert((S >= 2 && S <= 5) || S == 8 || S == 9, "level counts of the schemes");
+    Interval<S> r;
+    if constexpr (S <= 4) {
+        r.base = lv[0];
+        r.width = width[0];
+        uint64_t not_below[3] = {0, 0, 0};  // [t]: lanes whose element is not below level t, t = 1 .. S - 2
 #pragma unroll
-    for (int k = 0; k < S - 1; ++k) width[k] = lv[k + 1] - lv[k];
-    uint32_t bit_of[4];  // where element k of this lane sits in its 32-bit half of a packed word
-#pragma unroll
-    for (int k = 0; k < 4; ++k) bit_of[k] = 1u << (4u * (lane & 7u) + k);
-    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-    const uint32_t padded_len = (len + 63u) & ~63u;
-    const size_t word0 = begin / 64;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        constexpr bool ALL = FULL;
-        if constexpr (!FULL) {
-            if (256u * (uint32_t)c >= len) continue;  // nothing of the bucket in this chunk: no words to write
+        for (int t = 1; t < S - 1; ++t) {
+            const bool ge = lv[t] <= x;
+            not_below[t] = __ballot(ge);
+            r.base = ge ? lv[t] : r.base;
+            r.width = ge ? width[t] : r.width;
         }
-        const uint64_t block = (index_offset + begin + 256u * c + 4u * lane) >> 2;
+        r.bit[0] = not_below[1] ^ not_below[2];
+        r.bit[1] = not_below[2];
+    } else if constexpr (S == 5) {
+        const bool m1 = lv[2] <= x;
+        const float t = m1 ? lv[3] : lv[1];
+        const bool m0 = t <= x;
+        const float low = m1 ? lv[2] : lv[0], high = m1 ? lv[4] : lv[2];
+        r.base = m0 ? t : low;
+        r.width = (m0 ? high : t) - r.base;
+        r.bit[0] = __ballot(m0);
+        r.bit[1] = __ballot(m1);
+    } else {
+        const bool m2 = lv[4] <= x;
+        const float t1 = m2 ? lv[6] : lv[2];
+        const bool m1 = t1 <= x;
+        const float low7 = m2 ? lv[7] : lv[3], low5 = m2 ? lv[5] : lv[1];
+        const float t0 = m1 ? low7 : low5;
+        r.bit[2] = __ballot(m2);
+        r.bit[1] = __ballot(m1);
+        r.bit[0] = __ballot(t0 <= x);
+        if constexpr (S == 8) r.bit[0] &= ~(r.bit[1] & r.bit[2]);  // the top level begins no interval
+        const bool m0 = __builtin_amdgcn_inverse_ballot_w64(r.bit[0]);
+        const float low = m2 ? lv[4] : lv[0];
+        const float even = m1 ? t1 : low;
+        const float next_of_3 = S == 9 ? (m2 ? lv[S - 1] : lv[4]) : lv[4];
+        const float next = m1 ? next_of_3 : t1;
+        r.base = m0 ? t0 : even;
+        r.width = (m0 ? next : t0) - r.base;
+    }
+    return r;
+}
+
+// 2 x + (1 in the lanes of `mask`), as one add with carry (the compiler makes a select and a shift-and-or of it).
+// RAW: the mask comes straight from a vector compare, which needs two wait states before a vector instruction reads it
+// (the compiler does not look into the asm); a mask computed on the scalar unit needs none.
+template <bool RAW>
+__device__ __forceinline__ uint32_t push_bit(uint32_t x, uint64_t mask)
+{
+    uint32_t r;
+    uint64_t carry_out;
+    if constexpr (RAW) asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry_out) : "v"(x), "s"(mask));
+    else asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry_out) : "v"(x), "s"(mask));
+    return r;
+}
+
+// 8 x 8 transpose of nibbles inside every group of 8 lanes: lane i's nibble c and lane c's nibble i trade places.  Three
+// butterfly steps; those that move whole bytes are one cross-lane move and one byte permute.
+struct NibbleTranspose {
+    uint32_t swap16, swap8;  // byte selectors of the steps over lane bits 2 and 1
+    uint32_t take, turn;     // the step over lane bit 0: nibbles taken from the partner, right rotation that places them
+};
+
+__device__ __forceinline__ NibbleTranspose nibble_transpose_setup(uint32_t lane)
+{
+    // the lower lane of a pair keeps its low blocks and takes the partner's low blocks as its high blocks, the upper lane
+    // keeps its high blocks and takes the partner's high blocks as its low blocks (bytes 0 .. 3: own, 4 .. 7: partner's)
+    NibbleTranspose t;
+    t.swap16 = (lane & 4u) ? 0x03020706u : 0x05040100u;
+    t.swap8 = (lane & 2u) ? 0x03070105u : 0x06020400u;
+    t.take = (lane & 1u) ? 0x0F0F0F0Fu : 0xF0F0F0F0u;
+    t.turn = (lane & 1u) ? 4u : 28u;
+    return t;
+}
+
+__device__ __forceinline__ uint32_t nibble_transpose(uint32_t x, const NibbleTranspose& t, uint32_t lane)
+{
+    x = __builtin_amdgcn_perm(lane_xor<4>(x, lane), x, t.swap16);
+    x = __builtin_amdgcn_perm(lane_xor<2>(x, lane), x, t.swap8);
+    const uint32_t y = lane_xor<1>(x, lane);
+    // take ? turned : x, bit by bit, in one instruction (v_bitop3_b32, truth table 0xCA)
+    return __builtin_amdgcn_bitop3_b32(t.take, __builtin_amdgcn_alignbit(y, y, t.turn), x, 0xCA);
+}
+
+// What the encoder needs to know about the range of elements a wavefront encodes.
+struct EncodeRange {
+    uint32_t len;        // valid elements
+    uint64_t block;      // Philox block of the first one (a multiple of 16)
+    uint32_t k0, k1;     // Philox key
+    uint32_t* words;     // the first one's packed words
+};
+
+// Levels up to which the rounding test takes its width already multiplied by 2^-24 (above, the width is a difference of
+// two selected levels, see find_interval).
+constexpr int kScaledWidthLevels = 4;
+
+// Encodes and packs chunks c0 .. c0 + GROUP - 1 of the range (256 elements each, lane l: elements 256c + 4l + {0..3}).
+// CAREFUL: valid for every width and Philox block; otherwise encode_is_plain() holds.
+template <int GROUP, int S, int BITS, bool FULL, bool CAREFUL>
+__device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (&lv)[S], const float (&width)[S - 1], uint32_t c0,
+                                              const EncodeRange& range, const NibbleTranspose& transpose, uint32_t lane)
+{
+    constexpr bool SCALED = !CAREFUL && S <= kScaledWidthLevels;
+    constexpr int PLANES = 8 / GROUP;                // planes that share a register for the transpose
+    constexpr int REGS = (BITS + PLANES - 1) / PLANES;
+    const uint32_t len = range.len;
+    uint32_t plane[BITS];
+#pragma unroll
+    for (int p = 0; p < BITS; ++p) plane[p] = 0;
+#pragma unroll
+    for (int i = GROUP - 1; i >= 0; --i) {
+        const uint32_t c = c0 + (uint32_t)i;
+        if constexpr (!FULL) {
+            if (256u * c >= len) continue;
+        }
         uint32_t r[4];
-        philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), k0, k1, r);
-        uint32_t plane[BITS];
+        if constexpr (CAREFUL) {
+            const uint64_t block = range.block + 64u * c + lane;
+            philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), range.k0, range.k1, r);
+        } else {
+            philox4x32_10_uniform_c1((uint32_t)range.block + lane + 64u * c, (uint32_t)(range.block >> 32), range.k0, range.k1, r);
+        }
 #pragma unroll
-        for (int p = 0; p < BITS; ++p) plane[p] = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float x = v[c][k];
-            // interval: last level not above x, at most S-2
-            uint64_t not_below[S];  // [t]: lanes whose element is >= level t, t = 1 .. S-2
-            float base = lv[0], w = width[0];
-#pragma unroll
-            for (int t = 1; t < S - 1; ++t) {
-                const bool ge = lv[t] <= x;
-                not_below[t] = __ballot(ge);
-                base = ge ? lv[t] : base;
-                w = ge ? width[t] : w;
-            }
-            const float delta = x - base;
-            const float u = (float)(r[k] >> 8) * 0x1p-24f;
-            const float scaled = u * w;
+        for (int k = 3; k >= 0; --k) {
+            const float x = v[i][k];
+            const Interval<S> in = find_interval<S>(x, lv, width);
+            const float delta = x - in.base;
+            // u * width in fp32, u = the draw's upper 24 bits times 2^-24 (the factor is in the width where that is exact)
+            const float draw = SCALED ? (float)(r[k] >> 8) : (float)(r[k] >> 8) * 0x1p-24f;
+            const float scaled = draw * in.width;
             uint64_t carry = __ballot(scaled < delta);  // rounded up
-            if constexpr (!ALL) carry &= __ballot(256u * c + 4u * lane + k < len);
+            uint64_t valid = ~0ull;
+            if constexpr (!FULL) {
+                valid = __ballot(256u * c + 4u * lane + k < len);
+                carry &= valid;
+            }
 #pragma unroll
             for (int p = 0; p < BITS; ++p) {
-                // bit p of the number of levels 1..S-2 not above x
-                uint64_t index_bit = 0;
-#pragma unroll
-                for (int j = 1; (j << p) <= S - 2; j += 2) {
-                    const int lo_t = j << p, hi_t = (j + 1) << p;
-                    index_bit |= hi_t <= S - 2 ? (not_below[lo_t] & ~not_below[hi_t]) : not_below[lo_t];
-                }
-                if constexpr (!ALL) index_bit &= __ballot(256u * c + 4u * lane + k < len);
-                const uint64_t code_bit = index_bit ^ carry;
+                const uint64_t index_bit = p < Interval<S>::kIndexBits ? in.bit[p < 3 ? p : 0] & valid : 0ull;
+                plane[p] = push_bit<S == 2>(plane[p], index_bit ^ carry);
                 carry &= index_bit;
-                plane[p] |= __builtin_amdgcn_inverse_ballot_w64(code_bit) ? bit_of[k] : 0u;
-            }
-        }
-        // OR over the 8 lanes that make up one 32-bit half of a packed word
-#pragma unroll
-        for (int p = 0; p < BITS; ++p) {
-            uint32_t x = plane[p];
-            x |= dpp_u32<kDppXor1>(x);
-            x |= dpp_u32<kDppXor2>(x);
-            x |= dpp_u32<kDppHalfMirror>(x);
-            const uint32_t first = 256u * c + 32u * (lane >> 3);  // first element of this half word
-            if ((lane & 7u) == 0 && first < padded_len) {
-                const size_t word = (word0 + 4u * c + (lane >> 4)) * BITS + p;
-                codes32[word * 2 + ((lane >> 3) & 1u)] = x;
             }
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (GROUP == 1) {
+        // a single chunk: the 8 lanes of a half word or their nibbles together, and lane p of them stores plane p
+        const uint32_t j = lane & 7u, h = lane >> 3;
+        uint32_t mine = 0;
+#pragma unroll
+        for (int p = 0; p < BITS; ++p) {
+            uint32_t x = plane[p] << (4u * j);
+            x |= dpp_u32<kDppXor1>(x);
+            x |= dpp_u32<kDppXor2>(x);
+            x |= dpp_u32<kDppHalfMirror>(x);
+            mine = p == 0 || j == (uint32_t)p ? x : mine;
+        }
+        if (j < (uint32_t)BITS && (FULL || 256u * c0 + 32u * h < ((len + 63u) & ~63u)))
+            range.words[((4u * c0 + (h >> 1)) * (uint32_t)BITS + j) * 2u + (h & 1u)] = mine;
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < REGS; ++q) {
+        uint32_t x = plane[q * PLANES];
+#pragma unroll
+        for (int i = 1; i < PLANES; ++i)
+            if (q * PLANES + i < BITS) x |= plane[q * PLANES + i < BITS ? q * PLANES + i : 0] << (4 * GROUP * i);
+        x = nibble_transpose(x, transpose, lane);
+        // lane 8 h + j now holds half word h (32 elements) of chunk c0 + j % GROUP of plane q * PLANES + j / GROUP
+        const uint32_t j = lane & 7u, h = lane >> 3;
+        const uint32_t c = c0 + (j & (uint32_t)(GROUP - 1)), p = (uint32_t)(q * PLANES) + j / (uint32_t)GROUP;
+        const bool exists =
+            (BITS % PLANES == 0 || p < (uint32_t)BITS) && (FULL || 256u * c + 32u * h < ((len + 63u) & ~63u));
+        if (exists) range.words[((4u * c + (h >> 1)) * (uint32_t)BITS + p) * 2u + (h & 1u)] = x;
+    }
 }
+
+// Whether the lean form of encode_chunks may be used: all of the range's Philox blocks share the upper counter word, and
+// (where the widths are scaled) no width is so small that width * 2^-24 rounds.  Both hold for all but a few buckets
+// that one meets in earnest.
+template <int CHUNKS, int S>
+__device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], const EncodeRange& range)
+{
+    bool plain = (uint32_t)range.block <= 0xFFFFFFFFu - 64u * CHUNKS;
+    if constexpr (S <= kScaledWidthLevels) {
+        uint32_t smallest = 0xFFFFFFFFu;  // of the bit patterns minus 1: a width of 0 comes out largest
+#pragma unroll
+        for (int k = 0; k < S - 1; ++k) smallest = umin32(smallest, __float_as_uint(width[k]) - 1u);
+        plain = plain && __ballot(smallest < __float_as_uint(0x1p-102f) - 1u) == 0;
+    }
+    return plain;
+}
+
+// v: the 256*C elements a wavefront holds (lane l, chunk c: elements 256c + 4l + {0..3} of the range that
+// starts at global element `begin` and has `len` valid elements; FULL: len == 256*C); lv: the levels.
+// reload(c, y) fetches the lane's four elements of chunk c once more.
+//
+// Bound by vector-instruction issue: Philox takes 9.5 instructions per element, the rounding test 5 or 6, the interval
+// 0 .. 14 (find_interval).  The level index is assembled from the compare masks on the scalar unit.  Every bit plane keeps
+// one register for up to 8 chunks: the elements are taken in descending order and each shifts its bit in (one
+// instruction), so nibble c of lane l ends up holding the bits of this lane's four elements of chunk c.  One nibble
+// transpose among 8 lanes then leaves 32 consecutive bits of a packed word in every lane, stored with one instruction
+// for 8 chunks.  (Before: a select and an or per element and plane, then three cross-lane ors and a store by one lane
+// in eight per chunk and plane.)  The rare range that encode_is_plain() refuses is encoded chunk by chunk in a loop.
+template <int C, int S, int BITS, bool FULL, class ReloadFn>
+__device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
+                                           uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32, ReloadFn reload)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    float width[S - 1];
+#pragma unroll
+    for (int k = 0; k < S - 1; ++k) width[k] = lv[k + 1] - lv[k];
+    const EncodeRange range{len, (index_offset + begin) >> 2, (uint32_t)seed, (uint32_t)(seed >> 32),
+                            codes32 + begin / 64 * (2 * BITS)};
+    const NibbleTranspose transpose = nibble_transpose_setup(lane);
+    if (!encode_is_plain<C, S>(width, range)) {
+#pragma unroll 1
+        for (uint32_t c = 0; 256u * c < len; ++c) {
+            float y[1][4];
+            reload(c, y[0]);
+            encode_chunks<1, S, BITS, false, true>(y, lv, width, c, range, transpose, lane);
+        }
+        return;
+    }
+    if constexpr (S <= kScaledWidthLevels) {
+#pragma unroll
+        for (int k = 0; k < S - 1; ++k) width[k] *= 0x1p-24f;
+    }
+    constexpr int GROUP = C < 8 ? C : 8;
+#pragma unroll
+    for (int c0 = C - GROUP; c0 >= 0; c0 -= GROUP) {
+        if constexpr (!FULL) {
+            if (256u * (uint32_t)c0 >= len) continue;  // nothing of the bucket in these chunks: no words to write
+        }
+        encode_chunks<GROUP, S, BITS, FULL, false>(&v[c0], lv, width, (uint32_t)c0, range, transpose, lane);
+    }
+}
+
+// The reload function of orq_encode for a range in memory: g = its first element; limit = the clipping threshold
+// (infinity: none).
+struct ReloadFromMemory {
+    const float* g;
+    uint32_t len;
+    float limit;
+    __device__ __forceinline__ void operator()(uint32_t c, float (&y)[4]) const
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t e = 256u * c + 4u * (threadIdx.x & 63u) + (uint32_t)k;
+            y[k] = e < len ? fminf(fmaxf(g[e], -limit), limit) : 0.0f;
+        }
+    }
+};
 
 // Whether the bucket holds a non-zero element more than safe_binades(capacity) binades below its largest magnitude
 // (mag_max = its bit pattern), i.e. whether its fp64 sums may round.  Such elements sit in the bins next to zero: the
@@ -1250,9 +1469,10 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
             }
     }
 
+    float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if constexpr (CLIP) {
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
-        clip_in_registers<4 * C>(flat, len, clip, [&](int j) { return full || (64u * (j & ~3) + 4u * lane + (j & 3) < len); });
+        limit = clip_in_registers<4 * C>(flat, len, clip, [&](int j) { return full || (64u * (j & ~3) + 4u * lane + (j & 3) < len); });
     }
 
     // ---- extremes ------------------------------------------------------------------------------
@@ -1426,7 +1646,7 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
         for (int k = 0; k < S; ++k) levels[(size_t)bucket * S + k] = lv[k];
     }
 
-    orq_encode<C, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32);
+    orq_encode<C, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32, ReloadFromMemory{g, len, limit});
 }
 
 // C = 8 (2048-element buckets): 16 buckets fit the LDS of a CU, so the kernel is held to the 128 registers
@@ -1519,7 +1739,10 @@ __device__ __forceinline__ void even_small_span(const float* __restrict__ g, uin
 #pragma unroll
         for (int k = 0; k < S; ++k) levels[(size_t)(first_bucket + q) * S + k] = lv[k];
     }
-    orq_encode<1, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32);
+    orq_encode<1, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32, [&](uint32_t, float(&y)[4]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y[k] = v[0][k];
+    });
 }
 
 template <int S, int BITS, int NB>
@@ -1924,7 +2147,10 @@ __device__ __forceinline__ void sorted_small_span(const float* __restrict__ g, u
 #pragma unroll
         for (int k = 0; k < S; ++k) levels[(size_t)(first_bucket + q) * S + k] = lv[k];
     }
-    orq_encode<1, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32);
+    orq_encode<1, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32, [&](uint32_t, float(&y)[4]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y[k] = v[0][k];
+    });
 }
 
 template <int S, int BITS, int NB, int RULE>
@@ -2022,9 +2248,10 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
             }
     }
 
+    float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if (clip > 0.0f) {  // the same for every thread of the grid
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
-        clip_in_registers<4 * C>(
+        limit = clip_in_registers<4 * C>(
             flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * lane + (j & 3) < my_len); },
             [&](double x) { return team.sum(wave_sum(x)); });
     }
@@ -2220,7 +2447,8 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
         for (int k = 0; k < S; ++k) levels[(size_t)bucket * S + k] = lv[k];
     }
 
-    orq_encode<C, S, BITS, FULL>(v, lv, my_len, begin + first, seed, index_offset, codes32);
+    orq_encode<C, S, BITS, FULL>(v, lv, my_len, begin + first, seed, index_offset, codes32,
+                                 ReloadFromMemory{g + first, my_len, limit});
 }
 
 // C = 8 (2048 elements per wavefront): the LDS of a CU holds the buckets of 16 wavefronts, so the kernel is held to the

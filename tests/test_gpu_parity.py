@@ -749,3 +749,21 @@ def test_pb2_bench_workload_sampled():
     wl = synth.WORKLOADS["pb2"]
     nb = (wl.n + wl.bucket_size - 1) // wl.bucket_size
     _end_to_end(wl, [wl.gradient()], _sample(nb, 400, 6))
+
+
+# ------------------------------------------------------------------------------------------------
+# the encoder's careful form: Philox blocks on both sides of 2^32, widths whose product with 2^-24 would round
+# ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("d", [64, 128, 192, 256, 512, 1024, 1344, 2048, 4096, 8192, 32768])
+@pytest.mark.parametrize("scheme,bits", [(ogq.BINGRAD_PB, 1), (ogq.ORQ, 1), (ogq.ORQ, 2), (ogq.ORQ, 3), (ogq.ORQ_PAPER, 2),
+                                         (ogq.EVEN, 2), (ogq.EVEN, 3), (ogq.LINEAR, 4)])
+def test_encoder_careful_form(scheme, bits, d):
+    rng = np.random.default_rng(d + 10 * bits + scheme)
+    n = 2 * d + 333
+    for kind, scale in (("normal", 1.0), ("normal", 1e-29), ("heavy", 1e-36), ("normal", 1e-41)):
+        g = (_rng_bucket(rng, n, kind).astype(np.float64) * scale).astype(np.float32)
+        for offset in (0, (1 << 34) - 64, (1 << 34) - 64 * (d // 64) - 64, (1 << 34) - 2048, (1 << 34)):
+            parity.check_quantize(g, d, bits, scheme, 0, seed=77, index_offset=offset,
+                                  tag=f"careful-s{scheme}-b{bits}-d{d}-{kind}{scale}-o{offset}")
+        parity.check_quantize(g, d, bits, scheme, 0, seed=78, index_offset=(1 << 34) - 128, clip_factor=1.7,
+                              tag=f"careful-clip-s{scheme}-b{bits}-d{d}-{kind}{scale}")
