@@ -321,6 +321,55 @@ __device__ __forceinline__ uint32_t wave_sort_u32(uint32_t x, uint32_t lane, uin
     return wave_sort_merge<32>(x, lane);
 }
 
+// The key of 1-based rank `rank` among the first `count` (at most 64) lanes' keys, the other lanes holding 0xFFFFFFFF;
+// the answer is known to sit in one of the lanes `open`.  count_le = number of keys not above it; returns the lanes with
+// smaller keys.
+//
+// Quickselect on lane masks: a pivot costs one lane read and two compares on the vector unit, counting and narrowing are
+// scalar.  A bin of 20 keys takes about 5 pivots, i.e. 15 vector instructions where a bitonic sort of the keys takes 42
+// (65 above 32 keys); the kernels that call this are bound by vector-instruction issue.  The pivot is the first open
+// lane at or above lane rank - 1: the answer itself when the keys came in sorted.  Every round drops the pivot at least,
+// so the loop ends.  In assembly because the compiler spends twice the scalar instructions on it.  Wait states: two
+// between the lane read and the compares that take the key (s_nop 1); three scalar instructions lie between whatever
+// wrote `mine` and the lane read.  All lanes are active.
+__device__ __forceinline__ uint64_t select_rank(uint32_t mine, uint32_t count, uint32_t rank, uint64_t open, uint32_t& key_out,
+                                                uint32_t& count_le_out)
+{
+    const uint64_t valid = ~0ull >> (64u - count);  // (count >= 1)
+    const uint64_t from_rank = ~0ull << (rank - 1u);
+    uint32_t key, pivot, count_lt, count_le;
+    uint64_t lt, le;
+    asm("1:\n\t"
+        "s_and_b64 %[le], %[open], %[from]\n\t"
+        "s_cselect_b64 %[le], %[le], %[open]\n\t"
+        "s_ff1_i32_b64 %[pivot], %[le]\n\t"
+        "v_readlane_b32 %[key], %[mine], %[pivot]\n\t"
+        "s_nop 1\n\t"
+        "v_cmp_gt_u32_e64 %[lt], %[key], %[mine]\n\t"
+        "v_cmp_ge_u32_e64 %[le], %[key], %[mine]\n\t"
+        "s_bcnt1_i32_b64 %[count_lt], %[lt]\n\t"
+        "s_and_b64 %[le], %[le], %[valid]\n\t"
+        "s_bcnt1_i32_b64 %[count_le], %[le]\n\t"
+        "s_cmp_le_u32 %[rank], %[count_lt]\n\t"
+        "s_cbranch_scc1 2f\n\t"
+        "s_cmp_le_u32 %[rank], %[count_le]\n\t"
+        "s_cbranch_scc1 3f\n\t"
+        "s_andn2_b64 %[open], %[open], %[le]\n\t"
+        "s_cbranch_scc1 1b\n\t"
+        "s_branch 3f\n"
+        "2:\n\t"
+        "s_and_b64 %[open], %[open], %[lt]\n\t"
+        "s_cbranch_scc1 1b\n"
+        "3:"
+        : [open] "+&s"(open), [key] "=&s"(key), [pivot] "=&s"(pivot), [count_lt] "=&s"(count_lt), [count_le] "=&s"(count_le),
+          [lt] "=&s"(lt), [le] "=&s"(le)
+        : [mine] "v"(mine), [rank] "s"(rank), [valid] "s"(valid), [from] "s"(from_rank)
+        : "scc");
+    key_out = key;
+    count_le_out = count_le;
+    return lt;
+}
+
 // The bucket element of a given rank, with the counts and sums of the bucket elements strictly
 // below it and not above it.
 struct Picked {
@@ -337,36 +386,38 @@ template <int BLOCK, bool SUMS = true, class Lds>
 __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, uint32_t count, uint32_t rank, uint32_t lane)
 {
     static_assert(BLOCK <= 64, "the head of a block is read one position per lane");
-    const uint32_t r_in = rank - first;  // 1-based rank inside the bin
-
-    // sum of everything before the bin = prefix of its block + the block's positions before `first`
+    // The sum of everything before the bin is the prefix of its block plus the block's positions before `first` (the
+    // bin's "front").  Front and bin are neighbours in the grouped array, and every key of the front is smaller: where
+    // the two fit the lanes they are read, ranked and summed as one.
     const uint32_t block = first / BLOCK;
-    const uint32_t block_first = block * BLOCK;
+    const uint32_t front = SUMS ? first - block * BLOCK : 0u;
     double before_block = 0.0;
-    float head = 0.0f;
-    if constexpr (SUMS) {
-        before_block = uniform_f64(lds.block_prefix[block]);
-        head = lane < first - block_first ? __uint_as_float(lds.grouped[skewed(block_first + lane)]) : 0.0f;
-    }
+    if constexpr (SUMS) before_block = lds.block_prefix[block];
 
-    uint32_t key, c_lt, c_le;
+    uint32_t key, c_lt, c_le;  // counts from the bin's first position on
     double s_lt;
     if (count <= 64u) {
-        const uint32_t mine =
-            lane < count ? stored_key(lds.grouped[skewed(first + lane)]) : 0xFFFFFFFFu;
-        const uint32_t sorted = wave_sort_u32(mine, lane, count);
-        key = __builtin_amdgcn_readlane(sorted, r_in - 1u);
+        const uint32_t joint = front + count <= 64u ? front : 0u;  // lanes that hold the front
+        const uint32_t held = joint + count;
+        const float value =
+            __uint_as_float(lds.grouped[skewed(first - joint + (lane < held ? lane : 0u))]) + 0.0f;
+        const uint32_t mine = lane < held ? float_to_key(value) : 0xFFFFFFFFu;
+        float other = 0.0f;  // the front where it does not fit
+        if (SUMS && joint != front) other = lane < front ? __uint_as_float(lds.grouped[skewed(first - front + lane)]) : 0.0f;
+        const uint64_t lt =
+            select_rank(mine, held, rank - first + joint, (~0ull >> (64u - count)) << joint, key, c_le);
+        c_le -= joint;
+        c_lt = (uint32_t)__popcll(lt) - joint;
         if constexpr (SUMS) {
-            const bool lt = sorted < key;
-            const bool le = (sorted <= key) && (lane < count);
-            c_lt = (uint32_t)__popcll(__ballot(lt));
-            c_le = (uint32_t)__popcll(__ballot(le));
-            s_lt = wave_sum((double)head + (lt ? (double)key_to_float(sorted) : 0.0));
+            double part = __builtin_amdgcn_inverse_ballot_w64(lt) ? (double)value : 0.0;
+            if (joint != front) part += (double)other;
+            s_lt = wave_sum(part);
         } else {
-            c_lt = c_le = 0u;
             s_lt = 0.0;
         }
     } else {
+        const uint32_t r_in = rank - first;  // 1-based rank inside the bin
+        const float head = lane < front ? __uint_as_float(lds.grouped[skewed(first - front + lane)]) : 0.0f;
         // A crowded bin (many equal or nearly equal values): bisection on the key, over the bits in which the bin's
         // smallest and largest key differ (none when all its values are equal).  Up to 256 keys stay in registers.
         constexpr int HELD = 4;
@@ -436,7 +487,10 @@ __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, u
     p.count_lt = first + c_lt;
     p.count_le = first + c_le;
     p.sum_lt = before_block + s_lt;
-    p.sum_le = p.sum_lt + (double)(c_le - c_lt) * (double)key_to_float(key);
+    const uint32_t equal = c_le - c_lt;
+    double equal_sum = (double)key_to_float(key);
+    if (equal != 1u) equal_sum *= (double)equal;
+    p.sum_le = p.sum_lt + equal_sum;
     return p;
 }
 
@@ -1018,8 +1072,10 @@ __device__ __forceinline__ void orq_solve_one(Lds& lds, PickFn pick, uint32_t k,
                 lds.exact_limb[(threadIdx.x >> 6) & (sizeof(lds.exact_limb) / sizeof(lds.exact_limb[0]) - 1u)], lds.grouped, len,
                 lane, kWave, L, R, count_in, (uint32_t)m);
         }
-        rank = (m >= (double)cnt_le_R) ? 1u : cnt_le_R - (uint32_t)m;
-        rank = rank < 1u ? 1u : (rank > len ? len : rank);
+        // rank = cnt_le_R - m, at least 1 and at most len
+        const uint32_t below = uniform_u32((uint32_t)m);
+        rank = below >= cnt_le_R ? 1u : cnt_le_R - below;
+        rank = rank > len ? len : rank;
         if (rank == last_rank) return;  // same element as last time
         p = pick(rank);
         if (key_to_float(p.key) < L) copy_left = true;
@@ -1083,8 +1139,10 @@ __device__ __forceinline__ void orq_solve_one_in_registers(LevelRecords<S>& st, 
         // the fp64 sums do not decide floor(T): exact sums of the elements in [L, R] (rare)
         m = (double)exact_floor_t_grouped(lds.exact_limb[0], lds.grouped, len, lane, kWave, L, R, count_in, (uint32_t)m);
     }
-    uint32_t rank = (m >= (double)cnt_le_R) ? 1u : cnt_le_R - (uint32_t)m;
-    rank = rank < 1u ? 1u : (rank > len ? len : rank);
+    // rank = cnt_le_R - m, at least 1 and at most len
+    const uint32_t below = uniform_u32((uint32_t)m);
+    uint32_t rank = below >= cnt_le_R ? 1u : cnt_le_R - below;
+    rank = rank > len ? len : rank;
     if (rank == st.rank[K]) return;  // same element as last time
     const Picked p = pick(rank);
     if (key_to_float(p.key) < L) {
