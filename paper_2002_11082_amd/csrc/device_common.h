@@ -157,6 +157,8 @@ __device__ __forceinline__ float clip_in_registers(float (&v)[N], uint32_t len, 
     part = 0.0;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
+        // converted again: fp64 copies of 32 values kept from the first pass would not fit the registers
+        if constexpr (N >= 32) asm volatile("" : "+v"(v[j]));
         const double dv = (double)v[j] - mean;
         part += valid(j) ? dv * dv : 0.0;
     }

@@ -756,8 +756,10 @@ __device__ __forceinline__ Interval<S> find_interval(float x, const float (&lv)[
         for (int t = 1; t < S - 1; ++t) {
             const bool ge = lv[t] <= x;
             not_below[t] = __ballot(ge);
-            r.base = ge ? lv[t] : r.base;
-            r.width = ge ? width[t] : r.width;
+            // (values, not a choice between two objects: that one is compiled to an address in scratch memory)
+            const float base = lv[t], above = width[t], old_base = r.base, old_width = r.width;
+            r.base = ge ? base : old_base;
+            r.width = ge ? above : old_width;
         }
         r.bit[0] = not_below[1] ^ not_below[2];
         r.bit[1] = not_below[2];
@@ -832,21 +834,37 @@ __device__ __forceinline__ uint32_t nibble_transpose(uint32_t x, const NibbleTra
     return __builtin_amdgcn_bitop3_b32(t.take, __builtin_amdgcn_alignbit(y, y, t.turn), x, 0xCA);
 }
 
-// What the encoder needs to know about the range of elements a wavefront encodes.
+// How the elements a wavefront encodes lie in its registers; row = 16 lanes.
+//   OneRange: chunk c, lane l: elements 256c + 4l + {0..3} of one range.
+//   FourRows: row r holds a range of its own (consecutive ranges of equal length): chunk c, lane 16r + i: elements
+//             64c + 4i + {0..3} of range r.
+struct OneRange {
+    static constexpr uint32_t kBlocks = 64, kGroups = 4;  // Philox blocks and 64-element groups from chunk to chunk
+};
+struct FourRows {
+    static constexpr uint32_t kBlocks = 16, kGroups = 1;
+};
+
+// Which of the chunks' elements exist: all; those below `len`; or all of the chunks below len / 256.
+enum class Fill { kAll, kRagged, kWholeChunks };
+
+// What the encoder needs to know about the elements a wavefront encodes.
 struct EncodeRange {
-    uint32_t len;        // valid elements
-    uint64_t block;      // Philox block of the first one (a multiple of 16)
-    uint32_t k0, k1;     // Philox key
-    uint32_t* words;     // the first one's packed words
+    uint32_t len;         // valid elements
+    uint64_t block;       // Philox block of the first one (a multiple of 16)
+    uint32_t lane_block;  // Philox blocks from there to this lane's elements of chunk 0
+    uint32_t row_groups;  // 64-element groups from row to row
+    uint32_t k0, k1;      // Philox key
+    uint32_t* words;      // the first element's packed words
 };
 
 // Levels up to which the rounding test takes its width already multiplied by 2^-24 (above, the width is a difference of
 // two selected levels, see find_interval).
 constexpr int kScaledWidthLevels = 4;
 
-// Encodes and packs chunks c0 .. c0 + GROUP - 1 of the range (256 elements each, lane l: elements 256c + 4l + {0..3}).
-// CAREFUL: valid for every width and Philox block; otherwise encode_is_plain() holds.
-template <int GROUP, int S, int BITS, bool FULL, bool CAREFUL>
+// Encodes and packs chunks c0 .. c0 + GROUP - 1 (256 elements each).  CAREFUL: valid for every width and Philox block;
+// otherwise encode_is_plain() holds.
+template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL>
 __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (&lv)[S], const float (&width)[S - 1], uint32_t c0,
                                               const EncodeRange& range, const NibbleTranspose& transpose, uint32_t lane)
 {
@@ -860,15 +878,16 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
 #pragma unroll
     for (int i = GROUP - 1; i >= 0; --i) {
         const uint32_t c = c0 + (uint32_t)i;
-        if constexpr (!FULL) {
+        if constexpr (FILL != Fill::kAll) {
             if (256u * c >= len) continue;
         }
         uint32_t r[4];
         if constexpr (CAREFUL) {
-            const uint64_t block = range.block + 64u * c + lane;
+            const uint64_t block = range.block + Layout::kBlocks * c + range.lane_block;
             philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), range.k0, range.k1, r);
         } else {
-            philox4x32_10_uniform_c1((uint32_t)range.block + lane + 64u * c, (uint32_t)(range.block >> 32), range.k0, range.k1, r);
+            philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * c,
+                                     (uint32_t)(range.block >> 32), range.k0, range.k1, r);
         }
 #pragma unroll
         for (int k = 3; k >= 0; --k) {
@@ -880,7 +899,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
             const float scaled = draw * in.width;
             uint64_t carry = __ballot(scaled < delta);  // rounded up
             uint64_t valid = ~0ull;
-            if constexpr (!FULL) {
+            if constexpr (FILL == Fill::kRagged) {
                 valid = __ballot(256u * c + 4u * lane + k < len);
                 carry &= valid;
             }
@@ -905,8 +924,8 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
             x |= dpp_u32<kDppHalfMirror>(x);
             mine = p == 0 || j == (uint32_t)p ? x : mine;
         }
-        if (j < (uint32_t)BITS && (FULL || 256u * c0 + 32u * h < ((len + 63u) & ~63u)))
-            range.words[((4u * c0 + (h >> 1)) * (uint32_t)BITS + j) * 2u + (h & 1u)] = mine;
+        if (j < (uint32_t)BITS && (FILL != Fill::kRagged || 256u * c0 + 32u * h < ((len + 63u) & ~63u)))
+            range.words[((Layout::kGroups * c0 + (h >> 1) * range.row_groups) * (uint32_t)BITS + j) * 2u + (h & 1u)] = mine;
         return;
     }
 #pragma unroll
@@ -919,9 +938,10 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
         // lane 8 h + j now holds half word h (32 elements) of chunk c0 + j % GROUP of plane q * PLANES + j / GROUP
         const uint32_t j = lane & 7u, h = lane >> 3;
         const uint32_t c = c0 + (j & (uint32_t)(GROUP - 1)), p = (uint32_t)(q * PLANES) + j / (uint32_t)GROUP;
-        const bool exists =
-            (BITS % PLANES == 0 || p < (uint32_t)BITS) && (FULL || 256u * c + 32u * h < ((len + 63u) & ~63u));
-        if (exists) range.words[((4u * c + (h >> 1)) * (uint32_t)BITS + p) * 2u + (h & 1u)] = x;
+        const bool in_range = FILL == Fill::kAll || (FILL == Fill::kWholeChunks ? 256u * c < len
+                                                                                : 256u * c + 32u * h < ((len + 63u) & ~63u));
+        if ((BITS % PLANES == 0 || p < (uint32_t)BITS) && in_range)
+            range.words[((Layout::kGroups * c + (h >> 1) * range.row_groups) * (uint32_t)BITS + p) * 2u + (h & 1u)] = x;
     }
 }
 
@@ -952,23 +972,20 @@ __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], con
 // transpose among 8 lanes then leaves 32 consecutive bits of a packed word in every lane, stored with one instruction
 // for 8 chunks.  (Before: a select and an or per element and plane, then three cross-lane ors and a store by one lane
 // in eight per chunk and plane.)  The rare range that encode_is_plain() refuses is encoded chunk by chunk in a loop.
-template <int C, int S, int BITS, bool FULL, class ReloadFn>
-__device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
-                                           uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32, ReloadFn reload)
+template <class Layout, int C, int S, int BITS, Fill FILL, class ReloadFn>
+__device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (&lv)[S], const EncodeRange& range, ReloadFn reload)
 {
     const uint32_t lane = threadIdx.x & 63u;
     float width[S - 1];
 #pragma unroll
     for (int k = 0; k < S - 1; ++k) width[k] = lv[k + 1] - lv[k];
-    const EncodeRange range{len, (index_offset + begin) >> 2, (uint32_t)seed, (uint32_t)(seed >> 32),
-                            codes32 + begin / 64 * (2 * BITS)};
     const NibbleTranspose transpose = nibble_transpose_setup(lane);
     if (!encode_is_plain<C, S>(width, range)) {
 #pragma unroll 1
-        for (uint32_t c = 0; 256u * c < len; ++c) {
+        for (uint32_t c = 0; 256u * c < range.len; ++c) {
             float y[1][4];
             reload(c, y[0]);
-            encode_chunks<1, S, BITS, false, true>(y, lv, width, c, range, transpose, lane);
+            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true>(y, lv, width, c, range, transpose, lane);
         }
         return;
     }
@@ -979,11 +996,20 @@ __device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (
     constexpr int GROUP = C < 8 ? C : 8;
 #pragma unroll
     for (int c0 = C - GROUP; c0 >= 0; c0 -= GROUP) {
-        if constexpr (!FULL) {
-            if (256u * (uint32_t)c0 >= len) continue;  // nothing of the bucket in these chunks: no words to write
+        if constexpr (FILL != Fill::kAll) {
+            if (256u * (uint32_t)c0 >= range.len) continue;  // nothing in these chunks: no words to write
         }
-        encode_chunks<GROUP, S, BITS, FULL, false>(&v[c0], lv, width, (uint32_t)c0, range, transpose, lane);
+        encode_chunks<Layout, GROUP, S, BITS, FILL, false>(&v[c0], lv, width, (uint32_t)c0, range, transpose, lane);
     }
+}
+
+template <int C, int S, int BITS, bool FULL, class ReloadFn>
+__device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
+                                           uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32, ReloadFn reload)
+{
+    const EncodeRange range{len, (index_offset + begin) >> 2, threadIdx.x & 63u, 1u, (uint32_t)seed, (uint32_t)(seed >> 32),
+                            codes32 + begin / 64 * (2 * BITS)};
+    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged>(v, lv, range, reload);
 }
 
 // The reload function of orq_encode for a range in memory: g = its first element; limit = the clipping threshold
@@ -1528,7 +1554,7 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
     }
 
     float limit = __uint_as_float(0x7F800000u);  // clipping threshold
-    if constexpr (CLIP) {
+    if (CLIP && clip > 0.0f) {  // (the same for every thread of the grid)
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
         limit = clip_in_registers<4 * C>(flat, len, clip, [&](int j) { return full || (64u * (j & ~3) + 4u * lane + (j & 3) < len); });
     }

@@ -6,6 +6,7 @@
 // than two wavefronts of 4096: half the registers, twice the resident wavefronts); 104, 108: 4, 8 wavefronts of 4096
 // elements per bucket of at most 16384, 32768 (there eight of 2048 are slower, sixteen mixed).
 #include "rounding_kernels.h"
+#include "row_kernels.h"
 
 #include "launch.h"
 
@@ -24,9 +25,36 @@ void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32
     launch_orq_team_levels<2, 8>(g, n, p, nb, lv, codes, st);
 }
 #elif OGQ_PART < 100
+#if OGQ_PART <= 2
+// Four buckets per wavefront (row_kernels.h) where the gradient has enough of them to fill the chip that way: a
+// wavefront then takes about 1.5 times as long as one with a single bucket, so below one wavefront per SIMD (4096
+// buckets) it only adds latency.  Measured crossover, in buckets: 2000 to 4000 at 192 and 256 elements, 5000 to 7000 at
+// 128 and above 256 (there the LDS holds fewer wavefronts); without level solves about twice that.
+static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
+{
+    const bool solves = p->scheme != OGQ_EVEN && levels_per_bucket(p->scheme, p->bits) > 2;
+    const uint32_t d = p->bucket_size;
+    const uint32_t enough = d > 256 ? (solves ? 8192u : 16384u) : d > 128 ? (solves ? 4096u : 8192u) : 8192u;
+    if (nb < enough) return false;
+#if OGQ_PART == 1
+    switch (d) {
+        case 64: return false;  // (four buckets per wavefront already: sorted_small_kernel, even_small_kernel)
+        case 128: return launch_rows_levels<2, true>(g, n, p, nb, lv, codes, st);
+        case 192: return launch_rows_levels<4, false>(g, n, p, nb, lv, codes, st);
+        default: return launch_rows_levels<4, true>(g, n, p, nb, lv, codes, st);
+    }
+#else
+    return d == 512 ? launch_rows_levels<8, true>(g, n, p, nb, lv, codes, st)
+                    : launch_rows_levels<8, false>(g, n, p, nb, lv, codes, st);
+#endif
+}
+#endif
 void OGQ_CAT(launch_rounding_c, OGQ_PART)(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv,
                                           void* codes, hipStream_t st)
 {
+#if OGQ_PART <= 2
+    if (launch_row_part(g, n, p, nb, lv, codes, st)) return;
+#endif
     launch_orq_levels<OGQ_PART>(g, n, p, nb, lv, codes, st);
 }
 #elif OGQ_PART == 102

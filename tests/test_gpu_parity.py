@@ -767,3 +767,39 @@ def test_encoder_careful_form(scheme, bits, d):
                                   tag=f"careful-s{scheme}-b{bits}-d{d}-{kind}{scale}-o{offset}")
         parity.check_quantize(g, d, bits, scheme, 0, seed=78, index_offset=(1 << 34) - 128, clip_factor=1.7,
                               tag=f"careful-clip-s{scheme}-b{bits}-d{d}-{kind}{scale}")
+
+
+# ------------------------------------------------------------------------------------------------
+# four buckets per wavefront (long gradients in buckets of 128 .. 512 elements)
+# ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("d", [128, 192, 256, 320, 384, 448, 512])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 1),
+                                                (ogq.ORQ_PAPER, 3, 0), (ogq.ORQ_PAPER, 4, 0), (ogq.EVEN, 2, 0), (ogq.EVEN, 4, 0),
+                                                (ogq.LINEAR, 2, 0), (ogq.LINEAR, 4, 0)])
+def test_four_buckets_per_wavefront(scheme, bits, sweeps, d):
+    """Neighbouring buckets with nothing in common: spread, crowded and single-valued bins side by side in a wavefront,
+    three whole buckets and a cut-off one behind the last wavefront's four."""
+    rng = np.random.default_rng(d + 1000 * bits + scheme)
+    nb = (16384 if scheme == ogq.EVEN or bits == 1 else 8192) + 4
+    n = nb * d - 17
+    g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    kinds = ["const", "normal", "zeros", "heavy", "ints", "shifted"]
+    for b in range(0, 1500):
+        if b % 3 == 0:
+            buckets[b] = _rng_bucket(rng, d, kinds[(b // 3) % len(kinds)])
+        elif b % 7 == 1:
+            buckets[b, rng.random(d) < 0.9] = 0.0                     # sparse
+        elif b % 7 == 2:
+            buckets[b] = np.sort(buckets[b])
+        elif b % 7 == 3:
+            buckets[b] = np.float32(1.0) + rng.integers(0, 200, d).astype(np.float32) * np.float32(2.0 ** -23)  # one crowded bin
+        elif b % 7 == 4:
+            half = buckets[b, : d // 2].copy()
+            buckets[b, d // 2:] = -half                                # T exactly an integer
+        elif b % 7 == 5:
+            buckets[b] *= np.float32(1e-38)
+    g = g[:n]
+    for clip in (0.0, 2.5):
+        parity.check_quantize(g, d, bits, scheme, sweeps, seed=99, index_offset=64 * 3, clip_factor=clip,
+                              tag=f"rows-s{scheme}-b{bits}-d{d}-c{clip}")
