@@ -806,34 +806,6 @@ __device__ __forceinline__ uint32_t push_bit(uint32_t x, uint64_t mask)
     return r;
 }
 
-// 8 x 8 transpose of nibbles inside every group of 8 lanes: lane i's nibble c and lane c's nibble i trade places.  Three
-// butterfly steps; those that move whole bytes are one cross-lane move and one byte permute.
-struct NibbleTranspose {
-    uint32_t swap16, swap8;  // byte selectors of the steps over lane bits 2 and 1
-    uint32_t take, turn;     // the step over lane bit 0: nibbles taken from the partner, right rotation that places them
-};
-
-__device__ __forceinline__ NibbleTranspose nibble_transpose_setup(uint32_t lane)
-{
-    // the lower lane of a pair keeps its low blocks and takes the partner's low blocks as its high blocks, the upper lane
-    // keeps its high blocks and takes the partner's high blocks as its low blocks (bytes 0 .. 3: own, 4 .. 7: partner's)
-    NibbleTranspose t;
-    t.swap16 = (lane & 4u) ? 0x03020706u : 0x05040100u;
-    t.swap8 = (lane & 2u) ? 0x03070105u : 0x06020400u;
-    t.take = (lane & 1u) ? 0x0F0F0F0Fu : 0xF0F0F0F0u;
-    t.turn = (lane & 1u) ? 4u : 28u;
-    return t;
-}
-
-__device__ __forceinline__ uint32_t nibble_transpose(uint32_t x, const NibbleTranspose& t, uint32_t lane)
-{
-    x = __builtin_amdgcn_perm(lane_xor<4>(x, lane), x, t.swap16);
-    x = __builtin_amdgcn_perm(lane_xor<2>(x, lane), x, t.swap8);
-    const uint32_t y = lane_xor<1>(x, lane);
-    // take ? turned : x, bit by bit, in one instruction (v_bitop3_b32, truth table 0xCA)
-    return __builtin_amdgcn_bitop3_b32(t.take, __builtin_amdgcn_alignbit(y, y, t.turn), x, 0xCA);
-}
-
 // How the elements a wavefront encodes lie in its registers; row = 16 lanes.
 //   OneRange: chunk c, lane l: elements 256c + 4l + {0..3} of one range.
 //   FourRows: row r holds a range of its own (consecutive ranges of equal length): chunk c, lane 16r + i: elements

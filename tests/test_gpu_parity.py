@@ -660,6 +660,26 @@ def test_decode_average_many_identical_workers():
         parity.check_average(out.cpu().numpy(), ref, np.abs(single).astype(np.float64), tag=f"avg-identical-W{W}")
 
 
+@pytest.mark.parametrize("d", [192, 320, 448, 512, 576, 832, 960, 1024, 1088, 1344, 4160])
+@pytest.mark.parametrize("bits,scheme", [(1, ogq.BINGRAD_B), (2, ogq.ORQ), (2, ogq.EVEN), (3, ogq.ORQ), (3, ogq.LINEAR), (4, ogq.EVEN)])
+def test_decode_average_joint_lookups(bits, scheme, d):
+    """Several workers per look-up: worker counts that end inside a look-up, inside and behind a pair of them, spans
+    that touch one to seven buckets, ragged last spans down to a single element."""
+    rng = np.random.default_rng(31 * bits + d + scheme)
+    stride = oracle.levels_per_bucket(scheme, bits)
+    for n in (1, 2 * d + 1, 3 * 1024 + 5 * d + 77, 8 * 1024):
+        for W in (1, 2, 3, 4, 5, 8, 9, 17):
+            gs = [_rng_bucket(rng, n, "heavy" if w % 3 else "normal") * np.float32(1 + w) for w in range(W)]
+            q = [oracle.quantize(g, d, bits, scheme, 0, seed=40 + w) for w, g in enumerate(gs)]
+            ref = oracle.dequantize_average([w for _, w in q], [l for l, _ in q], n, d, bits, stride)
+            scale = parity.term_scale([l for l, _ in q], [w for _, w in q], n, d, bits, stride)
+            dl = [torch.from_numpy(np.concatenate([l, np.zeros(4, np.float32)])).to(DEV) for l, _ in q]
+            dc = [torch.from_numpy(np.concatenate([w, np.zeros(2, np.uint64)]).view(np.int64)).to(DEV) for _, w in q]
+            out = ogq.ogq_dequantize_average(dc, dl, n, ogq.make_params(d, bits, scheme))
+            torch.cuda.synchronize()
+            parity.check_average(out.cpu().numpy(), ref, scale, tag=f"avg-joint-b{bits}-s{scheme}-d{d}-n{n}-W{W}")
+
+
 # ------------------------------------------------------------------------------------------------
 # the benchmark configurations at full size
 # ------------------------------------------------------------------------------------------------
