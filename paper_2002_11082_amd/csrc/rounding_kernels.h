@@ -2652,7 +2652,9 @@ void launch_team_paper_counts(const float* g, size_t n, const ogq_params_t* p, u
                               hipStream_t st)
 {
     switch (p->bits) {  // 2^(bits-1) + 1 levels
-        case 2: launch_orq_team<W, C, 3, 2, RULE>(g, n, p, nb, lv, codes, st); break;
+        case 2:
+            if constexpr (RULE == kEven) launch_orq_team<W, C, 3, 2, RULE>(g, n, p, nb, lv, codes, st);
+            break;  // the other rules' three levels: orq_gather_kernel
         case 3: launch_orq_team<W, C, 5, 3, RULE>(g, n, p, nb, lv, codes, st); break;
         default: launch_orq_team<W, C, 9, 4, RULE>(g, n, p, nb, lv, codes, st); break;
     }

@@ -4,9 +4,11 @@
 // elements (measured 6-17 % faster there than one wavefront holding 64 elements per lane; for 2048 elements one
 // wavefront is the faster choice); 102: four wavefronts of 2048 elements per bucket of at most 8192 (22-37 % faster
 // than two wavefronts of 4096: half the registers, twice the resident wavefronts); 104, 108: 4, 8 wavefronts of 4096
-// elements per bucket of at most 16384, 32768 (there eight of 2048 are slower, sixteen mixed).
+// elements per bucket of at most 16384, 32768 (there eight of 2048 are slower, sixteen mixed).  ORQ-3 and Linear-3 above
+// 2048 elements have a kernel of their own, always wavefronts of 2048 elements.
 #include "rounding_kernels.h"
 #include "row_kernels.h"
+#include "gather_kernels.h"
 
 #include "launch.h"
 
@@ -22,6 +24,7 @@ namespace ogq {
 #if OGQ_PART == 16
 void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
+    if (launch_gather<2, 8>(g, n, p, nb, lv, codes, st)) return;
     launch_orq_team_levels<2, 8>(g, n, p, nb, lv, codes, st);
 }
 #elif OGQ_PART < 100
@@ -60,16 +63,19 @@ void OGQ_CAT(launch_rounding_c, OGQ_PART)(const float* g, size_t n, const ogq_pa
 #elif OGQ_PART == 102
 void launch_rounding_w2(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
+    if (launch_gather<4, 8>(g, n, p, nb, lv, codes, st)) return;
     launch_orq_team_levels<4, 8>(g, n, p, nb, lv, codes, st);
 }
 #elif OGQ_PART == 104
 void launch_rounding_w4(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
+    if (launch_gather<8, 8>(g, n, p, nb, lv, codes, st)) return;
     launch_orq_team_levels<4, 16>(g, n, p, nb, lv, codes, st);
 }
 #elif OGQ_PART == 108
 void launch_rounding_w8(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
+    if (launch_gather<16, 8>(g, n, p, nb, lv, codes, st)) return;
     launch_orq_team_levels<8, 16>(g, n, p, nb, lv, codes, st);
 }
 #else

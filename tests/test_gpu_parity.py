@@ -823,3 +823,28 @@ def test_four_buckets_per_wavefront(scheme, bits, sweeps, d):
     for clip in (0.0, 2.5):
         parity.check_quantize(g, d, bits, scheme, sweeps, seed=99, index_offset=64 * 3, clip_factor=clip,
                               tag=f"rows-s{scheme}-b{bits}-d{d}-c{clip}")
+
+
+# ------------------------------------------------------------------------------------------------
+# one interior level, buckets of several wavefronts (the wanted bin is collected, not the bucket grouped)
+# ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("d", [2112, 4096, 4160, 8192, 9984, 16384, 20480, 32768])
+@pytest.mark.parametrize("scheme", [ogq.ORQ_PAPER, ogq.LINEAR])
+def test_three_levels_in_large_buckets(scheme, d):
+    rng = np.random.default_rng(d + scheme)
+    parts = [_rng_bucket(rng, d, kind) for kind in ("normal", "heavy", "shifted", "ints", "const", "zeros")]
+    sparse = _rng_bucket(rng, d, "heavy")
+    sparse[rng.random(d) < 0.8] = 0.0
+    crowded = (np.float32(1.0) + rng.integers(0, 900, d).astype(np.float32) * np.float32(2.0 ** -23)).astype(np.float32)
+    crowded[:7] = [-3.0, 5.0, 0.25, -0.0, 0.0, 1e-30, -1e-39]
+    medium = _rng_bucket(rng, d, "normal")
+    medium[: d // 20] = np.float32(1e-3) * (1 + rng.integers(0, 40, d // 20).astype(np.float32) * np.float32(2.0 ** -20))
+    half = _rng_bucket(rng, d // 2, "heavy")
+    symmetric = np.concatenate([half, -half])                       # T is exactly an integer
+    tiny = symmetric.copy()
+    tiny[3] = 1e-38
+    g = np.concatenate(parts + [sparse, crowded, -crowded, medium, symmetric, tiny, np.sort(parts[0])])
+    for n in (g.size, g.size - 1, g.size - d // 2 - 3, 65):
+        for clip in (0.0, 2.5):
+            parity.check_quantize(g[:n], d, 2, scheme, 1, seed=17, index_offset=64 * 5, clip_factor=clip,
+                                  tag=f"three-levels-s{scheme}-d{d}-n{n}-c{clip}")
