@@ -64,39 +64,6 @@ __device__ __forceinline__ uint32_t exact_floor_t_team(unsigned long long* limb,
     return lo;
 }
 
-// The elements of this wavefront of the bucket of `len` elements at g; padding holds 0.
-template <int W, int C, bool FULL>
-__device__ __forceinline__ void gather_load(float (&v)[C][4], const float* __restrict__ g, uint32_t len)
-{
-    const uint32_t lane = threadIdx.x & 63u, first = 256u * C * uniform_u32(threadIdx.x >> 6);
-    const uint32_t my_len = len > first ? len - first : 0u;
-    if constexpr (FULL) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + first + 256 * c + 4 * lane));
-            v[c][0] = q.x; v[c][1] = q.y; v[c][2] = q.z; v[c][3] = q.w;
-        }
-    } else if (len % 4u == 0u) {
-        // whole 16-byte loads; the lanes past the end read the bucket's first elements and drop them
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const uint32_t e = 256u * c + 4u * lane;
-            const bool inside = e < my_len;
-            const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + (inside ? first + e : 0u)));
-            v[c][0] = inside ? q.x : 0.0f; v[c][1] = inside ? q.y : 0.0f;
-            v[c][2] = inside ? q.z : 0.0f; v[c][3] = inside ? q.w : 0.0f;
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t e = 256u * c + 4u * lane + k;
-                v[c][k] = e < my_len ? g[first + e] : 0.0f;
-            }
-    }
-}
-
 template <int W, int C, int BITS, bool FULL, int RULE>
 __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const float* __restrict__ g, uint32_t len, size_t begin,
                                                   uint32_t bucket, float clip, uint64_t seed, uint64_t index_offset,
@@ -116,7 +83,7 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
     for (uint32_t i = tid; i < B; i += THREADS) lds.bin_count[i] = 0u;
     if (tid == 0u) lds.list_count = 0u;
     float v[C][4];
-    gather_load<W, C, FULL>(v, g, len);
+    load_range<C, FULL>(v, g, first, len, my_len, lane);
 
     float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if (clip > 0.0f) {  // the same for every thread of the grid
@@ -124,20 +91,21 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
         limit = clip_in_registers<4 * C>(
             flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * lane + (j & 3) < my_len); },
             [&](double x) { return team.sum(wave_sum(x)); });
+        if constexpr (!FULL) set_padding<C>(v, my_len, lane);
     }
 
     // ---- extremes and (ORQ) total of the bucket ---------------------------------------------------------
-    float low = __uint_as_float(0x7F800000u), high = __uint_as_float(0xFF800000u);
+    float low, high;
+    uint32_t unused_zeros;
+    lane_extremes<C, false>(v, low, high, unused_zeros);
     double part = 0.0;
-    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
+    if constexpr (RULE == kOptimal) {
+        for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-            low = fminf(low, valid ? v[c][k] : __uint_as_float(0x7F800000u));
-            high = fmaxf(high, valid ? v[c][k] : __uint_as_float(0xFF800000u));
-            if constexpr (RULE == kOptimal) part += valid ? (double)v[c][k] : 0.0;
-        }
-    });
+            for (int k = 0; k < 4; ++k)
+                part += (double)(decltype(all)::value || 256u * c + 4u * lane + k < my_len ? v[c][k] : 0.0f);
+        });
+    }
     low = wave_min(low);
     high = wave_max(high);
     double total = 0.0;
@@ -161,7 +129,9 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-            if (valid) atomicAdd(&lds.bin_count[value_bin<(int)HALF, SHIFT>(v[c][k] + zero, t_low)], 1u);
+            // (padding adds 0 to one bin per lane: no branch)
+            const uint32_t bin = value_bin<(int)HALF, SHIFT>(v[c][k] + zero, t_low);
+            atomicAdd(&lds.bin_count[valid ? bin : lane], valid ? 1u : 0u);
         }
     });
     __syncthreads();

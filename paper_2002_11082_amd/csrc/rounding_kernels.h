@@ -717,6 +717,8 @@ __device__ __forceinline__ bool floor_t_from_sums(double Ssum, double width, dou
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
+constexpr float kNoElement = __builtin_nanf("");  // what a wavefront holds in place of elements past a range's end
+
 // Runs f(c, all) for the chunks c (256 elements each) that hold at least one of the `len` valid elements.  `all` is a
 // std::true_type when every element of the chunk is valid, so that f can drop its per-element bounds tests: at most one
 // chunk of a bucket is cut by its end, and the chunks past it are skipped altogether (wave-uniform branches).
@@ -817,7 +819,8 @@ struct FourRows {
     static constexpr uint32_t kBlocks = 16, kGroups = 1;
 };
 
-// Which of the chunks' elements exist: all; those below `len`; or all of the chunks below len / 256.
+// Which of the chunks' elements exist: all; those below `len`; or all of the chunks below len / 256.  Those that do not
+// exist in a chunk that does are NaN: no comparison with NaN holds, so their bits come out as 0.
 enum class Fill { kAll, kRagged, kWholeChunks };
 
 // What the encoder needs to know about the elements a wavefront encodes.
@@ -870,14 +873,9 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
             const float draw = SCALED ? (float)(r[k] >> 8) : (float)(r[k] >> 8) * 0x1p-24f;
             const float scaled = draw * in.width;
             uint64_t carry = __ballot(scaled < delta);  // rounded up
-            uint64_t valid = ~0ull;
-            if constexpr (FILL == Fill::kRagged) {
-                valid = __ballot(256u * c + 4u * lane + k < len);
-                carry &= valid;
-            }
 #pragma unroll
             for (int p = 0; p < BITS; ++p) {
-                const uint64_t index_bit = p < Interval<S>::kIndexBits ? in.bit[p < 3 ? p : 0] & valid : 0ull;
+                const uint64_t index_bit = p < Interval<S>::kIndexBits ? in.bit[p < 3 ? p : 0] : 0ull;
                 plane[p] = push_bit<S == 2>(plane[p], index_bit ^ carry);
                 carry &= index_bit;
             }
@@ -984,6 +982,155 @@ __device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (
     encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged>(v, lv, range, reload);
 }
 
+// The elements [first, first + my_len) of the bucket of `len` elements at g, read once (past the caches), element
+// 256 c + 4 lane + k of the range into v[c][k]; padding holds PAD.  A range shorter than its capacity takes whole 16-byte
+// loads too: the lanes past its end read the bucket's first elements and drop them, and where its length is not a
+// multiple of 4 (a ragged last bucket) the quad it ends in is filled from three loads of the whole wavefront.
+template <int C, bool FULL>
+__device__ __forceinline__ void load_range(float (&v)[C][4], const float* __restrict__ g, uint32_t first, uint32_t len,
+                                           uint32_t my_len, uint32_t lane, float pad = kNoElement)
+{
+    float tail[3] = {pad, pad, pad};
+    const uint32_t quad = my_len / 4u;
+    if constexpr (!FULL) {
+        if (my_len % 4u != 0u) {
+            const float* t = g + first + 4u * quad;
+            tail[0] = t[0];
+            if (my_len % 4u > 1u) tail[1] = t[1];
+            if (my_len % 4u > 2u) tail[2] = t[2];
+        }
+    }
+    if (FULL || len >= 4u) {
+        floatx4 q[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const uint32_t e = 256u * c + 4u * lane;
+            const bool inside = FULL || e + 4u <= my_len;
+            q[c] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + (inside ? first + e : 0u)));
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const bool inside = FULL || 256u * c + 4u * lane + 4u <= my_len;
+            v[c][0] = inside ? q[c].x : pad; v[c][1] = inside ? q[c].y : pad;
+            v[c][2] = inside ? q[c].z : pad; v[c][3] = inside ? q[c].w : pad;
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[c][k] = pad;
+    }
+    if constexpr (!FULL) {
+        if (my_len % 4u != 0u) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const bool mine = 64u * c + lane == quad;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) v[c][k] = mine ? tail[k] : v[c][k];
+            }
+        }
+    }
+}
+
+// Padding of a wavefront's elements: fminf and fmaxf pass over it, no comparison with it holds.
+template <int C>
+__device__ __forceinline__ void set_padding(float (&v)[C][4], uint32_t my_len, uint32_t lane)
+{
+    asm volatile("" : "+v"(lane));  // tested afresh: the lane masks of an earlier pass would not fit the scalar registers
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[c][k] = 256u * c + 4u * lane + k < my_len ? v[c][k] : kNoElement;
+}
+
+// Smallest and largest element that the lane holds, and (ZEROS) how many zeros; padding is NaN.
+template <int C, bool ZEROS>
+__device__ __forceinline__ void lane_extremes(const float (&v)[C][4], float& low, float& high, uint32_t& zeros)
+{
+    low = __uint_as_float(0x7F800000u);
+    high = __uint_as_float(0xFF800000u);
+    zeros = 0u;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            low = fminf(low, v[c][k]);
+            high = fmaxf(high, v[c][k]);
+            if constexpr (ZEROS) zeros += v[c][k] == 0.0f ? 1u : 0u;
+        }
+}
+
+// Counts the lane's elements into their bins; slot = bin | position inside the bin << 16 (pack_slot).  The returning LDS
+// add hands every element its position.  None of the answers is waited for before the last add has been sent, and the
+// elements of the chunk that the range ends in take no branch: padding adds 0 to one bin per lane.
+template <int C, bool FULL, int HALF, int SHIFT>
+__device__ __forceinline__ void count_into_bins(uint32_t (&slot)[C][4], const float (&v)[C][4], uint32_t* bins, uint32_t t_low,
+                                                uint32_t my_len, uint32_t lane)
+{
+    uint32_t position[C][4];
+    const float zero = opaque_zero();
+    if constexpr (!FULL) asm volatile("" : "+v"(lane));  // (see set_padding)
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        if (FULL || 256u * (uint32_t)(c + 1) <= my_len) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                slot[c][k] = value_bin<HALF, SHIFT>(v[c][k] + zero, t_low);
+                position[c][k] = atomicAdd(&bins[slot[c][k]], 1u);
+            }
+        } else if (256u * (uint32_t)c < my_len) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool valid = 256u * c + 4u * lane + k < my_len;
+                slot[c][k] = valid ? value_bin<HALF, SHIFT>(v[c][k] + zero, t_low) : lane;
+                position[c][k] = atomicAdd(&bins[slot[c][k]], valid ? 1u : 0u);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) slot[c][k] = position[c][k] = 0u;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) slot[c][k] = pack_slot(position[c][k], slot[c][k], (uint32_t)HALF);
+}
+
+// Scatters the lane's elements into their bins.  The bin starts of a group of elements are all read before the group's
+// values are written (a read behind a write to the same LDS object would wait for it).  Padding of a group that holds
+// elements goes where it lies in the bucket: behind all elements.
+template <int C, bool FULL>
+__device__ __forceinline__ void scatter_into_bins(uint32_t* grouped, const uint32_t* bin_start_middle, const uint32_t (&slot)[C][4],
+                                                  const float (&v)[C][4], uint32_t first, uint32_t my_len, uint32_t lane)
+{
+    constexpr int GROUP = C < 4 ? C : 4;
+    if constexpr (!FULL) asm volatile("" : "+v"(lane));  // (see set_padding)
+    auto scatter_group = [&](int c0, auto all) {
+        uint32_t to[GROUP][4];
+#pragma unroll
+        for (int c = 0; c < GROUP; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                to[c][k] = slot_bin_start(bin_start_middle, slot[c0 + c][k]) + (slot[c0 + c][k] >> 16);
+#pragma unroll
+        for (int c = 0; c < GROUP; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (!decltype(all)::value) {
+                    const uint32_t e = 256u * (uint32_t)(c0 + c) + 4u * lane + k;
+                    to[c][k] = e < my_len ? to[c][k] : first + e;
+                }
+                *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(grouped) + skewed_byte_offset(to[c][k])) =
+                    __float_as_uint(v[c0 + c][k]);
+            }
+    };
+#pragma unroll
+    for (int c0 = 0; c0 < C; c0 += GROUP) {
+        if (FULL || 256u * (uint32_t)(c0 + GROUP) <= my_len) scatter_group(c0, std::true_type{});
+        else if (256u * (uint32_t)c0 < my_len) scatter_group(c0, std::false_type{});
+    }
+}
+
 // The reload function of orq_encode for a range in memory: g = its first element; limit = the clipping threshold
 // (infinity: none).
 struct ReloadFromMemory {
@@ -995,7 +1142,7 @@ struct ReloadFromMemory {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint32_t e = 256u * c + 4u * (threadIdx.x & 63u) + (uint32_t)k;
-            y[k] = e < len ? fminf(fmaxf(g[e], -limit), limit) : 0.0f;
+            y[k] = e < len ? fminf(fmaxf(g[e], -limit), limit) : kNoElement;
         }
     }
 };
@@ -1498,51 +1645,19 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
 
     // ---- load (read once: bypass the caches); padding holds +0 and is never binned or encoded ----
     float v[C][4];
-    if (full) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + 256 * c + 4 * lane));
-            v[c][0] = q.x; v[c][1] = q.y; v[c][2] = q.z; v[c][3] = q.w;
-        }
-    } else if (len % 4u == 0u) {
-        // a bucket shorter than the wavefront's capacity whose length is a multiple of 4 (every bucket but a ragged
-        // last one): whole 16-byte loads, the lanes past the end read the bucket's first elements and drop them
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const uint32_t e = 256u * c + 4u * lane;
-            const bool inside = e < len;
-            const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + (inside ? e : 0u)));
-            v[c][0] = inside ? q.x : 0.0f; v[c][1] = inside ? q.y : 0.0f;
-            v[c][2] = inside ? q.z : 0.0f; v[c][3] = inside ? q.w : 0.0f;
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t e = 256u * c + 4u * lane + k;
-                v[c][k] = e < len ? g[e] : 0.0f;
-            }
-    }
+    load_range<C, FULL>(v, g, 0u, len, len, lane);
 
     float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if (CLIP && clip > 0.0f) {  // (the same for every thread of the grid)
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
         limit = clip_in_registers<4 * C>(flat, len, clip, [&](int j) { return full || (64u * (j & ~3) + 4u * lane + (j & 3) < len); });
+        if constexpr (!FULL) set_padding<C>(v, len, lane);
     }
 
     // ---- extremes ------------------------------------------------------------------------------
-    float lane_min = __uint_as_float(0x7F800000u), lane_max = __uint_as_float(0xFF800000u);
-    uint32_t lane_zeros = 0;
-    for_each_chunk<C, FULL>(len, [&](int c, auto all) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < len);
-            lane_min = fminf(lane_min, valid ? v[c][k] : __uint_as_float(0x7F800000u));
-            lane_max = fmaxf(lane_max, valid ? v[c][k] : __uint_as_float(0xFF800000u));
-            if constexpr (PB) lane_zeros += (valid && v[c][k] == 0.0f) ? 1u : 0u;
-        }
-    });
+    float lane_min, lane_max;
+    uint32_t lane_zeros;
+    lane_extremes<C, PB>(v, lane_min, lane_max, lane_zeros);
     const float bucket_min = wave_min(lane_min) + 0.0f;  // -0 -> +0
     const float bucket_max = wave_max(lane_max) + 0.0f;
     const uint32_t key_min = float_to_key(bucket_min), key_max = float_to_key(bucket_max);
@@ -1552,22 +1667,13 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
 
     float pb_level = 0.0f;
     if constexpr ((S > 2 && RULE != kEven) || PB) {
-        // ---- histogram: the returning LDS add hands every element its position inside its bin ------
+        // ---- histogram ------------------------------------------------------------------------------
 #pragma unroll
         for (int t = 0; t < PER; ++t) lds.bin_start[lane * PER + t] = 0u;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        uint32_t slot[C][4];  // bin | position inside the bin << 16 (pack_slot)
-        const float zero = opaque_zero();
-        for_each_chunk<C, FULL>(len, [&](int c, auto all) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < len);
-                const uint32_t bin = value_bin<HALF, SHIFT>(v[c][k] + zero, t_low);
-                slot[c][k] = 0u;
-                if (valid) slot[c][k] = pack_slot(atomicAdd(&lds.bin_start[bin], 1u), bin, (uint32_t)HALF);
-            }
-        });
+        uint32_t slot[C][4];
+        count_into_bins<C, FULL, HALF, SHIFT>(slot, v, lds.bin_start, t_low, len, lane);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 
@@ -1594,32 +1700,8 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 
-        // ---- scatter the values into their bins: the bin starts of a group of elements are all read before the
-        //      group's values are written (a read behind a write to the same LDS object would wait for it) ------
-        constexpr int GROUP = C < 4 ? C : 4;
-        auto scatter_group = [&](int c0, auto all) {
-#pragma unroll
-            for (int c = c0; c < c0 + GROUP; ++c)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < len);
-                    if (valid) slot[c][k] = slot_bin_start(&lds.bin_start[HALF], slot[c][k]) + (slot[c][k] >> 16);
-                }
-#pragma unroll
-            for (int c = c0; c < c0 + GROUP; ++c)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < len);
-                    if (valid)
-                        *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lds.grouped) + skewed_byte_offset(slot[c][k])) =
-                            __float_as_uint(v[c][k]);
-                }
-        };
-#pragma unroll
-        for (int c0 = 0; c0 < C; c0 += GROUP) {
-            if (full || 256u * (uint32_t)(c0 + GROUP) <= len) scatter_group(c0, std::true_type{});
-            else if (256u * (uint32_t)c0 < len) scatter_group(c0, std::false_type{});
-        }
+        // ---- scatter the values into their bins ---------------------------------------------------------
+        scatter_into_bins<C, FULL>(lds.grouped, &lds.bin_start[HALF], slot, v, 0u, len, lane);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 
@@ -1635,8 +1717,8 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
 #pragma unroll
                 for (uint32_t i = 0; i < BLOCK; ++i) {
                     const uint32_t position = lane * BLOCK + i;
-                    const float x = position < len ? __uint_as_float(lds.grouped[skewed(position)]) : 0.0f;
-                    part += (double)x;
+                    const float x = __uint_as_float(lds.grouped[skewed(position)]);  // (behind the elements: anything)
+                    part += (double)(FULL || position < len ? x : 0.0f);
                 }
                 incl = wave_inclusive_scan_f64(part);
                 lds.block_prefix[lane] = incl - part;
@@ -1767,15 +1849,7 @@ __device__ __forceinline__ void even_small_span(const float* __restrict__ g, uin
     constexpr uint32_t D = 256u / NB;          // elements per bucket
     const uint32_t lane = threadIdx.x & 63u;
     float v[1][4];
-    if (FULL || len % 4u == 0u) {
-        const bool inside = FULL || 4u * lane < len;
-        const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + (inside ? 4u * lane : 0u)));
-        v[0][0] = inside ? q.x : 0.0f; v[0][1] = inside ? q.y : 0.0f;
-        v[0][2] = inside ? q.z : 0.0f; v[0][3] = inside ? q.w : 0.0f;
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[0][k] = 4u * lane + k < len ? g[4u * lane + k] : 0.0f;
-    }
+    load_range<1, FULL>(v, g, 0u, len, len, lane, 0.0f);
     if (clip > 0.0f) clip_small_buckets<NB, FULL>(v[0], len, clip, lane);
     // largest magnitude of the lane's bucket (padding holds 0)
     uint32_t mag = 0;
@@ -1795,6 +1869,7 @@ __device__ __forceinline__ void even_small_span(const float* __restrict__ g, uin
 #pragma unroll
         for (int k = 0; k < S; ++k) levels[(size_t)(first_bucket + q) * S + k] = lv[k];
     }
+    if constexpr (!FULL) set_padding<1>(v, len, lane);
     orq_encode<1, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32, [&](uint32_t, float(&y)[4]) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) y[k] = v[0][k];
@@ -1984,15 +2059,7 @@ __device__ __forceinline__ void sorted_small_span(const float* __restrict__ g, u
     constexpr uint32_t D = 256u / NB;  // elements per bucket
     const uint32_t lane = threadIdx.x & 63u;
     float v[1][4];
-    if (FULL || len % 4u == 0u) {
-        const bool inside = FULL || 4u * lane < len;
-        const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + (inside ? 4u * lane : 0u)));
-        v[0][0] = inside ? q.x : 0.0f; v[0][1] = inside ? q.y : 0.0f;
-        v[0][2] = inside ? q.z : 0.0f; v[0][3] = inside ? q.w : 0.0f;
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[0][k] = 4u * lane + k < len ? g[4u * lane + k] : 0.0f;
-    }
+    load_range<1, FULL>(v, g, 0u, len, len, lane, 0.0f);
     if (clip > 0.0f) clip_small_buckets<NB, FULL>(v[0], len, clip, lane);
     const uint32_t q = lane / G;  // bucket of this lane inside the wavefront
     uint32_t count = D;           // elements of that bucket (the gradient may end inside or before it)
@@ -2203,6 +2270,7 @@ __device__ __forceinline__ void sorted_small_span(const float* __restrict__ g, u
 #pragma unroll
         for (int k = 0; k < S; ++k) levels[(size_t)(first_bucket + q) * S + k] = lv[k];
     }
+    if constexpr (!FULL) set_padding<1>(v, len, lane);
     orq_encode<1, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32, [&](uint32_t, float(&y)[4]) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) y[k] = v[0][k];
@@ -2277,32 +2345,7 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
     WaveTeam<W> team{lds.slots, wave, 0u};
 
     float v[C][4];
-    if (FULL) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const floatx4 q =
-                __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + first + 256 * c + 4 * lane));
-            v[c][0] = q.x; v[c][1] = q.y; v[c][2] = q.z; v[c][3] = q.w;
-        }
-    } else if (len % 4u == 0u) {
-        // whole 16-byte loads; the lanes past the end read the bucket's first elements and drop them
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const uint32_t e = 256u * c + 4u * lane;
-            const bool inside = e < my_len;
-            const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + (inside ? first + e : 0u)));
-            v[c][0] = inside ? q.x : 0.0f; v[c][1] = inside ? q.y : 0.0f;
-            v[c][2] = inside ? q.z : 0.0f; v[c][3] = inside ? q.w : 0.0f;
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t e = 256u * c + 4u * lane + k;
-                v[c][k] = e < my_len ? g[first + e] : 0.0f;
-            }
-    }
+    load_range<C, FULL>(v, g, first, len, my_len, lane);
 
     float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if (clip > 0.0f) {  // the same for every thread of the grid
@@ -2310,20 +2353,13 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
         limit = clip_in_registers<4 * C>(
             flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * lane + (j & 3) < my_len); },
             [&](double x) { return team.sum(wave_sum(x)); });
+        if constexpr (!FULL) set_padding<C>(v, my_len, lane);
     }
 
     // ---- extremes of the whole bucket ----------------------------------------------------------------
-    float lane_min = __uint_as_float(0x7F800000u), lane_max = __uint_as_float(0xFF800000u);
-    uint32_t lane_zeros = 0;
-    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-            lane_min = fminf(lane_min, valid ? v[c][k] : __uint_as_float(0x7F800000u));
-            lane_max = fmaxf(lane_max, valid ? v[c][k] : __uint_as_float(0xFF800000u));
-            if constexpr (PB) lane_zeros += (valid && v[c][k] == 0.0f) ? 1u : 0u;
-        }
-    });
+    float lane_min, lane_max;
+    uint32_t lane_zeros;
+    lane_extremes<C, PB>(v, lane_min, lane_max, lane_zeros);
     float bucket_min = wave_min(lane_min), bucket_max = wave_max(lane_max);
     uint32_t zeros = PB ? wave_sum_u32(lane_zeros) : 0u;
     {
@@ -2345,21 +2381,12 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
     const uint32_t t_low = __builtin_elementwise_sub_sat(t_max, (uint32_t)(HALF - 1));
 
     if constexpr ((S > 2 && RULE != kEven) || PB) {
-        // ---- histogram: the returning LDS add hands every element its position inside its bin ------------
+        // ---- histogram --------------------------------------------------------------------------------
         for (uint32_t i = tid; i < (uint32_t)B; i += THREADS) lds.bin_start[i] = 0u;
         if (tid == 0u) lds.tiny_flag = 0u;
         __syncthreads();
-        uint32_t slot[C][4];  // bin | position inside the bin << 16 (pack_slot)
-        const float zero = opaque_zero();
-        for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-                const uint32_t bin = value_bin<HALF, SHIFT>(v[c][k] + zero, t_low);
-                slot[c][k] = 0u;
-                if (valid) slot[c][k] = pack_slot(atomicAdd(&lds.bin_start[bin], 1u), bin, (uint32_t)HALF);
-            }
-        });
+        uint32_t slot[C][4];
+        count_into_bins<C, FULL, HALF, SHIFT>(slot, v, lds.bin_start, t_low, my_len, lane);
         __syncthreads();
 
         // ---- exclusive prefix over the bin counts (wavefront 0; lane l owns bins l*PER .. l*PER+PER-1) ------
@@ -2377,31 +2404,8 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
         }
         __syncthreads();
 
-        // ---- scatter the values into their bins (bin starts of a group of elements read before its writes) ------
-        constexpr int GROUP = C < 4 ? C : 4;
-        auto scatter_group = [&](int c0, auto all) {
-#pragma unroll
-            for (int c = c0; c < c0 + GROUP; ++c)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-                    if (valid) slot[c][k] = slot_bin_start(&lds.bin_start[HALF], slot[c][k]) + (slot[c][k] >> 16);
-                }
-#pragma unroll
-            for (int c = c0; c < c0 + GROUP; ++c)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-                    if (valid)
-                        *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lds.grouped) + skewed_byte_offset(slot[c][k])) =
-                            __float_as_uint(v[c][k]);
-                }
-        };
-#pragma unroll
-        for (int c0 = 0; c0 < C; c0 += GROUP) {
-            if (FULL || 256u * (uint32_t)(c0 + GROUP) <= my_len) scatter_group(c0, std::true_type{});
-            else if (256u * (uint32_t)c0 < my_len) scatter_group(c0, std::false_type{});
-        }
+        // ---- scatter the values into their bins ---------------------------------------------------------
+        scatter_into_bins<C, FULL>(lds.grouped, &lds.bin_start[HALF], slot, v, first, my_len, lane);
         __syncthreads();
 
         // ---- may the fp64 sums round?  (all threads look; combined before the records below are written) ----
@@ -2418,10 +2422,11 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
             if constexpr (SUMS) {
                 constexpr uint32_t BLOCK = OrqTeamLds<W, C>::BLOCK;
                 double part = 0.0;
+#pragma unroll 8
                 for (uint32_t i = 0; i < BLOCK; ++i) {
                     const uint32_t position = tid * BLOCK + i;
-                    const float x = position < len ? __uint_as_float(lds.grouped[skewed(position)]) : 0.0f;
-                    part += (double)x;
+                    const float x = __uint_as_float(lds.grouped[skewed(position)]);  // (behind the elements: anything)
+                    part += (double)(FULL || position < len ? x : 0.0f);
                 }
                 const double incl = wave_inclusive_scan_f64(part);
                 const TeamSlot* s = team.exchange(readlane_f64(incl, 63), 0u, 0u);
