@@ -37,30 +37,58 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 }
 
 // The same where c1 is wave-uniform: the first two rounds are then partly scalar (one product and one exclusive or of
-// each; written out because the compiler takes the scalar product for a vector one).
-__device__ __forceinline__ void philox4x32_10_uniform_c1(uint32_t c0, uint32_t c1, uint32_t k0, uint32_t k1, uint32_t (&r)[4])
+// each; written out because the compiler takes the scalar product for a vector one).  What depends on c1 and the key alone
+// is made once and held in scalar registers: the compiler would make it again behind every branch.
+struct PhiloxWords {
+    uint32_t first;       // k1
+    uint32_t second[2];   // of round 2: what x0 and x2 are combined with
+    uint32_t third;       // of round 3: what x2 is combined with
+    uint32_t k0[8], k1[7];  // the keys of rounds 3 .. 10 and 4 .. 10
+};
+
+__device__ __forceinline__ PhiloxWords philox_words(uint32_t c1, uint32_t k0, uint32_t k1)
 {
-    constexpr uint32_t kMulA = 0xD2511F53u, kMulB = 0xCD9E8D57u, kWeylA = 0x9E3779B9u, kWeylB = 0xBB67AE85u;
-    const uint64_t pa = (uint64_t)kMulA * c0;                    // round 1: c2 = c3 = 0
+    constexpr uint32_t kMulA = 0xD2511F53u, kWeylA = 0x9E3779B9u, kWeylB = 0xBB67AE85u;
+    PhiloxWords w;
     const uint64_t qa = (uint64_t)kMulA * uniform_u32(c1 ^ k0);  // round 2, the product of the uniform word
-    const uint64_t qb = (uint64_t)kMulB * ((uint32_t)(pa >> 32) ^ k1);
-    uint32_t x0 = (uint32_t)(qb >> 32) ^ (k0 + kWeylA), x1 = (uint32_t)qb;
-    uint32_t x2 = (uint32_t)pa ^ uniform_u32((uint32_t)(qa >> 32) ^ (k1 + kWeylB)), x3 = uniform_u32((uint32_t)qa);
-    k0 += 2u * kWeylA;
-    k1 += 2u * kWeylB;
+    w.first = k1;
+    w.second[0] = k0 + kWeylA;
+    w.second[1] = (uint32_t)(qa >> 32) ^ (k1 + kWeylB);
+    w.third = (uint32_t)qa ^ (k1 + 2u * kWeylB);
+#pragma unroll
+    for (uint32_t r = 0; r < 8; ++r) w.k0[r] = k0 + (r + 2u) * kWeylA;
+#pragma unroll
+    for (uint32_t r = 0; r < 7; ++r) w.k1[r] = k1 + (r + 3u) * kWeylB;
+    auto hold = [](uint32_t& x) {
+        x = uniform_u32(x);
+        asm("" : "+s"(x));
+    };
+    hold(w.first); hold(w.second[0]); hold(w.second[1]); hold(w.third);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) hold(w.k0[r]);
+#pragma unroll
+    for (int r = 0; r < 7; ++r) hold(w.k1[r]);
+    return w;
+}
+
+__device__ __forceinline__ void philox4x32_10_uniform_c1(uint32_t c0, const PhiloxWords& w, uint32_t (&r)[4])
+{
+    constexpr uint32_t kMulA = 0xD2511F53u, kMulB = 0xCD9E8D57u;
+    const uint64_t pa = (uint64_t)kMulA * c0;                    // round 1: c2 = c3 = 0
+    const uint64_t qb = (uint64_t)kMulB * ((uint32_t)(pa >> 32) ^ w.first);
+    uint32_t x0 = (uint32_t)(qb >> 32) ^ w.second[0], x1 = (uint32_t)qb;
+    uint32_t x2 = (uint32_t)pa ^ w.second[1], x3 = 0u;
 #pragma unroll
     for (int round = 2; round < 10; ++round) {
         const uint64_t ra = (uint64_t)kMulA * x0, rb = (uint64_t)kMulB * x2;
-        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(rb >> 32), x1, k0, 0x96);
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(rb >> 32), x1, w.k0[round - 2], 0x96);
         // (round 2: x3 and the key are both uniform)
-        const uint32_t n2 = round == 2 ? (uint32_t)(ra >> 32) ^ uniform_u32(x3 ^ k1)
-                                       : __builtin_amdgcn_bitop3_b32((uint32_t)(ra >> 32), x3, k1, 0x96);
+        const uint32_t n2 = round == 2 ? (uint32_t)(ra >> 32) ^ w.third
+                                       : __builtin_amdgcn_bitop3_b32((uint32_t)(ra >> 32), x3, w.k1[round > 2 ? round - 3 : 0], 0x96);
         x1 = (uint32_t)rb;
         x3 = (uint32_t)ra;
         x0 = n0;
         x2 = n2;
-        k0 += kWeylA;
-        k1 += kWeylB;
     }
     r[0] = x0; r[1] = x1; r[2] = x2; r[3] = x3;
 }
@@ -841,7 +869,8 @@ constexpr int kScaledWidthLevels = 4;
 // otherwise encode_is_plain() holds.
 template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL>
 __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (&lv)[S], const float (&width)[S - 1], uint32_t c0,
-                                              const EncodeRange& range, const NibbleTranspose& transpose, uint32_t lane)
+                                              const EncodeRange& range, const PhiloxWords& words,
+                                              const NibbleTranspose& transpose, uint32_t lane)
 {
     constexpr bool SCALED = !CAREFUL && S <= kScaledWidthLevels;
     constexpr int PLANES = 8 / GROUP;                // planes that share a register for the transpose
@@ -861,8 +890,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
             const uint64_t block = range.block + Layout::kBlocks * c + range.lane_block;
             philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), range.k0, range.k1, r);
         } else {
-            philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * c,
-                                     (uint32_t)(range.block >> 32), range.k0, range.k1, r);
+            philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * c, words, r);
         }
 #pragma unroll
         for (int k = 3; k >= 0; --k) {
@@ -955,7 +983,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         for (uint32_t c = 0; 256u * c < range.len; ++c) {
             float y[1][4];
             reload(c, y[0]);
-            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true>(y, lv, width, c, range, transpose, lane);
+            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true>(y, lv, width, c, range, PhiloxWords{}, transpose, lane);
         }
         return;
     }
@@ -963,13 +991,14 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
 #pragma unroll
         for (int k = 0; k < S - 1; ++k) width[k] *= 0x1p-24f;
     }
+    const PhiloxWords words = philox_words((uint32_t)(range.block >> 32), range.k0, range.k1);
     constexpr int GROUP = C < 8 ? C : 8;
 #pragma unroll
     for (int c0 = C - GROUP; c0 >= 0; c0 -= GROUP) {
         if constexpr (FILL != Fill::kAll) {
             if (256u * (uint32_t)c0 >= range.len) continue;  // nothing in these chunks: no words to write
         }
-        encode_chunks<Layout, GROUP, S, BITS, FILL, false>(&v[c0], lv, width, (uint32_t)c0, range, transpose, lane);
+        encode_chunks<Layout, GROUP, S, BITS, FILL, false>(&v[c0], lv, width, (uint32_t)c0, range, words, transpose, lane);
     }
 }
 
@@ -977,7 +1006,7 @@ template <int C, int S, int BITS, bool FULL, class ReloadFn>
 __device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
                                            uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32, ReloadFn reload)
 {
-    const EncodeRange range{len, (index_offset + begin) >> 2, threadIdx.x & 63u, 1u, (uint32_t)seed, (uint32_t)(seed >> 32),
+    const EncodeRange range{uniform_u32(len), (index_offset + begin) >> 2, threadIdx.x & 63u, 1u, (uint32_t)seed, (uint32_t)(seed >> 32),
                             codes32 + begin / 64 * (2 * BITS)};
     encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged>(v, lv, range, reload);
 }
