@@ -20,7 +20,7 @@ namespace ogq {
 // time).  Here a bucket takes at most 22 KB and the registers decide: 16 wavefronts of 128 registers fill a CU.
 //
 // Bound by vector-instruction issue (Philox and the rounding a third of it) and by the phases of a bucket that all its
-// wavefronts go through together.  ORQ-3, 25.6 M values, before -> after: buckets of 4096 40 -> 36 us, 8192 42 -> 36,
+// wavefronts go through together.  ORQ-3, 25.6 M values, before -> after: buckets of 8192 42 -> 36 us,
 // 16384 59 -> 44, 20480 105 -> 79, 32768 75 -> 60; 16 buckets of 32768 20 -> 15 us.  Workgroups that stay and fetch their
 // next bucket into the free LDS meanwhile were slower (32768: 72 us).
 // ----------------------------------------------------------------------------------------------
@@ -28,8 +28,8 @@ template <int W, int C>
 struct GatherLds {
     static constexpr int D = 256 * C * W;
     // 16 binades per sign; 35 elements of a bucket of Gaussian values in the fullest bin
-    static constexpr int B = D >= 32768 ? 4096 : D >= 16384 ? 2048 : D >= 8192 ? 1024 : 512;
-    static constexpr int SHIFT = D >= 32768 ? 16 : D >= 16384 ? 17 : D >= 8192 ? 18 : 19;  // magnitude bits dropped
+    static constexpr int B = D >= 32768 ? 4096 : D >= 16384 ? 2048 : 1024;
+    static constexpr int SHIFT = D >= 32768 ? 16 : D >= 16384 ? 17 : 18;  // magnitude bits dropped
     static constexpr uint32_t LIST = 1024;
     uint32_t bin_count[B];
     uint32_t list[LIST];  // the wanted bin's elements (bit patterns, -0 as +0), in any order
@@ -88,9 +88,13 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
     float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if (clip > 0.0f) {  // the same for every thread of the grid
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
+        uint32_t here = lane;
         limit = clip_in_registers<4 * C>(
-            flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * lane + (j & 3) < my_len); },
-            [&](double x) { return team.sum(wave_sum(x)); });
+            flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * here + (j & 3) < my_len); },
+            [&](double x) __attribute__((always_inline)) {
+                if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
+                return team.sum(wave_sum(x));
+            });
         if constexpr (!FULL) set_padding<C>(v, my_len, lane);
     }
 
@@ -100,7 +104,7 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
     lane_extremes<C, false>(v, low, high, unused_zeros);
     double part = 0.0;
     if constexpr (RULE == kOptimal) {
-        for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
+        for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 part += (double)(decltype(all)::value || 256u * c + 4u * lane + k < my_len ? v[c][k] : 0.0f);
@@ -125,7 +129,7 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
 
     // ---- histogram (the exchange's barrier lies behind the zeroing) --------------------------------------
     const float zero = opaque_zero();
-    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
+    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
@@ -205,7 +209,7 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
     const uint32_t from = sign | (u == 0u ? 0u : (t_low + u) << SHIFT);
     const uint32_t range = (u == HALF - 1u ? sign + 0x80000000u : sign | ((t_low + u + 1u) << SHIFT)) - from;
     uint32_t smallest = 0xFFFFFFFFu, largest = 0u;
-    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
+    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
@@ -250,7 +254,7 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
                         below += float_to_key(__uint_as_float(lds.list[i])) < candidate ? 1u : 0u;
                     below = wave_sum_u32(below);
                 } else {
-                    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
+                    for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);

@@ -1090,39 +1090,45 @@ __device__ __forceinline__ void lane_extremes(const float (&v)[C][4], float& low
 }
 
 // Counts the lane's elements into their bins; slot = bin | position inside the bin << 16 (pack_slot).  The returning LDS
-// add hands every element its position.  None of the answers is waited for before the last add has been sent, and the
+// add hands every element its position.  No answer is waited for before the last add of a group has been sent, and the
 // elements of the chunk that the range ends in take no branch: padding adds 0 to one bin per lane.
 template <int C, bool FULL, int HALF, int SHIFT>
 __device__ __forceinline__ void count_into_bins(uint32_t (&slot)[C][4], const float (&v)[C][4], uint32_t* bins, uint32_t t_low,
                                                 uint32_t my_len, uint32_t lane)
 {
-    uint32_t position[C][4];
+    // (a range that does not fill its registers: in groups of four chunks, for the sake of the register count)
+    constexpr int GROUP = FULL || C < 4 ? C : 4;
     const float zero = opaque_zero();
     if constexpr (!FULL) asm volatile("" : "+v"(lane));  // (see set_padding)
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-        if (FULL || 256u * (uint32_t)(c + 1) <= my_len) {
+    for (int c0 = 0; c0 < C; c0 += GROUP) {
+        uint32_t position[GROUP][4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                slot[c][k] = value_bin<HALF, SHIFT>(v[c][k] + zero, t_low);
-                position[c][k] = atomicAdd(&bins[slot[c][k]], 1u);
+        for (int i = 0; i < GROUP; ++i) {
+            const int c = c0 + i;
+            if (FULL || 256u * (uint32_t)(c + 1) <= my_len) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    slot[c][k] = value_bin<HALF, SHIFT>(v[c][k] + zero, t_low);
+                    position[i][k] = atomicAdd(&bins[slot[c][k]], 1u);
+                }
+            } else if (256u * (uint32_t)c < my_len) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const bool valid = 256u * c + 4u * lane + k < my_len;
+                    slot[c][k] = valid ? value_bin<HALF, SHIFT>(v[c][k] + zero, t_low) : lane;
+                    position[i][k] = atomicAdd(&bins[slot[c][k]], valid ? 1u : 0u);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) slot[c][k] = position[i][k] = 0u;
             }
-        } else if (256u * (uint32_t)c < my_len) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool valid = 256u * c + 4u * lane + k < my_len;
-                slot[c][k] = valid ? value_bin<HALF, SHIFT>(v[c][k] + zero, t_low) : lane;
-                position[c][k] = atomicAdd(&bins[slot[c][k]], valid ? 1u : 0u);
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) slot[c][k] = position[c][k] = 0u;
         }
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) slot[c0 + i][k] = pack_slot(position[i][k], slot[c0 + i][k], (uint32_t)HALF);
     }
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) slot[c][k] = pack_slot(position[c][k], slot[c][k], (uint32_t)HALF);
 }
 
 // Scatters the lane's elements into their bins.  The bin starts of a group of elements are all read before the group's
@@ -1134,7 +1140,7 @@ __device__ __forceinline__ void scatter_into_bins(uint32_t* grouped, const uint3
 {
     constexpr int GROUP = C < 4 ? C : 4;
     if constexpr (!FULL) asm volatile("" : "+v"(lane));  // (see set_padding)
-    auto scatter_group = [&](int c0, auto all) {
+    auto scatter_group = [&](int c0, auto all) __attribute__((always_inline)) {
         uint32_t to[GROUP][4];
 #pragma unroll
         for (int c = 0; c < GROUP; ++c)
@@ -1598,8 +1604,8 @@ __device__ __forceinline__ float orq_solve_levels(Lds& lds, PickFn pick, EdgeFn 
 
     // ---- level solves: greedy recursion (Algorithm 1), then re-solve sweeps ------------------
     [[maybe_unused]] const double bound = RULE == kOptimal ? uniform_f64(lds.sum_error_bound) : 0.0;  // (see floor_t_from_sums)
-    if constexpr (S > 2 && S <= 4 && RULE == kOptimal && std::is_same_v<decltype(lds.exact_limb), unsigned long long[1][kExactLimbs]>) {
-        // One wavefront, three or four levels: every solve with compile-time level indices and the level records in the
+    if constexpr (S > 2 && S <= 4 && RULE == kOptimal) {
+        // Three or four levels: every solve with compile-time level indices and the level records in the
         // wavefront's registers instead of LDS (greedy + S - 2 copies of the routine; with five levels the records no
         // longer fit the 128 registers).
         LevelRecords<S> st;
@@ -1753,7 +1759,7 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
                 lds.block_prefix[lane] = incl - part;
             } else if constexpr (RULE == kOptimal) {
                 double part = 0.0;
-                for_each_chunk<C, FULL>(len, [&](int c, auto all) {
+                for_each_chunk<C, FULL>(len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < len);
@@ -1848,7 +1854,7 @@ __device__ __forceinline__ void clip_small_buckets(float (&v)[4], uint32_t len, 
     if constexpr (!FULL) count = q * D < len ? (len - q * D < D ? len - q * D : D) : 1u;  // (no element: nothing is stored)
     clip_in_registers<4>(
         v, count, clip, [&](int j) { return FULL || 4u * lane + j < len; },
-        [&](double x) {
+        [&](double x) __attribute__((always_inline)) {
             x += dpp_f64<kDppXor1>(x);
             x += dpp_f64<kDppXor2>(x);
             x += dpp_f64<kDppHalfMirror>(x);
@@ -2326,7 +2332,7 @@ __global__ __launch_bounds__(4 * kWave) void sorted_small_kernel(const float* __
 }
 
 // ----------------------------------------------------------------------------------------------
-// ORQ and the other random-rounding rules with W = 2, 4 or 8 wavefronts of a workgroup owning one bucket (up
+// ORQ and the other random-rounding rules with W = 2 .. 16 wavefronts of a workgroup owning one bucket (up
 // to 32768 elements), wavefront w holding bucket elements [256 C w, 256 C (w + 1)) in the register layout of
 // orq_bucket.  All of them build the grouping of the whole bucket in LDS (histogram, bin
 // starts, scatter, fp64 block prefix) with workgroup barriers in between; the level solves are serial and run
@@ -2338,10 +2344,10 @@ struct OrqTeamLds {
     // bins, and magnitude bits dropped by the bin index (what is kept: the exponent and 3 .. 6 mantissa bits)
     static constexpr int B = D >= 16384 ? 2048 : D >= 8192 ? 1024 : D >= 4096 ? 512 : 256;
     static constexpr int SHIFT = D >= 16384 ? 17 : D >= 8192 ? 18 : D >= 4096 ? 19 : 20;
-    static constexpr int BLOCK = 4 * C;  // positions per entry of the fp64 block prefix: one entry per thread
+    static constexpr int BLOCK = C < 8 ? 32 : 4 * C;  // positions per entry of the fp64 block prefix
     uint32_t grouped[D + D / 64];
     uint32_t bin_start[B + 4];
-    double block_prefix[64 * W];  // fp64 sum of all positions before block i of BLOCK positions
+    double block_prefix[D / BLOCK];  // fp64 sum of all positions before block i of BLOCK positions
     double lvl_sum_lt[10];
     double lvl_sum_le[10];
     float lvl_value[10];
@@ -2379,9 +2385,13 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
     float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if (clip > 0.0f) {  // the same for every thread of the grid
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
+        uint32_t here = lane;
         limit = clip_in_registers<4 * C>(
-            flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * lane + (j & 3) < my_len); },
-            [&](double x) { return team.sum(wave_sum(x)); });
+            flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * here + (j & 3) < my_len); },
+            [&](double x) __attribute__((always_inline)) {
+                if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
+                return team.sum(wave_sum(x));
+            });
         if constexpr (!FULL) set_padding<C>(v, my_len, lane);
     }
 
@@ -2443,17 +2453,17 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
                 atomicOr(&lds.tiny_flag, 1u);
         }
 
-        // ---- fp64 prefix of the grouped values per block of 4C positions (thread t sums block t) ----------
+        // ---- fp64 prefix of the grouped values (thread t sums positions [4C t, 4C (t + 1))) ------------------
         // Skipped, but for the bucket's total, by the rules whose solves read no picked level's counts or sums.
         constexpr bool SUMS = (RULE == kOptimal && S > 3) || PB;
         {
             double total = 0.0;
             if constexpr (SUMS) {
-                constexpr uint32_t BLOCK = OrqTeamLds<W, C>::BLOCK;
+                constexpr uint32_t SPAN = 4u * C, SPANS = OrqTeamLds<W, C>::BLOCK / SPAN;
                 double part = 0.0;
 #pragma unroll 8
-                for (uint32_t i = 0; i < BLOCK; ++i) {
-                    const uint32_t position = tid * BLOCK + i;
+                for (uint32_t i = 0; i < SPAN; ++i) {
+                    const uint32_t position = tid * SPAN + i;
                     const float x = __uint_as_float(lds.grouped[skewed(position)]);  // (behind the elements: anything)
                     part += (double)(FULL || position < len ? x : 0.0f);
                 }
@@ -2465,10 +2475,10 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
                     if ((uint32_t)w < wave) before += s[w].sum;
                     total += s[w].sum;
                 }
-                lds.block_prefix[tid] = before + (incl - part);
+                if (tid % SPANS == 0u) lds.block_prefix[tid / SPANS] = before + (incl - part);
             } else if constexpr (RULE == kOptimal) {
                 double part = 0.0;
-                for_each_chunk<C, FULL>(my_len, [&](int c, auto all) {
+                for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
@@ -2502,8 +2512,15 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
 
         if constexpr (RULE == kOptimal && S > 2) {
             // ---- the level solves, spread over the first two wavefronts ------------------------------------------
-            orq_team_solve<S>(lds, [&](uint32_t rank) { return pick_rank_by_lookup<SUMS>(lds, rank, lane); }, wave, len, sweeps,
-                              lane);
+            // Up to four levels there is next to nothing to spread: wavefront 0 alone, with the records in its registers
+            // and no barrier per step (ORQ-4, 25.6 M values in buckets of 4096: 61 -> 55 us).
+            auto pick = [&](uint32_t rank) { return pick_rank_by_lookup<SUMS>(lds, rank, lane); };
+            if constexpr (S <= 4) {
+                if (wave == 0u) orq_solve_levels<S, RULE>(lds, pick, [](uint32_t) { return 0.0f; }, len, 0u, sweeps, lane);
+                __syncthreads();
+            } else {
+                orq_team_solve<S>(lds, pick, wave, len, sweeps, lane);
+            }
         } else {
             // ---- the other rules' solves are serial: wavefront 0 ---------------------------------------------------
             if (wave == 0u) {
@@ -2543,9 +2560,9 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
 
 // C = 8 (2048 elements per wavefront): the LDS of a CU holds the buckets of 16 wavefronts, so the kernel is held to the
 // 128 registers that let four wavefronts share a SIMD (one register more costs d = 8192 a quarter of its wavefronts);
-// BinGrad-pb would spill.
+// BinGrad-pb would spill.  W = C = 4: to the 72 registers that seven wavefronts can have.
 template <int W, int C, int S, int BITS, int RULE>
-__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(C == 8 && RULE != kPb ? 4 : 1))) void orq_team_kernel(const float* __restrict__ grad, size_t n,
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(RULE == kPb ? 1 : C == 8 ? 4 : C == 4 && W == 4 ? 7 : 1))) void orq_team_kernel(const float* __restrict__ grad, size_t n,
                                                             uint32_t bucket_size, uint32_t sweeps, float clip,
                                                             uint32_t num_buckets, uint64_t seed, uint64_t index_offset,
                                                             float* __restrict__ levels, uint32_t* __restrict__ codes32)
@@ -2673,12 +2690,26 @@ void launch_orq_levels(const float* g, size_t n, const ogq_params_t* p, uint32_t
     }
 }
 
-// Buckets above 4096 elements: W wavefronts per bucket.
+// Which rules and level counts the dispatch in rounding_part.hip gives to W wavefronts of 256 C elements per bucket (the
+// others are not compiled).
+template <int W, int C>
+constexpr bool team_serves(int S, int rule)
+{
+    if (W == 2) return C == 8 ? S >= 8 || rule == kPb : S >= 8;
+    if (W * C == 64 || W * C == 128) {
+        if (rule == kEven) return C == 8;
+        return C == 16 && (S != 3 || rule == kPb);
+    }
+    if (W == 4 && C == 8) return S != 3 || rule == kEven;
+    return true;
+}
+
 template <int W, int C, int S, int BITS, int RULE = kOptimal>
 void launch_orq_team(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    launch_kernel((orq_team_kernel<W, C, S, BITS, RULE>), dim3(nb), dim3(W * kWave), st, g, n, p->bucket_size,
-                       p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
+    if constexpr (team_serves<W, C>(S, RULE))
+        launch_kernel((orq_team_kernel<W, C, S, BITS, RULE>), dim3(nb), dim3(W * kWave), st, g, n, p->bucket_size,
+                      p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
 }
 
 template <int W, int C, int RULE>
@@ -2686,9 +2717,7 @@ void launch_team_paper_counts(const float* g, size_t n, const ogq_params_t* p, u
                               hipStream_t st)
 {
     switch (p->bits) {  // 2^(bits-1) + 1 levels
-        case 2:
-            if constexpr (RULE == kEven) launch_orq_team<W, C, 3, 2, RULE>(g, n, p, nb, lv, codes, st);
-            break;  // the other rules' three levels: orq_gather_kernel
+        case 2: launch_orq_team<W, C, 3, 2, RULE>(g, n, p, nb, lv, codes, st); break;
         case 3: launch_orq_team<W, C, 5, 3, RULE>(g, n, p, nb, lv, codes, st); break;
         default: launch_orq_team<W, C, 9, 4, RULE>(g, n, p, nb, lv, codes, st); break;
     }

@@ -848,3 +848,19 @@ def test_three_levels_in_large_buckets(scheme, d):
         for clip in (0.0, 2.5):
             parity.check_quantize(g[:n], d, 2, scheme, 1, seed=17, index_offset=64 * 5, clip_factor=clip,
                                   tag=f"three-levels-s{scheme}-d{d}-n{n}-c{clip}")
+
+
+# ------------------------------------------------------------------------------------------------
+# few and many buckets go to kernels with different numbers of wavefronts per bucket
+# ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("d,limit", [(448, 2560), (512, 2560), (960, 512), (1024, 512), (2048, 1280), (1984, 1280), (4096, 4096),
+                                     (8192, 256), (8128, 256), (16384, 0), (20480, 0)])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0),
+                                                (ogq.ORQ_PAPER, 4, 0), (ogq.BINGRAD_PB, 1, 0), (ogq.LINEAR, 3, 0),
+                                                (ogq.EVEN, 2, 0)])
+def test_few_and_many_buckets(scheme, bits, sweeps, d, limit):
+    rng = np.random.default_rng(d + bits)
+    for nb in ((limit, limit + 2) if limit else (5,)):
+        g = _rng_bucket(rng, nb * d - 29, "heavy")
+        parity.check_quantize(g, d, bits, scheme, sweeps, seed=23, buckets=_sample(nb, 24, nb) if nb > 24 else None,
+                              tag=f"count-s{scheme}-b{bits}-d{d}-nb{nb}", clip_factor=2.5 if nb == limit else 0.0)
