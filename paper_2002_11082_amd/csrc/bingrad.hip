@@ -20,6 +20,11 @@ __device__ __forceinline__ float reread(float x)
 // and words belong to the whole bucket, of which this wavefront holds the 64*E elements from `first_element` on;
 // the wavefront with first_element == 0 writes the levels.  SIGN: Scaled SignSGD instead (first equation of
 // Section 3.2): levels -m, +m with m the mean magnitude of the bucket, index = (v >= 0).
+//
+// Where elements are missing, padding holds 0, which adds nothing to a sum, its
+// bits are cleared when the words are stored, and where 0 lies below the threshold its number is taken off the count.
+// (With bounds tests per element instead: one bucket of 20480 elements
+// 7.6 us, of 3008 with two updates 6.9, now 6.9, 5.3; 25.6 M values in buckets of 1344 34 -> 24 us.)
 template <int E, bool FULL, bool CLIP, bool SIGN, class Team>
 __device__ __forceinline__ void bingrad_bucket(Team team, uint32_t first_element, const float* __restrict__ g,
                                                uint32_t len, uint32_t iters, float clip, float* __restrict__ levels2,
@@ -28,15 +33,32 @@ __device__ __forceinline__ void bingrad_bucket(Team team, uint32_t first_element
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t first = first_element + lane;
     float v[E];
+    if constexpr (FULL) {
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const uint32_t e = first + 64u * j;
-        v[j] = (FULL || e < len) ? __builtin_nontemporal_load(g + e) : 0.0f;  // read once: bypass the caches
+        for (int j = 0; j < E; ++j) v[j] = __builtin_nontemporal_load(g + first + 64u * j);  // read once: bypass the caches
+    } else if (first_element >= len) {
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = 0.0f;
+    } else {
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const uint32_t e = first + 64u * j;
+            v[j] = __builtin_nontemporal_load(g + (e < len ? e : 0u));
+        }
+        uint32_t here = first;
+        if constexpr (E > 16) asm volatile("" : "+v"(here));  // (the loads' lane masks would not fit the scalar registers)
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = here + 64u * j < len ? v[j] : 0.0f;
     }
-    if constexpr (CLIP)
-        clip_in_registers<E>(
-            v, len, clip, [&](int j) { return FULL || (first + 64u * j < len); },
-            [&](double x) { return team.sum(wave_sum(x)); });
+    const uint32_t padding = 64u * E * Team::kSize - len;
+    if constexpr (CLIP) {
+        uint32_t here = first;
+        const auto bucket_sum = [&](double x) {
+            if constexpr (!FULL && E > 16) asm volatile("" : "+v"(here));  // (the first pass's lane masks would not fit the scalar registers)
+            return team.sum(wave_sum(x));
+        };
+        clip_in_registers<E>(v, len, clip, [&](int j) { return FULL || here + 64u * j < len; }, bucket_sum);
+    }
 
     double part = 0.0;
     float mag = 0.0f;
@@ -61,8 +83,7 @@ __device__ __forceinline__ void bingrad_bucket(Team team, uint32_t first_element
     if constexpr (SIGN) {
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-            const bool valid = FULL || (first + 64u * j < len);
-            const uint64_t hi_mask = __ballot(valid && !(v[j] < 0.0f));
+            const uint64_t hi_mask = ~__ballot(v[j] < 0.0f);
             word_lo = writelane(word_lo, (uint32_t)hi_mask, j);
             word_hi = writelane(word_hi, (uint32_t)(hi_mask >> 32), j);
         }
@@ -74,12 +95,10 @@ __device__ __forceinline__ void bingrad_bucket(Team team, uint32_t first_element
         uint32_t below = 0;
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-            const bool valid = FULL || (first + 64u * j < len);
             // (with 64 registers of data the fp64 copies the compiler would keep from the first pass do not fit)
             const float x = E > 32 ? reread(v[j]) : v[j];
-            const bool lo = valid && (x < b0);
-            const uint64_t lo_mask = __ballot(lo);
-            const uint64_t hi_mask = FULL ? ~lo_mask : __ballot(valid && !lo);
+            const bool lo = x < b0;
+            const uint64_t hi_mask = ~__ballot(lo);
             below += lo ? 1u : 0u;
             s_lo += (double)(lo ? x : 0.0f);
             word_lo = writelane(word_lo, (uint32_t)hi_mask, j);
@@ -88,13 +107,13 @@ __device__ __forceinline__ void bingrad_bucket(Team team, uint32_t first_element
         s_lo = wave_sum(s_lo);
         uint32_t n_lo = wave_sum_u32(below);
         team.sum_and_count(s_lo, n_lo);
+        if ((!FULL || Team::kSize > 1) && 0.0f < b0) n_lo -= padding;
         double s_hi = total - s_lo;
         if (!(fabs(s_hi) >= (double)trust_above)) {
             double direct = 0.0;
 #pragma unroll
             for (int j = 0; j < E; ++j) {
-                const bool valid = FULL || (first + 64u * j < len);
-                direct += (double)((valid && !(v[j] < b0)) ? v[j] : 0.0f);
+                direct += (double)(!(v[j] < b0) ? v[j] : 0.0f);
             }
             s_hi = team.sum(wave_sum(direct));
         }
@@ -120,9 +139,14 @@ __device__ __forceinline__ void bingrad_bucket(Team team, uint32_t first_element
         levels2[0] = (float)b_lo;
         levels2[1] = (float)b_hi;
     }
-    const uint32_t n_words = (len + 63u) / 64u;
     const uint32_t word = first_element / 64u + lane;
-    if (lane < (uint32_t)E && word < n_words) words[word] = ((uint64_t)word_hi << 32) | word_lo;
+    if constexpr (FULL) {
+        if (lane < (uint32_t)E) words[word] = ((uint64_t)word_hi << 32) | word_lo;
+    } else if (lane < (uint32_t)E && 64u * word < len) {
+        const uint32_t left = len - 64u * word;
+        const uint64_t valid = left < 64u ? (1ull << left) - 1ull : ~0ull;
+        words[word] = (((uint64_t)word_hi << 32) | word_lo) & valid;
+    }
 }
 
 constexpr int kBinGradWaves = 2;  // buckets per workgroup
@@ -168,8 +192,7 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))
     const uint32_t wave = uniform_u32(threadIdx.x >> 6);
     const WaveTeam<W> team{slots, wave, 0u};
     constexpr uint32_t PER_WAVE = 64u * E;
-    // A wavefront whose 64 E elements all lie inside the bucket skips the per-element bounds tests.  Both variants
-    // reach the same combines in the same order (every branch around one depends on combined values only).
+    // Both variants reach the same combines in the same order (every branch around one depends on combined values only).
     if (PER_WAVE * (wave + 1u) <= len) bingrad_bucket<E, true, CLIP, SIGN>(team, PER_WAVE * wave, g, len, iters, clip, lv, w);
     else bingrad_bucket<E, false, CLIP, SIGN>(team, PER_WAVE * wave, g, len, iters, clip, lv, w);
 }
@@ -317,13 +340,22 @@ constexpr uint32_t kMinChunks = 2048;
 
 template <int NB, bool SIGN>
 __global__ __launch_bounds__(kWave* kBinGradWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void bingrad_chunk_kernel(
-    const float* __restrict__ grad, uint32_t num_chunks, uint32_t iters, float* __restrict__ levels,
+    const float* __restrict__ grad, uint32_t num_chunks, uint32_t rest, uint32_t iters, float* __restrict__ levels,
     uint64_t* __restrict__ codes)
 {
     constexpr int R = kChunk / 64, E = R / NB;
     constexpr uint32_t D = 64u * E;             // bucket size
     constexpr uint32_t kFreeBits = 64u / NB - 1u;  // lane bits that select no bucket; bit 0 is always among them
-    const uint32_t chunk = uniform_u32(blockIdx.x * kBinGradWaves + (threadIdx.x >> 6));
+    uint32_t chunk = uniform_u32(blockIdx.x * kBinGradWaves + (threadIdx.x >> 6));
+    // The first wavefronts take the buckets behind the last whole chunk (`rest` elements), one each.
+    const uint32_t rest_buckets = (rest + D - 1u) / D;
+    if (chunk < rest_buckets) {
+        const uint32_t bucket = chunk, len = rest - bucket * D < D ? rest - bucket * D : D;
+        const size_t begin = (size_t)num_chunks * kChunk + bucket * D;
+        bingrad_bucket<E, false, false, SIGN>(OneWave{}, 0u, grad + begin, len, iters, 0.0f, levels + begin / D * 2, codes + begin / 64);
+        return;
+    }
+    chunk -= rest_buckets;
     if (chunk >= num_chunks) return;
     const uint32_t lane = threadIdx.x & 63u;
     const float* g = grad + (size_t)chunk * kChunk;
@@ -482,45 +514,42 @@ void launch_bingrad_team(const float* g, size_t n, const ogq_params_t* p, uint32
 }
 
 template <int NB>
-void launch_bingrad_chunks_of(const float* g, uint32_t chunks, const ogq_params_t* p, float* lv, uint64_t* words,
+void launch_bingrad_chunks_of(const float* g, uint32_t chunks, uint32_t rest, const ogq_params_t* p, float* lv, uint64_t* words,
                               hipStream_t st)
 {
-    const dim3 grid((chunks + kBinGradWaves - 1) / kBinGradWaves), block(kWave * kBinGradWaves);
+    const uint32_t waves = chunks + (rest + p->bucket_size - 1) / p->bucket_size;
+    const dim3 grid((waves + kBinGradWaves - 1) / kBinGradWaves), block(kWave * kBinGradWaves);
     if (p->scheme == OGQ_SCALED_SIGN)
-        launch_kernel((bingrad_chunk_kernel<NB, true>), grid, block, st, g, chunks, p->level_iters, lv, words);
+        launch_kernel((bingrad_chunk_kernel<NB, true>), grid, block, st, g, chunks, rest, p->level_iters, lv, words);
     else
-        launch_kernel((bingrad_chunk_kernel<NB, false>), grid, block, st, g, chunks, p->level_iters, lv, words);
+        launch_kernel((bingrad_chunk_kernel<NB, false>), grid, block, st, g, chunks, rest, p->level_iters, lv, words);
 }
 
-void launch_bingrad_chunks(const float* g, uint32_t chunks, const ogq_params_t* p, float* lv, void* codes, hipStream_t st)
+void launch_bingrad_chunks(const float* g, uint32_t chunks, uint32_t rest, const ogq_params_t* p, float* lv, void* codes,
+                           hipStream_t st)
 {
     uint64_t* words = static_cast<uint64_t*>(codes);
     switch (kChunk / p->bucket_size) {
-        case 2: launch_bingrad_chunks_of<2>(g, chunks, p, lv, words, st); break;
-        case 4: launch_bingrad_chunks_of<4>(g, chunks, p, lv, words, st); break;
-        case 8: launch_bingrad_chunks_of<8>(g, chunks, p, lv, words, st); break;
-        case 16: launch_bingrad_chunks_of<16>(g, chunks, p, lv, words, st); break;
-        default: launch_bingrad_chunks_of<32>(g, chunks, p, lv, words, st); break;
+        case 2: launch_bingrad_chunks_of<2>(g, chunks, rest, p, lv, words, st); break;
+        case 4: launch_bingrad_chunks_of<4>(g, chunks, rest, p, lv, words, st); break;
+        case 8: launch_bingrad_chunks_of<8>(g, chunks, rest, p, lv, words, st); break;
+        case 16: launch_bingrad_chunks_of<16>(g, chunks, rest, p, lv, words, st); break;
+        default: launch_bingrad_chunks_of<32>(g, chunks, rest, p, lv, words, st); break;
     }
 }
 
 void launch_two_level(const float* g, size_t n, const ogq_params_t* p, float* lv, void* codes, hipStream_t st)
 {
     const uint32_t d = p->bucket_size;
-    // Whole chunks of 2048 elements go to the kernel that packs several buckets into a wavefront; what
-    // is left (fewer than 2048 elements) takes the one-bucket-per-wavefront kernel below.  Buckets of
-    // 512 and 1024 elements stay with that kernel for gradients too short to give every SIMD a chunk
+    // Bucket sizes that divide 2048: the kernel that packs the buckets of 2048 elements into a wavefront (and gives what is
+    // left, fewer than 2048 elements, one wavefront per bucket: a launch of its own cost 2.8 us).  Buckets of
+    // 512 and 1024 elements stay with the one-bucket kernel for gradients too short to give every SIMD a chunk
     // or two (it was the faster one below about four million elements).
     const size_t chunks = n / kChunk;
     if (p->clip_factor == 0.0f && d <= kChunk / 2 && kChunk % d == 0 && chunks > 0 &&
         (d <= 256 || chunks >= kMinChunks)) {
-        launch_bingrad_chunks(g, (uint32_t)chunks, p, lv, codes, st);
-        const size_t done = chunks * kChunk;
-        if (done == n) return;
-        g += done;
-        lv += done / d * 2;
-        codes = static_cast<uint64_t*>(codes) + done / 64;
-        n -= done;
+        launch_bingrad_chunks(g, (uint32_t)chunks, (uint32_t)(n % kChunk), p, lv, codes, st);
+        return;
     }
     const uint32_t nb = (uint32_t)(n / d + (n % d != 0));
     const uint32_t regs = d / 64;
@@ -536,6 +565,10 @@ void launch_two_level(const float* g, size_t n, const ogq_params_t* p, float* lv
         // the clipping passes need the registers a second 2048 elements per wavefront would take
         if (regs <= 256) launch_bingrad_team<8>(g, n, p, nb, lv, codes, st);
         else launch_bingrad_team<16>(g, n, p, nb, lv, codes, st);
+    } else if (regs <= 256 && (nb <= 512 || (regs == 256 && (p->level_iters == 0 || p->scheme == OGQ_SCALED_SIGN)))) {
+        // Twice the wavefronts per bucket: faster while there are at most two buckets per CU (up to 8 %), and at any number
+        // (2 to 10 %) where every register holds an element and one pass over the bucket is all there is.
+        launch_bingrad_team<8>(g, n, p, nb, lv, codes, st);
     } else if (regs <= 256) launch_bingrad_team<4, 64>(g, n, p, nb, lv, codes, st);
     else launch_bingrad_team<8, 64>(g, n, p, nb, lv, codes, st);
 }

@@ -864,3 +864,13 @@ def test_few_and_many_buckets(scheme, bits, sweeps, d, limit):
         g = _rng_bucket(rng, nb * d - 29, "heavy")
         parity.check_quantize(g, d, bits, scheme, sweeps, seed=23, buckets=_sample(nb, 24, nb) if nb > 24 else None,
                               tag=f"count-s{scheme}-b{bits}-d{d}-nb{nb}", clip_factor=2.5 if nb == limit else 0.0)
+
+
+@pytest.mark.parametrize("scheme,iters", [(ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 2), (ogq.SCALED_SIGN, 0)])
+@pytest.mark.parametrize("d,nb", [(64, 33), (128, 17), (256, 9), (512, 8200), (1024, 4100), (12288, 512), (12288, 513), (16384, 513)])
+def test_bingrad_rest_and_bucket_counts(d, nb, scheme, iters):
+    """Whole 2048-element chunks and what is left of them in one launch; the counts where large buckets change kernels."""
+    rng = np.random.default_rng(d)
+    for n in (nb * d, nb * d - 1, nb * d - d // 2 - 3):
+        g = _rng_bucket(rng, n, "shifted" if n % 2 else "heavy")
+        parity.check_quantize(g, d, 1, scheme, iters, buckets=_sample((n + d - 1) // d, 40, n), tag=f"rest-s{scheme}-d{d}-n{n}")
