@@ -11,6 +11,7 @@
 
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdio>
@@ -124,7 +125,8 @@ PyObject* give_back(PyObject* given, const at::Tensor& made)
     return THPVariable_Wrap(made);
 }
 
-// Runs f() and turns what it throws into a Python error.
+// Runs f() and turns what it throws into a Python error: torch's own exceptions (an allocation may raise them) into the types
+// that torch gives them, so that a caller sees torch.OutOfMemoryError, or the error of a Python mode that was asked.
 template <class F>
 PyObject* guarded(F f)
 {
@@ -132,8 +134,8 @@ PyObject* guarded(F f)
         require(bound.check != nullptr, "bind() comes first");
         return f();
     } catch (const PythonError&) {
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (const std::exception&) {
+        torch::translate_exception_to_python(std::current_exception());
     }
     return nullptr;
 }
