@@ -140,7 +140,7 @@ def _load_marshal():
     L = lib()
     addresses = [ctypes.cast(f, ctypes.c_void_p).value
                  for f in (L.ogq_quantize, L.ogq_dequantize_average, L.ogq_levels_count, L.ogq_codes_bytes)]
-    module.bind(*addresses, torch._C._cuda_getCurrentRawStream, _check)
+    module.bind(*addresses, torch._C._cuda_getCurrentRawStream, _check, Params)
     _marshal = module
     return module
 

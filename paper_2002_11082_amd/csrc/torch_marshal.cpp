@@ -33,6 +33,7 @@ struct Bound {
     CountFn levels_count = nullptr, codes_bytes = nullptr;
     PyObject* raw_stream = nullptr;  // callable: device index -> address of torch's current stream
     PyObject* check = nullptr;       // callable: raises OgqError for a status other than 0
+    PyTypeObject* params = nullptr;  // the class of the caller's parameters
 } bound;
 
 // Thrown where the Python error is already set.
@@ -75,9 +76,14 @@ void holds(const at::Tensor& t, at::ScalarType dtype, size_t elements, const cha
     throw PythonError{};
 }
 
-// The caller's Params (a ctypes structure) through the buffer protocol.
+// The caller's Params (a ctypes structure) through the buffer protocol.  Nothing else is taken, whatever its size: its bytes
+// would be read as parameters.
 ogq_params_t params_of(PyObject* o)
 {
+    if (!PyObject_TypeCheck(o, bound.params)) {
+        PyErr_Format(PyExc_TypeError, "params: expected Params, got %s", Py_TYPE(o)->tp_name);
+        throw PythonError{};
+    }
     Py_buffer view;
     if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw PythonError{};
     ogq_params_t p;
@@ -249,10 +255,14 @@ PyObject* dequantize_average(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     });
 }
 
-// bind(address of ogq_quantize, of ogq_dequantize_average, of ogq_levels_count, of ogq_codes_bytes, raw_stream, check)
+// bind(address of ogq_quantize, of ogq_dequantize_average, of ogq_levels_count, of ogq_codes_bytes, raw_stream, check, Params)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t nargs)
 {
-    if (!argument_count(nargs, 6)) return nullptr;
+    if (!argument_count(nargs, 7)) return nullptr;
+    if (!PyType_Check(args[6])) {
+        PyErr_SetString(PyExc_TypeError, "Params: expected a class");
+        return nullptr;
+    }
     void* address[4];
     for (int i = 0; i < 4; ++i) {
         address[i] = PyLong_AsVoidPtr(args[i]);
@@ -267,10 +277,13 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     bound.codes_bytes = reinterpret_cast<CountFn>(address[3]);
     Py_INCREF(args[4]);
     Py_INCREF(args[5]);
+    Py_INCREF(args[6]);
     Py_XDECREF(bound.raw_stream);
     Py_XDECREF(bound.check);
+    Py_XDECREF(reinterpret_cast<PyObject*>(bound.params));
     bound.raw_stream = args[4];
     bound.check = args[5];
+    bound.params = reinterpret_cast<PyTypeObject*>(args[6]);
     Py_RETURN_NONE;
 }
 

@@ -1,5 +1,7 @@
-"""What the two calls on tensors do with errors that torch raises while they allocate outputs.  A program that catches
-torch.OutOfMemoryError to free memory and try again has to see that type, as from torch.empty itself."""
+"""The two calls on tensors: the errors that torch raises while they allocate outputs, and what they take for parameters.
+A program that catches torch.OutOfMemoryError to free memory and try again has to see that type, as from torch.empty itself."""
+import ctypes
+
 import pytest
 import torch
 from torch._subclasses.fake_tensor import FakeTensorMode
@@ -34,6 +36,23 @@ def test_an_error_while_allocating_outputs_keeps_its_type(error):
         with RefuseToAllocate(error), pytest.raises(type(error)) as caught:
             call()
         assert caught.value is error
+
+
+class OtherStructure(ctypes.Structure):
+    _fields_ = [("words", ctypes.c_uint32 * 10)]
+
+
+@pytest.mark.parametrize("params", [bytes(40), bytearray(40), OtherStructure(), None, 512],
+                         ids=["bytes", "bytearray", "structure", "none", "number"])
+def test_only_params_are_taken_for_parameters(params):
+    """Forty bytes of anything else were read as a bucket size, a scheme and so on."""
+    with FakeTensorMode():
+        grad = torch.empty(4096, device="cuda")
+        codes = torch.empty(128, dtype=torch.int64, device="cuda")
+    with pytest.raises(TypeError):
+        ogq.ogq_quantize(grad, params)
+    with pytest.raises(TypeError):
+        ogq.ogq_dequantize_average([codes], [grad], 4096, params)
 
 
 @pytest.mark.gpu
