@@ -2690,8 +2690,9 @@ void launch_orq_levels(const float* g, size_t n, const ogq_params_t* p, uint32_t
     }
 }
 
-// Which rules and level counts the dispatch in rounding_part.hip gives to W wavefronts of 256 C elements per bucket (the
-// others are not compiled).
+// Which rules and level counts the dispatch in rounding_part.hip gives to W wavefronts of 256 C elements per bucket.  The
+// others are not compiled, and asking for one fails like a launch that the runtime refuses: a call must not return success
+// over outputs that nothing has written.
 template <int W, int C>
 constexpr bool team_serves(int S, int rule)
 {
@@ -2710,6 +2711,8 @@ void launch_orq_team(const float* g, size_t n, const ogq_params_t* p, uint32_t n
     if constexpr (team_serves<W, C>(S, RULE))
         launch_kernel((orq_team_kernel<W, C, S, BITS, RULE>), dim3(nb), dim3(W * kWave), st, g, n, p->bucket_size,
                       p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
+    else
+        launch_status() = hipErrorInvalidDeviceFunction;
 }
 
 template <int W, int C, int RULE>

@@ -1,0 +1,72 @@
+"""Test infrastructure: makes the calls below on the built library, with record_launches.cpp preloaded in place of the HIP
+runtime, and prints what they launched.  Run as a child process by test_dispatch.py; argument: the stand-in's path.
+
+Every scheme and width, every bucket size, clipping on and off, every power of two of buckets and its neighbours (the limits
+of the dispatch are at or near powers of two, or listed), whole and ragged last buckets; the decoder with every number of
+workers at which it changes its form."""
+import ctypes
+import json
+import sys
+
+import paper_2002_11082_amd as ogq
+
+SCHEMES = ((ogq.BINGRAD_B, (1,)), (ogq.ORQ, (1, 2, 3)), (ogq.BINGRAD_PB, (1,)), (ogq.ORQ_PAPER, (2, 3, 4)), (ogq.SCALED_SIGN, (1,)),
+           (ogq.EVEN, (2, 3, 4)), (ogq.LINEAR, (2, 3, 4)))
+SIZES = range(64, 32768 + 1, 64)
+BUCKETS = sorted({max(1, limit + step) for limit in [1 << k for k in range(17)] + [1280, 2560, 65536] for step in (-1, 0, 1)})
+WORKERS = (1, 2, 3, 4, 5, 8, 9, 64)
+ADDRESS = 0x10000  # aligned; never looked at
+
+
+def main():
+    stub = ctypes.CDLL(sys.argv[1])
+    for name in ("recorded_launches", "recorded_unknown", "recorded_launches_of"):
+        getattr(stub, name).restype = ctypes.c_uint64
+    for name in ("recorded_kernels", "recorded_last"):
+        getattr(stub, name).restype = ctypes.c_size_t
+    stub.recorded_name.restype = ctypes.c_char_p
+    stub.recorded_name.argtypes = stub.recorded_launches_of.argtypes = [ctypes.c_size_t]
+    lib = ogq.lib()
+    quantize, average = lib.ogq_quantize, lib.ogq_dequantize_average
+    wrong, decoders = [], {}
+    seen = stub.recorded_launches()
+
+    def once(what, status):
+        nonlocal seen
+        now = stub.recorded_launches()
+        if status != 0 or now != seen + 1:
+            wrong.append([what, status, now - seen])
+        seen = now
+
+    calls = 0
+    for scheme, widths in SCHEMES:
+        for bits in widths:
+            for d in SIZES:
+                for clip in (0.0, 2.5):
+                    p = ogq.make_params(d, bits, scheme, 0, 0, 0, clip)
+                    by = ctypes.byref(p)
+                    for nb in BUCKETS:
+                        for n in (nb * d, nb * d - 1):
+                            once(f"quantize scheme {scheme} bits {bits} d {d} n {n} clip {clip}",
+                                 quantize(ADDRESS, n, by, ADDRESS, ADDRESS, None))
+                            calls += 1
+    pointers = (ctypes.c_void_p * 64)(*[ADDRESS] * 64)
+    at = ctypes.addressof(pointers)
+    for scheme, bits in ((ogq.ORQ, 1), (ogq.ORQ, 2), (ogq.ORQ, 3), (ogq.ORQ_PAPER, 2), (ogq.ORQ_PAPER, 3), (ogq.ORQ_PAPER, 4)):
+        for d in SIZES:
+            by = ctypes.byref(ogq.make_params(d, bits, scheme))
+            for workers in WORKERS:
+                once(f"decode scheme {scheme} bits {bits} d {d} workers {workers}",
+                     average(at, at, workers, 100 * d + 1, by, ADDRESS, None))
+                decoders.setdefault(stub.recorded_last(), set()).add(d)
+                calls += 1
+    once("probe_read", lib.ogq_probe_read(ADDRESS, 64, ADDRESS, None))
+    once("probe_copy", lib.ogq_probe_copy(ADDRESS, ADDRESS, 64, None))
+    names = [stub.recorded_name(i).decode() for i in range(stub.recorded_kernels())]
+    print(json.dumps({"calls": calls, "wrong": wrong[:20], "unknown": stub.recorded_unknown(),
+                      "launches": {name: stub.recorded_launches_of(i) for i, name in enumerate(names)},
+                      "decoded_sizes": {names[i]: sorted(sizes) for i, sizes in decoders.items()}}))
+
+
+if __name__ == "__main__":
+    main()

@@ -1,0 +1,45 @@
+"""Which kernel a call ends in, without a GPU: a call that the entry points accept is one kernel launch or an error, and
+none may return success without having launched anything."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+STUBS = os.path.join(ROOT, "tests", "host_stubs")
+
+
+def test_a_combination_that_is_not_compiled_is_an_error(tmp_path):
+    from paper_2002_11082_amd import build
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    program = str(tmp_path / "team_without_kernel")
+    flags = [f for f in build.HIPCC_FLAGS if f != "-O3"]
+    subprocess.run([hipcc, *flags, "-O0", os.path.join(STUBS, "team_without_kernel.hip"), "-o", program], check=True, timeout=300)
+    res = subprocess.run([program], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+@pytest.fixture(scope="module")
+def recorded(tmp_path_factory):
+    """The launches of every_call.py on the built library."""
+    from paper_2002_11082_amd import binding, build
+    if not os.path.exists(binding.LIB_PATH):
+        build.build()
+    stub = str(tmp_path_factory.mktemp("record") / "record_launches.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", os.path.join(STUBS, "record_launches.cpp"), "-o", stub], check=True)
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = ":".join(x for x in (stub, env.get("LD_PRELOAD")) if x)
+    env["PYTHONPATH"] = ROOT + os.pathsep + env.get("PYTHONPATH", "")
+    res = subprocess.run([sys.executable, os.path.join(STUBS, "every_call.py"), stub], cwd=ROOT, env=env, capture_output=True,
+                         text=True, timeout=300)
+    assert res.returncode == 0, res.stdout + res.stderr
+    return json.loads(res.stdout)
+
+
+def test_every_accepted_call_is_one_launch(recorded):
+    assert recorded["calls"] > 1_000_000
+    assert recorded["wrong"] == [] and recorded["unknown"] == 0
