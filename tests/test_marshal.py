@@ -59,15 +59,18 @@ def test_only_params_are_taken_for_parameters(params):
 def test_out_of_memory_is_torch_out_of_memory():
     """The allocator's own refusal (a limit on this process's share of the memory, nothing is exhausted), and the calls
     work again once it is lifted."""
-    # (packed words of 16 MB: below 10 MB the allocator rounds its blocks up, and the rest of one could serve the next)
     dev, n = "cuda:0", 128 << 20
     p = ogq.make_params(2048, 1, ogq.BINGRAD_B)
     grad = torch.randn(n, device=dev)
     levels, codes = ogq.ogq_quantize(grad, p)
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
+    held = []
     torch.cuda.set_per_process_memory_fraction(1e-6, 0)
     try:
+        with pytest.raises(torch.OutOfMemoryError):  # what the allocator still has, in pieces of the smaller output's size
+            while True:
+                held.append(torch.empty_like(codes))
         with pytest.raises(torch.OutOfMemoryError):
             ogq.ogq_quantize(grad, p, levels)
         with pytest.raises(torch.OutOfMemoryError):
