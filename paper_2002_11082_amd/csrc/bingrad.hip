@@ -508,8 +508,12 @@ void launch_bingrad_team(const float* g, size_t n, const ogq_params_t* p, uint32
             return;
         }
     }
-    if (sign) OGQ_LAUNCH(false, true);
-    else OGQ_LAUNCH(false, false);
+    if constexpr (W < 16) {  // (without clipping the caller never asks for 16 wavefronts: see launch_two_level)
+        if (sign) OGQ_LAUNCH(false, true);
+        else OGQ_LAUNCH(false, false);
+    } else {
+        launch_status() = hipErrorInvalidDeviceFunction;
+    }
 #undef OGQ_LAUNCH
 }
 

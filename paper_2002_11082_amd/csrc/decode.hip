@@ -568,12 +568,24 @@ struct DecodeCall {
     }
 };
 
+// From 512 elements per bucket on only a single worker gets here (launch_by_bucket_size): nothing else is compiled.
 template <int BITS, int S, int WPB>
 void launch_by_worker(const DecodeCall& call)
 {
-    if (call.num_workers == 1u) call.launch<1>(dequantize_average_kernel<BITS, S, WPB, 1>);
-    else if (call.num_workers <= (uint32_t)kFewWorkers) call.launch<kFewWorkers>(dequantize_average_kernel<BITS, S, WPB, kFewWorkers>);
-    else call.launch<OGQ_MAX_WORKERS>(dequantize_average_kernel<BITS, S, WPB, OGQ_MAX_WORKERS>);
+    if constexpr (WPB < 8) {
+        if (call.num_workers > (uint32_t)kFewWorkers) {
+            call.launch<OGQ_MAX_WORKERS>(dequantize_average_kernel<BITS, S, WPB, OGQ_MAX_WORKERS>);
+            return;
+        }
+        if (call.num_workers > 1u) {
+            call.launch<kFewWorkers>(dequantize_average_kernel<BITS, S, WPB, kFewWorkers>);
+            return;
+        }
+    } else if (call.num_workers > 1u) {
+        launch_status() = hipErrorInvalidDeviceFunction;
+        return;
+    }
+    call.launch<1>(dequantize_average_kernel<BITS, S, WPB, 1>);
 }
 
 template <int BITS, int S, uint32_t BUCKETS>

@@ -2696,7 +2696,7 @@ void launch_orq_levels(const float* g, size_t n, const ogq_params_t* p, uint32_t
 template <int W, int C>
 constexpr bool team_serves(int S, int rule)
 {
-    if (W == 2) return C == 8 ? S >= 8 || rule == kPb : S >= 8;
+    if (W == 2) return (S >= 8 && rule == kOptimal) || (C == 8 && rule == kPb);
     if (W * C == 64 || W * C == 128) {
         if (rule == kEven) return C == 8;
         return C == 16 && (S != 3 || rule == kPb);

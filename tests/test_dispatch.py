@@ -43,3 +43,8 @@ def recorded(tmp_path_factory):
 def test_every_accepted_call_is_one_launch(recorded):
     assert recorded["calls"] > 1_000_000
     assert recorded["wrong"] == [] and recorded["unknown"] == 0
+
+
+def test_every_kernel_of_the_library_is_reached(recorded):
+    assert len(recorded["launches"]) > 400
+    assert [name for name, launches in recorded["launches"].items() if launches == 0] == []
