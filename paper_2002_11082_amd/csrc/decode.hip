@@ -296,7 +296,10 @@ __global__ __launch_bounds__(kBlock) void dequantize_average_kernel(WorkerPtrs<M
 //   - The index looks up the sum of the K workers' levels, tabulated in LDS for all 256 combinations (fp64).  With at most
 //     K workers the table holds the averages themselves, rounded to fp32, and one look-up per element is all.
 // A span touches at most BUCKETS buckets: one if the bucket size is a multiple of 1024, two from 1024 elements on or with
-// 512, three from 512 on, seven from 192 on.  Each has its own table.
+// 512, three from 512 on, four from 320 on, six with 192.  Each has its own table, 2 KB per wavefront with fp64 sums; the
+// LDS limits the wavefronts of a CU (room for seven tables from 192 to 448 elements: two workgroups of fp64 tables; with
+// six three, with four four.  25.6 M values, eight two-bit workers: 192 elements 54.7 -> 43.2 us, 320 48.0 -> 32.5, 448
+// 48.1 -> 31.6.  One-bit codes of eight workers, whose tables are fp32, 6.4 M: 8.3 -> 7.9, 25.6 M: 22.3 -> 22.7).
 // ----------------------------------------------------------------------------------------------
 constexpr uint32_t kJointEntries = 256;
 
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(kBlock) void dequantize_joint_kernel(WorkerPtrs<MOS
     const uint32_t words = total_words - word0 < (uint32_t)kSpanWords ? total_words - word0 : (uint32_t)kSpanWords;
     const uint32_t first_bucket = word0 / words_per_bucket;
     // The bucket of a word of the span, counted from the first one: up to three buckets by the words with which the second
-    // and the third begin, for more (of 3 to 7 words) by a product with the reciprocal (exact: the factors stay below 22).
+    // and the third begin, for more (of 3 to 7 words) by a product with the reciprocal (exact: the words counted stay below 22).
     const uint32_t skipped = word0 - first_bucket * words_per_bucket;
     const uint32_t second = words_per_bucket - skipped, third = second + words_per_bucket;
     const uint32_t reciprocal = BUCKETS > 3u ? 65536u / words_per_bucket + 1u : 0u;
@@ -611,7 +614,8 @@ void launch_joint(const DecodeCall& call)
     if (wpb % kSpanWords == 0) launch_joint_buckets<BITS, S, 1>(call);
     else if (wpb > kSpanWords || wpb == 8u) launch_joint_buckets<BITS, S, 2>(call);
     else if (wpb > 8u) launch_joint_buckets<BITS, S, 3>(call);
-    else launch_joint_buckets<BITS, S, 7>(call);
+    else if (wpb > 4u) launch_joint_buckets<BITS, S, 4>(call);
+    else launch_joint_buckets<BITS, S, 6>(call);
 }
 
 template <int BITS, int S>

@@ -2,6 +2,7 @@
 none may return success without having launched anything."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -48,3 +49,24 @@ def test_every_accepted_call_is_one_launch(recorded):
 def test_every_kernel_of_the_library_is_reached(recorded):
     assert len(recorded["launches"]) > 400
     assert [name for name, launches in recorded["launches"].items() if launches == 0] == []
+
+
+def _buckets_of_a_span(d):
+    """The most buckets that any 1024 consecutive elements touch which begin at a multiple of 1024."""
+    return max((start % d + 1023) // d + 1 for start in range(0, 1024 * d, 1024))
+
+
+def test_joint_decoder_holds_the_buckets_of_a_span(recorded):
+    """dequantize_joint_kernel<BITS, S, BUCKETS, ...> keeps BUCKETS tables in LDS per wavefront: as many as a span of one of
+    its bucket sizes touches, neither fewer (a write out of its range) nor more (wavefronts that do not fit)."""
+    tables = {}
+    for name, sizes in recorded["decoded_sizes"].items():
+        form = re.search(r"dequantize_joint_kernelILi(\d+)ELi(\d+)ELj(\d+)E", name)
+        if form:
+            for d in sizes:
+                tables.setdefault(d, set()).add(int(form.group(3)))
+    assert len(tables) > 500
+    for d, held in tables.items():
+        assert len(held) == 1 and min(held) >= _buckets_of_a_span(d), (d, held)
+        if d < 512:
+            assert held == {_buckets_of_a_span(d)}, (d, held)
