@@ -61,24 +61,48 @@ def read_note(file_name: str, kernel_key: str):
     return None
 
 
-def quantize_kernel_name(synth, wl, n: int) -> str:
+def quantize_kernel(synth, wl, n: int, levels: int):
+    """Name of the kernel that ogq_quantize launches for the workload's recipe at n elements, and its wavefronts per bucket
+    (the library's dispatch by scheme, bucket size and number of buckets)."""
     d = wl.bucket_size
-    two_level_means = wl.scheme in (synth.BINGRAD_B, synth.SCALED_SIGN)
-    if not two_level_means and d in (64, 128):
-        return "even_small_kernel" if wl.scheme == synth.EVEN else "sorted_small_kernel"
-    if not two_level_means:
-        return "orq_quantize_kernel" if d <= 2048 else "orq_team_kernel"
-    if d > 2048:
-        return "bingrad_team_kernel"
-    if wl.clip_factor == 0 and 2048 % d == 0 and d < 2048 and (d <= 256 or n // 2048 >= 2048):
-        return "bingrad_chunk_kernel"
-    return "bingrad_quantize_kernel"
+    nb = -(-n // d)
+    if wl.scheme in (synth.BINGRAD_B, synth.SCALED_SIGN):
+        if d > 2048:
+            clip, once = wl.clip_factor > 0, wl.level_iters == 0 or wl.scheme == synth.SCALED_SIGN
+            if d <= 8192:
+                return "bingrad_team_kernel", 2 if d <= 4096 else 4
+            if d > 16384:
+                return "bingrad_team_kernel", 16 if clip else 8
+            return "bingrad_team_kernel", 8 if clip or nb <= 512 or (d == 16384 and once) else 4
+        if wl.clip_factor == 0 and 2048 % d == 0 and d < 2048 and n >= 2048 and (d <= 256 or n // 2048 >= 2048):
+            return "bingrad_chunk_kernel", d / 2048
+        return "bingrad_quantize_kernel", 1
+    pb, even, linear = (wl.scheme == s for s in (synth.BINGRAD_PB, synth.EVEN, synth.LINEAR))
+    solves = not even and levels > 2
+    long_solves = pb or (solves and not linear and levels >= 8)
+    if 64 < d <= 512 and not pb:
+        enough = (8192 if solves else 16384) if d > 256 else (4096 if solves else 8192) if d > 128 else 8192
+        if nb >= enough:
+            return "orq_rows_kernel", 0.25
+    if d in (64, 128):
+        return "even_small_kernel" if even else "sorted_small_kernel", d / 256
+    if d <= 2048:
+        few = 0 if d <= 256 else (2560 if long_solves and not pb else 0) if d <= 512 else 512 if d <= 1024 else 1280
+        return ("orq_team_kernel", 2 if d <= 512 else 4) if nb <= few else ("orq_quantize_kernel", 1)
+    if d <= 4096:
+        return "orq_team_kernel", 2 if long_solves and nb > 4096 else 4
+    if d <= 8192 and nb <= 256:
+        return "orq_team_kernel", 8
+    wavefronts = 4 if d <= 8192 else 8 if d <= 16384 else 16
+    if levels == 3 and not even:
+        return "orq_gather_kernel", wavefronts
+    return "orq_team_kernel", wavefronts if even or d <= 8192 else wavefronts // 2
 
 
-def wavefronts_per_bucket(two_level_means: bool, d: int) -> int:
-    if two_level_means:
-        return 1
-    return 1 if d <= 2048 else 2 if d <= 4096 else 4 if d <= 16384 else 8
+def decode_kernel_name(d: int, workers: int) -> str:
+    """Name of the kernel that ogq_dequantize_average launches."""
+    fixed = d % 1024 == 0 or 1024 % d == 0
+    return "dequantize_joint_kernel" if not fixed or (workers > 1 and d >= 512) else "dequantize_average_kernel"
 
 
 class Measurement:
@@ -123,7 +147,8 @@ class Measurement:
                                  ctypes.c_void_p(self.codes[b][w].data_ptr()), sp) for w in range(W)])
             self.a_args.append(self._average_args(self.codes[b], self.levels[b], self.outs[b]))
         self.q_bytes, self.a_bytes = algorithmic_bytes(n, d, bits, W, self.levels_per_bucket)
-        self.quant_name = quantize_kernel_name(synth, wl, n)
+        self.quant_name, self.wavefronts_per_bucket = quantize_kernel(synth, wl, n, self.levels_per_bucket)
+        self.decode_name = decode_kernel_name(d, W)
         self.two_level_means = wl.scheme in (synth.BINGRAD_B, synth.SCALED_SIGN)
 
     def _average_args(self, codes, levels, out):
@@ -241,7 +266,7 @@ class Measurement:
                 e["traffic_source"] = "profiles/hbm_traffic.txt: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier run of this workload (recorded, not measured in this run)"
             return e
         quant = entry(self.quant_name, self.q_bytes, q_ms)
-        dec = entry("dequantize_average_kernel", self.a_bytes, warm_ms)
+        dec = entry(self.decode_name, self.a_bytes, warm_ms)
         cold_gbs = self.a_bytes / (cold_ms * 1e-3) / 1e9
         dec.update({"cold_avg_launch_us": round(cold_ms * 1e3, 2), "cold_achieved": round(cold_gbs, 1),
                     "cold_frac": round(cold_gbs / HBM_PEAK_GBS, 4), "cold_input_sets": self.n_sets})
@@ -255,7 +280,7 @@ class Measurement:
         if valu_per_wave is None or self.two_level_means:
             return None
         buckets = (self.n + self.d - 1) // self.d
-        lane_ops = valu_per_wave * 64 * wavefronts_per_bucket(self.two_level_means, self.d) * buckets
+        lane_ops = valu_per_wave * 64 * self.wavefronts_per_bucket * buckets
         achieved = lane_ops / (q_ms * 1e-3) / 1e12
         simds = 256 * 4
         e = {"bound": "alu", "kernel": self.quant_name, "achieved": round(achieved, 2), "peak": ALU_PEAK_TLANEOPS,

@@ -3,12 +3,15 @@ runtime, and prints what they launched.  Run as a child process by test_dispatch
 
 Every scheme and width, every bucket size, clipping on and off, every power of two of buckets and its neighbours (the limits
 of the dispatch are at or near powers of two, or listed), whole and ragged last buckets; the decoder with every number of
-workers at which it changes its form."""
+workers at which it changes its form.  Also the benchmark's workloads at several lengths, with the kernels that the benchmark
+says they take."""
 import ctypes
 import json
 import sys
 
+import bench
 import paper_2002_11082_amd as ogq
+from paper_2002_11082_amd import synth
 
 SCHEMES = ((ogq.BINGRAD_B, (1,)), (ogq.ORQ, (1, 2, 3)), (ogq.BINGRAD_PB, (1,)), (ogq.ORQ_PAPER, (2, 3, 4)), (ogq.SCALED_SIGN, (1,)),
            (ogq.EVEN, (2, 3, 4)), (ogq.LINEAR, (2, 3, 4)))
@@ -60,11 +63,23 @@ def main():
                      average(at, at, workers, 100 * d + 1, by, ADDRESS, None))
                 decoders.setdefault(stub.recorded_last(), set()).add(d)
                 calls += 1
+    named = []
+    for name in bench.WORKLOAD_NAMES:
+        wl = synth.WORKLOADS[name]
+        for n in (1000, 100_000, 1_000_000, 10_000_000, 25_600_000, wl.n, 400_000_000):
+            p = ogq.make_params(wl.bucket_size, wl.bits, wl.scheme, wl.level_iters, 0, 0, wl.clip_factor)
+            once(f"quantize {name} at {n}", quantize(ADDRESS, n, ctypes.byref(p), ADDRESS, ADDRESS, None))
+            kernel, wavefronts = bench.quantize_kernel(synth, wl, n, ogq.ogq_levels_per_bucket(p))
+            here = stub.recorded_last_blocks() * stub.recorded_last_threads() / 64 * wl.bucket_size / n
+            named.append([f"quantize {name} at {n}", kernel, stub.recorded_last(), wavefronts, here])
+            once(f"decode {name} at {n}", average(at, at, wl.workers, n, ctypes.byref(p), ADDRESS, None))
+            named.append([f"decode {name} at {n}", bench.decode_kernel_name(wl.bucket_size, wl.workers), stub.recorded_last(), 0, 0])
     once("probe_read", lib.ogq_probe_read(ADDRESS, 64, ADDRESS, None))
     once("probe_copy", lib.ogq_probe_copy(ADDRESS, ADDRESS, 64, None))
     names = [stub.recorded_name(i).decode() for i in range(stub.recorded_kernels())]
     print(json.dumps({"calls": calls, "wrong": wrong[:20], "unknown": stub.recorded_unknown(),
                       "launches": {name: stub.recorded_launches_of(i) for i, name in enumerate(names)},
+                      "named": [[what, kernel, names[i], stated, here] for what, kernel, i, stated, here in named],
                       "decoded_sizes": {names[i]: sorted(sizes) for i, sizes in decoders.items()}}))
 
 

@@ -51,6 +51,14 @@ def test_every_kernel_of_the_library_is_reached(recorded):
     assert [name for name, launches in recorded["launches"].items() if launches == 0] == []
 
 
+def test_the_benchmark_names_the_kernels_that_run(recorded):
+    assert len(recorded["named"]) > 200
+    for what, stated, launched, wavefronts, wavefronts_launched in recorded["named"]:
+        assert re.search(rf"ogq\d+{stated}I", launched), (what, stated, launched)
+        if wavefronts and what.endswith("at 400000000"):  # (few buckets: whole workgroups, whole groups of buckets)
+            assert abs(wavefronts_launched / wavefronts - 1) < 0.01, (what, wavefronts, wavefronts_launched)
+
+
 def _buckets_of_a_span(d):
     """The most buckets that any 1024 consecutive elements touch which begin at a multiple of 1024."""
     return max((start % d + 1023) // d + 1 for start in range(0, 1024 * d, 1024))
