@@ -504,8 +504,8 @@ def test_non_finite_values_stay_inside_their_bucket():
 
 def test_calls_can_be_captured_in_a_graph():
     """The entry points only enqueue kernels, so a quantize + decode-average pair can be captured once and replayed
-    on new inputs: every replay must give what the eager calls give (several kernel families, a gradient that takes
-    two launches, several replays with other work in between)."""
+    on new inputs: every replay must give what the eager calls give (several kernel families, a gradient whose whole
+    chunks and rest share a launch, several replays with other work in between)."""
     rng = np.random.default_rng(31)
     cases = [(ogq.BINGRAD_B, 1, 512, 2100 * 2048 + 700, 0), (ogq.ORQ, 2, 2048, 9 * 2048 + 100, 2),
              (ogq.ORQ_PAPER, 2, 8192, 3 * 8192 + 5, 0)]
@@ -664,7 +664,7 @@ def test_decode_average_many_identical_workers():
 @pytest.mark.parametrize("bits,scheme", [(1, ogq.BINGRAD_B), (2, ogq.ORQ), (2, ogq.EVEN), (3, ogq.ORQ), (3, ogq.LINEAR), (4, ogq.EVEN)])
 def test_decode_average_joint_lookups(bits, scheme, d):
     """Several workers per look-up: worker counts that end inside a look-up, inside and behind a pair of them, spans
-    that touch one to seven buckets, ragged last spans down to a single element."""
+    that touch one to six buckets, ragged last spans down to a single element."""
     rng = np.random.default_rng(31 * bits + d + scheme)
     stride = oracle.levels_per_bucket(scheme, bits)
     for n in (1, 2 * d + 1, 3 * 1024 + 5 * d + 77, 8 * 1024):
@@ -825,6 +825,46 @@ def test_four_buckets_per_wavefront(scheme, bits, sweeps, d):
                               tag=f"rows-s{scheme}-b{bits}-d{d}-c{clip}")
 
 
+@pytest.mark.parametrize("d", [128, 192, 256, 448, 512])
+@pytest.mark.parametrize("scheme,bits", [(ogq.ORQ, 1), (ogq.ORQ, 2), (ogq.ORQ, 3), (ogq.ORQ_PAPER, 2), (ogq.EVEN, 3), (ogq.LINEAR, 4)])
+def test_encoder_careful_form_of_four_buckets_per_wavefront(scheme, bits, d):
+    """The encoder's careful form (above) in the layout of four buckets per wavefront: widths that are too small in some of
+    a wavefront's buckets only, and Philox blocks that pass 2^32 inside a bucket in the middle of the gradient."""
+    rng = np.random.default_rng(d + 10 * bits + scheme)
+    nb = (16384 if scheme == ogq.EVEN or bits == 1 else 8192) + 3
+    scale = rng.choice([1.0, 1.0, 1.0, 1.0, 1e-29, 1e-36, 1e-41], size=nb)
+    g = (rng.standard_t(3, (nb, d)) * 1e-2 * scale[:, None]).astype(np.float32).reshape(-1)[: nb * d - 5]
+    crossing = (nb // 2) * d + 64 * (d // 128)  # the element with global index 2^34
+    for clip in (0.0, 1.7):
+        parity.check_quantize(g, d, bits, scheme, 0, seed=77, index_offset=(1 << 34) - crossing, clip_factor=clip,
+                              tag=f"careful-rows-s{scheme}-b{bits}-d{d}-c{clip}")
+
+
+@pytest.mark.parametrize("d", [128, 320, 512])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0), (ogq.ORQ_PAPER, 4, 0),
+                                                (ogq.EVEN, 2, 0), (ogq.LINEAR, 3, 0)])
+def test_non_finite_values_stay_inside_one_of_four_buckets(scheme, bits, sweeps, d):
+    """As test_non_finite_values_stay_inside_their_bucket, for gradients long enough that four buckets share a wavefront:
+    the buckets beside a poisoned one match the oracle."""
+    rng = np.random.default_rng(d + 10 * bits + scheme)
+    nb = (16384 if scheme == ogq.EVEN or bits == 1 else 8192) + 2
+    g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+    poisoned = list(range(5, 4 * 60, 7)) + [nb - 2]
+    for i, b in enumerate(poisoned):
+        if i % 3 == 2:
+            g[b * d:(b + 1) * d] = np.nan
+        else:
+            where = b * d + rng.choice(d, size=5, replace=False)
+            g[where] = [np.nan, np.inf, -np.inf, np.nan, np.inf] if i % 3 == 0 else np.inf
+    beside = sorted(set(range(4 * 61)) - set(poisoned)) + list(range(nb - 7, nb - 2)) + [nb - 1]
+    for clip in (0.0, 2.5):
+        lv, codes, rep = parity.check_quantize(g, d, bits, scheme, sweeps, seed=4, buckets=beside, clip_factor=clip,
+                                               tag=f"nonfinite-rows-s{scheme}-b{bits}-d{d}-c{clip}")
+        out = ogq.ogq_dequantize_average([codes], [lv], nb * d, ogq.make_params(d, bits, scheme))
+        torch.cuda.synchronize()
+        assert out.numel() == nb * d
+
+
 # ------------------------------------------------------------------------------------------------
 # one interior level, buckets of several wavefronts (the wanted bin is collected, not the bucket grouped)
 # ------------------------------------------------------------------------------------------------
@@ -864,6 +904,44 @@ def test_few_and_many_buckets(scheme, bits, sweeps, d, limit):
         g = _rng_bucket(rng, nb * d - 29, "heavy")
         parity.check_quantize(g, d, bits, scheme, sweeps, seed=23, buckets=_sample(nb, 24, nb) if nb > 24 else None,
                               tag=f"count-s{scheme}-b{bits}-d{d}-nb{nb}", clip_factor=2.5 if nb == limit else 0.0)
+
+
+@pytest.mark.parametrize("d,nb", [(448, 2600), (512, 2600), (704, 600), (1024, 600), (1472, 1400), (2048, 1400), (3008, 4200), (4096, 4200)])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0), (ogq.ORQ_PAPER, 3, 1),
+                                                (ogq.ORQ_PAPER, 4, 0), (ogq.BINGRAD_PB, 1, 0), (ogq.LINEAR, 3, 0), (ogq.EVEN, 2, 0)])
+def test_unlike_buckets_of_long_gradients(scheme, bits, sweeps, d, nb):
+    """The tests above with special values take a few buckets, which several wavefronts share; here there are enough that
+    each has one wavefront (two or four above 2048 elements): constant, crowded, sparse, sorted and tiny buckets, T exactly an
+    integer, NaN and infinities in some, Philox blocks that pass 2^32, a cut-off last bucket."""
+    rng = np.random.default_rng(d + 1000 * bits + scheme)
+    g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    kinds = ["const", "normal", "zeros", "heavy", "ints", "shifted"]
+    poisoned = []
+    for b in range(0, 110):
+        if b % 2 == 0:
+            buckets[b] = _rng_bucket(rng, d, kinds[(b // 2) % len(kinds)])
+        elif b % 9 == 1:
+            buckets[b, rng.random(d) < 0.9] = 0.0                     # sparse
+        elif b % 9 == 2:
+            buckets[b] = np.sort(buckets[b])
+        elif b % 9 == 3:
+            buckets[b] = np.float32(1.0) + rng.integers(0, 900, d).astype(np.float32) * np.float32(2.0 ** -23)  # one crowded bin
+        elif b % 9 == 4:
+            half = buckets[b, : d // 2].copy()
+            buckets[b, d // 2:] = -half                                # T exactly an integer
+        elif b % 9 == 5:
+            buckets[b] *= np.float32(1e-38)
+        elif b % 9 == 6:
+            poisoned.append(b)
+            buckets[b, rng.choice(d, size=5, replace=False)] = [np.nan, np.inf, -np.inf, np.nan, np.inf]
+        elif b % 9 == 7:
+            poisoned.append(b)
+            buckets[b] = np.nan
+    checked = [b for b in list(range(0, 110)) + _sample(nb, 20, nb) + [nb - 1] if b not in poisoned]
+    for cut, clip in ((29, 0.0), (d - 65, 2.5)):
+        parity.check_quantize(g[: nb * d - cut], d, bits, scheme, sweeps, seed=61, index_offset=(1 << 34) - 55 * d - 64 * (d // 128),
+                              buckets=checked, clip_factor=clip, tag=f"long-s{scheme}-b{bits}-d{d}-c{clip}")
 
 
 @pytest.mark.parametrize("scheme,iters", [(ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 2), (ogq.SCALED_SIGN, 0)])
