@@ -857,6 +857,10 @@ def test_non_finite_values_stay_inside_one_of_four_buckets(scheme, bits, sweeps,
             where = b * d + rng.choice(d, size=5, replace=False)
             g[where] = [np.nan, np.inf, -np.inf, np.nan, np.inf] if i % 3 == 0 else np.inf
     beside = sorted(set(range(4 * 61)) - set(poisoned)) + list(range(nb - 7, nb - 2)) + [nb - 1]
+    for b in beside[::5]:  # T exactly an integer beside fp64 sums that may round: exact ones decide
+        half = g[b * d:b * d + d // 2]
+        half[3] = 1e-38
+        g[b * d + d // 2:(b + 1) * d] = -half
     for clip in (0.0, 2.5):
         lv, codes, rep = parity.check_quantize(g, d, bits, scheme, sweeps, seed=4, buckets=beside, clip_factor=clip,
                                                tag=f"nonfinite-rows-s{scheme}-b{bits}-d{d}-c{clip}")
@@ -929,7 +933,10 @@ def test_unlike_buckets_of_long_gradients(scheme, bits, sweeps, d, nb):
             buckets[b] = np.float32(1.0) + rng.integers(0, 900, d).astype(np.float32) * np.float32(2.0 ** -23)  # one crowded bin
         elif b % 9 == 4:
             half = buckets[b, : d // 2].copy()
+            if b % 4 == 1:
+                half[3] = 1e-38                                        # (and fp64 sums that may round: exact ones decide)
             buckets[b, d // 2:] = -half                                # T exactly an integer
+            buckets[b, : d // 2] = half
         elif b % 9 == 5:
             buckets[b] *= np.float32(1e-38)
         elif b % 9 == 6:
