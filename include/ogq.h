@@ -19,10 +19,9 @@
  *     and the call returns without synchronising.
  *   - Return value: OGQ_OK (0) or a negative ogq_status_t.  On an argument error (every code but
  *     OGQ_ERR_LAUNCH) nothing was enqueued and no output byte was written.  OGQ_ERR_LAUNCH means the HIP
- *     runtime refused a kernel launch of this call (its own return code, not the thread's sticky last
- *     error); nothing is enqueued after the refused launch, but a call that takes two launches
- *     (OGQ_BINGRAD_B / OGQ_SCALED_SIGN with a bucket size dividing 2048, without clipping, when n is not
- *     a multiple of 2048) may already have enqueued its first one.  The library never throws and never aborts.
+ *     runtime refused the kernel launch of this call (its own return code, not the thread's sticky last
+ *     error); every call is one launch, so nothing was enqueued then either.  The library never throws and
+ *     never aborts.
  *   - Input values must be finite.  Non-finite input gives unspecified levels and codes but no
  *     out-of-bounds access.
  *   - n == 0 is a successful no-op.
@@ -123,7 +122,7 @@ size_t ogq_codes_bytes(size_t n, const ogq_params_t* params);
 /* Quantize one worker's gradient: levels + packed codes (what Algorithm 2 has a worker compute,
  * quantize and encode before sending).
  *
- *   d_grad    in   n fp32, device, read once.
+ *   d_grad    in   n fp32, device, must not change before the enqueued work is done (a bucket may be read twice).
  *   d_levels  out  levels_count fp32, device; bucket b owns entries
  *                  [b * levels_per_bucket, (b+1) * levels_per_bucket), non-decreasing.
  *                  BINGRAD_B: {b_{-1}, b_1} = means of the elements below / not below the

@@ -3,16 +3,19 @@
 // Method: "Optimal Gradient Quantization Condition for Communication-Efficient Distributed
 // Training" (arXiv 2002.11082).  A bucket stays with one wavefront (several small buckets share one, a large
 // bucket takes the wavefronts of one workgroup) from the HBM load to the packed store, so the gradient is read
-// exactly once:
+// once, but for the rare buckets that the encoder's careful form or an exact sum reads again:
 //   bingrad.hip            BinGrad-b (Section 3.2) and Scaled SignSGD: fp64 wave reductions for the mean and the
 //                          two conditional means; the code bits of 64 consecutive elements are a lane mask.
 //   rounding_kernels.h     ORQ (Theorem 1, its discrete remark, Corollary 1, Algorithm 1; random rounding of
 //                          Section 3.1), BinGrad-pb and the evenly spaced / Linear-s comparison rules: every
 //                          level solve is a range sum plus an exact rank selection over the bucket grouped in
 //                          LDS; Philox4x32-10 draws keyed by (seed, global element index).
-//   decode.hip             decode-average (server step of Algorithm 2): a bit-matrix transpose across the lanes turns
-//                          the packed words into per-element level indices, which address level tables in LDS
-//                          (several workers per look-up through tables of pre-summed level combinations).
+//   row_kernels.h          the same for small buckets of long gradients, four per wavefront.
+//   gather_kernels.h       one interior level in buckets above 4096 elements: the bin of the wanted rank is collected
+//                          from the registers, the bucket not grouped.
+//   decode.hip             decode-average (server step of Algorithm 2): bit transposes across the lanes turn the packed
+//                          words into per-element level indices, which address level tables in LDS (several workers
+//                          per look-up through tables of pre-summed level combinations).
 // This file validates the arguments and picks the launcher (launch.h).
 //
 // Compile with -ffp-contract=off: the rounding decision of ORQ is specified op by op in fp32.

@@ -19,10 +19,12 @@ namespace ogq {
 // wavefronts per CU, whose phases nothing overlaps (ORQ-3, 25.6 M values: 75 us with the vector units busy 46 % of the
 // time).  Here a bucket takes at most 22 KB and the registers decide: 16 wavefronts of 128 registers fill a CU.
 //
-// Bound by vector-instruction issue (Philox and the rounding a third of it) and by the phases of a bucket that all its
-// wavefronts go through together.  ORQ-3, 25.6 M values, before -> after: buckets of 8192 42 -> 36 us,
-// 16384 59 -> 44, 20480 105 -> 79, 32768 75 -> 60; 16 buckets of 32768 20 -> 15 us.  Workgroups that stay and fetch their
-// next bucket into the free LDS meanwhile were slower (32768: 72 us).
+// Bound by the phases of a bucket that all its wavefronts go through together: at 32768 elements one workgroup fills a CU, so
+// nothing overlaps a bucket's loads and barriers, and 782 buckets on 256 CUs take a fourth round for the last 14
+// (SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES 0.62, 3.7 ns per vector instruction and SIMD; of 59 us the loads, extremes and
+// total take 22, the histogram 7, the level 11, encoding 19).  ORQ-3, 25.6 M values, before -> after: buckets of 8192 42
+// -> 36 us, 16384 59 -> 44, 20480 105 -> 79, 32768 75 -> 60; 16 buckets of 32768 20 -> 15 us.  Workgroups that stay and
+// fetch their next bucket into the free LDS meanwhile were slower (32768: 72 us).
 // ----------------------------------------------------------------------------------------------
 template <int W, int C>
 struct GatherLds {

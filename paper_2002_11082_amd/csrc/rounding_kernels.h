@@ -101,10 +101,15 @@ __device__ __forceinline__ void philox4x32_10_uniform_c1(uint32_t c0, const Phil
 // A level solve needs (a) counts and sums of the elements below a level and (b) the element of a
 // given rank.  The bucket is therefore grouped once, in LDS, by a monotone bin of the value (sign,
 // exponent and top mantissa bits, relative to the largest magnitude of the bucket; everything more
-// than 16 binades below that shares the two centre bins).  Per-bin counts and fp64 sums are
-// prefix-summed; after that a solve touches one bin: the bin holding the wanted rank is sorted
-// across the 64 lanes, and the counts and sums below the chosen element are added to the bin's
-// prefix.  All values of a regular bin share sign and exponent, so its fp64 sum is exact.
+// than 16 binades below that shares the two centre bins).  The bin counts and the fp64 sums of blocks
+// of positions are prefix-summed; after that a solve touches one bin: the element of the wanted rank is
+// selected among the bin's keys, one per lane (select_rank), and the counts and sums below it are added
+// to what lies before the bin.
+//
+// What bounds it: vector-instruction issue and, in the solves, a scalar chain.  Of 1,944 vector instructions per bucket of
+// 2048 at four levels the solves take 525, with 516 scalar ones in a chain of lane read, compare and scalar count;
+// SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES is 0.86, and 0.92 in a build without the solves (profiles/phase_budgets.txt:
+// 25.6 M values 51 us = load and extremes 14, grouping 11, solves 12.5, encode 14).
 // ----------------------------------------------------------------------------------------------
 // Order-preserving map of fp32 onto unsigned integers.
 __device__ __forceinline__ uint32_t float_to_key(float f)
@@ -355,9 +360,9 @@ __device__ __forceinline__ uint32_t wave_sort_u32(uint32_t x, uint32_t lane, uin
 //
 // Quickselect on lane masks: a pivot costs one lane read and two compares on the vector unit, counting and narrowing are
 // scalar.  A bin of 20 keys takes about 5 pivots, i.e. 15 vector instructions where a bitonic sort of the keys takes 42
-// (65 above 32 keys); the kernels that call this are bound by vector-instruction issue.  The pivot is the first open
-// lane at or above lane rank - 1: the answer itself when the keys came in sorted.  Every round drops the pivot at least,
-// so the loop ends.  In assembly because the compiler spends twice the scalar instructions on it.  Wait states: two
+// (65 above 32 keys), which the issue of vector instructions bound; what a solve now waits for is the pivots' scalar chain.
+// The pivot is the first open lane at or above lane rank - 1: the answer itself when the keys came in sorted.  Every round
+// drops the pivot at least, so the loop ends.  In assembly because the compiler spends twice the scalar instructions on it.  Wait states: two
 // between the lane read and the compares that take the key (s_nop 1); three scalar instructions lie between whatever
 // wrote `mine` and the lane read.  All lanes are active.
 __device__ __forceinline__ uint64_t select_rank(uint32_t mine, uint32_t count, uint32_t rank, uint64_t open, uint32_t& key_out,
@@ -1678,7 +1683,7 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
     constexpr bool PB = RULE == kPb;
     const uint32_t lane = threadIdx.x & 63u;
 
-    // ---- load (read once: bypass the caches); padding holds +0 and is never binned or encoded ----
+    // ---- load (past the caches); padding holds NaN and is never binned or encoded ----
     float v[C][4];
     load_range<C, FULL>(v, g, 0u, len, len, lane);
 
@@ -2335,8 +2340,12 @@ __global__ __launch_bounds__(4 * kWave) void sorted_small_kernel(const float* __
 // ORQ and the other random-rounding rules with W = 2 .. 16 wavefronts of a workgroup owning one bucket (up
 // to 32768 elements), wavefront w holding bucket elements [256 C w, 256 C (w + 1)) in the register layout of
 // orq_bucket.  All of them build the grouping of the whole bucket in LDS (histogram, bin
-// starts, scatter, fp64 block prefix) with workgroup barriers in between; the level solves are serial and run
-// on wavefront 0 alone; then every wavefront encodes its own elements.
+// starts, scatter, fp64 block prefix) with workgroup barriers in between; the level solves run on wavefront 0, those of
+// five and more levels on the first two (orq_team_solve); then every wavefront encodes its own elements.
+//
+// What bounds it (eight levels, two sweeps, two wavefronts, 143.7 M values in buckets of 4096: 423 us): the solves, 185 us of
+// it, 11 steps that end in a barrier each; both wavefronts spend 64 lanes on one scalar chain.  2,819 vector instructions per
+// wavefront, SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES 0.81 (1.05 in a build without the solves).
 // ----------------------------------------------------------------------------------------------
 template <int W, int C>
 struct OrqTeamLds {

@@ -21,9 +21,11 @@ namespace ogq {
 #define OGQ_CAT(a, b) OGQ_CAT2(a, b)
 
 // Few buckets: where a gradient has at most a few of them per CU, the time of a call is that of one bucket, and several
-// wavefronts per bucket shorten it (ORQ-8, one bucket of 2048: 21.4 -> 14.1 us with four; ORQ-3: 5.7 -> 4.2).  Each limit
-// is the largest measured number of buckets up to which no rule lost; beyond it the barriers and the registers of the idle
-// wavefronts cost more than the shorter bucket gains.
+// wavefronts per bucket shorten it (64 buckets of 2048, one wavefront and four: eight levels 21.6 -> 14.4 us, three 6.0 ->
+// 4.8); beyond, the barriers and the registers of the idle wavefronts cost more than the shorter bucket gains (4096 buckets:
+// 39.2 -> 50.0, 13.6 -> 16.2).  profiles/few_buckets_scan.txt has both sides for all rules and sizes.  Each limit is a measured
+// number of buckets up to which no rule loses more than 3 %; one number serves all rules, so those with long solves
+// would gain somewhat further (1536 buckets of 1024: eight levels 22.8 -> 19.2, where BinGrad-pb loses, 7.4 -> 8.3).
 template <int W, int C>
 bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes,
                 hipStream_t st)
@@ -41,8 +43,11 @@ static bool long_solves(const ogq_params_t* p)
 }
 
 #if OGQ_PART == 16
-// Four wavefronts of 1024 elements (28 of them in a CU, where two of 2048 make 16) are 1 to 12 % faster on the passes over
-// the elements; with long serial solves that is lost again above some 4000 buckets, which two wavefronts serve better.
+// Four wavefronts of 1024 elements (28 of them in a CU, where two of 2048 make 16) are up to 18 % faster than two on the passes
+// over the elements; with long serial solves that is lost again above some 4000 buckets, which two wavefronts serve better
+// (8192 buckets of 4096: eight levels 106 us with two, 107 with four, BinGrad-pb 50.8 and 53.4).  The exception that the rule
+// leaves alone: around 2048 buckets, one round more for workgroups of four, long solves are faster with two (eight levels
+// 31.1 against 37.6).
 void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     if (launch_few<4, 4>(long_solves(p) ? 4096u : ~0u, g, n, p, nb, lv, codes, st)) return;
@@ -52,8 +57,11 @@ void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32
 #if OGQ_PART <= 2
 // Four buckets per wavefront (row_kernels.h) where the gradient has enough of them to fill the chip that way: a
 // wavefront then takes about 1.5 times as long as one with a single bucket, so below one wavefront per SIMD (4096
-// buckets) it only adds latency.  Measured crossover, in buckets: 2000 to 4000 at 192 and 256 elements, 5000 to 7000 at
-// 128 and above 256 (there the LDS holds fewer wavefronts); without level solves about twice that.
+// buckets) it only adds latency.  Measured crossover, in buckets (profiles/row_kernels_scan.txt has both sides): 6000 to 8000 at
+// 128 elements, against a kernel that already takes two per wavefront; 2000 to 4000 at 192 to 448; up to 8000 at 512, where the
+// LDS holds fewer wavefronts.  Without level solves 3000 to 8000, at 128 elements 16000 to 20000.  The limits lie where
+// the rules with most solves gain (ORQ-9, 8192 buckets of 512: 23.6 -> 17.1 us; 32768: 73.6 -> 51.9); Linear-5 in buckets of
+// 512 loses up to 11 % by them (16384: 17.2 -> 19.1).
 static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     const bool solves = p->scheme != OGQ_EVEN && levels_per_bucket(p->scheme, p->bits) > 2;

@@ -12,10 +12,13 @@ namespace ogq {
 // ORQ, Linear-s and evenly spaced levels for bucket sizes d = 64 m up to 512, four whole buckets per wavefront: row r (16
 // lanes) owns bucket r of the wavefront's span of 4 d elements and holds its elements 64c + 4i + {0..3} in lane i, chunk c.
 //
-// What bounds it: vector-instruction issue.  With one bucket per wavefront (orq_quantize_kernel) a bucket of 512 elements
-// costs 1,400 instructions at nine levels, of which its 8 x 64 elements need about 350: the solves, reductions and scans
-// are the same for 2048 elements as for 512, and in a solve all 64 lanes do one bucket's arithmetic.  Here every such
-// instruction works for four buckets.  The phases are those of orq_bucket: extremes, grouping in LDS by value bins, fp64
+// What bounds it: vector-instruction issue (ORQ-9, buckets of 512, clipping, 25.6 M values: 3,337 vector instructions per
+// wavefront at 2.2 ns per SIMD, SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES 0.96; ORQ-3, buckets of 128: 573 at 1.9 ns, 1.16).  With
+// one bucket per wavefront (orq_quantize_kernel) a bucket of 512 elements costs 1,400 instructions at nine levels, of
+// which its 8 x 64 elements need about 350: the solves, reductions and scans are the same for 2048 elements as for 512,
+// and in a solve all 64 lanes do one bucket's arithmetic.  Here every such instruction works for four buckets: 834 per
+// bucket.  25.6 M values, before -> after: ORQ-9 with clipping and the decoding of four workers 163 -> 105 us, ORQ-3 in
+// buckets of 128 69 -> 44.  The phases are those of orq_bucket: extremes, grouping in LDS by value bins, fp64
 // prefix, level solves, encode.  What differs: reductions and scans stay inside a row; bins are twice as wide (a bucket of
 // 512 elements has at most about 20 elements in one), and the elements of the wanted bin are sorted across the row's 16
 // lanes, one, two or four keys per lane.
