@@ -79,18 +79,29 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         return "bingrad_quantize_kernel", 1
     pb, even, linear = (wl.scheme == s for s in (synth.BINGRAD_PB, synth.EVEN, synth.LINEAR))
     solves = not even and levels > 2
-    long_solves = pb or (solves and not linear and levels >= 8)
+    long_solves = solves and not linear and levels >= 8
     if 64 < d <= 512 and not pb:
         enough = (8192 if solves else 16384) if d > 256 else (4096 if solves else 8192) if d > 128 else 8192
         if nb >= enough:
             return "orq_rows_kernel", 0.25
     if d in (64, 128):
         return "even_small_kernel" if even else "sorted_small_kernel", d / 256
+    if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= (8 if d <= 1024 else 5):
+        capacity = 1024 if d <= 1024 else 2048 if d <= 2048 else 4096
+        number = (levels - 2) * (1 + wl.level_iters)
+        if d <= 1024:
+            enough = 513
+        elif d == capacity:
+            enough = 16 if number >= 6 else 513
+        else:
+            enough = 513 if number >= 12 else 8193 if levels == 5 and d <= 2048 else 1281
+        if nb >= enough:
+            return "orq_pool_kernel", 2 if d > 2048 else 1
     if d <= 2048:
-        few = 0 if d <= 256 else (2560 if long_solves and not pb else 0) if d <= 512 else 512 if d <= 1024 else 1280
+        few = 0 if d <= 256 else (2560 if long_solves else 0) if d <= 512 else 512 if d <= 1024 else 1280
         return ("orq_team_kernel", 2 if d <= 512 else 4) if nb <= few else ("orq_quantize_kernel", 1)
     if d <= 4096:
-        return "orq_team_kernel", 2 if long_solves and nb > 4096 else 4
+        return "orq_team_kernel", 2 if pb and nb > 4096 else 4
     if d <= 8192 and nb <= 256:
         return "orq_team_kernel", 8
     wavefronts = 4 if d <= 8192 else 8 if d <= 16384 else 16

@@ -85,6 +85,15 @@ __device__ __forceinline__ double wave_sum(double x)
     return readlane_f64(x, 63);
 }
 
+__device__ __forceinline__ float wave_sum_f32(float x)
+{
+    x += dpp_f32<kDppXor1>(x);
+    x += dpp_f32<kDppXor2>(x);
+    x += dpp_f32<kDppHalfMirror>(x);
+    x += dpp_f32<kDppMirror>(x);
+    return (readlane_f32(x, 0) + readlane_f32(x, 16)) + (readlane_f32(x, 32) + readlane_f32(x, 48));
+}
+
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)
 {
     x += dpp_u32<kDppXor1>(x);

@@ -1,0 +1,409 @@
+// Internal header of libogq: level solves of several buckets side by side in one wavefront, each by its own group of lanes.
+// Included by the kernels that group whole buckets in LDS (pool_kernels.h).  Compile with -ffp-contract=off.
+#ifndef OGQ_GROUP_SOLVE_H
+#define OGQ_GROUP_SOLVE_H
+
+#include "rounding_kernels.h"
+
+namespace ogq {
+
+constexpr uint32_t kGroupLanes = 16;  // lanes per bucket (and chain): a row
+
+// Per level: what OrqLds keeps.
+struct __attribute__((aligned(16))) GroupLevel {
+    double sum_lt, sum_le;
+    float value;
+    uint16_t count_lt, count_le;
+    uint16_t rank;  // the rank the level was picked at (0 = not picked by rank)
+};
+
+// Bins of a bucket, HALF per sign, monotone in the value: the bin of a magnitude grows like the logarithm of
+// y = (magnitude + unit) / (largest + unit), so the bins are linear below `unit` and logarithmic above, and end at the bucket's
+// largest magnitude.  With unit = mean magnitude / 32 the bin of a level of a bucket of 4096 with 1024 bins holds 8 elements of Gaussian,
+// 6.5 of Student-t and 4 of two-scale values, and more than 16 in 2 to 4 % of the cases; 16 binades with 32 bins each (value_bin) hold
+// 16, 10 and 4, and more than 16 in 42, 21 and 4 %.  The bins only say where an element is looked for, so neither the mean
+// (that of a sample) nor the rounding in here touches a result; but every use must round alike.
+struct ScaledBins {
+    float scale, offset;  // y = magnitude * scale + offset
+    uint32_t factor;      // bins per unit in the last place of y, times 2^32
+};
+
+template <int HALF>
+__device__ __forceinline__ ScaledBins scaled_bins(float mean_magnitude, uint32_t mag_max)
+{
+    const float largest = __uint_as_float(mag_max);
+    const float unit = fmaxf(mean_magnitude, largest * 0x1p-12f) * 0x1p-5f;  // at most 17 binades above `unit`
+    ScaledBins b;
+    b.scale = fminf(__builtin_amdgcn_rcpf(unit + largest), 0x1.fffffep127f);
+    b.offset = fminf(unit * b.scale, 1.0f);  // (infinities: 1)
+    const uint32_t range = 0x3F800000u - __float_as_uint(b.offset);
+    b.factor = (uint32_t)fminf((float)HALF * 0x1p32f * __builtin_amdgcn_rcpf((float)range + 1.0f), 0x1.fffffep31f);
+    return b;
+}
+
+template <int HALF>
+__device__ __forceinline__ uint32_t magnitude_bin(float value, const ScaledBins& b)
+{
+    const uint32_t y = __float_as_uint(__builtin_fmaf(__builtin_fabsf(value), b.scale, b.offset));
+    return umin32(__umulhi(y - __float_as_uint(b.offset), b.factor), (uint32_t)(HALF - 1));  // (rounding near the largest; NaN)
+}
+
+// Bin of a value (with -0 already turned into +0) counted from the middle: -HALF .. HALF - 1.
+template <int HALF>
+__device__ __forceinline__ int32_t signed_bin(float canonical, const ScaledBins& b)
+{
+    return (int32_t)magnitude_bin<HALF>(canonical, b) ^ ((int32_t)__float_as_uint(canonical) >> 31);
+}
+
+// A bucket in LDS as one lane of its group sees it.
+struct GroupBucket {
+    const char* grouped;        // fp32 bit patterns by bin
+    const uint16_t* bin_start;  // byte offset of every bin's first position in `grouped`; points at the middle bin's
+    const double* prefix;       // sum of everything before every BLOCK-th position
+    GroupLevel* level;
+    unsigned long long* limb;   // workspace of exact_floor_t
+    ScaledBins bins;
+    uint32_t len;               // elements
+    double bound;               // sum_error_bound (floor_t_from_sums)
+    bool ordinary;              // at least 20 elements, none of them NaN
+};
+
+__device__ __forceinline__ float grouped_value(const char* at) { return __uint_as_float(*reinterpret_cast<const uint32_t*>(at)) + 0.0f; }
+
+// Ascending sort of K keys per lane over every group of G lanes: element K * (lane in the group) + register.  The first step
+// of a merge of runs of N elements pairs e with e ^ (2 N - 1), the others e with e ^ J (see wave_sort_merge).
+template <int J, int K>
+__device__ __forceinline__ void group_sort_steps(uint32_t (&x)[K], uint32_t lane)
+{
+    if constexpr (J >= K) {
+        const uint32_t bound = upper_lanes<J / K>(lane);
+#pragma unroll
+        for (int r = 0; r < K; ++r) x[r] = smaller_or_larger(x[r], lane_xor<J / K>(x[r], lane), bound);
+    } else if constexpr (J >= 1) {
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+            if ((r & J) == 0) sort_pair(x[r], x[r | J]);
+    }
+    if constexpr (J > 1) group_sort_steps<J / 2, K>(x, lane);
+}
+
+template <int G, int K, int N = 1>
+__device__ __forceinline__ void group_sort(uint32_t (&x)[K], uint32_t lane)
+{
+    if constexpr (2 * N <= K * G) {
+        if constexpr (2 * N <= K) {
+#pragma unroll
+            for (int r = 0; r < K; ++r)
+                if (r < (r ^ (2 * N - 1))) sort_pair(x[r], x[r ^ (2 * N - 1)]);
+        } else {
+            const uint32_t bound = upper_lanes<N / K>(lane);
+            uint32_t y[K];
+#pragma unroll
+            for (int r = 0; r < K; ++r) y[r] = lane_reverse<N / K>(x[K - 1 - r], lane);
+#pragma unroll
+            for (int r = 0; r < K; ++r) x[r] = smaller_or_larger(x[r], y[r], bound);
+        }
+        if constexpr (N > 1) group_sort_steps<N / 2, K>(x, lane);
+        group_sort<G, K, 2 * N>(x, lane);
+    }
+}
+
+// An element picked by rank, the same in all lanes of a group; counts and sum are those of its bin.
+struct GroupPicked {
+    float value;
+    uint32_t count_lt, count_le;
+    double part;  // this lane's share of the sum of the smaller elements
+};
+
+// The element of index `index` (0-based) among the n (at most G K) values at `at`.
+template <int G, int K, bool SUMS>
+__device__ __forceinline__ GroupPicked group_pick_sorted(const char* at, uint32_t n, uint32_t index, uint32_t lane)
+{
+    const uint32_t i = lane & (uint32_t)(G - 1);
+    float value[K];
+    uint32_t mine[K], x[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        // (a lane past the n reads whatever of the LDS record follows and drops it)
+        value[k] = grouped_value(at + 4u * (i + (uint32_t)(G * k)));
+        mine[k] = i + (uint32_t)(G * k) < n ? float_to_key(value[k]) : 0xFFFFFFFFu;
+        x[k] = mine[k];
+    }
+    group_sort<G, K>(x, lane);
+    // element `index`, handed to all lanes of the group as the largest of what they offer
+    uint32_t offer[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) offer[k] = x[k];
+#pragma unroll
+    for (int half = K / 2, bit = 0; half >= 1; half /= 2, ++bit) {
+#pragma unroll
+        for (int k = 0; k < half; ++k) offer[k] = (index & (1u << bit)) ? offer[2 * k + 1] : offer[2 * k];
+    }
+    const uint32_t key = row_max_u32<G>(i == index / (uint32_t)K ? offer[0] : 0u, lane);
+    GroupPicked p{key_to_float(key), 0u, 0u, 0.0};
+    if constexpr (SUMS) {
+        uint32_t counts = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool below = mine[k] < key;
+            counts += (below ? 1u : 0u) + (mine[k] <= key ? 0x10000u : 0u);
+            p.part += (double)(below ? value[k] : 0.0f);
+        }
+        counts = row_sum_u32<G>(counts, lane);
+        p.count_lt = counts & 0xFFFFu;
+        p.count_le = umin32(counts >> 16, n);  // (a key of all ones, a NaN, equals the padding)
+    }
+    return p;
+}
+
+// The same for a crowded bin (some group's bin holds more than fits the sort): the key is found by bisection over the bits in
+// which any group's smallest and largest key of the bin differ (none when all its values are equal).
+template <int G, bool SUMS>
+__device__ __forceinline__ GroupPicked group_pick_bisected(const char* at, uint32_t n, uint32_t index, uint32_t lane)
+{
+    const uint32_t i = lane & (uint32_t)(G - 1);
+    auto each = [&](auto f) {
+        for (uint32_t p = i; p < n; p += (uint32_t)G) f(grouped_value(at + 4u * p));
+    };
+    uint32_t smallest = 0xFFFFFFFFu, largest = 0u;
+    each([&](float x) {
+        smallest = umin32(smallest, float_to_key(x));
+        largest = umax32(largest, float_to_key(x));
+    });
+    smallest = row_min_u32<G>(smallest, lane);
+    largest = row_max_u32<G>(largest, lane);
+    const uint32_t any = uniform_u32(wave_max_u32(smallest <= largest ? smallest ^ largest : 0u));
+    uint32_t key = smallest;
+    if (any != 0u) {
+        const int top = 31 - __builtin_clz(any);
+        key = top == 31 ? 0u : smallest & ~((2u << top) - 1u);
+#pragma unroll 1
+        for (int bit = top; bit >= 0; --bit) {
+            const uint32_t candidate = key | (1u << bit);
+            uint32_t below = 0;
+            each([&](float x) { below += float_to_key(x) < candidate ? 1u : 0u; });
+            below = row_sum_u32<G>(below, lane);
+            if (below <= index) key = candidate;
+        }
+    }
+    GroupPicked p{key_to_float(key), 0u, 0u, 0.0};
+    if constexpr (SUMS) {
+        uint32_t counts = 0;
+        each([&](float x) {
+            const bool below = float_to_key(x) < key;
+            counts += (below ? 1u : 0u) + (float_to_key(x) <= key ? 0x10000u : 0u);
+            p.part += (double)(below ? x : 0.0f);
+        });
+        counts = row_sum_u32<G>(counts, lane);
+        p.count_lt = counts & 0xFFFFu;
+        p.count_le = counts >> 16;
+    }
+    return p;
+}
+
+// floor(T) of a group's bucket in exact arithmetic (see exact_floor_t).
+static __device__ __attribute__((noinline)) uint32_t exact_floor_t_group(unsigned long long* limb, const char* grouped, uint32_t len,
+                                                                         uint32_t lane_in_group, uint32_t lanes, float L, float R,
+                                                                         uint32_t count_in, uint32_t guess)
+{
+    return exact_floor_t(limb, lane_in_group, lanes, L, R, count_in, guess, [&](auto add) {
+        for (uint32_t i = lane_in_group; i < len; i += lanes) add(grouped_value(grouped + 4u * i));
+    });
+}
+
+// Truncation that takes negative values and NaN to 0 (v_cvt_u32_f64 saturates; the conversion of the language does not).
+__device__ __forceinline__ uint32_t truncated_u32(double x)
+{
+    uint32_t r;
+    asm("v_cvt_u32_f64_e32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// Lanes of this lane's row for which the condition holds.
+__device__ __forceinline__ uint32_t row_count(bool condition, uint32_t lane)
+{
+    return (uint32_t)__popc((uint32_t)(__ballot(condition) >> (lane & 48u)) & 0xFFFFu);
+}
+
+// One level solve per group, run by a whole wavefront: level k between the levels l and r of the group's bucket (see
+// orq_solve_one), entry = k | l << 4 | r << 8, 0 for a group with nothing to do.  Shape: HALF (signed_bin) and BLOCK,
+// the positions per entry of the prefix.  SUMS = false: one interior level, whose solve reads the bucket's total alone.
+//
+// The wavefront waits for itself here, so what counts is the length of the chain: the bin of a rank needs no search (the element
+// at that position of the grouped bucket is in it), and a bin of at most 16 elements is not sorted: every lane counts the elements
+// smaller than its own among 20 that begin at a multiple of 4.  What they hold beside the bin changes nothing: it is smaller or
+// larger than everything in it.
+template <bool SUMS, class Shape>
+__device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry, uint32_t lane)
+{
+    constexpr uint32_t BLOCK = Shape::BLOCK, G = kGroupLanes;
+    static_assert(BLOCK % G == 0, "the elements in front of a bin are read G at a time");
+    const uint32_t i = lane & (G - 1u);
+    GroupLevel* const level = b.level + (entry & 15u);
+    const GroupLevel left = b.level[(entry >> 4) & 15u], right = b.level[entry >> 8];
+    const uint32_t last_rank = level->rank;
+    const float L = left.value, R = right.value;
+    const bool ordered = L < R;
+    // S = sum_{L<=v<=R} (v - L),  T = S / (R - L),  level = element of rank #{v<=R} - floor(T)
+    const uint32_t count_in = (uint32_t)right.count_le - left.count_lt;
+    const double width = (double)R - (double)L;
+    const double Ssum = __builtin_fma(-(double)L, (double)count_in, right.sum_le - left.sum_lt);
+    // floor_t_from_sums without branches; m is not used when L == R
+    uint32_t m = truncated_u32(Ssum * __builtin_amdgcn_rcp(width));
+    const double rest = __builtin_fma(-(double)m, width, Ssum);
+    const bool over = rest >= width, under = rest < 0.0 && m > 0u;
+    m = m + (over ? 1u : 0u) - (under ? 1u : 0u);
+    const double settled = rest - (over ? width : under ? -width : 0.0);
+    const bool undecided = ordered && b.bound != 0.0 && !(settled > b.bound && width - settled > b.bound);
+    if (__ballot(undecided) != 0) {
+        if (undecided) m = exact_floor_t_group(b.limb, b.grouped, b.len, i, G, L, R, count_in, m);
+    }
+    const uint32_t rank = umin32(umax32(__builtin_elementwise_sub_sat((uint32_t)right.count_le, m), 1u), b.len);
+    const bool same = entry == 0u || (ordered && rank == last_rank);  // same element as last time
+    if (__ballot(!same) == 0) return;
+
+    const uint32_t at = rank > 0u ? rank - 1u : 0u;  // (rank 0: an empty bucket)
+    const int32_t bin = signed_bin<Shape::HALF>(grouped_value(b.grouped + 4u * at), b.bins);
+    const uint32_t first = (uint32_t)b.bin_start[bin] >> 2, last = (uint32_t)b.bin_start[bin + 1] >> 2;
+    // 20 elements that end inside the bucket, and the 16 of them that are the lanes' own
+    const uint32_t end = __builtin_elementwise_sub_sat(b.len, G + 4u) & ~3u;
+    const bool at_end = (first & ~3u) > end;
+    const uint32_t window = at_end ? end : first & ~3u, own_first = at_end ? end + 4u : first;
+    const bool windowed = __ballot(last > own_first + G || !b.ordinary) == 0;
+    const uint32_t from = windowed ? own_first : first;
+    double before = 0.0, part = 0.0;
+    if constexpr (SUMS) {
+        // the sum of everything before `from`: the prefix of its block, and the block's positions in front of it
+        before = b.prefix[from / BLOCK];
+        const uint32_t in_front = from & (BLOCK - 1u);
+        const char* block = b.grouped + 4u * (from - in_front + i);
+#pragma unroll
+        for (uint32_t c = 0; c < BLOCK / G; ++c) {
+            const float x = __uint_as_float(*reinterpret_cast<const uint32_t*>(block + 4u * G * c));
+            part += (double)(i + G * c < in_front ? x : 0.0f);
+        }
+    }
+    float value;
+    uint32_t count_lt = 0, count_le = 0;  // from `from` on
+    if (windowed) {
+        const float4* around = reinterpret_cast<const float4*>(b.grouped + 4u * window);
+        const float own = grouped_value(b.grouped + 4u * (from + i));
+        uint32_t smaller = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < G / 4u + 1u; ++q) {
+            const float4 x = around[q];
+            smaller += x.x < own ? 1u : 0u;
+            smaller += x.y < own ? 1u : 0u;
+            smaller += x.z < own ? 1u : 0u;
+            smaller += x.w < own ? 1u : 0u;
+        }
+        // the wanted element is the largest one that has at most `at - window` smaller ones
+        value = smaller <= at - window ? own : -__builtin_inff();
+        value = fmaxf(value, dpp_f32<kDppXor1>(value));
+        value = fmaxf(value, dpp_f32<kDppXor2>(value));
+        value = fmaxf(value, dpp_f32<kDppHalfMirror>(value));
+        value = fmaxf(value, dpp_f32<kDppMirror>(value));
+        if constexpr (SUMS) {
+            const bool below = own < value;
+            count_lt = row_count(below, lane);
+            count_le = row_count(own <= value, lane);
+            part += (double)(below ? own : 0.0f);
+        }
+    } else {
+        const uint32_t n = last - first;
+        const char* keys = b.grouped + 4u * first;
+        GroupPicked p;
+        if (__ballot(n > 2u * G) == 0) p = group_pick_sorted<(int)G, 2, SUMS>(keys, n, at - first, lane);
+        else if (__ballot(n > 4u * G) == 0) p = group_pick_sorted<(int)G, 4, SUMS>(keys, n, at - first, lane);
+        else p = group_pick_bisected<(int)G, SUMS>(keys, n, at - first, lane);
+        value = p.value;
+        count_lt = p.count_lt;
+        count_le = p.count_le;
+        part += p.part;
+    }
+    const bool copy_left = !ordered || value < L;  // the level coincides with the left end
+    GroupLevel now;
+    now.value = copy_left ? L : value;
+    now.rank = (uint16_t)(copy_left ? 0u : rank);
+    now.count_lt = now.count_le = 0;
+    now.sum_lt = now.sum_le = 0.0;
+    if constexpr (SUMS) {
+        const double sum_lt = before + row_sum_f64<(int)G>(part, lane);
+        const double sum_le = __builtin_fma((double)(count_le - count_lt), (double)value, sum_lt);
+        now.count_lt = (uint16_t)(copy_left ? left.count_lt : from + count_lt);
+        now.count_le = (uint16_t)(copy_left ? (ordered ? left.count_le : right.count_le) : from + count_le);
+        now.sum_lt = copy_left ? left.sum_lt : sum_lt;
+        now.sum_le = copy_left ? (ordered ? left.sum_le : right.sum_le) : sum_le;
+    }
+    if (i == 0u && !same) *level = now;
+    wave_lds_sync();
+}
+
+// The greedy steps of a chain, 12 bits each; head: with the first solves of the first sweep in the steps that have room for them.
+constexpr uint64_t packed_entries(const TeamGreedy& greedy, int chain, bool head)
+{
+    uint64_t packed = 0;
+    for (int step = 0; step < greedy.steps; ++step) {
+        uint64_t e = greedy.entry[chain][step];
+        for (int h = 0; h < 2; ++h)
+            if (head && greedy.head_step[h] == step) e = (uint64_t)(h + 1) * 0x111u + 0x0F0u;
+        packed |= e << (12 * step);
+    }
+    return packed;
+}
+
+// All level solves of the groups' buckets, CHAINS = 1 or 2 groups per bucket (group lane / 16 of the wavefront is chain
+// (lane / 16) % CHAINS of its bucket).  One chain: Algorithm 1's order, then the sweeps.  Two chains: the schedule of
+// orq_team_solve, i.e. the halves on either side of Algorithm 1's first level, and of each pair of sweeps the second two levels
+// behind the first; the results are those of the serial order.
+template <int CHAINS, int S, class Shape>
+__device__ __forceinline__ void group_solve_levels(const GroupBucket& b, uint32_t sweeps, uint32_t lane)
+{
+    constexpr bool SUMS = S > 3;
+    constexpr uint32_t INTERIOR = S - 2;
+    constexpr uint32_t kNext = 0x111u, kFirst = 0x201u;  // from a level's entry of a sweep to the next one's; that of level 1
+    if constexpr (CHAINS == 1) {
+        constexpr GreedyOrder order = greedy_order<S>();
+        static_assert(order.count <= 5, "12 bits per step");
+        uint32_t steps = order.count + (S > 3 ? sweeps * INTERIOR : 0u);  // (one interior level: sweeps repeat it)
+        uint64_t ahead = order.packed[0];
+        uint32_t entry = 0;
+#pragma unroll 1
+        for (uint32_t step = 0; step < steps; ++step) {
+            // what is packed gives out first, then one level after the other
+            if (ahead != 0u) entry = (uint32_t)ahead & 0xFFFu;
+            else entry = step == (uint32_t)order.count || (entry & 15u) == INTERIOR ? kFirst : entry + kNext;
+            ahead >>= 12;
+            group_solve<SUMS, Shape>(b, entry, lane);
+        }
+    } else {
+        constexpr TeamGreedy greedy = team_greedy<S>();
+        static_assert(greedy.steps <= 5, "12 bits per step");
+        const bool second = (lane & kGroupLanes) != 0u;
+        const uint64_t packed_first = sweeps > 0u ? packed_entries(greedy, 0, true) : packed_entries(greedy, 0, false);
+        constexpr uint64_t packed_second = packed_entries(greedy, 1, false);
+        uint64_t ahead = second ? packed_second : packed_first;
+#pragma unroll 1
+        for (int step = 0; step < greedy.steps; ++step) {
+            group_solve<SUMS, Shape>(b, (uint32_t)ahead & 0xFFFu, lane);
+            ahead >>= 12;
+        }
+        uint32_t t = (uint32_t)greedy.head;  // (the first pair begins behind its head start)
+#pragma unroll 1
+        for (uint32_t left = sweeps; left > 0u;) {
+            const bool pair = left > 1u;
+            const uint32_t end = INTERIOR + (pair ? 2u : 0u), mine = second ? 2u : 0u;
+#pragma unroll 1
+            for (; t < end; ++t) {
+                const uint32_t at = t - mine;  // level at + 1 of this chain's sweep
+                const bool active = at < INTERIOR && (pair || !second);
+                group_solve<SUMS, Shape>(b, active ? at * kNext + kFirst : 0u, lane);
+            }
+            t = 0;
+            left -= pair ? 2u : 1u;
+        }
+    }
+}
+
+}  // namespace ogq
+#endif  // OGQ_GROUP_SOLVE_H

@@ -1,0 +1,357 @@
+// Internal header of libogq: the random-rounding quantize kernel for buckets of 513 to 4096 elements whose rule solves several
+// interior levels (ORQ with five levels and more), two buckets per workgroup.  Included by rounding_part.hip after
+// rounding_kernels.h, whose exact sums and encoder it uses.  Compile with -ffp-contract=off.
+#ifndef OGQ_POOL_KERNELS_H
+#define OGQ_POOL_KERNELS_H
+
+#include "group_solve.h"
+
+namespace ogq {
+
+// ----------------------------------------------------------------------------------------------
+// NB buckets per workgroup, W wavefronts each, wavefront w of a bucket holding its elements [256 C w, 256 C (w + 1)) in the register
+// layout of orq_bucket.  The phases are those of orq_team_kernel: load, extremes, grouping in LDS, fp64 prefix, level solves,
+// encode; but one wavefront of the workgroup solves the levels of all NB buckets side by side, a row of 16 lanes for each of a
+// bucket's two chains of solves (group_solve.h).
+//
+// A solve is some 200 vector instructions on values that are the same for the whole bucket, in one chain of LDS reads and
+// fp64 operations.  With a wavefront's 64 lanes on one solve (orq_team_kernel), eight levels and two sweeps took 1,080 of 2,819
+// vector instructions of each wavefront and as many scalar ones, 11 steps behind workgroup barriers; here the four rows work
+// for two buckets, the steps need no barrier, and the kernel has 2,358 vector and 429 scalar instructions per wavefront.
+// 143.7 M values in buckets of 4096: 421 -> 373 us; 25.6 M values in buckets of 2048: 124 -> 80.
+// Bound by the solves' latency: of a workgroup's 46,000 cycles they take 21,000, during which its other wavefronts wait, and the
+// LDS (16 KB of values per bucket of 4096) holds the buckets of four workgroups; the vector units issue 75 % of the time.
+// The solving wavefront runs at a raised priority (its instructions go first on its SIMD): 30,000 -> 25,000 cycles of solves.
+// Four buckets per workgroup, in rows of 8 lanes, were slower (418 us): fewer workgroups overlap.
+// ----------------------------------------------------------------------------------------------
+// LDS through its own address space: addresses of 32 bits, of which the histogram keeps 16 with every element.
+typedef __attribute__((address_space(3))) uint32_t LdsWord;
+typedef __attribute__((address_space(3))) uint16_t LdsHalf;
+
+template <int W, int C, int S>
+struct PoolBucket {
+    static constexpr int D = 256 * C * W;                      // element capacity
+    static constexpr int B = D / 4, HALF = B / 2;              // bins
+    static constexpr int BLOCK = 4 * C;                        // positions per entry of the fp64 prefix: one lane's
+    union {
+        uint32_t bin_count[B];  // bytes: 4 per element
+        uint32_t grouped[D];    // fp32 bit patterns by bin
+    };
+    double prefix[D / BLOCK];
+    GroupLevel level[S];
+    double wave_sum[W];
+    TeamSlot slots[2][W];
+    uint16_t bin_start[B + 2];  // byte offset of each bin's first position in `grouped`; [B] = end of the last bin
+    ScaledBins bins;
+    uint32_t tiny;              // set where an element is too small for exact sums
+};
+
+template <int W, int C, int S>
+struct PoolLds {
+    static constexpr int CHAINS = S > 4 ? 2 : 1, NB = 4 / CHAINS;
+    PoolBucket<W, C, S> bucket[NB];
+    unsigned long long exact_limb[NB * CHAINS][kExactLimbs];
+};
+
+template <int W, int C, int S, int BITS, bool FULL>
+__device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const float* __restrict__ grad, size_t n,
+                                               uint32_t bucket_size, uint32_t sweeps, float clip, uint32_t num_buckets, uint64_t seed,
+                                               uint64_t index_offset, float* __restrict__ levels, uint32_t* __restrict__ codes32)
+{
+    static_assert(W == 1 || W == 2, "the bin starts of a second wavefront follow from its own total");
+    using Bucket = PoolBucket<W, C, S>;
+    constexpr uint32_t PER_WAVE = 256u * C, B = Bucket::B, HALF = Bucket::HALF, BLOCK = Bucket::BLOCK;
+    constexpr int CHAINS = PoolLds<W, C, S>::CHAINS, NB = PoolLds<W, C, S>::NB;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = uniform_u32(threadIdx.x >> 6);
+    const uint32_t slot_of = wave / (uint32_t)W, part = wave % (uint32_t)W;  // bucket of the workgroup, wavefront of the bucket
+    const uint32_t bucket = blockIdx.x * (uint32_t)NB + slot_of;
+    Bucket& my = lds.bucket[slot_of];
+    const bool exists = FULL || bucket < num_buckets;
+    const size_t begin = exists ? (size_t)bucket * bucket_size : 0u;
+    uint32_t len = (uint32_t)Bucket::D;
+    if constexpr (!FULL) {
+        const size_t rest = n - begin;
+        len = !exists ? 0u : rest < bucket_size ? (uint32_t)rest : bucket_size;
+    }
+    const float* g = grad + begin;
+    const uint32_t first = PER_WAVE * part;
+    const uint32_t my_len = FULL ? PER_WAVE : len > first ? (len - first < PER_WAVE ? len - first : PER_WAVE) : 0u;
+    auto sync = [&]() __attribute__((always_inline)) {  // of the wavefronts that hold a bucket
+        if constexpr (W == 1) wave_lds_sync();
+        else __syncthreads();
+    };
+
+    float v[C][4];
+    load_range<C, FULL>(v, g, first, len, my_len, lane);
+    {
+        constexpr uint32_t ZEROS = B / (64u * W) / 4u;
+        uint4* mine = reinterpret_cast<uint4*>(my.bin_count) + ZEROS * (64u * part + lane);
+#pragma unroll
+        for (uint32_t i = 0; i < ZEROS; ++i) mine[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (part == 0u && lane == 0u) my.tiny = 0u;
+    }
+    WaveTeam<W> team{my.slots, part, 0u};
+
+    float limit = __uint_as_float(0x7F800000u);  // clipping threshold
+    if (clip > 0.0f) {  // the same for every thread of the grid
+        float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
+        uint32_t here = lane;
+        limit = clip_in_registers<4 * C>(
+            flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * here + (j & 3) < my_len); },
+            [&](double x) __attribute__((always_inline)) {
+                if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
+                if constexpr (W == 1) return wave_sum(x);
+                else return team.sum(wave_sum(x));
+            });
+        if constexpr (!FULL) set_padding<C>(v, my_len, lane);
+    }
+
+    // ---- extremes of the bucket ------------------------------------------------------------------------
+    float low, high;
+    uint32_t unused_zeros;
+    lane_extremes<C, false>(v, low, high, unused_zeros);
+    low = wave_min(low);
+    high = wave_max(high);
+    // mean magnitude of every fourth element (padding is NaN)
+    float sample = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) sample += FULL || v[c][0] == v[c][0] ? __builtin_fabsf(v[c][0]) : 0.0f;
+    double magnitudes = (double)wave_sum_f32(sample);
+    if constexpr (W > 1) {
+        const TeamSlot* s = team.exchange(magnitudes, __float_as_uint(low), __float_as_uint(high));
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            low = fminf(low, __uint_as_float(s[w].a));
+            high = fmaxf(high, __uint_as_float(s[w].b));
+        }
+        magnitudes = s[0].sum + s[W - 1].sum;
+    } else {
+        wave_lds_sync();  // the zeroed bins
+    }
+    low = uniform_f32(low + 0.0f);  // -0 -> +0
+    high = uniform_f32(high + 0.0f);
+    const uint32_t mag_max = umax32(__float_as_uint(low) & 0x7FFFFFFFu, __float_as_uint(high) & 0x7FFFFFFFu);
+    const float mean = (float)magnitudes * __builtin_amdgcn_rcpf((float)((len + 3u) / 4u));
+    ScaledBins bins_of = scaled_bins<(int)HALF>(mean, mag_max);
+    bins_of.factor = uniform_u32(bins_of.factor);
+
+    // ---- histogram: the returning LDS add hands every element its position inside its bin ------------------
+    uint32_t slot[C][4];  // LDS address of the bin's counter | 4 * position inside the bin << 16
+    {
+        const float zero = opaque_zero();
+        uint32_t middle = (uint32_t)(uintptr_t)((LdsWord*)my.bin_count + HALF);
+        asm("" : "+s"(middle));  // (one addition with the bin, not two)
+        uint32_t here = lane;
+        if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (FULL || 256u * (uint32_t)c < my_len) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const bool valid = FULL || 256u * c + 4u * here + k < my_len;
+                    // (padding adds 0 to one bin per lane: no branch)
+                    const uint32_t counter = middle + 4u * (uint32_t)(valid ? signed_bin<(int)HALF>(v[c][k] + zero, bins_of) : (int32_t)here);
+                    const uint32_t position = __hip_atomic_fetch_add((LdsWord*)(uintptr_t)counter, valid ? 4u : 0u, __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+                    slot[c][k] = __builtin_amdgcn_perm(position, counter, 0x05040100u);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) slot[c][k] = 0u;
+            }
+        }
+    }
+    sync();
+
+    // ---- bin starts: wavefront `part` owns the bins [part B / W, (part + 1) B / W) ---------------------------
+    {
+        constexpr uint32_t PER = B / (64u * W);  // bins per lane: 8
+        const uint4* mine = reinterpret_cast<const uint4*>(my.bin_count) + PER / 4u * (64u * part + lane);
+        uint32_t count[PER], total = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < PER / 4u; ++q) {
+            const uint4 x = mine[q];
+            count[4 * q] = x.x; count[4 * q + 1] = x.y; count[4 * q + 2] = x.z; count[4 * q + 3] = x.w;
+        }
+#pragma unroll
+        for (uint32_t t = 0; t < PER; ++t) total += count[t];
+        const uint32_t incl = wave_inclusive_scan_u32(total);
+        uint32_t start = incl - total;
+        if constexpr (W == 2)  // all counts together make the bucket
+            start += part == 0u ? 0u : 4u * len - __builtin_amdgcn_readlane(incl, 63);
+        uint32_t* pairs = reinterpret_cast<uint32_t*>(my.bin_start) + PER / 2u * (64u * part + lane);
+#pragma unroll
+        for (uint32_t t = 0; t < PER / 2u; ++t) {
+            const uint32_t next = start + count[2 * t];
+            pairs[t] = start | next << 16;
+            start = next + count[2 * t + 1];
+        }
+        if (part == (uint32_t)W - 1u && lane == 63u) my.bin_start[B] = (uint16_t)start;  // = 4 len
+    }
+    sync();
+
+    // ---- scatter the values into their bins (bin starts of a group of chunks read before its writes) ----------
+    {
+        char* grouped = reinterpret_cast<char*>(my.grouped);
+        // (a start is half as wide as a counter)
+        const uint32_t starts = (uint32_t)(uintptr_t)((LdsWord*)my.bin_start) - (uint32_t)(uintptr_t)((LdsWord*)my.bin_count) / 2u;
+        constexpr int GROUP = C < 4 ? C : 4;
+        uint32_t here = lane;
+        if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
+#pragma unroll
+        for (int c0 = 0; c0 < C; c0 += GROUP) {
+            if (!FULL && 256u * (uint32_t)c0 >= my_len) continue;
+#pragma unroll
+            for (int c = c0; c < c0 + GROUP; ++c)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    slot[c][k] = *(const LdsHalf*)(uintptr_t)(starts + __builtin_amdgcn_ubfe(slot[c][k], 1u, 15u)) + (slot[c][k] >> 16);
+#pragma unroll
+            for (int c = c0; c < c0 + GROUP; ++c)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    uint32_t at = slot[c][k], bits = __float_as_uint(v[c][k]);
+                    if constexpr (!FULL) {
+                        // padding goes where it lies in the bucket, behind all elements, as zeros that the prefix may add
+                        const uint32_t e = 256u * c + 4u * here + k;
+                        const bool valid = e < my_len;
+                        at = valid ? at : 4u * (first + e);
+                        bits = valid ? bits : 0u;
+                    }
+                    *reinterpret_cast<uint32_t*>(grouped + at) = bits;
+                }
+        }
+    }
+    sync();
+
+    // ---- fp64 prefix of the grouped values: a lane sums the BLOCK positions of one entry -----------------------
+    {
+        const float4* from = reinterpret_cast<const float4*>(my.grouped + PER_WAVE * part + BLOCK * lane);
+        // every lane begins at another of its 16-byte pieces, so that the lanes meet different LDS banks
+        const uint32_t turn = lane / (C < 8 ? 8u / C : 1u);
+        double sum = 0.0;
+#pragma unroll
+        for (uint32_t q = 0; q < (uint32_t)C; ++q) {
+            const float4 x = from[(q + turn) & (uint32_t)(C - 1)];
+            sum += (double)x.x;
+            sum += (double)x.y;
+            sum += (double)x.z;
+            sum += (double)x.w;
+        }
+        // (blocks behind the last group of chunks that holds elements have not been written)
+        if constexpr (!FULL) sum = BLOCK * lane < my_len ? sum : 0.0;
+        const double incl = wave_inclusive_scan_f64(sum);
+        my.prefix[64u * part + lane] = incl - sum;  // within the wavefront's positions, for the time being
+        if (lane == 63u) my.wave_sum[part] = incl;
+
+        // may the fp64 sums round?  (small elements sit in the bins next to zero: see any_tiny_element)
+        constexpr uint32_t SAFE = safe_binades((uint32_t)Bucket::D);
+        const uint32_t biased = mag_max >> 23;
+        if (biased > SAFE) {
+            const uint32_t mag_safe = (biased - SAFE) << 23;
+            const uint32_t near = magnitude_bin<(int)HALF>(__uint_as_float(mag_safe), bins_of) + 1u;
+            const char* grouped = reinterpret_cast<const char*>(my.grouped);
+            const uint32_t last = my.bin_start[HALF + near];
+            bool tiny = false;
+            for (uint32_t p = my.bin_start[HALF - near] + 4u * (64u * part + lane); p < last; p += 4u * 64u * W) {
+                const uint32_t magnitude = *reinterpret_cast<const uint32_t*>(grouped + p) & 0x7FFFFFFFu;
+                tiny = tiny || (magnitude != 0u && magnitude < mag_safe);
+            }
+            if (tiny) my.tiny = 1u;
+        }
+        // the level records of the ends: the bottom level is only ever the left end of a solve, the top level the right end
+        if (part == 0u && lane < (uint32_t)S) {
+            const bool top = lane == (uint32_t)(S - 1);
+            GroupLevel end;
+            end.value = top ? high : low;
+            end.count_lt = end.count_le = (uint16_t)(top ? len : 0u);
+            end.sum_lt = end.sum_le = 0.0;  // (the top level's follows below)
+            end.rank = 0u;
+            my.level[lane] = end;
+            my.bins = bins_of;
+        }
+    }
+    __syncthreads();
+
+    // ---- the levels of all buckets, on one wavefront (another one from workgroup to workgroup: a CU's wavefronts are dealt
+    //      to its SIMDs in order) -----------------------------------------------------------------------------------------
+    if (wave == (blockIdx.x * 0x9E3779B1u >> 16) % (uint32_t)(NB * W)) {
+        __builtin_amdgcn_s_setprio(3);
+        if constexpr (W == 2) {
+            // the second wavefronts' prefixes count from their own first position
+            double before[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) before[b] = lds.bucket[b].wave_sum[0] + lds.bucket[b].prefix[64u + lane];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) lds.bucket[b].prefix[64u + lane] = before[b];
+        }
+        constexpr uint32_t G = kGroupLanes;
+        static_assert(NB * CHAINS * G == 64, "one group per bucket and chain");
+        Bucket& b = lds.bucket[lane / (G * CHAINS)];
+        double total = b.wave_sum[0];
+        if constexpr (W == 2) total += b.wave_sum[1];
+        b.level[S - 1].sum_le = total;  // (the same from all lanes of the bucket)
+        wave_lds_sync();
+        const uint32_t of_bucket = blockIdx.x * (uint32_t)NB + lane / (G * CHAINS);
+        uint32_t its_len = (uint32_t)Bucket::D;
+        if constexpr (!FULL) {
+            const size_t at = (size_t)of_bucket * bucket_size;
+            its_len = of_bucket >= num_buckets ? 0u : n - at < bucket_size ? (uint32_t)(n - at) : bucket_size;
+        }
+        const uint32_t largest = umax32(__float_as_uint(b.level[0].value) & 0x7FFFFFFFu, __float_as_uint(b.level[S - 1].value) & 0x7FFFFFFFu);
+        const GroupBucket view{reinterpret_cast<const char*>(b.grouped),
+                               b.bin_start + HALF,
+                               b.prefix,
+                               b.level,
+                               lds.exact_limb[lane / G],
+                               b.bins,
+                               its_len,
+                               b.tiny != 0u ? sum_error_bound_of(largest, (uint32_t)Bucket::D) : 0.0,
+                               its_len >= G + 4u && total == total};
+        group_solve_levels<CHAINS, S, Bucket>(view, sweeps, lane);
+        __builtin_amdgcn_s_setprio(0);
+    }
+    __syncthreads();
+
+    float lv[S];
+    lv[0] = low;
+    lv[S - 1] = high;
+#pragma unroll
+    for (int k = 1; k < S - 1; ++k) lv[k] = my.level[k].value;
+    if (part == 0u && exists) {
+        float mine = lv[0];
+#pragma unroll
+        for (int k = 1; k < S; ++k) mine = lane == (uint32_t)k ? lv[k] : mine;
+        if (lane < (uint32_t)S) levels[(size_t)bucket * S + lane] = mine;
+    }
+    orq_encode<C, S, BITS, FULL>(v, lv, my_len, begin + first, seed, index_offset, codes32, ReloadFromMemory{g + first, my_len, limit});
+}
+
+template <int W, int C, int S, int BITS>
+__global__ __launch_bounds__((S > 4 ? 2 : 4) * W * kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 4 : 1))) void orq_pool_kernel(
+    const float* __restrict__ grad, size_t n, uint32_t bucket_size, uint32_t sweeps, float clip, uint32_t num_buckets, uint64_t seed,
+    uint64_t index_offset, float* __restrict__ levels, uint32_t* __restrict__ codes32)
+{
+    __shared__ __attribute__((aligned(16))) PoolLds<W, C, S> lds;
+    static_assert(sizeof(lds) <= 65536, "an LDS address in 16 bits");
+    constexpr uint32_t D = PoolBucket<W, C, S>::D;
+    if (bucket_size == D && ((size_t)blockIdx.x + 1u) * (PoolLds<W, C, S>::NB * D) <= n)
+        orq_pool_group<W, C, S, BITS, true>(lds, grad, n, bucket_size, sweeps, clip, num_buckets, seed, index_offset, levels, codes32);
+    else
+        orq_pool_group<W, C, S, BITS, false>(lds, grad, n, bucket_size, sweeps, clip, num_buckets, seed, index_offset, levels, codes32);
+}
+
+// ----------------------------------------------------------------------------------------------
+// host side
+// ----------------------------------------------------------------------------------------------
+template <int W, int C, int S, int BITS>
+void launch_orq_pool(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
+{
+    constexpr int NB = PoolLds<W, C, S>::NB;
+    launch_kernel((orq_pool_kernel<W, C, S, BITS>), dim3((nb + NB - 1) / NB), dim3(NB * W * kWave), st, g, n, p->bucket_size, p->level_iters,
+                  p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
+}
+
+}  // namespace ogq
+#endif  // OGQ_POOL_KERNELS_H

@@ -674,14 +674,14 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// floor(T), exactly.  Called by all lanes that hold the bucket (a wavefront, or the group of lanes of a small bucket)
+// floor(T), exactly.  Called by all lanes that hold the bucket (a wavefront, or the group of `lanes` lanes of a small bucket)
 // with the same limb array, L < R, count_in = #{L <= v <= R} and a first guess; each_of_mine(f) runs f(x) on the bucket
 // elements this lane answers for; lane_in_group counts the calling lanes from 0.
 template <class EachFn>
-__device__ __forceinline__ uint32_t exact_floor_t(unsigned long long* limb, uint32_t lane_in_group, float L, float R,
+__device__ __forceinline__ uint32_t exact_floor_t(unsigned long long* limb, uint32_t lane_in_group, uint32_t lanes, float L, float R,
                                                   uint32_t count_in, uint32_t guess, EachFn each_of_mine)
 {
-    if (lane_in_group < (uint32_t)kExactLimbs) limb[lane_in_group] = 0ull;
+    for (uint32_t i = lane_in_group; i < (uint32_t)kExactLimbs; i += lanes) limb[i] = 0ull;
     wave_lds_sync();
     each_of_mine([&](float x) {
         if (L <= x && x <= R) exact_add_shared(limb, x);
@@ -708,7 +708,7 @@ static __device__ __attribute__((noinline)) uint32_t exact_floor_t_grouped(unsig
                                                                    uint32_t len, uint32_t lane, uint32_t stride, float L,
                                                                    float R, uint32_t count_in, uint32_t guess)
 {
-    return exact_floor_t(limb, lane, L, R, count_in, guess, [&](auto add) {
+    return exact_floor_t(limb, lane, stride, L, R, count_in, guess, [&](auto add) {
         for (uint32_t i = lane; i < len; i += stride) add(__uint_as_float(grouped[skewed(i)]));
     });
 }
@@ -718,7 +718,7 @@ static __device__ __attribute__((noinline)) uint32_t exact_floor_t_registers(uns
                                                                      float L, float R, uint32_t count_in, uint32_t guess,
                                                                      float x0, float x1, float x2, float x3, uint32_t valid)
 {
-    return exact_floor_t(limb, lane_in_group, L, R, count_in, guess, [&](auto add) {
+    return exact_floor_t(limb, lane_in_group, (uint32_t)kExactLimbs, L, R, count_in, guess, [&](auto add) {
         if (valid > 0u) add(x0);
         if (valid > 1u) add(x1);
         if (valid > 2u) add(x2);
@@ -2007,14 +2007,14 @@ __device__ __forceinline__ uint32_t row_fetch(const uint32_t (&x)[4], uint32_t i
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)((first_lane + (index >> 2)) << 2), (int)mine);
 }
 
-// Sum over the group of G lanes, in every lane of the group.
+// Sum over the group of G = 8, 16 or 32 lanes, in every lane of the group.
 template <int G>
 __device__ __forceinline__ double row_sum_f64(double x, uint32_t lane)
 {
     x += dpp_f64<kDppXor1>(x);
     x += dpp_f64<kDppXor2>(x);
     x += dpp_f64<kDppHalfMirror>(x);
-    x += dpp_f64<kDppMirror>(x);
+    if constexpr (G >= 16) x += dpp_f64<kDppMirror>(x);
     if constexpr (G == 32) {
         const uint64_t u = (uint64_t)__double_as_longlong(x);
         const uint32_t lo = lane_xor<16>((uint32_t)u, lane), hi = lane_xor<16>((uint32_t)(u >> 32), lane);
@@ -2029,7 +2029,7 @@ __device__ __forceinline__ uint32_t row_sum_u32(uint32_t x, uint32_t lane)
     x += dpp_u32<kDppXor1>(x);
     x += dpp_u32<kDppXor2>(x);
     x += dpp_u32<kDppHalfMirror>(x);
-    x += dpp_u32<kDppMirror>(x);
+    if constexpr (G >= 16) x += dpp_u32<kDppMirror>(x);
     if constexpr (G == 32) x += lane_xor<16>(x, lane);
     return x;
 }
@@ -2041,7 +2041,7 @@ __device__ __forceinline__ uint32_t row_min_u32(uint32_t x, uint32_t lane)
     x = umin32(x, dpp_u32<kDppXor1>(x));
     x = umin32(x, dpp_u32<kDppXor2>(x));
     x = umin32(x, dpp_u32<kDppHalfMirror>(x));
-    x = umin32(x, dpp_u32<kDppMirror>(x));
+    if constexpr (G >= 16) x = umin32(x, dpp_u32<kDppMirror>(x));
     if constexpr (G == 32) x = umin32(x, lane_xor<16>(x, lane));
     return x;
 }
@@ -2343,9 +2343,8 @@ __global__ __launch_bounds__(4 * kWave) void sorted_small_kernel(const float* __
 // starts, scatter, fp64 block prefix) with workgroup barriers in between; the level solves run on wavefront 0, those of
 // five and more levels on the first two (orq_team_solve); then every wavefront encodes its own elements.
 //
-// What bounds it (eight levels, two sweeps, two wavefronts, 143.7 M values in buckets of 4096: 423 us): the solves, 185 us of
-// it, 11 steps that end in a barrier each; both wavefronts spend 64 lanes on one scalar chain.  2,819 vector instructions per
-// wavefront, SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES 0.81 (1.05 in a build without the solves).
+// What bounds it: with few buckets the latency of one; with many (buckets above 4096 elements) the solves, a step of which ends in
+// a barrier and spends 64 lanes on one scalar chain (buckets up to 4096 elements: pool_kernels.h).
 // ----------------------------------------------------------------------------------------------
 template <int W, int C>
 struct OrqTeamLds {
@@ -2591,10 +2590,21 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(RULE =
 // ----------------------------------------------------------------------------------------------
 // host side
 // ----------------------------------------------------------------------------------------------
+// Which rules and level counts the dispatch in rounding_part.hip gives to one wavefront of 256 C elements per bucket, and (below) to
+// W wavefronts.  The others are not compiled, and asking for one fails like a launch that the runtime refuses: a call must not
+// return success over outputs that nothing has written.
+template <int C>
+constexpr bool wave_serves(int S, int rule)
+{
+    return !(rule == kOptimal && S >= 8 && (C == 4 || C == 8));
+}
+
 template <int C, int S, int BITS, int RULE = kOptimal>
 void launch_orq(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    if (p->clip_factor > 0.0f)
+    if constexpr (!wave_serves<C>(S, RULE))
+        launch_status() = hipErrorInvalidDeviceFunction;
+    else if (p->clip_factor > 0.0f)
         launch_kernel((orq_quantize_kernel<C, S, BITS, true, RULE>), dim3(nb), dim3(kWave), st, g, n, p->bucket_size,
                            p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv,
                            static_cast<uint32_t*>(codes));
@@ -2699,13 +2709,10 @@ void launch_orq_levels(const float* g, size_t n, const ogq_params_t* p, uint32_t
     }
 }
 
-// Which rules and level counts the dispatch in rounding_part.hip gives to W wavefronts of 256 C elements per bucket.  The
-// others are not compiled, and asking for one fails like a launch that the runtime refuses: a call must not return success
-// over outputs that nothing has written.
 template <int W, int C>
 constexpr bool team_serves(int S, int rule)
 {
-    if (W == 2) return (S >= 8 && rule == kOptimal) || (C == 8 && rule == kPb);
+    if (W == 2) return C == 8 ? rule == kPb : S >= 8 && rule == kOptimal;
     if (W * C == 64 || W * C == 128) {
         if (rule == kEven) return C == 8;
         return C == 16 && (S != 3 || rule == kPb);

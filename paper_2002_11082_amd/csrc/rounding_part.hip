@@ -8,6 +8,7 @@
 #include "rounding_kernels.h"
 #include "row_kernels.h"
 #include "gather_kernels.h"
+#include "pool_kernels.h"
 
 #include "launch.h"
 
@@ -35,22 +36,44 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
     return true;
 }
 
-// Rules with many level solves, or BinGrad-pb.
-static bool long_solves(const ogq_params_t* p)
+#if OGQ_PART == 4 || OGQ_PART == 8 || OGQ_PART == 16
+// Two buckets per workgroup whose levels one wavefront solves side by side (pool_kernels.h), where the solves are what a bucket
+// waits for.  Both sides measured (Gaussian values, us; team or wavefront per bucket -> pool):
+//   18 solves (eight levels, two sweeps)   256 buckets of 2048 21.8 -> 16.1, 2048 buckets 38.3 -> 20.7, 25000 220 -> 144; of 4096
+//                                          22.9 -> 16.6, 45.5 -> 25.1, 12500: 172 -> 143; of 1344 29.4 -> 19.8 at 1300 buckets, level
+//                                          at 512; of 2112 26.3 -> 21.6, 18.0 -> 18.1 at 256; of 1024 22.0 -> 14.4 at 520 buckets
+//                                          (a single bucket is the slower one's half of a workgroup: of 2048 17.0 -> 18.6)
+//   7 solves (nine levels)                 256 buckets of 2048 11.7 -> 10.4, 25000 129 -> 103; buckets that do not fill their
+//                                          wavefronts pay for the tests: of 1344 11.6 -> 12.9 at 1024 buckets, 17.9 -> 13.6 at 1536
+//   3 solves (five levels)                 1024 buckets of 2048 10.6 -> 10.1, 25000 87.6 -> 79.7; of 1344 15.7 -> 17.1 at 3072 buckets,
+//                                          47.5 -> 44.9 at 12500; of 1024 equal
+template <int W, int C>
+static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    return p->scheme == OGQ_BINGRAD_PB ||
-           (p->scheme != OGQ_EVEN && p->scheme != OGQ_LINEAR && levels_per_bucket(p->scheme, p->bits) >= 8);
+    if (p->scheme != OGQ_ORQ && p->scheme != OGQ_ORQ_PAPER) return false;
+    const uint32_t levels = levels_per_bucket(p->scheme, p->bits);
+    if (levels < (C == 4 ? 8u : 5u)) return false;
+    const uint64_t solves = (uint64_t)(levels - 2u) * (1u + (uint64_t)p->level_iters);
+    const bool exact = p->bucket_size == 256u * C * W;
+    const uint32_t from = C == 4 ? 513u
+                          : exact ? (solves >= 6u ? 16u : 513u)
+                                  : solves >= 12u ? 513u : levels == 5u && C * W == 8 ? 8193u : 1281u;
+    if (nb < from) return false;
+    if (levels == 8u) launch_orq_pool<W, C, 8, 3>(g, n, p, nb, lv, codes, st);
+    else if (levels == 9u) launch_orq_pool<W, C, 9, 4>(g, n, p, nb, lv, codes, st);
+    else if constexpr (C > 4) launch_orq_pool<W, C, 5, 3>(g, n, p, nb, lv, codes, st);
+    return true;
 }
+#endif
 
 #if OGQ_PART == 16
 // Four wavefronts of 1024 elements (28 of them in a CU, where two of 2048 make 16) are up to 18 % faster than two on the passes
-// over the elements; with long serial solves that is lost again above some 4000 buckets, which two wavefronts serve better
-// (8192 buckets of 4096: eight levels 106 us with two, 107 with four, BinGrad-pb 50.8 and 53.4).  The exception that the rule
-// leaves alone: around 2048 buckets, one round more for workgroups of four, long solves are faster with two (eight levels
-// 31.1 against 37.6).
+// over the elements; with BinGrad-pb's long solve that is lost again above some 4000 buckets, which two wavefronts serve better
+// (8192 buckets of 4096: 50.8 us with two, 53.4 with four).
 void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    if (launch_few<4, 4>(long_solves(p) ? 4096u : ~0u, g, n, p, nb, lv, codes, st)) return;
+    if (launch_pool_part<2, 8>(g, n, p, nb, lv, codes, st)) return;
+    if (launch_few<4, 4>(p->scheme == OGQ_BINGRAD_PB ? 4096u : ~0u, g, n, p, nb, lv, codes, st)) return;
     launch_orq_team_levels<2, 8>(g, n, p, nb, lv, codes, st);
 }
 #elif OGQ_PART < 100
@@ -87,13 +110,17 @@ void OGQ_CAT(launch_rounding_c, OGQ_PART)(const float* g, size_t n, const ogq_pa
 #if OGQ_PART <= 2
     if (launch_row_part(g, n, p, nb, lv, codes, st)) return;
 #endif
+#if OGQ_PART == 4 || OGQ_PART == 8
+    if (launch_pool_part<1, OGQ_PART>(g, n, p, nb, lv, codes, st)) return;
+#endif
 #if OGQ_PART == 8
     if (launch_few<4, 2>(1280u, g, n, p, nb, lv, codes, st)) return;
 #elif OGQ_PART == 4
     if (launch_few<4, 1>(512u, g, n, p, nb, lv, codes, st)) return;
 #elif OGQ_PART == 2
     // one chunk per wavefront: two share the solves of eight or nine levels, nothing else is long enough to share
-    if (p->scheme != OGQ_BINGRAD_PB && long_solves(p) && launch_few<2, 1>(2560u, g, n, p, nb, lv, codes, st)) return;
+    if ((p->scheme == OGQ_ORQ || p->scheme == OGQ_ORQ_PAPER) && levels_per_bucket(p->scheme, p->bits) >= 8u &&
+        launch_few<2, 1>(2560u, g, n, p, nb, lv, codes, st)) return;
 #endif
     launch_orq_levels<OGQ_PART>(g, n, p, nb, lv, codes, st);
 }

@@ -4,7 +4,7 @@
 #ifndef OGQ_ROW_KERNELS_H
 #define OGQ_ROW_KERNELS_H
 
-#include "rounding_kernels.h"
+#include "group_solve.h"
 
 namespace ogq {
 
@@ -58,12 +58,6 @@ struct RowLds {
     unsigned long long exact_limb[kRows][kExactLimbs];
 };
 
-// Lanes of this lane's row for which the condition holds.
-__device__ __forceinline__ uint32_t row_count(bool condition, uint32_t lane)
-{
-    return (uint32_t)__popc((uint32_t)(__ballot(condition) >> (lane & 48u)) & 0xFFFFu);
-}
-
 __device__ __forceinline__ uint32_t row_inclusive_scan_u32(uint32_t x)
 {
     x += dpp_or_zero_u32<kDppRowShr1, 0xF>(x);
@@ -78,7 +72,7 @@ static __device__ __attribute__((noinline)) uint32_t exact_floor_t_row(unsigned 
                                                                        uint32_t len, uint32_t lane_in_row, float L, float R,
                                                                        uint32_t count_in, uint32_t guess)
 {
-    return exact_floor_t(limb, lane_in_row, L, R, count_in, guess, [&](auto add) {
+    return exact_floor_t(limb, lane_in_row, kRowLanes, L, R, count_in, guess, [&](auto add) {
         for (uint32_t i = lane_in_row; i < len; i += kRowLanes) add(__uint_as_float(grouped[i]) + 0.0f);
     });
 }

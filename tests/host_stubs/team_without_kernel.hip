@@ -1,5 +1,5 @@
-// Test infrastructure: asks the launcher of the team kernels for combinations of rule and level count that team_serves()
-// leaves uncompiled, and says what status the call ends with.  Nothing is launched and no GPU is needed.
+// Test infrastructure: asks the launchers of the team and one-wavefront kernels for combinations of rule and level count that
+// team_serves() and wave_serves() leave uncompiled, and says what status the call ends with.  Nothing is launched and no GPU is needed.
 #include <cstdio>
 
 #include "rounding_kernels.h"
@@ -26,6 +26,20 @@ void ask()
             ++silent;
             printf("no launch and no error: %d wavefronts of %d elements, %d levels, rule %d\n", W, 256 * C, S, RULE);
         }
+    }
+}
+
+template <int C, int S, int BITS>
+void ask_wave()
+{
+    static_assert(!wave_serves<C>(S, kOptimal), "a combination without a kernel");
+    const ogq_params_t p{};
+    launch_status() = hipSuccess;
+    launch_orq<C, S, BITS, kOptimal>(nullptr, 0, &p, 1u, nullptr, nullptr, nullptr);
+    ++asked;
+    if (launch_status() == hipSuccess) {
+        ++silent;
+        printf("no launch and no error: one wavefront of %d elements, %d levels\n", 256 * C, S);
     }
 }
 
@@ -59,6 +73,10 @@ int main()
     ask_all<8, 8>();
     ask_all<8, 16>();
     ask_all<16, 8>();
+    ask_wave<4, 8, 3>();
+    ask_wave<4, 9, 4>();
+    ask_wave<8, 8, 3>();
+    ask_wave<8, 9, 4>();
     printf("%d combinations without a kernel\n", asked);
     return asked == 0 || silent != 0;
 }

@@ -951,6 +951,29 @@ def test_unlike_buckets_of_long_gradients(scheme, bits, sweeps, d, nb):
                               buckets=checked, clip_factor=clip, tag=f"long-s{scheme}-b{bits}-d{d}-c{clip}")
 
 
+@pytest.mark.parametrize("d,nb", [(576, 514), (1024, 513), (1088, 1282), (1536, 1281), (2048, 16), (2048, 33), (2112, 515), (3968, 514),
+                                  (4096, 16), (4096, 49)])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 0), (ogq.ORQ, 3, 1), (ogq.ORQ, 3, 2), (ogq.ORQ, 3, 5), (ogq.ORQ_PAPER, 3, 3),
+                                                (ogq.ORQ_PAPER, 4, 0), (ogq.ORQ_PAPER, 4, 2)])
+def test_several_buckets_per_workgroup(scheme, bits, sweeps, d, nb):
+    """Buckets whose levels one wavefront solves side by side: unlike neighbours, odd numbers of buckets, a cut-off last bucket of
+    one element, of a few and of all but one."""
+    rng = np.random.default_rng(d + 100 * bits + sweeps)
+    g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    kinds = ["const", "normal", "zeros", "heavy", "ints", "shifted"]
+    for b in range(0, 14):
+        buckets[b] = _rng_bucket(rng, d, kinds[b % len(kinds)])
+    buckets[1] = np.float32(1.0) + rng.integers(0, 900, d).astype(np.float32) * np.float32(2.0 ** -23)   # one crowded bin
+    buckets[3, d // 2:] = -buckets[3, : d // 2]                                                        # T exactly an integer
+    buckets[5] *= np.float32(1e-38)
+    buckets[7] = rng.choice(np.array([0.0, -0.0, 1e-3, -2e-3], dtype=np.float32), d)
+    checked = sorted(set(list(range(15)) + _sample(nb, 12, nb) + [nb - 2, nb - 1]))
+    for cut, clip in ((0, 0.0), (1, 2.5), (d - 1, 0.0), (d - 19, 0.0)):
+        parity.check_quantize(g[: nb * d - cut], d, bits, scheme, sweeps, seed=29, index_offset=(1 << 34) - 64 * 9, buckets=checked,
+                              clip_factor=clip, tag=f"pool-s{scheme}-b{bits}-i{sweeps}-d{d}-nb{nb}-cut{cut}")
+
+
 @pytest.mark.parametrize("scheme,iters", [(ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 2), (ogq.SCALED_SIGN, 0)])
 @pytest.mark.parametrize("d,nb", [(64, 33), (128, 17), (256, 9), (512, 8200), (1024, 4100), (12288, 512), (12288, 513), (16384, 513)])
 def test_bingrad_rest_and_bucket_counts(d, nb, scheme, iters):
