@@ -106,7 +106,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         return "orq_team_kernel", 8
     wavefronts = 4 if d <= 8192 else 8 if d <= 16384 else 16
     if levels == 3 and not even:
-        return "orq_gather_kernel", wavefronts
+        return "orq_gather_kernel", 8 if d > 16384 and nb > 256 else wavefronts
     return "orq_team_kernel", wavefronts if even or d <= 8192 else wavefronts // 2
 
 

@@ -19,12 +19,13 @@ namespace ogq {
 // wavefronts per CU, whose phases nothing overlaps (ORQ-3, 25.6 M values: 75 us with the vector units busy 46 % of the
 // time).  Here a bucket takes at most 22 KB and the registers decide: 16 wavefronts of 128 registers fill a CU.
 //
-// Bound by the phases of a bucket that all its wavefronts go through together: at 32768 elements one workgroup fills a CU, so
-// nothing overlaps a bucket's loads and barriers, and 782 buckets on 256 CUs take a fourth round for the last 14
-// (SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES 0.62, 3.7 ns per vector instruction and SIMD; of 59 us the loads, extremes and
-// total take 22, the histogram 7, the level 11, encoding 19).  ORQ-3, 25.6 M values, before -> after: buckets of 8192 42
-// -> 36 us, 16384 59 -> 44, 20480 105 -> 79, 32768 75 -> 60; 16 buckets of 32768 20 -> 15 us.  Workgroups that stay and
-// fetch their next bucket into the free LDS meanwhile were slower (32768: 72 us).
+// Bound by the phases of a bucket that all its wavefronts go through together.  Two buckets share a CU: above 16384 elements as
+// 2 x 8 wavefronts that hold 64 elements per lane (103 of 128 registers); 16 wavefronts with 32 elements per lane fill a CU with one
+// bucket, whose loads and barriers nothing overlaps.  It also matters that every pass makes what it needs of an element afresh
+// (opaque_zero): kept from the histogram to the collection, v + 0 and the lane masks of the tests cost 64 registers.
+// ORQ-3, 25.6 M values, orq_team_kernel -> 16 wavefronts, one bucket per CU -> now: buckets of 8192 42 -> 36 -> 36 us, 16384 59 -> 41 -> 35,
+// 20480 105 -> 78 -> 60, 32768 75 -> 59 -> 45; 16 buckets of 32768 20 -> 14.  Workgroups that stay and fetch their next bucket into the free
+// LDS meanwhile were slower (32768: 72 us).
 // ----------------------------------------------------------------------------------------------
 template <int W, int C>
 struct GatherLds {
@@ -211,11 +212,13 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
     const uint32_t from = sign | (u == 0u ? 0u : (t_low + u) << SHIFT);
     const uint32_t range = (u == HALF - 1u ? sign + 0x80000000u : sign | ((t_low + u + 1u) << SHIFT)) - from;
     uint32_t smallest = 0xFFFFFFFFu, largest = 0u;
+    // (another zero, here and in the bisection: what an earlier pass made of the elements is made again, not kept in registers)
+    const float again = opaque_zero();
     for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-            const float x = v[c][k] + zero;
+            const float x = v[c][k] + again;
             if (valid && __float_as_uint(x) - from < range) {
                 const uint32_t at = atomicAdd(&lds.list_count, 1u);
                 if (at < Lds::LIST) lds.list[at] = __float_as_uint(x);
@@ -256,11 +259,12 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
                         below += float_to_key(__uint_as_float(lds.list[i])) < candidate ? 1u : 0u;
                     below = wave_sum_u32(below);
                 } else {
+                    const float once_more = opaque_zero();
                     for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-                            const float x = v[c][k] + zero;
+                            const float x = v[c][k] + once_more;
                             below += valid && __float_as_uint(x) - from < range && float_to_key(x) < candidate ? 1u : 0u;
                         }
                     });

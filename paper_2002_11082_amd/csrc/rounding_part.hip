@@ -4,7 +4,7 @@
 // there are few buckets); 16: four or two wavefronts per bucket of at most 4096 elements; 102: four wavefronts of 2048
 // elements per bucket of at most 8192 (22-37 % faster than two wavefronts of 4096: half the registers, twice the resident
 // wavefronts); 104, 108: 4, 8 wavefronts of 4096 elements per bucket of at most 16384, 32768.  ORQ-3 and Linear-3 above
-// 4096 elements have a kernel of their own, always wavefronts of 2048 elements.
+// 4096 elements have a kernel of their own (gather_kernels.h).
 #include "rounding_kernels.h"
 #include "row_kernels.h"
 #include "gather_kernels.h"
@@ -144,7 +144,10 @@ void launch_rounding_w4(const float* g, size_t n, const ogq_params_t* p, uint32_
 #elif OGQ_PART == 108
 void launch_rounding_w8(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    if (launch_gather<16, 8>(g, n, p, nb, lv, codes, st)) return;
+    // Up to one bucket per CU: 16 wavefronts of 2048 elements each; beyond, 8 of 4096, so that two buckets share a CU and one's loads
+    // and barriers overlap the other's work (ORQ-3: 512 buckets of 32768 43.6 -> 30.9 us, 782 58.6 -> 44.8, 1562 of 20480 97 -> 75; 256 of
+    // 20480 15.2 -> 18.8).
+    if (nb <= 256u ? launch_gather<16, 8>(g, n, p, nb, lv, codes, st) : launch_gather<8, 16>(g, n, p, nb, lv, codes, st)) return;
     if (p->scheme == OGQ_EVEN) {
         launch_orq_team_levels<16, 8>(g, n, p, nb, lv, codes, st);
         return;

@@ -897,6 +897,28 @@ def test_three_levels_in_large_buckets(scheme, d):
 # ------------------------------------------------------------------------------------------------
 # few and many buckets go to kernels with different numbers of wavefronts per bucket
 # ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("d", [16448, 20480, 28736, 32768])
+@pytest.mark.parametrize("scheme", [ogq.ORQ_PAPER, ogq.LINEAR])
+def test_three_levels_in_many_large_buckets(scheme, d):
+    """More than one bucket per CU: wavefronts of 4096 elements.  Unlike buckets, crowded and sparse ones, NaN and infinities in
+    some, Philox blocks that pass 2^32, a cut-off last bucket."""
+    rng = np.random.default_rng(d + scheme)
+    nb = 258
+    g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    for b, kind in enumerate(["const", "normal", "zeros", "heavy", "ints", "shifted"]):
+        buckets[b] = _rng_bucket(rng, d, kind)
+    buckets[6] = np.float32(1.0) + rng.integers(0, 4000, d).astype(np.float32) * np.float32(2.0 ** -23)  # one crowded bin
+    buckets[7, rng.random(d) < 0.97] = 0.0
+    buckets[8, d // 2:] = -buckets[8, : d // 2]                                                            # T exactly an integer
+    buckets[9] *= np.float32(1e-38)
+    buckets[10, rng.choice(d, size=5, replace=False)] = [np.nan, np.inf, -np.inf, np.nan, np.inf]
+    checked = [*range(10), 11, 100, nb - 2, nb - 1]
+    for cut, clip in ((0, 0.0), (d - 70, 2.5)):
+        parity.check_quantize(g[: nb * d - cut], d, 2, scheme, 0, seed=31, index_offset=(1 << 34) - 3 * d, buckets=checked,
+                              clip_factor=clip, tag=f"gather-s{scheme}-d{d}-c{clip}")
+
+
 @pytest.mark.parametrize("d,limit", [(448, 2560), (512, 2560), (960, 512), (1024, 512), (2048, 1280), (1984, 1280), (4096, 4096),
                                      (8192, 256), (8128, 256), (16384, 0), (20480, 0)])
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0),
