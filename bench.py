@@ -81,9 +81,17 @@ def quantize_kernel(synth, wl, n: int, levels: int):
     solves = not even and levels > 2
     long_solves = solves and not linear and levels >= 8
     if 64 < d <= 512 and not pb:
-        enough = (8192 if solves else 16384) if d > 256 else (4096 if solves else 8192) if d > 128 else 8192
+        several = solves and not linear and levels > 3
+        if d > 448:
+            enough = 8192 if not several else 4096 if levels < 8 else 2048
+        elif d > 256:
+            enough = 4096 if not several or levels < 8 else 2048
+        elif d > 128:
+            enough = 8192 if not solves else 3072 if not several or levels < 8 else 256
+        else:
+            enough = 8192
         if nb >= enough:
-            return "orq_rows_kernel", 0.25
+            return "orq_rows_kernel", 0.125 if d == 128 and nb >= 16384 else 0.25
     if d in (64, 128):
         return "even_small_kernel" if even else "sorted_small_kernel", d / 256
     if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= (8 if d <= 1024 else 5):
@@ -98,7 +106,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         if nb >= enough:
             return "orq_pool_kernel", 2 if d > 2048 else 1
     if d <= 2048:
-        few = 0 if d <= 256 else (2560 if long_solves else 0) if d <= 512 else 512 if d <= 1024 else 1280
+        few = 0 if d <= 256 else (2047 if long_solves else 0) if d <= 512 else 512 if d <= 1024 else 1280
         return ("orq_team_kernel", 2 if d <= 512 else 4) if nb <= few else ("orq_quantize_kernel", 1)
     if d <= 4096:
         return "orq_team_kernel", 2 if pb and nb > 4096 else 4

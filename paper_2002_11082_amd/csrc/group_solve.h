@@ -7,14 +7,15 @@
 
 namespace ogq {
 
-constexpr uint32_t kGroupLanes = 16;  // lanes per bucket (and chain): a row
+// LDS through its own address space: addresses of 32 bits, of which the histogram keeps 16 with every element.
+typedef __attribute__((address_space(3))) uint32_t LdsWord;
+typedef __attribute__((address_space(3))) uint16_t LdsHalf;
 
 // Per level: what OrqLds keeps.
-struct __attribute__((aligned(16))) GroupLevel {
+struct GroupLevel {
     double sum_lt, sum_le;
     float value;
     uint16_t count_lt, count_le;
-    uint16_t rank;  // the rank the level was picked at (0 = not picked by rank)
 };
 
 // Bins of a bucket, HALF per sign, monotone in the value: the bin of a magnitude grows like the logarithm of
@@ -59,13 +60,14 @@ __device__ __forceinline__ int32_t signed_bin(float canonical, const ScaledBins&
 struct GroupBucket {
     const char* grouped;        // fp32 bit patterns by bin
     const uint16_t* bin_start;  // byte offset of every bin's first position in `grouped`; points at the middle bin's
-    const double* prefix;       // sum of everything before every BLOCK-th position
+    const double* prefix;       // sum of the bucket's elements before every BLOCK-th position of `grouped`
     GroupLevel* level;
-    unsigned long long* limb;   // workspace of exact_floor_t
+    uint16_t* rank;             // per level: the rank it was picked at (0 = not picked by rank)
+    unsigned long long* limb;   // workspace of exact_floor_t, the same for all groups
     ScaledBins bins;
-    uint32_t len;               // elements
+    uint32_t origin, len;       // the bucket's first position in `grouped`, its elements
     double bound;               // sum_error_bound (floor_t_from_sums)
-    bool ordinary;              // at least 20 elements, none of them NaN
+    bool ordinary;              // (windows of elements, see group_solve) at least 20 elements, none of them NaN
 };
 
 __device__ __forceinline__ float grouped_value(const char* at) { return __uint_as_float(*reinterpret_cast<const uint32_t*>(at)) + 0.0f; }
@@ -201,13 +203,14 @@ __device__ __forceinline__ GroupPicked group_pick_bisected(const char* at, uint3
     return p;
 }
 
-// floor(T) of a group's bucket in exact arithmetic (see exact_floor_t).
-static __device__ __attribute__((noinline)) uint32_t exact_floor_t_group(unsigned long long* limb, const char* grouped, uint32_t len,
-                                                                         uint32_t lane_in_group, uint32_t lanes, float L, float R,
-                                                                         uint32_t count_in, uint32_t guess)
+// floor(T) of one group's bucket in exact arithmetic (see exact_floor_t), by the whole wavefront; elements = the LDS address of the
+// bucket's first one.
+static __device__ __attribute__((noinline)) uint32_t exact_floor_t_group(unsigned long long* limb, uint32_t elements, uint32_t len,
+                                                                         uint32_t lane, float L, float R, uint32_t count_in,
+                                                                         uint32_t guess)
 {
-    return exact_floor_t(limb, lane_in_group, lanes, L, R, count_in, guess, [&](auto add) {
-        for (uint32_t i = lane_in_group; i < len; i += lanes) add(grouped_value(grouped + 4u * i));
+    return exact_floor_t(limb, lane, L, R, count_in, guess, [&](auto add) {
+        for (uint32_t i = lane; i < len; i += kWave) add(__uint_as_float(((const LdsWord*)(uintptr_t)elements)[i]) + 0.0f);
     });
 }
 
@@ -225,23 +228,25 @@ __device__ __forceinline__ uint32_t row_count(bool condition, uint32_t lane)
     return (uint32_t)__popc((uint32_t)(__ballot(condition) >> (lane & 48u)) & 0xFFFFu);
 }
 
-// One level solve per group, run by a whole wavefront: level k between the levels l and r of the group's bucket (see
-// orq_solve_one), entry = k | l << 4 | r << 8, 0 for a group with nothing to do.  Shape: HALF (signed_bin) and BLOCK,
-// the positions per entry of the prefix.  SUMS = false: one interior level, whose solve reads the bucket's total alone.
+// One level solve per group of G lanes, run by a whole wavefront: level k between the levels l and r of the group's bucket (see
+// orq_solve_one), entry = k | l << 4 | r << 8, 0 for a group with nothing to do.  SUMS = false: one interior level,
+// whose solve reads the bucket's total alone.  Shape: HALF (signed_bin), BLOCK (positions per entry of the
+// prefix), END_OF_BUCKET (the entry behind a bucket's last bin is not its end) and WINDOWED.
 //
-// The wavefront waits for itself here, so what counts is the length of the chain: the bin of a rank needs no search (the element
-// at that position of the grouped bucket is in it), and a bin of at most 16 elements is not sorted: every lane counts the elements
-// smaller than its own among 20 that begin at a multiple of 4.  What they hold beside the bin changes nothing: it is smaller or
-// larger than everything in it.
-template <bool SUMS, class Shape>
+// The bin of a rank needs no search: the element at that position of the grouped bucket is in it.  The element of the rank is then
+// found by sorting the bin, or (WINDOWED, G = 16) by counting: every lane counts the elements smaller than its own among 20 that
+// begin at a multiple of 4; what they hold beside the bin changes nothing, it is smaller or larger than everything in it.  Counting
+// takes a few vector instructions more than the sort of 16 keys but a shorter chain: for a wavefront that others wait for.
+template <int G, bool SUMS, class Shape>
 __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry, uint32_t lane)
 {
-    constexpr uint32_t BLOCK = Shape::BLOCK, G = kGroupLanes;
-    static_assert(BLOCK % G == 0, "the elements in front of a bin are read G at a time");
-    const uint32_t i = lane & (G - 1u);
-    GroupLevel* const level = b.level + (entry & 15u);
+    constexpr uint32_t BLOCK = Shape::BLOCK, LANES = (uint32_t)G;
+    static_assert(!SUMS || BLOCK % LANES == 0, "the elements in front of a bin are read G at a time");
+    static_assert(!Shape::WINDOWED || G == 16, "one element per lane");
+    const uint32_t i = lane & (LANES - 1u);
+    const uint32_t k = entry & 15u;
     const GroupLevel left = b.level[(entry >> 4) & 15u], right = b.level[entry >> 8];
-    const uint32_t last_rank = level->rank;
+    const uint32_t last_rank = b.rank[k];
     const float L = left.value, R = right.value;
     const bool ordered = L < R;
     // S = sum_{L<=v<=R} (v - L),  T = S / (R - L),  level = element of rank #{v<=R} - floor(T)
@@ -255,22 +260,33 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
     m = m + (over ? 1u : 0u) - (under ? 1u : 0u);
     const double settled = rest - (over ? width : under ? -width : 0.0);
     const bool undecided = ordered && b.bound != 0.0 && !(settled > b.bound && width - settled > b.bound);
-    if (__ballot(undecided) != 0) {
-        if (undecided) m = exact_floor_t_group(b.limb, b.grouped, b.len, i, G, L, R, count_in, m);
+    for (uint64_t todo = __ballot(undecided && i == 0u); todo != 0; todo &= todo - 1u) {  // (rare) one group after the other
+        const uint32_t of = (uint32_t)__builtin_ctzll(todo);
+        const uint32_t elements = (uint32_t)(uintptr_t)((const LdsWord*)b.grouped) + 4u * b.origin;
+        const uint32_t exact = exact_floor_t_group(b.limb, __builtin_amdgcn_readlane(elements, of), __builtin_amdgcn_readlane(b.len, of), lane, readlane_f32(L, of), readlane_f32(R, of),
+                                                   __builtin_amdgcn_readlane(count_in, of), __builtin_amdgcn_readlane(m, of));
+        m = lane / LANES == of / LANES ? exact : m;
     }
     const uint32_t rank = umin32(umax32(__builtin_elementwise_sub_sat((uint32_t)right.count_le, m), 1u), b.len);
     const bool same = entry == 0u || (ordered && rank == last_rank);  // same element as last time
     if (__ballot(!same) == 0) return;
 
-    const uint32_t at = rank > 0u ? rank - 1u : 0u;  // (rank 0: an empty bucket)
+    const uint32_t at = b.origin + (rank > 0u ? rank - 1u : 0u);  // (rank 0: an empty bucket)
     const int32_t bin = signed_bin<Shape::HALF>(grouped_value(b.grouped + 4u * at), b.bins);
-    const uint32_t first = (uint32_t)b.bin_start[bin] >> 2, last = (uint32_t)b.bin_start[bin + 1] >> 2;
-    // 20 elements that end inside the bucket, and the 16 of them that are the lanes' own
-    const uint32_t end = __builtin_elementwise_sub_sat(b.len, G + 4u) & ~3u;
-    const bool at_end = (first & ~3u) > end;
-    const uint32_t window = at_end ? end : first & ~3u, own_first = at_end ? end + 4u : first;
-    const bool windowed = __ballot(last > own_first + G || !b.ordinary) == 0;
-    const uint32_t from = windowed ? own_first : first;
+    const uint32_t first = (uint32_t)b.bin_start[bin] >> 2;
+    uint32_t last = (uint32_t)b.bin_start[bin + 1] >> 2;
+    if constexpr (Shape::END_OF_BUCKET) last = umin32(last, b.origin + b.len);
+    uint32_t from = first, window = 0u;
+    bool windowed = false;
+    if constexpr (Shape::WINDOWED) {
+        // 20 elements that end inside the bucket (origin = 0), and the 16 of them that are the lanes' own
+        const uint32_t end = __builtin_elementwise_sub_sat(b.len, LANES + 4u) & ~3u;
+        const bool at_end = (first & ~3u) > end;
+        window = at_end ? end : first & ~3u;
+        const uint32_t own_first = at_end ? end + 4u : first;
+        windowed = __ballot(last > own_first + LANES || !b.ordinary) == 0;
+        from = windowed ? own_first : first;
+    }
     double before = 0.0, part = 0.0;
     if constexpr (SUMS) {
         // the sum of everything before `from`: the prefix of its block, and the block's positions in front of it
@@ -278,19 +294,19 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
         const uint32_t in_front = from & (BLOCK - 1u);
         const char* block = b.grouped + 4u * (from - in_front + i);
 #pragma unroll
-        for (uint32_t c = 0; c < BLOCK / G; ++c) {
-            const float x = __uint_as_float(*reinterpret_cast<const uint32_t*>(block + 4u * G * c));
-            part += (double)(i + G * c < in_front ? x : 0.0f);
+        for (uint32_t c = 0; c < BLOCK / LANES; ++c) {
+            const float x = __uint_as_float(*reinterpret_cast<const uint32_t*>(block + 4u * LANES * c));
+            part += (double)(i + LANES * c < in_front ? x : 0.0f);
         }
     }
     float value;
     uint32_t count_lt = 0, count_le = 0;  // from `from` on
-    if (windowed) {
+    if (Shape::WINDOWED && windowed) {
         const float4* around = reinterpret_cast<const float4*>(b.grouped + 4u * window);
         const float own = grouped_value(b.grouped + 4u * (from + i));
         uint32_t smaller = 0;
 #pragma unroll
-        for (uint32_t q = 0; q < G / 4u + 1u; ++q) {
+        for (uint32_t q = 0; q < LANES / 4u + 1u; ++q) {
             const float4 x = around[q];
             smaller += x.x < own ? 1u : 0u;
             smaller += x.y < own ? 1u : 0u;
@@ -313,9 +329,10 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
         const uint32_t n = last - first;
         const char* keys = b.grouped + 4u * first;
         GroupPicked p;
-        if (__ballot(n > 2u * G) == 0) p = group_pick_sorted<(int)G, 2, SUMS>(keys, n, at - first, lane);
-        else if (__ballot(n > 4u * G) == 0) p = group_pick_sorted<(int)G, 4, SUMS>(keys, n, at - first, lane);
-        else p = group_pick_bisected<(int)G, SUMS>(keys, n, at - first, lane);
+        if (!Shape::WINDOWED && __ballot(n > LANES) == 0) p = group_pick_sorted<G, 1, SUMS>(keys, n, at - first, lane);
+        else if (__ballot(n > 2u * LANES) == 0) p = group_pick_sorted<G, 2, SUMS>(keys, n, at - first, lane);
+        else if (__ballot(n > 4u * LANES) == 0) p = group_pick_sorted<G, 4, SUMS>(keys, n, at - first, lane);
+        else p = group_pick_bisected<G, SUMS>(keys, n, at - first, lane);
         value = p.value;
         count_lt = p.count_lt;
         count_le = p.count_le;
@@ -324,19 +341,39 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
     const bool copy_left = !ordered || value < L;  // the level coincides with the left end
     GroupLevel now;
     now.value = copy_left ? L : value;
-    now.rank = (uint16_t)(copy_left ? 0u : rank);
     now.count_lt = now.count_le = 0;
     now.sum_lt = now.sum_le = 0.0;
     if constexpr (SUMS) {
-        const double sum_lt = before + row_sum_f64<(int)G>(part, lane);
+        const double sum_lt = before + row_sum_f64<G>(part, lane);
         const double sum_le = __builtin_fma((double)(count_le - count_lt), (double)value, sum_lt);
-        now.count_lt = (uint16_t)(copy_left ? left.count_lt : from + count_lt);
-        now.count_le = (uint16_t)(copy_left ? (ordered ? left.count_le : right.count_le) : from + count_le);
+        const uint32_t in_front = from - b.origin;
+        now.count_lt = (uint16_t)(copy_left ? left.count_lt : in_front + count_lt);
+        now.count_le = (uint16_t)(copy_left ? (ordered ? left.count_le : right.count_le) : in_front + count_le);
         now.sum_lt = copy_left ? left.sum_lt : sum_lt;
         now.sum_le = copy_left ? (ordered ? left.sum_le : right.sum_le) : sum_le;
     }
-    if (i == 0u && !same) *level = now;
+    if (i == 0u && !same) {
+        b.level[k] = now;
+        b.rank[k] = (uint16_t)(copy_left ? 0u : rank);
+    }
     wave_lds_sync();
+}
+
+// The element of 0-based index `index` of every group's sorted bucket (one chain).
+template <int G, class Shape>
+__device__ __forceinline__ float group_element(const GroupBucket& b, uint32_t index, uint32_t lane)
+{
+    const uint32_t at = b.origin + index;
+    const int32_t bin = signed_bin<Shape::HALF>(grouped_value(b.grouped + 4u * at), b.bins);
+    const uint32_t first = (uint32_t)b.bin_start[bin] >> 2;
+    uint32_t last = (uint32_t)b.bin_start[bin + 1] >> 2;
+    if constexpr (Shape::END_OF_BUCKET) last = umin32(last, b.origin + b.len);
+    const uint32_t n = last - first;
+    const char* keys = b.grouped + 4u * first;
+    if (__ballot(n > (uint32_t)G) == 0) return group_pick_sorted<G, 1, false>(keys, n, at - first, lane).value;
+    if (__ballot(n > 2u * (uint32_t)G) == 0) return group_pick_sorted<G, 2, false>(keys, n, at - first, lane).value;
+    if (__ballot(n > 4u * (uint32_t)G) == 0) return group_pick_sorted<G, 4, false>(keys, n, at - first, lane).value;
+    return group_pick_bisected<G, false>(keys, n, at - first, lane).value;
 }
 
 // The greedy steps of a chain, 12 bits each; head: with the first solves of the first sweep in the steps that have room for them.
@@ -352,11 +389,11 @@ constexpr uint64_t packed_entries(const TeamGreedy& greedy, int chain, bool head
     return packed;
 }
 
-// All level solves of the groups' buckets, CHAINS = 1 or 2 groups per bucket (group lane / 16 of the wavefront is chain
-// (lane / 16) % CHAINS of its bucket).  One chain: Algorithm 1's order, then the sweeps.  Two chains: the schedule of
+// All level solves of the groups' buckets, CHAINS = 1 or 2 groups per bucket (group lane / G of the wavefront is chain
+// (lane / G) % CHAINS of its bucket).  One chain: Algorithm 1's order, then the sweeps.  Two chains: the schedule of
 // orq_team_solve, i.e. the halves on either side of Algorithm 1's first level, and of each pair of sweeps the second two levels
 // behind the first; the results are those of the serial order.
-template <int CHAINS, int S, class Shape>
+template <int G, int CHAINS, int S, class Shape>
 __device__ __forceinline__ void group_solve_levels(const GroupBucket& b, uint32_t sweeps, uint32_t lane)
 {
     constexpr bool SUMS = S > 3;
@@ -364,28 +401,26 @@ __device__ __forceinline__ void group_solve_levels(const GroupBucket& b, uint32_
     constexpr uint32_t kNext = 0x111u, kFirst = 0x201u;  // from a level's entry of a sweep to the next one's; that of level 1
     if constexpr (CHAINS == 1) {
         constexpr GreedyOrder order = greedy_order<S>();
-        static_assert(order.count <= 5, "12 bits per step");
         uint32_t steps = order.count + (S > 3 ? sweeps * INTERIOR : 0u);  // (one interior level: sweeps repeat it)
-        uint64_t ahead = order.packed[0];
         uint32_t entry = 0;
 #pragma unroll 1
         for (uint32_t step = 0; step < steps; ++step) {
-            // what is packed gives out first, then one level after the other
-            if (ahead != 0u) entry = (uint32_t)ahead & 0xFFFu;
-            else entry = step == (uint32_t)order.count || (entry & 15u) == INTERIOR ? kFirst : entry + kNext;
-            ahead >>= 12;
-            group_solve<SUMS, Shape>(b, entry, lane);
+            if (step < (uint32_t)order.count)
+                entry = (uint32_t)(step < 5u ? order.packed[0] >> (12 * step) : order.packed[1] >> (12 * (step - 5u))) & 0xFFFu;
+            else
+                entry = step == (uint32_t)order.count || (entry & 15u) == INTERIOR ? kFirst : entry + kNext;
+            group_solve<G, SUMS, Shape>(b, entry, lane);
         }
     } else {
         constexpr TeamGreedy greedy = team_greedy<S>();
         static_assert(greedy.steps <= 5, "12 bits per step");
-        const bool second = (lane & kGroupLanes) != 0u;
+        const bool second = (lane & (uint32_t)G) != 0u;
         const uint64_t packed_first = sweeps > 0u ? packed_entries(greedy, 0, true) : packed_entries(greedy, 0, false);
         constexpr uint64_t packed_second = packed_entries(greedy, 1, false);
         uint64_t ahead = second ? packed_second : packed_first;
 #pragma unroll 1
         for (int step = 0; step < greedy.steps; ++step) {
-            group_solve<SUMS, Shape>(b, (uint32_t)ahead & 0xFFFu, lane);
+            group_solve<G, SUMS, Shape>(b, (uint32_t)ahead & 0xFFFu, lane);
             ahead >>= 12;
         }
         uint32_t t = (uint32_t)greedy.head;  // (the first pair begins behind its head start)
@@ -397,7 +432,7 @@ __device__ __forceinline__ void group_solve_levels(const GroupBucket& b, uint32_
             for (; t < end; ++t) {
                 const uint32_t at = t - mine;  // level at + 1 of this chain's sweep
                 const bool active = at < INTERIOR && (pair || !second);
-                group_solve<SUMS, Shape>(b, active ? at * kNext + kFirst : 0u, lane);
+                group_solve<G, SUMS, Shape>(b, active ? at * kNext + kFirst : 0u, lane);
             }
             t = 0;
             left -= pair ? 2u : 1u;

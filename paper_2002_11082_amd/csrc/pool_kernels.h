@@ -24,15 +24,12 @@ namespace ogq {
 // The solving wavefront runs at a raised priority (its instructions go first on its SIMD): 30,000 -> 25,000 cycles of solves.
 // Four buckets per workgroup, in rows of 8 lanes, were slower (418 us): fewer workgroups overlap.
 // ----------------------------------------------------------------------------------------------
-// LDS through its own address space: addresses of 32 bits, of which the histogram keeps 16 with every element.
-typedef __attribute__((address_space(3))) uint32_t LdsWord;
-typedef __attribute__((address_space(3))) uint16_t LdsHalf;
-
 template <int W, int C, int S>
-struct PoolBucket {
+struct alignas(16) PoolBucket {
     static constexpr int D = 256 * C * W;                      // element capacity
     static constexpr int B = D / 4, HALF = B / 2;              // bins
     static constexpr int BLOCK = 4 * C;                        // positions per entry of the fp64 prefix: one lane's
+    static constexpr bool END_OF_BUCKET = false, WINDOWED = true;  // (group_solve)
     union {
         uint32_t bin_count[B];  // bytes: 4 per element
         uint32_t grouped[D];    // fp32 bit patterns by bin
@@ -42,6 +39,7 @@ struct PoolBucket {
     double wave_sum[W];
     TeamSlot slots[2][W];
     uint16_t bin_start[B + 2];  // byte offset of each bin's first position in `grouped`; [B] = end of the last bin
+    uint16_t rank[S];
     ScaledBins bins;
     uint32_t tiny;              // set where an element is too small for exact sums
 };
@@ -50,7 +48,7 @@ template <int W, int C, int S>
 struct PoolLds {
     static constexpr int CHAINS = S > 4 ? 2 : 1, NB = 4 / CHAINS;
     PoolBucket<W, C, S> bucket[NB];
-    unsigned long long exact_limb[NB * CHAINS][kExactLimbs];
+    unsigned long long exact_limb[kExactLimbs];
 };
 
 template <int W, int C, int S, int BITS, bool FULL>
@@ -267,8 +265,8 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
             end.value = top ? high : low;
             end.count_lt = end.count_le = (uint16_t)(top ? len : 0u);
             end.sum_lt = end.sum_le = 0.0;  // (the top level's follows below)
-            end.rank = 0u;
             my.level[lane] = end;
+            my.rank[lane] = 0u;
             my.bins = bins_of;
         }
     }
@@ -286,7 +284,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 #pragma unroll
             for (int b = 0; b < NB; ++b) lds.bucket[b].prefix[64u + lane] = before[b];
         }
-        constexpr uint32_t G = kGroupLanes;
+        constexpr uint32_t G = 16;
         static_assert(NB * CHAINS * G == 64, "one group per bucket and chain");
         Bucket& b = lds.bucket[lane / (G * CHAINS)];
         double total = b.wave_sum[0];
@@ -304,12 +302,14 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                                b.bin_start + HALF,
                                b.prefix,
                                b.level,
-                               lds.exact_limb[lane / G],
+                               b.rank,
+                               lds.exact_limb,
                                b.bins,
+                               0u,
                                its_len,
                                b.tiny != 0u ? sum_error_bound_of(largest, (uint32_t)Bucket::D) : 0.0,
                                its_len >= G + 4u && total == total};
-        group_solve_levels<CHAINS, S, Bucket>(view, sweeps, lane);
+        group_solve_levels<(int)G, CHAINS, S, Bucket>(view, sweeps, lane);
         __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();

@@ -674,14 +674,14 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// floor(T), exactly.  Called by all lanes that hold the bucket (a wavefront, or the group of `lanes` lanes of a small bucket)
+// floor(T), exactly.  Called by all lanes that hold the bucket (a wavefront, or the group of lanes of a small bucket)
 // with the same limb array, L < R, count_in = #{L <= v <= R} and a first guess; each_of_mine(f) runs f(x) on the bucket
 // elements this lane answers for; lane_in_group counts the calling lanes from 0.
 template <class EachFn>
-__device__ __forceinline__ uint32_t exact_floor_t(unsigned long long* limb, uint32_t lane_in_group, uint32_t lanes, float L, float R,
+__device__ __forceinline__ uint32_t exact_floor_t(unsigned long long* limb, uint32_t lane_in_group, float L, float R,
                                                   uint32_t count_in, uint32_t guess, EachFn each_of_mine)
 {
-    for (uint32_t i = lane_in_group; i < (uint32_t)kExactLimbs; i += lanes) limb[i] = 0ull;
+    if (lane_in_group < (uint32_t)kExactLimbs) limb[lane_in_group] = 0ull;
     wave_lds_sync();
     each_of_mine([&](float x) {
         if (L <= x && x <= R) exact_add_shared(limb, x);
@@ -708,7 +708,7 @@ static __device__ __attribute__((noinline)) uint32_t exact_floor_t_grouped(unsig
                                                                    uint32_t len, uint32_t lane, uint32_t stride, float L,
                                                                    float R, uint32_t count_in, uint32_t guess)
 {
-    return exact_floor_t(limb, lane, stride, L, R, count_in, guess, [&](auto add) {
+    return exact_floor_t(limb, lane, L, R, count_in, guess, [&](auto add) {
         for (uint32_t i = lane; i < len; i += stride) add(__uint_as_float(grouped[skewed(i)]));
     });
 }
@@ -718,7 +718,7 @@ static __device__ __attribute__((noinline)) uint32_t exact_floor_t_registers(uns
                                                                      float L, float R, uint32_t count_in, uint32_t guess,
                                                                      float x0, float x1, float x2, float x3, uint32_t valid)
 {
-    return exact_floor_t(limb, lane_in_group, (uint32_t)kExactLimbs, L, R, count_in, guess, [&](auto add) {
+    return exact_floor_t(limb, lane_in_group, L, R, count_in, guess, [&](auto add) {
         if (valid > 0u) add(x0);
         if (valid > 1u) add(x1);
         if (valid > 2u) add(x2);
@@ -841,15 +841,26 @@ __device__ __forceinline__ uint32_t push_bit(uint32_t x, uint64_t mask)
     return r;
 }
 
-// How the elements a wavefront encodes lie in its registers; row = 16 lanes.
+// How the elements a wavefront encodes lie in its registers.  kBlocks: Philox blocks from chunk to chunk.  group, half:
+// which half of which 64-element group the lanes 8 h .. 8 h + 7 hold of chunk c; row_groups =
+// 64-element groups from row to row.
 //   OneRange: chunk c, lane l: elements 256c + 4l + {0..3} of one range.
-//   FourRows: row r holds a range of its own (consecutive ranges of equal length): chunk c, lane 16r + i: elements
-//             64c + 4i + {0..3} of range r.
+//   Rows<LANES>: every row of LANES = 16 or 8 lanes holds a range of its own (consecutive ranges of equal length), chunk c, lane i of
+//                the row: elements 4 LANES c + 4i + {0..3} of that range.
 struct OneRange {
-    static constexpr uint32_t kBlocks = 64, kGroups = 4;  // Philox blocks and 64-element groups from chunk to chunk
+    static constexpr uint32_t kBlocks = 64;
+    static __device__ __forceinline__ uint32_t group(uint32_t c, uint32_t h, uint32_t row_groups) { return 4u * c + (h >> 1) * row_groups; }
+    static __device__ __forceinline__ uint32_t half(uint32_t, uint32_t h) { return h & 1u; }
 };
-struct FourRows {
-    static constexpr uint32_t kBlocks = 16, kGroups = 1;
+template <int LANES>
+struct Rows {
+    static_assert(LANES == 16 || LANES == 8, "a chunk of a row is 64 or 32 elements");
+    static constexpr uint32_t kBlocks = LANES;
+    static __device__ __forceinline__ uint32_t group(uint32_t c, uint32_t h, uint32_t row_groups)
+    {
+        return LANES == 16 ? c + (h >> 1) * row_groups : (c >> 1) + h * row_groups;
+    }
+    static __device__ __forceinline__ uint32_t half(uint32_t c, uint32_t h) { return (LANES == 16 ? h : c) & 1u; }
 };
 
 // Which of the chunks' elements exist: all; those below `len`; or all of the chunks below len / 256.  Those that do not
@@ -928,7 +939,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
             mine = p == 0 || j == (uint32_t)p ? x : mine;
         }
         if (j < (uint32_t)BITS && (FILL != Fill::kRagged || 256u * c0 + 32u * h < ((len + 63u) & ~63u)))
-            range.words[((Layout::kGroups * c0 + (h >> 1) * range.row_groups) * (uint32_t)BITS + j) * 2u + (h & 1u)] = mine;
+            range.words[(Layout::group(c0, h, range.row_groups) * (uint32_t)BITS + j) * 2u + Layout::half(c0, h)] = mine;
         return;
     }
 #pragma unroll
@@ -944,7 +955,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
         const bool in_range = FILL == Fill::kAll || (FILL == Fill::kWholeChunks ? 256u * c < len
                                                                                 : 256u * c + 32u * h < ((len + 63u) & ~63u));
         if ((BITS % PLANES == 0 || p < (uint32_t)BITS) && in_range)
-            range.words[((Layout::kGroups * c + (h >> 1) * range.row_groups) * (uint32_t)BITS + p) * 2u + (h & 1u)] = x;
+            range.words[(Layout::group(c, h, range.row_groups) * (uint32_t)BITS + p) * 2u + Layout::half(c, h)] = x;
     }
 }
 
@@ -2596,7 +2607,7 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(RULE =
 template <int C>
 constexpr bool wave_serves(int S, int rule)
 {
-    return !(rule == kOptimal && S >= 8 && (C == 4 || C == 8));
+    return !(rule == kOptimal && S >= 8 && C >= 2 && C <= 8);
 }
 
 template <int C, int S, int BITS, int RULE = kOptimal>

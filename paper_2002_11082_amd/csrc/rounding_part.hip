@@ -78,29 +78,35 @@ void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32
 }
 #elif OGQ_PART < 100
 #if OGQ_PART <= 2
-// Four buckets per wavefront (row_kernels.h) where the gradient has enough of them to fill the chip that way: a
-// wavefront then takes about 1.5 times as long as one with a single bucket, so below one wavefront per SIMD (4096
-// buckets) it only adds latency.  Measured crossover, in buckets (profiles/row_kernels_scan.txt has both sides): 6000 to 8000 at
-// 128 elements, against a kernel that already takes two per wavefront; 2000 to 4000 at 192 to 448; up to 8000 at 512, where the
-// LDS holds fewer wavefronts.  Without level solves 3000 to 8000, at 128 elements 16000 to 20000.  The limits lie where
-// the rules with most solves gain (ORQ-9, 8192 buckets of 512: 23.6 -> 17.1 us; 32768: 73.6 -> 51.9); Linear-5 in buckets of
-// 512 loses up to 11 % by them (16384: 17.2 -> 19.1).
+// Four buckets per wavefront, eight of 128 elements (row_kernels.h), where the gradient has enough of them: a wavefront takes
+// longer than one with a single bucket, so where it has a SIMD to itself it only adds latency, unless the solves are what takes long.
+// Measured crossover in buckets (profiles/row_kernels_scan.txt has both sides; Gaussian values, us, other kernels -> this one):
+//   eight and nine levels   of 256 and less elements always (512 buckets of 256: 9.2 -> 7.2 with nine levels), above some 2000 (4096 of
+//                           512: 16.2 -> 10.7; 1024: 8.6 -> 9.8), of 128 some 8000 (32768: 30.0 -> 18.8)
+//   four and five levels    of 256 some 3000, of 512 3000 to 4000 (8192: 17.1 -> 14.9), of 128 8000
+//   three levels, Linear-s  of 256 3000, of 320 3000 to 4000, of 512 4000 to 8000, of 128 6000 to 8000
+//   no solves               of 256 equal, of 320 4000 (8192: 5.9 -> 4.4), of 512 8000, of 128 equal up to 16000
 static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    const bool solves = p->scheme != OGQ_EVEN && levels_per_bucket(p->scheme, p->bits) > 2;
-    const uint32_t d = p->bucket_size;
-    const uint32_t enough = d > 256 ? (solves ? 8192u : 16384u) : d > 128 ? (solves ? 4096u : 8192u) : 8192u;
+    const uint32_t levels = levels_per_bucket(p->scheme, p->bits), d = p->bucket_size;
+    const bool optimal = (p->scheme == OGQ_ORQ || p->scheme == OGQ_ORQ_PAPER) && levels > 3u;
+    const bool solves = p->scheme != OGQ_EVEN && levels > 2u;
+    const uint32_t enough = d > 448u   ? (!optimal ? 8192u : levels < 8u ? 4096u : 2048u)
+                            : d > 256u ? (!optimal || levels < 8u ? 4096u : 2048u)
+                            : d > 128u ? (!solves ? 8192u : !optimal || levels < 8u ? 3072u : 256u)
+                                       : 8192u;
     if (nb < enough) return false;
 #if OGQ_PART == 1
     switch (d) {
         case 64: return false;  // (four buckets per wavefront already: sorted_small_kernel, even_small_kernel)
-        case 128: return launch_rows_levels<2, true>(g, n, p, nb, lv, codes, st);
-        case 192: return launch_rows_levels<4, false>(g, n, p, nb, lv, codes, st);
-        default: return launch_rows_levels<4, true>(g, n, p, nb, lv, codes, st);
+        case 128:  // eight buckets per wavefront where that leaves two wavefronts per SIMD (ORQ-3: 12288 buckets 5.7 against 5.3 us with four)
+            return nb < 16384u ? launch_rows_levels<16, 2, true>(g, n, p, nb, lv, codes, st) : launch_rows_levels<8, 4, true>(g, n, p, nb, lv, codes, st);
+        case 192: return launch_rows_levels<16, 4, false>(g, n, p, nb, lv, codes, st);
+        default: return launch_rows_levels<16, 4, true>(g, n, p, nb, lv, codes, st);
     }
 #else
-    return d == 512 ? launch_rows_levels<8, true>(g, n, p, nb, lv, codes, st)
-                    : launch_rows_levels<8, false>(g, n, p, nb, lv, codes, st);
+    return d == 512 ? launch_rows_levels<16, 8, true>(g, n, p, nb, lv, codes, st)
+                    : launch_rows_levels<16, 8, false>(g, n, p, nb, lv, codes, st);
 #endif
 }
 #endif
@@ -118,9 +124,10 @@ void OGQ_CAT(launch_rounding_c, OGQ_PART)(const float* g, size_t n, const ogq_pa
 #elif OGQ_PART == 4
     if (launch_few<4, 1>(512u, g, n, p, nb, lv, codes, st)) return;
 #elif OGQ_PART == 2
-    // one chunk per wavefront: two share the solves of eight or nine levels, nothing else is long enough to share
+    // one chunk per wavefront: two share the solves of eight or nine levels where the rows above do not take them, nothing else is
+    // long enough to share
     if ((p->scheme == OGQ_ORQ || p->scheme == OGQ_ORQ_PAPER) && levels_per_bucket(p->scheme, p->bits) >= 8u &&
-        launch_few<2, 1>(2560u, g, n, p, nb, lv, codes, st)) return;
+        launch_few<2, 1>(~0u, g, n, p, nb, lv, codes, st)) return;
 #endif
     launch_orq_levels<OGQ_PART>(g, n, p, nb, lv, codes, st);
 }

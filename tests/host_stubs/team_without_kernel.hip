@@ -73,6 +73,8 @@ int main()
     ask_all<8, 8>();
     ask_all<8, 16>();
     ask_all<16, 8>();
+    ask_wave<2, 8, 3>();
+    ask_wave<2, 9, 4>();
     ask_wave<4, 8, 3>();
     ask_wave<4, 9, 4>();
     ask_wave<8, 8, 3>();

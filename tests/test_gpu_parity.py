@@ -825,6 +825,41 @@ def test_four_buckets_per_wavefront(scheme, bits, sweeps, d):
                               tag=f"rows-s{scheme}-b{bits}-d{d}-c{clip}")
 
 
+@pytest.mark.parametrize("d,nb,scheme,bits,sweeps", [
+    *[(128, 16384 + 7, scheme, bits, sweeps) for scheme, bits, sweeps in (
+        (ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 1), (ogq.ORQ_PAPER, 2, 1), (ogq.ORQ_PAPER, 3, 0), (ogq.ORQ_PAPER, 4, 2),
+        (ogq.EVEN, 2, 0), (ogq.EVEN, 4, 0), (ogq.LINEAR, 2, 0), (ogq.LINEAR, 4, 0))],
+    (192, 259, ogq.ORQ, 3, 3), (256, 263, ogq.ORQ, 3, 0), (256, 258, ogq.ORQ_PAPER, 4, 2), (320, 2049, ogq.ORQ, 3, 2),
+    (448, 2051, ogq.ORQ_PAPER, 4, 1), (512, 2050, ogq.ORQ, 3, 1), (256, 3075, ogq.ORQ_PAPER, 3, 2), (512, 4098, ogq.ORQ, 2, 2)])
+def test_many_buckets_per_wavefront_at_their_limits(d, nb, scheme, bits, sweeps):
+    """Eight buckets of 128 elements per wavefront, and the smallest gradients that four longer ones are taken for.  Unlike
+    neighbours, T exactly an integer with sums that may round in several buckets of a wavefront and in both halves of one,
+    widths too small for the plain encoder, Philox blocks that pass 2^32, NaN and infinities, whole buckets and a cut-off one
+    behind the last wavefront's."""
+    rng = np.random.default_rng(d + 1000 * bits + scheme)
+    g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    kinds = ["const", "normal", "zeros", "heavy", "ints", "shifted"]
+    poisoned = []
+    for b in range(0, 240):
+        if b % 3 == 0:
+            buckets[b] = _rng_bucket(rng, d, kinds[(b // 3) % len(kinds)])
+        elif b % 8 in (1, 2):
+            buckets[b, d // 2:] = -buckets[b, : d // 2]
+            buckets[b, [3, d // 2 + 3]] = [1e-38, -1e-38]
+        elif b % 8 == 4:
+            buckets[b] = np.float32(1.0) + rng.integers(0, 200, d).astype(np.float32) * np.float32(2.0 ** -23)
+        elif b % 8 == 5:
+            buckets[b] *= np.float32(rng.choice([1e-30, 1e-38]))
+        elif b % 8 == 7:
+            poisoned.append(b)
+            buckets[b, rng.choice(d, size=5, replace=False)] = [np.nan, np.inf, -np.inf, np.nan, np.inf]
+    checked = [b for b in sorted(set(range(240)) | set(_sample(nb, 40, nb)) | set(range(nb - 9, nb))) if b not in poisoned]
+    for cut, clip in ((17, 0.0), (d - 1, 2.5)):
+        parity.check_quantize(g[: nb * d - cut], d, bits, scheme, sweeps, seed=37, index_offset=(1 << 34) - 117 * d, buckets=checked,
+                              clip_factor=clip, tag=f"rows-limit-s{scheme}-b{bits}-d{d}-c{clip}")
+
+
 @pytest.mark.parametrize("d", [128, 192, 256, 448, 512])
 @pytest.mark.parametrize("scheme,bits", [(ogq.ORQ, 1), (ogq.ORQ, 2), (ogq.ORQ, 3), (ogq.ORQ_PAPER, 2), (ogq.EVEN, 3), (ogq.LINEAR, 4)])
 def test_encoder_careful_form_of_four_buckets_per_wavefront(scheme, bits, d):
@@ -990,6 +1025,9 @@ def test_several_buckets_per_workgroup(scheme, bits, sweeps, d, nb):
     buckets[3, d // 2:] = -buckets[3, : d // 2]                                                        # T exactly an integer
     buckets[5] *= np.float32(1e-38)
     buckets[7] = rng.choice(np.array([0.0, -0.0, 1e-3, -2e-3], dtype=np.float32), d)
+    for b in (8, 9, 11):  # the same where fp64 sums may round: exact ones decide, in one bucket of a workgroup and in both
+        buckets[b, d // 2:] = -buckets[b, : d // 2]
+        buckets[b, [3, d // 2 + 3]] = [1e-38, -1e-38]
     checked = sorted(set(list(range(15)) + _sample(nb, 12, nb) + [nb - 2, nb - 1]))
     for cut, clip in ((0, 0.0), (1, 2.5), (d - 1, 0.0), (d - 19, 0.0)):
         parity.check_quantize(g[: nb * d - cut], d, bits, scheme, sweeps, seed=29, index_offset=(1 << 34) - 64 * 9, buckets=checked,
