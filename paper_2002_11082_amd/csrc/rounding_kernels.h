@@ -1545,8 +1545,7 @@ __device__ __forceinline__ float orq_solve_levels(Lds& lds, PickFn pick, EdgeFn 
             const uint32_t first_above = uniform_u32(lds.bin_start[bin_lo + 1u]);
             // Then the value inside it.  A bin of at most 64 elements is sorted once and every distinct positive value
             // of it gets its gap in its own lane (the sum of the strictly smaller elements is an exclusive scan at the
-            // first lane that holds the value); larger bins, and the case that the wanted value is the first one
-            // above the bin, take the bisection over ranks below.
+            // first lane that holds the value); where none of them is the wanted one, that is the first element above the bin.
             const uint32_t count = first_above - first_of_bin;
             bool done = false;
             if (count > 0u && count <= 64u) {
@@ -1559,11 +1558,18 @@ __device__ __forceinline__ float orq_solve_levels(Lds& lds, PickFn pick, EdgeFn 
                 const bool candidate = lane < count && value > 0.0f && (lane == 0u || previous != sorted);
                 const double gap = (double)value * (double)positives - (total - smaller);
                 const uint64_t not_negative = __ballot(candidate && gap >= 0.0);
-                if (not_negative != 0) {
-                    const uint32_t at = (uint32_t)__builtin_ctzll(not_negative);  // first lane of the wanted value
-                    const uint32_t up_key = __builtin_amdgcn_readlane(sorted, at);
-                    const double gap_up = lane_entry_f64(gap, at);
-                    pb_level = key_to_float(up_key);
+                if (not_negative != 0 || first_above < len) {
+                    // first lane of the wanted value; past the bin's: it is the first element above the bin
+                    const uint32_t at = not_negative != 0 ? (uint32_t)__builtin_ctzll(not_negative) : count;
+                    double gap_up;
+                    if (not_negative != 0) {
+                        pb_level = key_to_float(__builtin_amdgcn_readlane(sorted, at));
+                        gap_up = lane_entry_f64(gap, at);
+                    } else {
+                        const Picked up = pick(first_above + 1u);
+                        pb_level = key_to_float(up.key);
+                        gap_up = (double)pb_level * (double)positives - (total - up.sum_lt);
+                    }
                     const uint32_t count_lt = first_of_bin + at;  // elements of the bucket below the wanted value
                     if (count_lt > not_positive) {  // a smaller positive value exists
                         float down;
@@ -1584,25 +1590,66 @@ __device__ __forceinline__ float orq_solve_levels(Lds& lds, PickFn pick, EdgeFn 
                 }
             }
             if (!done) {
-                // 1-based ranks; the first element above the bin, like the largest value of the bucket, always has
-                // gap >= 0
-                const uint32_t hi_rank = umin32(len, first_above + 1u);
-                uint32_t lo = umin32(umax32(not_positive, first_of_bin) + 1u, hi_rank), hi = hi_rank;
+                // A crowded bin, an empty one, or the last one that holds elements.  The gap grows with the value also between the
+                // bin's elements: a bisection over the keys finds the smallest one whose gap is not negative, each step one sum
+                // over the bin, and the wanted value is the first element from there on.
+                auto each = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll 1
+                    for (uint32_t i = lane; i < count; i += kWave) f(__uint_as_float(lds.grouped[skewed(first_of_bin + i)]) + 0.0f);
+                };
+                const double below_bin = count != 0u ? sum_before_position(lds, first_of_bin, lane) : 0.0;
+                auto smaller_than = [&](float t) __attribute__((always_inline)) {  // sum of the bucket's elements below t, t in the bin
+                    double part = 0.0;
+                    each([&](float x) __attribute__((always_inline)) { part += (double)(x < t ? x : 0.0f); });
+                    return below_bin + wave_sum(part);
+                };
+                uint32_t lo = 0xFFFFFFFFu, largest = 0u;  // keys of the bin's positive elements
+                each([&](float x) __attribute__((always_inline)) {
+                    lo = x > 0.0f ? umin32(lo, float_to_key(x)) : lo;
+                    largest = x > 0.0f ? umax32(largest, float_to_key(x)) : largest;
+                });
+                lo = wave_min_u32(lo);
+                largest = wave_max_u32(largest);
+                uint32_t hi = largest + 1u;  // (no positive element: 1, and lo lies above)
                 while (lo < hi) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    const Picked p = pick(mid);
-                    const double gap = (double)key_to_float(p.key) * (double)positives - (total - p.sum_lt);
-                    if (gap >= 0.0) hi = mid;
+                    const uint32_t mid = lo + ((hi - lo) >> 1);
+                    const float t = key_to_float(mid);
+                    if ((double)t * (double)positives - (total - smaller_than(t)) >= 0.0) hi = mid;
                     else lo = mid + 1u;
                 }
-                const Picked up = pick(lo);
-                const double gap_up = (double)key_to_float(up.key) * (double)positives - (total - up.sum_lt);
-                pb_level = key_to_float(up.key);
-                if (up.count_lt > not_positive) {  // a smaller positive value exists: rank count_lt is the next one down
-                    const Picked down = pick(up.count_lt);
-                    const double gap_down =
-                        (double)key_to_float(down.key) * (double)positives - (total - down.sum_lt);
-                    if (fabs(gap_down) <= fabs(gap_up)) pb_level = key_to_float(down.key);  // ties take the smaller value
+                // the first element from `lo` on: in the bin, or above it; the bucket's last where only rounding (or NaN) says that there is none
+                double gap_up;
+                uint32_t count_lt = 0;  // elements of the bucket below it
+                if (lo <= largest) {
+                    uint32_t up = 0xFFFFFFFFu;
+                    each([&](float x) __attribute__((always_inline)) { up = float_to_key(x) >= lo ? umin32(up, float_to_key(x)) : up; });
+                    pb_level = key_to_float(wave_min_u32(up));
+                    gap_up = (double)pb_level * (double)positives - (total - smaller_than(pb_level));
+                    each([&](float x) __attribute__((always_inline)) { count_lt += x < pb_level ? 1u : 0u; });
+                    count_lt = first_of_bin + wave_sum_u32(count_lt);
+                } else {
+                    const Picked up = pick(umin32(first_above + 1u, len));
+                    pb_level = key_to_float(up.key);
+                    gap_up = (double)pb_level * (double)positives - (total - up.sum_lt);
+                    count_lt = up.count_lt;
+                }
+                if (count_lt > not_positive) {  // a smaller positive value exists
+                    uint32_t down_key = 0u;
+                    each([&](float x) __attribute__((always_inline)) {
+                        down_key = x > 0.0f && x < pb_level ? umax32(down_key, float_to_key(x)) : down_key;
+                    });
+                    down_key = wave_max_u32(down_key);
+                    float down;
+                    double gap_down;
+                    if (down_key != 0u) {
+                        down = key_to_float(down_key);
+                        gap_down = (double)down * (double)positives - (total - smaller_than(down));
+                    } else {
+                        const Picked below = pick(count_lt);
+                        down = key_to_float(below.key);
+                        gap_down = (double)down * (double)positives - (total - below.sum_lt);
+                    }
+                    if (fabs(gap_down) <= fabs(gap_up)) pb_level = down;  // ties take the smaller value
                 }
             }
         }

@@ -113,6 +113,34 @@ def test_bingrad_pb_small(d):
     parity.check_quantize(g, d, 1, ogq.BINGRAD_PB, 0, seed=5, clip_factor=2.5, tag=f"bingradpb-clip-d{d}")
 
 
+@pytest.mark.parametrize("d", [192, 512, 1344, 2048, 2112, 8192])
+def test_bingrad_pb_where_the_level_lies(d):
+    """The positive level inside a bin of the kernel's grouping that holds few elements, more than a wavefront's lanes, several
+    times that; the first element above a bin; the largest; behind bins without elements; repeated values; among zeros."""
+    rng = np.random.default_rng(d)
+
+    def bucket(*clusters):
+        parts = [np.float32(at) * (np.float32(1) + rng.integers(0, spread, count).astype(np.float32) * np.float32(2.0 ** -22))
+                 for at, count, spread in clusters]
+        x = rng.permutation(np.concatenate(parts).astype(np.float32))[: d - 8]
+        x = np.concatenate([x, -np.abs(rng.normal(0, 1e-3, d - x.size)).astype(np.float32)])
+        rng.shuffle(x)
+        return x
+
+    n = d // 2
+    g = [bucket((1.0, n, 4000)), bucket((1.0, n, 5)), bucket((1.0, n, 1)), bucket((0.01, n - 70, 9000), (1.0, 70, 9000)),
+         bucket((0.5, n // 2, 900), (0.75, 20, 3)), bucket((1e-3, n // 3, 100), (1.0, n // 3, 100), (1.99, 3, 100)),
+         bucket((0.4, 70, 1000), (1.0, 60, 1000)), bucket((0.647, 130, 3000), (1.0, 90, 60000), (0.2, 60, 1000))]
+    sparse = bucket((1.0, n, 4000))
+    sparse[rng.random(d) < 0.9] = rng.choice([0.0, -0.0])
+    lone = np.full(d, -1.0, dtype=np.float32)
+    lone[7] = 0.25
+    tiny = bucket((1e-5, n - 5, 4000), (1.0, 5, 1000))  # (far smaller ones: gaps that are equal in 64 bits)
+    g = np.concatenate(g + [sparse, lone, tiny, np.abs(rng.standard_cauchy(d)).astype(np.float32)])
+    for size in (g.size, g.size - d // 2 - 3):
+        parity.check_quantize(g[:size], d, 1, ogq.BINGRAD_PB, 0, seed=41, tag=f"pb-where-d{d}-n{size}")
+
+
 def test_bingrad_pb_resnet50_size_sampled():
     wl = synth.WORKLOADS["cfg2"]
     g = wl.gradient()
