@@ -157,12 +157,10 @@ constexpr int kExactLimbs = 10;
 
 // LDS of one bucket: D = element capacity, B = number of bins.
 template <int D_, int B_, int S_>
-struct OrqLds {
+struct alignas(16) OrqLds {
     static constexpr int D = D_, B = B_;
     static constexpr int BLOCK = D_ / 64;  // positions per entry of the fp64 block prefix
-    // fp32 bit patterns grouped by bin (-0 lies with +0), unsorted inside a bin.  Position i lives at
-    // word i + i/64, so that the 64 lanes reading consecutive blocks of D/64 positions hit distinct banks.
-    uint32_t grouped[D + D / 64];
+    uint32_t grouped[D];  // fp32 bit patterns grouped by bin (-0 lies with +0), unsorted inside a bin
     uint32_t bin_start[B + 1];  // histogram, then first position of each bin; [B] = bucket length
     double block_prefix[64];    // fp64 sum of all positions before block l (block = D/64 positions)
     // per level k: value; #{v < value}; #{v <= value}; sum{v < value}; sum{v <= value}; the rank it
@@ -176,17 +174,6 @@ struct OrqLds {
     double sum_error_bound;  // 0 when every fp64 sum of the bucket is exact (see floor_t_from_sums)
     unsigned long long exact_limb[1][kExactLimbs];  // workspace of exact_floor_t
 };
-
-__device__ __forceinline__ uint32_t skewed(uint32_t position) { return position + (position >> 6); }
-
-// Byte offset of a skewed position in the grouped array, as one shift and one add-and-shift (v_add_lshl_u32; written
-// in plain C++ the compiler distributes the shift over the sum and needs three instructions).
-__device__ __forceinline__ uint32_t skewed_byte_offset(uint32_t position)
-{
-    uint32_t offset;
-    asm("v_add_lshl_u32 %0, %1, %2, 2" : "=v"(offset) : "v"(position), "v"(position >> 6));
-    return offset;
-}
 
 // A zero the compiler cannot see through.  x + this turns -0 into +0 like x + 0.0f does, and, unlike that, is not
 // recognised as the same value in a later phase: what is derived from the register-resident bucket is computed again
@@ -433,10 +420,10 @@ __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, u
         const uint32_t joint = front + count <= 64u ? front : 0u;  // lanes that hold the front
         const uint32_t held = joint + count;
         const float value =
-            __uint_as_float(lds.grouped[skewed(first - joint + (lane < held ? lane : 0u))]) + 0.0f;
+            __uint_as_float(lds.grouped[first - joint + (lane < held ? lane : 0u)]) + 0.0f;
         const uint32_t mine = lane < held ? float_to_key(value) : 0xFFFFFFFFu;
         float other = 0.0f;  // the front where it does not fit
-        if (SUMS && joint != front) other = lane < front ? __uint_as_float(lds.grouped[skewed(first - front + lane)]) : 0.0f;
+        if (SUMS && joint != front) other = lane < front ? __uint_as_float(lds.grouped[first - front + lane]) : 0.0f;
         const uint64_t lt =
             select_rank(mine, held, rank - first + joint, (~0ull >> (64u - count)) << joint, key, c_le);
         c_le -= joint;
@@ -450,7 +437,7 @@ __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, u
         }
     } else {
         const uint32_t r_in = rank - first;  // 1-based rank inside the bin
-        const float head = lane < front ? __uint_as_float(lds.grouped[skewed(first - front + lane)]) : 0.0f;
+        const float head = lane < front ? __uint_as_float(lds.grouped[first - front + lane]) : 0.0f;
         // A crowded bin (many equal or nearly equal values): bisection on the key, over the bits in which the bin's
         // smallest and largest key differ (none when all its values are equal).  Up to 256 keys stay in registers.
         constexpr int HELD = 4;
@@ -462,7 +449,7 @@ __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, u
             for (int c = 0; c < HELD; ++c) {
                 const uint32_t i = 64u * c + lane;
                 const bool valid = i < count;
-                mine[c] = valid ? stored_key(lds.grouped[skewed(first + (valid ? i : 0u))]) : 0xFFFFFFFFu;
+                mine[c] = valid ? stored_key(lds.grouped[first + (valid ? i : 0u)]) : 0xFFFFFFFFu;
                 smallest = umin32(smallest, mine[c]);
                 largest = umax32(largest, valid ? mine[c] : 0u);
             }
@@ -470,7 +457,7 @@ __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, u
             for (uint32_t base = 0; base < count; base += 64u) {
                 const uint32_t i = base + lane;
                 if (i < count) {
-                    const uint32_t k = stored_key(lds.grouped[skewed(first + i)]);
+                    const uint32_t k = stored_key(lds.grouped[first + i]);
                     smallest = umin32(smallest, k);
                     largest = umax32(largest, k);
                 }
@@ -492,7 +479,7 @@ __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, u
                 } else {
                     for (uint32_t base = 0; base < count; base += 64u) {
                         const uint32_t i = base + lane;
-                        const uint32_t k = i < count ? stored_key(lds.grouped[skewed(first + i)]) : 0xFFFFFFFFu;
+                        const uint32_t k = i < count ? stored_key(lds.grouped[first + i]) : 0xFFFFFFFFu;
                         below += (uint32_t)__popcll(__ballot(k < cand));
                     }
                 }
@@ -506,7 +493,7 @@ __device__ __forceinline__ Picked pick_in_span(const Lds& lds, uint32_t first, u
         if constexpr (SUMS)
         for (uint32_t base = 0; base < count; base += 64u) {
             const uint32_t i = base + lane;
-            const float x = i < count ? __uint_as_float(lds.grouped[skewed(first + i)]) + 0.0f : 0.0f;
+            const float x = i < count ? __uint_as_float(lds.grouped[first + i]) + 0.0f : 0.0f;
             const uint32_t k = i < count ? float_to_key(x) : 0xFFFFFFFFu;
             const bool lt = k < key;
             c_lt += (uint32_t)__popcll(__ballot(lt));
@@ -709,7 +696,7 @@ static __device__ __attribute__((noinline)) uint32_t exact_floor_t_grouped(unsig
                                                                    float R, uint32_t count_in, uint32_t guess)
 {
     return exact_floor_t(limb, lane, L, R, count_in, guess, [&](auto add) {
-        for (uint32_t i = lane; i < len; i += stride) add(__uint_as_float(grouped[skewed(i)]));
+        for (uint32_t i = lane; i < len; i += stride) add(__uint_as_float(grouped[i]));
     });
 }
 
@@ -1149,7 +1136,7 @@ __device__ __forceinline__ void count_into_bins(uint32_t (&slot)[C][4], const fl
 
 // Scatters the lane's elements into their bins.  The bin starts of a group of elements are all read before the group's
 // values are written (a read behind a write to the same LDS object would wait for it).  Padding of a group that holds
-// elements goes where it lies in the bucket: behind all elements.
+// elements goes where it lies in the bucket, behind all elements, as zeros.
 template <int C, bool FULL>
 __device__ __forceinline__ void scatter_into_bins(uint32_t* grouped, const uint32_t* bin_start_middle, const uint32_t (&slot)[C][4],
                                                   const float (&v)[C][4], uint32_t first, uint32_t my_len, uint32_t lane)
@@ -1171,8 +1158,9 @@ __device__ __forceinline__ void scatter_into_bins(uint32_t* grouped, const uint3
                     const uint32_t e = 256u * (uint32_t)(c0 + c) + 4u * lane + k;
                     to[c][k] = e < my_len ? to[c][k] : first + e;
                 }
-                *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(grouped) + skewed_byte_offset(to[c][k])) =
-                    __float_as_uint(v[c0 + c][k]);
+                uint32_t bits = __float_as_uint(v[c0 + c][k]);
+                if constexpr (!decltype(all)::value) bits = 256u * (uint32_t)(c0 + c) + 4u * lane + k < my_len ? bits : 0u;
+                grouped[to[c][k]] = bits;
             }
     };
 #pragma unroll
@@ -1180,6 +1168,26 @@ __device__ __forceinline__ void scatter_into_bins(uint32_t* grouped, const uint3
         if (FULL || 256u * (uint32_t)(c0 + GROUP) <= my_len) scatter_group(c0, std::true_type{});
         else if (256u * (uint32_t)c0 < my_len) scatter_group(c0, std::false_type{});
     }
+}
+
+// fp64 sum of the 4 C grouped positions of thread `thread`; the bucket has `len` of them, zeros behind them up to the end of the
+// thread's positions, if those begin below `len`.  16-byte reads; every thread begins at another of its pieces, so that
+// neighbours meet different LDS banks.
+template <int C>
+__device__ __forceinline__ double sum_of_positions(const uint32_t* grouped, uint32_t thread, uint32_t len)
+{
+    const float4* from = reinterpret_cast<const float4*>(grouped) + C * thread;
+    const uint32_t turn = thread / (C < 8 ? 8u / C : 1u);
+    double part = 0.0;
+#pragma unroll
+    for (uint32_t q = 0; q < (uint32_t)C; ++q) {
+        const float4 x = from[(q + turn) & (uint32_t)(C - 1)];
+        part += (double)x.x;
+        part += (double)x.y;
+        part += (double)x.z;
+        part += (double)x.w;
+    }
+    return 4u * C * thread < len ? part : 0.0;
 }
 
 // The reload function of orq_encode for a range in memory: g = its first element; limit = the clipping threshold
@@ -1218,7 +1226,7 @@ __device__ __forceinline__ bool any_tiny_element(const Lds& lds, uint32_t capaci
     const uint32_t last = uniform_u32(lds.bin_start[(uint32_t)HALF + bins]);
     bool tiny = false;
     for (uint32_t i = first + thread; i < last; i += threads) {
-        const uint32_t magnitude = lds.grouped[skewed(i)] & 0x7FFFFFFFu;
+        const uint32_t magnitude = lds.grouped[i] & 0x7FFFFFFFu;
         tiny = tiny || (magnitude != 0u && magnitude < mag_safe);
     }
     return tiny;
@@ -1459,7 +1467,7 @@ __device__ __forceinline__ double sum_before_position(const Lds& lds, uint32_t p
     constexpr uint32_t BLOCK = Lds::BLOCK;
     const uint32_t block = position / BLOCK;
     const uint32_t block_first = block * BLOCK;
-    const float head = lane < position - block_first ? __uint_as_float(lds.grouped[skewed(block_first + lane)]) : 0.0f;
+    const float head = lane < position - block_first ? __uint_as_float(lds.grouped[block_first + lane]) : 0.0f;
     return uniform_f64(lds.block_prefix[block]) + wave_sum((double)head);
 }
 
@@ -1549,7 +1557,7 @@ __device__ __forceinline__ float orq_solve_levels(Lds& lds, PickFn pick, EdgeFn 
             const uint32_t count = first_above - first_of_bin;
             bool done = false;
             if (count > 0u && count <= 64u) {
-                const uint32_t mine = lane < count ? stored_key(lds.grouped[skewed(first_of_bin + lane)]) : 0xFFFFFFFFu;
+                const uint32_t mine = lane < count ? stored_key(lds.grouped[first_of_bin + lane]) : 0xFFFFFFFFu;
                 const uint32_t sorted = wave_sort_u32(mine, lane, count);
                 const float value = lane < count ? key_to_float(sorted) : 0.0f;
                 const double below_bin = sum_before_position(lds, first_of_bin, lane);
@@ -1595,7 +1603,7 @@ __device__ __forceinline__ float orq_solve_levels(Lds& lds, PickFn pick, EdgeFn 
                 // over the bin, and the wanted value is the first element from there on.
                 auto each = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll 1
-                    for (uint32_t i = lane; i < count; i += kWave) f(__uint_as_float(lds.grouped[skewed(first_of_bin + i)]) + 0.0f);
+                    for (uint32_t i = lane; i < count; i += kWave) f(__uint_as_float(lds.grouped[first_of_bin + i]) + 0.0f);
                 };
                 const double below_bin = count != 0u ? sum_before_position(lds, first_of_bin, lane) : 0.0;
                 auto smaller_than = [&](float t) __attribute__((always_inline)) {  // sum of the bucket's elements below t, t in the bin
@@ -1810,14 +1818,7 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
         {
             double incl = 0.0;
             if constexpr (SUMS) {
-                constexpr uint32_t BLOCK = D / 64;
-                double part = 0.0;
-#pragma unroll
-                for (uint32_t i = 0; i < BLOCK; ++i) {
-                    const uint32_t position = lane * BLOCK + i;
-                    const float x = __uint_as_float(lds.grouped[skewed(position)]);  // (behind the elements: anything)
-                    part += (double)(FULL || position < len ? x : 0.0f);
-                }
+                const double part = sum_of_positions<C>(lds.grouped, lane, FULL ? (uint32_t)D : len);
                 incl = wave_inclusive_scan_f64(part);
                 lds.block_prefix[lane] = incl - part;
             } else if constexpr (RULE == kOptimal) {
@@ -2405,13 +2406,13 @@ __global__ __launch_bounds__(4 * kWave) void sorted_small_kernel(const float* __
 // a barrier and spends 64 lanes on one scalar chain (buckets up to 4096 elements: pool_kernels.h).
 // ----------------------------------------------------------------------------------------------
 template <int W, int C>
-struct OrqTeamLds {
+struct alignas(16) OrqTeamLds {
     static constexpr int D = 256 * C * W;
     // bins, and magnitude bits dropped by the bin index (what is kept: the exponent and 3 .. 6 mantissa bits)
     static constexpr int B = D >= 16384 ? 2048 : D >= 8192 ? 1024 : D >= 4096 ? 512 : 256;
     static constexpr int SHIFT = D >= 16384 ? 17 : D >= 8192 ? 18 : D >= 4096 ? 19 : 20;
     static constexpr int BLOCK = C < 8 ? 32 : 4 * C;  // positions per entry of the fp64 block prefix
-    uint32_t grouped[D + D / 64];
+    uint32_t grouped[D];
     uint32_t bin_start[B + 4];
     double block_prefix[D / BLOCK];  // fp64 sum of all positions before block i of BLOCK positions
     double lvl_sum_lt[10];
@@ -2525,14 +2526,8 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
         {
             double total = 0.0;
             if constexpr (SUMS) {
-                constexpr uint32_t SPAN = 4u * C, SPANS = OrqTeamLds<W, C>::BLOCK / SPAN;
-                double part = 0.0;
-#pragma unroll 8
-                for (uint32_t i = 0; i < SPAN; ++i) {
-                    const uint32_t position = tid * SPAN + i;
-                    const float x = __uint_as_float(lds.grouped[skewed(position)]);  // (behind the elements: anything)
-                    part += (double)(FULL || position < len ? x : 0.0f);
-                }
+                constexpr uint32_t SPANS = OrqTeamLds<W, C>::BLOCK / (4u * C);
+                const double part = sum_of_positions<C>(lds.grouped, tid, FULL ? (uint32_t)OrqTeamLds<W, C>::D : len);
                 const double incl = wave_inclusive_scan_f64(part);
                 const TeamSlot* s = team.exchange(readlane_f64(incl, 63), 0u, 0u);
                 double before = 0.0;
