@@ -7,10 +7,6 @@
 
 namespace ogq {
 
-// LDS through its own address space: addresses of 32 bits, of which the histogram keeps 16 with every element.
-typedef __attribute__((address_space(3))) uint32_t LdsWord;
-typedef __attribute__((address_space(3))) uint16_t LdsHalf;
-
 // Per level: what OrqLds keeps.
 struct GroupLevel {
     double sum_lt, sum_le;

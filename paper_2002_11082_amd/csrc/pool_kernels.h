@@ -325,7 +325,8 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         for (int k = 1; k < S; ++k) mine = lane == (uint32_t)k ? lv[k] : mine;
         if (lane < (uint32_t)S) levels[(size_t)bucket * S + lane] = mine;
     }
-    orq_encode<C, S, BITS, FULL>(v, lv, my_len, begin + first, seed, index_offset, codes32, ReloadFromMemory{g + first, my_len, limit});
+    orq_encode<C, S, BITS, FULL>(v, lv, my_len, begin + first, seed, index_offset, codes32, ReloadFromMemory{g + first, my_len, limit},
+                                 encoder_table<S, true>(my.grouped, part));
 }
 
 template <int W, int C, int S, int BITS>

@@ -343,7 +343,12 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
 
     const EncodeRange range{256u * chunks, (index_offset + begin) >> 2, row * (len / 4u) + i, len / 64u, (uint32_t)seed,
                             (uint32_t)(seed >> 32), codes32 + begin / 64 * (2 * BITS)};
-    encode_all<Rows<LANES>, C, S, BITS, EXACT ? Fill::kAll : Fill::kWholeChunks>(v, lv, range, ReloadRow<LANES>{g, limit});
+    constexpr Fill FILL = EXACT ? Fill::kAll : Fill::kWholeChunks;
+    if constexpr (GROUPED && S > kScaledWidthLevels)  // (72 bytes from table to table: other LDS banks)
+        encode_all<Rows<LANES>, C, S, BITS, FILL>(v, lv, range, ReloadRow<LANES>{g, limit},
+                                                  PairsInLds{(uint32_t)(uintptr_t)((LdsWord*)lds.grouped) + 72u * row, i == 0u});
+    else
+        encode_all<Rows<LANES>, C, S, BITS, FILL>(v, lv, range, ReloadRow<LANES>{g, limit});
 }
 
 // Blocks 0 .. singles - 1 take the buckets behind the last whole span (a few whole ones and a cut-off one), one each as in
