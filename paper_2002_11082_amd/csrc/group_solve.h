@@ -106,6 +106,39 @@ __device__ __forceinline__ void group_sort(uint32_t (&x)[K], uint32_t lane)
     }
 }
 
+// Largest key of the group, in all its lanes.
+template <int G>
+__device__ __forceinline__ uint32_t group_max(uint32_t x)
+{
+    x = umax32(x, dpp_u32<kDppXor1>(x));
+    x = umax32(x, dpp_u32<kDppXor2>(x));
+    x = umax32(x, dpp_u32<kDppHalfMirror>(x));
+    if constexpr (G == 16) x = umax32(x, dpp_u32<kDppMirror>(x));
+    return x;
+}
+
+// Lanes of this lane's group of G for which the condition holds.
+template <int G>
+__device__ __forceinline__ uint32_t group_count(bool condition, uint32_t lane)
+{
+    return (uint32_t)__popc((uint32_t)(__ballot(condition) >> (lane & (64u - (uint32_t)G))) & ((1u << G) - 1u));
+}
+
+// x[index % K].  By masks: a choice between two elements of an array becomes a load from a chosen address before the array is
+// split into registers, and then it stays in scratch memory, or is moved to LDS with the lane's place computed from the dispatch
+// packet in host memory, which every wavefront waits 13 us for.
+template <int K>
+__device__ __forceinline__ uint32_t picked_register(const uint32_t (&x)[K], uint32_t index)
+{
+    static_assert(K == 1 || K == 2 || K == 4, "");
+    if constexpr (K == 1) return x[0];
+    const uint32_t odd = 0u - (index & 1u);
+    const uint32_t low = (x[0] & ~odd) | (x[K > 1 ? 1 : 0] & odd);
+    if constexpr (K == 2) return low;
+    const uint32_t high = (x[K > 2 ? 2 : 0] & ~odd) | (x[K > 2 ? 3 : 0] & odd), upper = 0u - (index >> 1 & 1u);
+    return (low & ~upper) | (high & upper);
+}
+
 // An element picked by rank, the same in all lanes of a group; counts and sum are those of its bin.
 struct GroupPicked {
     float value;
@@ -113,8 +146,8 @@ struct GroupPicked {
     double part;  // this lane's share of the sum of the smaller elements
 };
 
-// The element of index `index` (0-based) among the n (at most G K) values at `at`.
-template <int G, int K, bool SUMS>
+// The element of index `index` (0-based) among the n (at most WITHIN K, WITHIN <= G) values at `at`.
+template <int G, int K, bool SUMS, int WITHIN = G>
 __device__ __forceinline__ GroupPicked group_pick_sorted(const char* at, uint32_t n, uint32_t index, uint32_t lane)
 {
     const uint32_t i = lane & (uint32_t)(G - 1);
@@ -127,19 +160,16 @@ __device__ __forceinline__ GroupPicked group_pick_sorted(const char* at, uint32_
         mine[k] = i + (uint32_t)(G * k) < n ? float_to_key(value[k]) : 0xFFFFFFFFu;
         x[k] = mine[k];
     }
-    group_sort<G, K>(x, lane);
+    group_sort<WITHIN, K>(x, lane);  // (past WITHIN lanes there is only padding)
     // element `index`, handed to all lanes of the group as the largest of what they offer
-    uint32_t offer[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) offer[k] = x[k];
-#pragma unroll
-    for (int half = K / 2, bit = 0; half >= 1; half /= 2, ++bit) {
-#pragma unroll
-        for (int k = 0; k < half; ++k) offer[k] = (index & (1u << bit)) ? offer[2 * k + 1] : offer[2 * k];
-    }
-    const uint32_t key = row_max_u32<G>(i == index / (uint32_t)K ? offer[0] : 0u, lane);
+    const uint32_t key = group_max<G>(i == index / (uint32_t)K ? picked_register<K>(x, index) : 0u);
     GroupPicked p{key_to_float(key), 0u, 0u, 0.0};
-    if constexpr (SUMS) {
+    if constexpr (SUMS && K == 1) {
+        const bool below = mine[0] < key;
+        p.part = (double)(below ? value[0] : 0.0f);
+        p.count_lt = group_count<G>(below, lane);
+        p.count_le = umin32(group_count<G>(mine[0] <= key, lane), n);  // (a key of all ones, a NaN, equals the padding)
+    } else if constexpr (SUMS) {
         uint32_t counts = 0;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -149,7 +179,7 @@ __device__ __forceinline__ GroupPicked group_pick_sorted(const char* at, uint32_
         }
         counts = row_sum_u32<G>(counts, lane);
         p.count_lt = counts & 0xFFFFu;
-        p.count_le = umin32(counts >> 16, n);  // (a key of all ones, a NaN, equals the padding)
+        p.count_le = umin32(counts >> 16, n);
     }
     return p;
 }
@@ -216,12 +246,6 @@ __device__ __forceinline__ uint32_t truncated_u32(double x)
     uint32_t r;
     asm("v_cvt_u32_f64_e32 %0, %1" : "=v"(r) : "v"(x));
     return r;
-}
-
-// Lanes of this lane's row for which the condition holds.
-__device__ __forceinline__ uint32_t row_count(bool condition, uint32_t lane)
-{
-    return (uint32_t)__popc((uint32_t)(__ballot(condition) >> (lane & 48u)) & 0xFFFFu);
 }
 
 // One level solve per group of G lanes, run by a whole wavefront: level k between the levels l and r of the group's bucket (see
@@ -317,15 +341,16 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
         value = fmaxf(value, dpp_f32<kDppMirror>(value));
         if constexpr (SUMS) {
             const bool below = own < value;
-            count_lt = row_count(below, lane);
-            count_le = row_count(own <= value, lane);
+            count_lt = group_count<G>(below, lane);
+            count_le = group_count<G>(own <= value, lane);
             part += (double)(below ? own : 0.0f);
         }
     } else {
         const uint32_t n = last - first;
         const char* keys = b.grouped + 4u * first;
         GroupPicked p;
-        if (!Shape::WINDOWED && __ballot(n > LANES) == 0) p = group_pick_sorted<G, 1, SUMS>(keys, n, at - first, lane);
+        if (!Shape::WINDOWED && __ballot(n > 8u) == 0) p = group_pick_sorted<G, 1, SUMS, 8>(keys, n, at - first, lane);
+        else if (!Shape::WINDOWED && __ballot(n > LANES) == 0) p = group_pick_sorted<G, 1, SUMS>(keys, n, at - first, lane);
         else if (__ballot(n > 2u * LANES) == 0) p = group_pick_sorted<G, 2, SUMS>(keys, n, at - first, lane);
         else if (__ballot(n > 4u * LANES) == 0) p = group_pick_sorted<G, 4, SUMS>(keys, n, at - first, lane);
         else p = group_pick_bisected<G, SUMS>(keys, n, at - first, lane);
@@ -334,23 +359,29 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
         count_le = p.count_le;
         part += p.part;
     }
-    const bool copy_left = !ordered || value < L;  // the level coincides with the left end
-    GroupLevel now;
-    now.value = copy_left ? L : value;
-    now.count_lt = now.count_le = 0;
-    now.sum_lt = now.sum_le = 0.0;
+    GroupLevel now{0.0, 0.0, value, 0, 0};
+    uint32_t picked_at = rank;
     if constexpr (SUMS) {
-        const double sum_lt = before + row_sum_f64<G>(part, lane);
-        const double sum_le = __builtin_fma((double)(count_le - count_lt), (double)value, sum_lt);
+        now.sum_lt = before + row_sum_f64<G>(part, lane);
+        now.sum_le = __builtin_fma((double)(count_le - count_lt), (double)value, now.sum_lt);
         const uint32_t in_front = from - b.origin;
-        now.count_lt = (uint16_t)(copy_left ? left.count_lt : in_front + count_lt);
-        now.count_le = (uint16_t)(copy_left ? (ordered ? left.count_le : right.count_le) : in_front + count_le);
-        now.sum_lt = copy_left ? left.sum_lt : sum_lt;
-        now.sum_le = copy_left ? (ordered ? left.sum_le : right.sum_le) : sum_le;
+        now.count_lt = (uint16_t)(in_front + count_lt);
+        now.count_le = (uint16_t)(in_front + count_le);
+    }
+    const bool copy_left = !ordered || value < L;  // the level coincides with the left end
+    if (__ballot(copy_left) != 0) {                // (rare: nothing to select otherwise)
+        now.value = copy_left ? L : now.value;
+        picked_at = copy_left ? 0u : picked_at;
+        if constexpr (SUMS) {
+            now.count_lt = copy_left ? left.count_lt : now.count_lt;
+            now.count_le = copy_left ? (ordered ? left.count_le : right.count_le) : now.count_le;
+            now.sum_lt = copy_left ? left.sum_lt : now.sum_lt;
+            now.sum_le = copy_left ? (ordered ? left.sum_le : right.sum_le) : now.sum_le;
+        }
     }
     if (i == 0u && !same) {
         b.level[k] = now;
-        b.rank[k] = (uint16_t)(copy_left ? 0u : rank);
+        b.rank[k] = (uint16_t)picked_at;
     }
     wave_lds_sync();
 }
