@@ -91,7 +91,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         else:
             enough = 8192
         if nb >= enough:
-            return "orq_rows_kernel", 0.125 if d == 128 and nb >= 16384 else 0.25
+            return "orq_rows_kernel", 0.125 if d == 128 and nb >= (16384 if levels > 3 else 32768) else 0.25
     if d in (64, 128):
         return "even_small_kernel" if even else "sorted_small_kernel", d / 256
     if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= (8 if d <= 1024 else 5):
@@ -99,10 +99,12 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         number = (levels - 2) * (1 + wl.level_iters)
         if d <= 1024:
             enough = 513
-        elif d == capacity:
-            enough = 16 if number >= 6 else 513
+        elif d != capacity:
+            enough = 641 if number >= 12 and d > 2048 else 8193 if levels == 5 and d <= 2048 else 1281
+        elif d == 4096:
+            enough = 16 if number >= 18 else 385 if number >= 12 else 641 if levels > 5 else 769
         else:
-            enough = 513 if number >= 12 else 8193 if levels == 5 and d <= 2048 else 1281
+            enough = 385 if number >= 18 else 1025 if number >= 12 else 1281
         if nb >= enough:
             return "orq_pool_kernel", 2 if d > 2048 else 1
     if d <= 2048:

@@ -38,15 +38,17 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 
 #if OGQ_PART == 4 || OGQ_PART == 8 || OGQ_PART == 16
 // Two buckets per workgroup whose levels one wavefront solves side by side (pool_kernels.h), where the solves are what a bucket
-// waits for.  Both sides measured (Gaussian values, us; team or wavefront per bucket -> pool):
-//   18 solves (eight levels, two sweeps)   256 buckets of 2048 21.8 -> 16.1, 2048 buckets 38.3 -> 20.7, 25000 220 -> 144; of 4096
-//                                          22.9 -> 16.6, 45.5 -> 25.1, 12500: 172 -> 143; of 1344 29.4 -> 19.8 at 1300 buckets, level
-//                                          at 512; of 2112 26.3 -> 21.6, 18.0 -> 18.1 at 256; of 1024 22.0 -> 14.4 at 520 buckets
-//                                          (a single bucket is the slower one's half of a workgroup: of 2048 17.0 -> 18.6)
-//   7 solves (nine levels)                 256 buckets of 2048 11.7 -> 10.4, 25000 129 -> 103; buckets that do not fill their
-//                                          wavefronts pay for the tests: of 1344 11.6 -> 12.9 at 1024 buckets, 17.9 -> 13.6 at 1536
-//   3 solves (five levels)                 1024 buckets of 2048 10.6 -> 10.1, 25000 87.6 -> 79.7; of 1344 15.7 -> 17.1 at 3072 buckets,
-//                                          47.5 -> 44.9 at 12500; of 1024 equal
+// waits for.  What a solve takes depends on the values: the other kernels' bins suit a mixture of scales and are crowded with
+// Gaussian values, the pool's suit both.  Both sides measured (us, Gaussian values / a mixture; team or wavefront per bucket -> pool),
+// and each limit the number of buckets from which no kind of values loses more than 4 %:
+//   18 solves (eight levels, two sweeps)   256 buckets of 4096 22 -> 17 / 17.4 -> 17.3 (21 solves), 12500: 172 -> 143; of 2048 at 256
+//                                          21.8 -> 15.7 / 15.9 -> 16.5 (21), at 400 / 17.5 -> 16.5; of 1344 at 800 5 % less / 8 % more, at 1300
+//                                          34 % less / 27 % less; of 1024 at 520 35 % less / 27 % less
+//   12 solves (one sweep)                  of 4096 / 313 15.8 -> 16.5, 400 15.9 -> 14.9; of 2048 / 800 15.6 -> 16.5, 1100 17.5 -> 17.2
+//   7 solves (nine levels)                 of 4096 / 313 11.4 -> 12.3, 600 13.3 -> 13.3, 800 15.0 -> 13.8; of 2048 1100 16 % less / 12.7 ->
+//                                          12.8 (Student-t 8 % more), 1600 / 17.3 -> 13.4; of 1344 at 1300 26 % less / 21 % less
+//   3 solves (five levels)                 of 4096 / 600 10.4 -> 11.2, 800 11.9 -> 11.4; of 2048 / 1100 9.8 -> 10.3, 1600 12.2 -> 11.1; of
+//                                          1344 15.7 -> 17.1 at 3072 buckets, 47.5 -> 44.9 at 12500; of 1024 equal
 template <int W, int C>
 static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
@@ -55,9 +57,11 @@ static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, ui
     if (levels < (C == 4 ? 8u : 5u)) return false;
     const uint64_t solves = (uint64_t)(levels - 2u) * (1u + (uint64_t)p->level_iters);
     const bool exact = p->bucket_size == 256u * C * W;
+    const bool large = C * W == 16;
     const uint32_t from = C == 4 ? 513u
-                          : exact ? (solves >= 6u ? 16u : 513u)
-                                  : solves >= 12u ? 513u : levels == 5u && C * W == 8 ? 8193u : 1281u;
+                          : !exact ? (solves >= 12u && large ? 641u : levels == 5u && !large ? 8193u : 1281u)
+                          : large ? (solves >= 18u ? 16u : solves >= 12u ? 385u : levels > 5u ? 641u : 769u)
+                                  : (solves >= 18u ? 385u : solves >= 12u ? 1025u : 1281u);
     if (nb < from) return false;
     if (levels == 8u) launch_orq_pool<W, C, 8, 3>(g, n, p, nb, lv, codes, st);
     else if (levels == 9u) launch_orq_pool<W, C, 9, 4>(g, n, p, nb, lv, codes, st);
@@ -99,8 +103,9 @@ static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uin
 #if OGQ_PART == 1
     switch (d) {
         case 64: return false;  // (four buckets per wavefront already: sorted_small_kernel, even_small_kernel)
-        case 128:  // eight buckets per wavefront where that leaves two wavefronts per SIMD (ORQ-3: 12288 buckets 5.7 against 5.3 us with four)
-            return nb < 16384u ? launch_rows_levels<16, 2, true>(g, n, p, nb, lv, codes, st) : launch_rows_levels<8, 4, true>(g, n, p, nb, lv, codes, st);
+        case 128:  // eight buckets per wavefront where that leaves two wavefronts per SIMD, with three levels four (four buckets per
+                   // wavefront -> eight, us: ORQ-3 20000 buckets 7.0 -> 7.3, 32768 9.9 -> 8.9; ORQ-4 20000 9.2 -> 9.1, 24000 10.7 -> 9.4)
+            return nb < (levels > 3u ? 16384u : 32768u) ? launch_rows_levels<16, 2, true>(g, n, p, nb, lv, codes, st) : launch_rows_levels<8, 4, true>(g, n, p, nb, lv, codes, st);
         case 192: return launch_rows_levels<16, 4, false>(g, n, p, nb, lv, codes, st);
         default: return launch_rows_levels<16, 4, true>(g, n, p, nb, lv, codes, st);
     }

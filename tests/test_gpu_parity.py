@@ -857,6 +857,8 @@ def test_four_buckets_per_wavefront(scheme, bits, sweeps, d):
     *[(128, 16384 + 7, scheme, bits, sweeps) for scheme, bits, sweeps in (
         (ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 1), (ogq.ORQ_PAPER, 2, 1), (ogq.ORQ_PAPER, 3, 0), (ogq.ORQ_PAPER, 4, 2),
         (ogq.EVEN, 2, 0), (ogq.EVEN, 4, 0), (ogq.LINEAR, 2, 0), (ogq.LINEAR, 4, 0))],
+    *[(128, 32768 + 5, scheme, bits, sweeps) for scheme, bits, sweeps in (
+        (ogq.ORQ, 1, 0), (ogq.ORQ_PAPER, 2, 1), (ogq.EVEN, 2, 0), (ogq.LINEAR, 2, 0))],
     (192, 259, ogq.ORQ, 3, 3), (256, 263, ogq.ORQ, 3, 0), (256, 258, ogq.ORQ_PAPER, 4, 2), (320, 2049, ogq.ORQ, 3, 2),
     (448, 2051, ogq.ORQ_PAPER, 4, 1), (512, 2050, ogq.ORQ, 3, 1), (256, 3075, ogq.ORQ_PAPER, 3, 2), (512, 4098, ogq.ORQ, 2, 2)])
 def test_many_buckets_per_wavefront_at_their_limits(d, nb, scheme, bits, sweeps):
@@ -1036,8 +1038,8 @@ def test_unlike_buckets_of_long_gradients(scheme, bits, sweeps, d, nb):
                               buckets=checked, clip_factor=clip, tag=f"long-s{scheme}-b{bits}-d{d}-c{clip}")
 
 
-@pytest.mark.parametrize("d,nb", [(576, 514), (1024, 513), (1088, 1282), (1536, 1281), (2048, 16), (2048, 33), (2112, 515), (3968, 514),
-                                  (4096, 16), (4096, 49)])
+@pytest.mark.parametrize("d,nb", [(576, 514), (1024, 513), (1088, 1282), (1536, 1281), (2048, 16), (2048, 385), (2048, 1281), (2112, 643),
+                                  (3968, 1282), (4096, 16), (4096, 49), (4096, 641)])
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 0), (ogq.ORQ, 3, 1), (ogq.ORQ, 3, 2), (ogq.ORQ, 3, 5), (ogq.ORQ_PAPER, 3, 3),
                                                 (ogq.ORQ_PAPER, 4, 0), (ogq.ORQ_PAPER, 4, 2)])
 def test_several_buckets_per_workgroup(scheme, bits, sweeps, d, nb):
