@@ -1064,6 +1064,26 @@ def test_several_buckets_per_workgroup(scheme, bits, sweeps, d, nb):
                               clip_factor=clip, tag=f"pool-s{scheme}-b{bits}-i{sweeps}-d{d}-nb{nb}-cut{cut}")
 
 
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 4, 1), (ogq.ORQ_PAPER, 3, 2)])
+def test_levels_in_bins_beyond_the_sort(scheme, bits, sweeps):
+    """A level among 31 to 64 values of one bin, around the 32 that 8 lanes sort and the 48 that they keep in registers; distinct
+    values, equal ones, and neighbours in the wavefront with other counts."""
+    d, nb = 512, 4100
+    rng = np.random.default_rng(7 * bits + sweeps)
+    g = rng.standard_normal(nb * d).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    counts = [31, 32, 33, 40, 47, 48, 49, 50, 64]
+    for b in range(0, 90):
+        k = counts[b % len(counts)]
+        base = np.float32([0.25, -0.75, 0.01, 1.25][(b // 9) % 4])
+        step = np.float32(0.0 if b % 5 == 4 else 2.0 ** -22)
+        buckets[b, :k] = base + np.arange(k, dtype=np.float32) * step
+        if b % 2:  # the rest far away, so that the cluster holds a level
+            buckets[b, k:] = np.where(rng.random(d - k) < 0.5, -3.0, 3.0).astype(np.float32) + rng.standard_normal(d - k).astype(np.float32) * 0.1
+    parity.check_quantize(g, d, bits, scheme, sweeps, seed=17, buckets=list(range(0, 92)) + _sample(nb, 8, nb),
+                          tag=f"beyond-sort-s{scheme}-b{bits}")
+
+
 @pytest.mark.parametrize("scheme,iters", [(ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 2), (ogq.SCALED_SIGN, 0)])
 @pytest.mark.parametrize("d,nb", [(64, 33), (128, 17), (256, 9), (512, 8200), (1024, 4100), (12288, 512), (12288, 513), (16384, 513)])
 def test_bingrad_rest_and_bucket_counts(d, nb, scheme, iters):
