@@ -100,9 +100,9 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         if d <= 1024:
             enough = 513
         elif d != capacity:
-            enough = 641 if number >= 12 and d > 2048 else 8193 if levels == 5 and d <= 2048 else 1281
+            enough = 641 if number >= 12 and d > 2048 else 12289 if levels == 5 and d <= 2048 else 1281
         elif d == 4096:
-            enough = 16 if number >= 18 else 385 if number >= 12 else 641 if levels > 5 else 769
+            enough = 16 if number >= 18 else 385 if number >= 12 else 1025 if levels > 5 else 1281
         else:
             enough = 385 if number >= 18 else 1025 if number >= 12 else 1281
         if nb >= enough:

@@ -45,10 +45,10 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 //                                          21.8 -> 15.7 / 15.9 -> 16.5 (21), at 400 / 17.5 -> 16.5; of 1344 at 800 5 % less / 8 % more, at 1300
 //                                          34 % less / 27 % less; of 1024 at 520 35 % less / 27 % less
 //   12 solves (one sweep)                  of 4096 / 313 15.8 -> 16.5, 400 15.9 -> 14.9; of 2048 / 800 15.6 -> 16.5, 1100 17.5 -> 17.2
-//   7 solves (nine levels)                 of 4096 / 313 11.4 -> 12.3, 600 13.3 -> 13.3, 800 15.0 -> 13.8; of 2048 1100 16 % less / 12.7 ->
-//                                          12.8 (Student-t 8 % more), 1600 / 17.3 -> 13.4; of 1344 at 1300 26 % less / 21 % less
-//   3 solves (five levels)                 of 4096 / 600 10.4 -> 11.2, 800 11.9 -> 11.4; of 2048 / 1100 9.8 -> 10.3, 1600 12.2 -> 11.1; of
-//                                          1344 15.7 -> 17.1 at 3072 buckets, 47.5 -> 44.9 at 12500; of 1024 equal
+//   7 solves (nine levels)                 of 4096 768 15.1 -> 13.7 / 13.0 -> 13.8, 1100 18.4 -> 16.0 / 16.1 -> 16.1; of 2048 1100 14.8 -> 12.9 /
+//                                          12.5 -> 12.8, 1300 20.1 -> 12.9 / 16.3 -> 13.1; of 1344 at 1300 16.9 -> 13.1 / 15.8 -> 13.2
+//   3 solves (five levels)                 of 4096 768 12.4 -> 11.5 / 10.6 -> 11.5, 1300 16.4 -> 14.0 / 14.9 -> 13.9; of 2048 1100 / 10.0 -> 10.6,
+//                                          1300 / 11.4 -> 10.7; of 1344 8192 30.4 -> 31.8 / 30.0 -> 32.2, 12500 47.5 -> 44.9; of 1024 equal
 template <int W, int C>
 static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
@@ -59,8 +59,8 @@ static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, ui
     const bool exact = p->bucket_size == 256u * C * W;
     const bool large = C * W == 16;
     const uint32_t from = C == 4 ? 513u
-                          : !exact ? (solves >= 12u && large ? 641u : levels == 5u && !large ? 8193u : 1281u)
-                          : large ? (solves >= 18u ? 16u : solves >= 12u ? 385u : levels > 5u ? 641u : 769u)
+                          : !exact ? (solves >= 12u && large ? 641u : levels == 5u && !large ? 12289u : 1281u)
+                          : large ? (solves >= 18u ? 16u : solves >= 12u ? 385u : levels > 5u ? 1025u : 1281u)
                                   : (solves >= 18u ? 385u : solves >= 12u ? 1025u : 1281u);
     if (nb < from) return false;
     if (levels == 8u) launch_orq_pool<W, C, 8, 3>(g, n, p, nb, lv, codes, st);

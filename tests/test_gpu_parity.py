@@ -1039,7 +1039,7 @@ def test_unlike_buckets_of_long_gradients(scheme, bits, sweeps, d, nb):
 
 
 @pytest.mark.parametrize("d,nb", [(576, 514), (1024, 513), (1088, 1282), (1536, 1281), (2048, 16), (2048, 385), (2048, 1281), (2112, 643),
-                                  (3968, 1282), (4096, 16), (4096, 49), (4096, 641)])
+                                  (3968, 1282), (4096, 16), (4096, 49), (4096, 1283)])
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 0), (ogq.ORQ, 3, 1), (ogq.ORQ, 3, 2), (ogq.ORQ, 3, 5), (ogq.ORQ_PAPER, 3, 3),
                                                 (ogq.ORQ_PAPER, 4, 0), (ogq.ORQ_PAPER, 4, 2)])
 def test_several_buckets_per_workgroup(scheme, bits, sweeps, d, nb):
