@@ -106,10 +106,10 @@ __device__ __forceinline__ void philox4x32_10_uniform_c1(uint32_t c0, const Phil
 // selected among the bin's keys, one per lane (select_rank), and the counts and sums below it are added
 // to what lies before the bin.
 //
-// What bounds it: vector-instruction issue and, in the solves, a scalar chain.  Of 1,944 vector instructions per bucket of
-// 2048 at four levels the solves take 525, with 516 scalar ones in a chain of lane read, compare and scalar count;
-// SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES is 0.86, and 0.92 in a build without the solves (profiles/phase_budgets.txt:
-// 25.6 M values 51 us = load and extremes 14, grouping 11, solves 12.5, encode 14).
+// What bounds it: vector-instruction issue and, in the solves, a scalar chain.  A bucket of 2048 at four levels takes 1,918 vector
+// and 771 scalar instructions, of which the solves about 500 each, in a chain of lane read, compare and scalar count;
+// SQ_ACTIVE_INST_VALU / SQ_BUSY_CU_CYCLES is 0.85 (profiles/orq_cfg3_issue_counters_pmc.txt; 25.6 M values 51 us among other passes,
+// 57 alone).
 // ----------------------------------------------------------------------------------------------
 // Order-preserving map of fp32 onto unsigned integers.
 __device__ __forceinline__ uint32_t float_to_key(float f)

@@ -84,7 +84,8 @@ void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32
 #if OGQ_PART <= 2
 // Four buckets per wavefront, eight of 128 elements (row_kernels.h), where the gradient has enough of them: a wavefront takes
 // longer than one with a single bucket, so where it has a SIMD to itself it only adds latency, unless the solves are what takes long.
-// Measured crossover in buckets (profiles/row_kernels_scan.txt has both sides; Gaussian values, us, other kernels -> this one):
+// Measured crossover in buckets (profiles/row_kernels_scan.txt has both sides for a mixture of scales; here Gaussian values, us, other
+// kernels -> this one):
 //   eight and nine levels   of 256 and less elements always (512 buckets of 256: 9.2 -> 7.2 with nine levels), above some 2000 (4096 of
 //                           512: 16.2 -> 10.7; 1024: 8.6 -> 9.8), of 128 some 8000 (32768: 30.0 -> 18.8)
 //   four and five levels    of 256 some 3000, of 512 3000 to 4000 (8192: 17.1 -> 14.9), of 128 8000

@@ -16,8 +16,8 @@ namespace ogq {
 // 2048 elements as for 512, and in a solve all 64 lanes do one bucket's arithmetic.  Here every such instruction works for four or
 // eight buckets.  From five levels on a row of 16 lanes is two groups of 8, one for each chain of solves (group_solve.h): 4 steps
 // instead of 7 at nine levels.  Buckets of 128 take rows of 8 lanes: what a wavefront does once it does for eight of them.
-// 25.6 M values, one bucket per wavefront -> four, serial solves -> now: nine levels, buckets of 512, clipping 129 -> 78.6 -> 66.5 us; three
-// levels, buckets of 128 69 -> 43.7 -> 38.8; eight levels, two sweeps, 512: 137.6 -> 93.4 (the last two).
+// 25.6 M values, one bucket per wavefront -> four, serial solves -> now: nine levels, buckets of 512, clipping 129 -> 78.6 -> 62.5 us; three
+// levels, buckets of 128 69 -> 43.7 -> 38.7; eight levels, two sweeps, 512: 137.6 -> 93.4 (the last two).
 // The phases are those of orq_bucket: extremes, grouping in LDS by value bins (ScaledBins), fp64 prefix, level solves, encode.
 //
 // Positions and bin counts are kept in bytes (times 4), bin starts as offsets into the wavefront's values, so that the scatter
