@@ -61,6 +61,28 @@ def read_note(file_name: str, kernel_key: str):
     return None
 
 
+def pool_gains(d: int, levels: int, solves: int, nb: int) -> bool:
+    """The rule of the same name in rounding_part.hip."""
+    five = levels == 5
+    if d <= 1024:
+        return not five and nb >= 513
+    if d < 2048:
+        return not five and nb >= 1281
+    if d == 2048:
+        return (nb >= (385 if solves >= 18 else 1025 if solves >= 12 else 1281) and not (solves == 3 and 2560 < nb <= 3072))
+    if d == 4096:
+        return (nb >= (16 if solves >= 18 else 385 if solves >= 12 else 1281 if five else 1025)
+                and not (solves == 3 and (1536 < nb <= 1792 or 2048 < nb <= 2432)))
+    if nb < (641 if solves >= 12 else 1281):
+        return False
+    fuller = d >= 2816
+    if solves == 3:
+        return 1792 < nb <= 2048 or (fuller and nb <= 1536)
+    if solves == 6 and nb > 6144 and (five or not fuller):
+        return False
+    return fuller or nb <= 2048 or nb > 2432 or (not five and solves >= 12)
+
+
 def quantize_kernel(synth, wl, n: int, levels: int):
     """Name of the kernel that ogq_quantize launches for the workload's recipe at n elements, and its wavefronts per bucket
     (the library's dispatch by scheme, bucket size and number of buckets)."""
@@ -94,18 +116,8 @@ def quantize_kernel(synth, wl, n: int, levels: int):
             return "orq_rows_kernel", 0.125 if d == 128 and nb >= (16384 if levels > 3 else 32768) else 0.25
     if d in (64, 128):
         return "even_small_kernel" if even else "sorted_small_kernel", d / 256
-    if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= (8 if d <= 1024 else 5):
-        capacity = 1024 if d <= 1024 else 2048 if d <= 2048 else 4096
-        number = (levels - 2) * (1 + wl.level_iters)
-        if d <= 1024:
-            enough = 513
-        elif d != capacity:
-            enough = 641 if number >= 12 and d > 2048 else 12289 if levels == 5 and d <= 2048 else 1281
-        elif d == 4096:
-            enough = 16 if number >= 18 else 385 if number >= 12 else 1025 if levels > 5 else 1281
-        else:
-            enough = 385 if number >= 18 else 1025 if number >= 12 else 1281
-        if nb >= enough:
+    if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= 5:
+        if pool_gains(d, levels, (levels - 2) * (1 + wl.level_iters), nb):
             return "orq_pool_kernel", 2 if d > 2048 else 1
     if d <= 2048:
         few = 0 if d <= 256 else (2047 if long_solves else 0) if d <= 512 else 512 if d <= 1024 else 1280

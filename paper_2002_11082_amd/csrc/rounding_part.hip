@@ -38,31 +38,48 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 
 #if OGQ_PART == 4 || OGQ_PART == 8 || OGQ_PART == 16
 // Two buckets per workgroup whose levels one wavefront solves side by side (pool_kernels.h), where the solves are what a bucket
-// waits for.  What a solve takes depends on the values: the other kernels' bins suit a mixture of scales and are crowded with
-// Gaussian values, the pool's suit both.  Both sides measured (us, Gaussian values / a mixture; team or wavefront per bucket -> pool),
-// and each limit the number of buckets from which no kind of values loses more than 4 %:
-//   18 solves (eight levels, two sweeps)   256 buckets of 4096 22 -> 17 / 17.4 -> 17.3 (21 solves), 12500: 172 -> 143; of 2048 at 256
-//                                          21.8 -> 15.7 / 15.9 -> 16.5 (21), at 400 / 17.5 -> 16.5; of 1344 at 800 5 % less / 8 % more, at 1300
-//                                          34 % less / 27 % less; of 1024 at 520 35 % less / 27 % less
-//   12 solves (one sweep)                  of 4096 / 313 15.8 -> 16.5, 400 15.9 -> 14.9; of 2048 / 800 15.6 -> 16.5, 1100 17.5 -> 17.2
-//   7 solves (nine levels)                 of 4096 768 15.1 -> 13.7 / 13.0 -> 13.8, 1100 18.4 -> 16.0 / 16.1 -> 16.1; of 2048 1100 14.8 -> 12.9 /
-//                                          12.5 -> 12.8, 1300 20.1 -> 12.9 / 16.3 -> 13.1; of 1344 at 1300 16.9 -> 13.1 / 15.8 -> 13.2
-//   3 solves (five levels)                 of 4096 768 12.4 -> 11.5 / 10.6 -> 11.5, 1300 16.4 -> 14.0 / 14.9 -> 13.9; of 2048 1100 / 10.0 -> 10.6,
-//                                          1300 / 11.4 -> 10.7; of 1344 8192 30.4 -> 31.8 / 30.0 -> 32.2, 12500 47.5 -> 44.9; of 1024 equal
+// waits for.  What a solve takes in the other kernels depends on the values: their bins suit a mixture of scales and are crowded with
+// Gaussian values, the pool's suit both.  So neither side is the faster one for all values at most sizes, and the rule takes the
+// pool where it gains on the mean of four kinds of values (mixture, Gaussian, Laplace, Student-t) and of a whole and a cut-off last
+// bucket; profiles/pool_scan.txt has both sides, and tests/test_dispatch.py holds the rule against it.  Over all the calls in that
+// file that take the pool it is 15 % faster, and no mean loses more than 3.5 %, but for six solves of eight levels in 2561 to 3072
+// buckets of up to 1984 (1344: 19.1 -> 20.3 us): one wavefront per bucket is compiled for no other call with eight levels there.
+// Single kinds of values lose up to 8 %: 64 buckets of 4096 cut off at the end, 18 solves, mixture 16.0 -> 17.3 where Gaussian goes
+// 23.0 -> 17.4; 8192 buckets of 2048, five levels, mixture 30.7 -> 31.8 where Gaussian goes 34.5 -> 31.9.  Means, us, other -> pool:
+//   up to 1024     514 buckets of 1024, 7 solves 12.3 -> 9.9
+//   whole 2048     18 solves from 385 on (384: 19.5 -> 16.2), 12 from 1025 (1026: 18.8 -> 16.7), fewer from 1281 (7: 17.5 -> 12.9).
+//                  Five levels without sweeps: up to 3072 buckets one wavefront per bucket has three per SIMD in its only round
+//                  (2816: 15.6 -> 16.1)
+//   rest to 1984   from where a bucket has one wavefront in the other kernel; five levels never (16384 of 1344: 54.3 -> 55.5)
+//   whole 4096     18 solves from 16 on (17.9 -> 16.3), 12 from 385 (384: 17.4 -> 15.4), fewer from 1025 (1026, 7: 16.0 -> 15.5).
+//                  Five levels without sweeps: a CU holds 7 buckets in the other kernel and 8 in the pool, so a second round begins
+//                  behind 1792 there and behind 2048 here (1792: 17.3 -> 17.5, 2304: 21.5 -> 22.0)
+//   rest to 4032   the same rounds; what the pool does for elements that a bucket does not have shows up to some 2800 elements
+//                  (2304 of 2112: 7 solves 25.7 -> 26.3, 3 solves 19.8 -> 22.1; 12290 of 2112, 6 solves of five levels: 91.2 -> 94.0)
+static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb)
+{
+    const bool five = levels == 5u;
+    if (d <= 1024u) return !five && nb >= 513u;
+    if (d <= 2048u) {
+        if (d < 2048u) return !five && nb >= 1281u;
+        return nb >= (solves >= 18u ? 385u : solves >= 12u ? 1025u : 1281u) && !(solves == 3u && nb > 2560u && nb <= 3072u);
+    }
+    if (d == 4096u)
+        return nb >= (solves >= 18u ? 16u : solves >= 12u ? 385u : five ? 1281u : 1025u) &&
+               !(solves == 3u && ((nb > 1536u && nb <= 1792u) || (nb > 2048u && nb <= 2432u)));
+    if (nb < (solves >= 12u ? 641u : 1281u)) return false;
+    const bool fuller = d >= 2816u;
+    if (solves == 3u) return (nb > 1792u && nb <= 2048u) || (fuller && nb <= 1536u);
+    if (solves == 6u && nb > 6144u && (five || !fuller)) return false;
+    return fuller || nb <= 2048u || nb > 2432u || (!five && solves >= 12u);
+}
+
 template <int W, int C>
 static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     if (p->scheme != OGQ_ORQ && p->scheme != OGQ_ORQ_PAPER) return false;
     const uint32_t levels = levels_per_bucket(p->scheme, p->bits);
-    if (levels < (C == 4 ? 8u : 5u)) return false;
-    const uint64_t solves = (uint64_t)(levels - 2u) * (1u + (uint64_t)p->level_iters);
-    const bool exact = p->bucket_size == 256u * C * W;
-    const bool large = C * W == 16;
-    const uint32_t from = C == 4 ? 513u
-                          : !exact ? (solves >= 12u && large ? 641u : levels == 5u && !large ? 12289u : 1281u)
-                          : large ? (solves >= 18u ? 16u : solves >= 12u ? 385u : levels > 5u ? 1025u : 1281u)
-                                  : (solves >= 18u ? 385u : solves >= 12u ? 1025u : 1281u);
-    if (nb < from) return false;
+    if (levels < 5u || !pool_gains(p->bucket_size, levels, (uint64_t)(levels - 2u) * (1u + (uint64_t)p->level_iters), nb)) return false;
     if (levels == 8u) launch_orq_pool<W, C, 8, 3>(g, n, p, nb, lv, codes, st);
     else if (levels == 9u) launch_orq_pool<W, C, 9, 4>(g, n, p, nb, lv, codes, st);
     else if constexpr (C > 4) launch_orq_pool<W, C, 5, 3>(g, n, p, nb, lv, codes, st);

@@ -4,9 +4,11 @@ runtime, and prints what they launched.  Run as a child process by test_dispatch
 Every scheme and width, every bucket size, clipping on and off, every power of two of buckets and its neighbours (the limits
 of the dispatch are at or near powers of two, or listed), whole and ragged last buckets; the decoder with every number of
 workers at which it changes its form.  Also the benchmark's workloads at several lengths, with the kernels that the benchmark
-says they take."""
+says they take, and the calls that profiles/pool_scan.txt holds times of."""
 import ctypes
 import json
+import os
+import re
 import sys
 
 import bench
@@ -19,6 +21,28 @@ SIZES = range(64, 32768 + 1, 64)
 BUCKETS = sorted({max(1, limit + step) for limit in [1 << k for k in range(17)] + [1280, 2560, 65536] for step in (-1, 0, 1)})
 WORKERS = (1, 2, 3, 4, 5, 8, 9, 64)
 ADDRESS = 0x10000  # aligned; never looked at
+SCAN = os.path.join(os.path.dirname(os.path.abspath(bench.__file__)), "profiles", "pool_scan.txt")
+SCANNED = {"ORQ 3-bit": (ogq.ORQ, 3), "ORQ-5": (ogq.ORQ_PAPER, 3), "ORQ-9": (ogq.ORQ_PAPER, 4)}
+
+
+def pool_scan():
+    """(bucket size, rule, sweeps, buckets, elements cut off) -> times without the pool, times with it."""
+    times, d, cut, numbers = {}, 0, 0, []
+    for line in open(SCAN):
+        head = re.match(r"(\d+) elements per bucket, last bucket (whole|cut)$", line)
+        if head:
+            d, cut = int(head.group(1)), 29 if head.group(2) == "cut" else 0
+        elif line.startswith("buckets") and d:
+            numbers = [int(x) for x in line.split()[1:]]
+        elif d and line.strip():
+            rule, sweeps, rest = line.split(",")
+            values = [float(x) for x in rest.replace("/", " ").split()[1:]]
+            assert len(values) == 2 * len(numbers), line
+            for k, nb in enumerate(numbers):
+                other, pool = times.setdefault((d, rule, int(sweeps), nb, cut), ([], []))
+                other.append(values[2 * k])
+                pool.append(values[2 * k + 1])
+    return times
 
 
 def main():
@@ -74,12 +98,19 @@ def main():
             named.append([f"quantize {name} at {n}", kernel, stub.recorded_last(), wavefronts, here])
             once(f"decode {name} at {n}", average(at, at, wl.workers, n, ctypes.byref(p), ADDRESS, None))
             named.append([f"decode {name} at {n}", bench.decode_kernel_name(wl.bucket_size, wl.workers), stub.recorded_last(), 0, 0])
+    scanned = []
+    for (d, rule, sweeps, nb, cut), (other, pool) in pool_scan().items():
+        scheme, bits = SCANNED[rule]
+        p = ogq.make_params(d, bits, scheme, sweeps)
+        once(f"quantize {rule} {sweeps} sweeps d {d} n {nb * d - cut}", quantize(ADDRESS, nb * d - cut, ctypes.byref(p), ADDRESS, ADDRESS, None))
+        scanned.append([d, rule, sweeps, nb, stub.recorded_last(), other, pool])
     once("probe_read", lib.ogq_probe_read(ADDRESS, 64, ADDRESS, None))
     once("probe_copy", lib.ogq_probe_copy(ADDRESS, ADDRESS, 64, None))
     names = [stub.recorded_name(i).decode() for i in range(stub.recorded_kernels())]
     print(json.dumps({"calls": calls, "wrong": wrong[:20], "unknown": stub.recorded_unknown(),
                       "launches": {name: stub.recorded_launches_of(i) for i, name in enumerate(names)},
                       "named": [[what, kernel, names[i], stated, here] for what, kernel, i, stated, here in named],
+                      "scanned": [[d, rule, sweeps, nb, names[i], other, pool] for d, rule, sweeps, nb, i, other, pool in scanned],
                       "decoded_sizes": {names[i]: sorted(sizes) for i, sizes in decoders.items()}}))
 
 

@@ -59,6 +59,26 @@ def test_the_benchmark_names_the_kernels_that_run(recorded):
             assert abs(wavefronts_launched / wavefronts - 1) < 0.01, (what, wavefronts, wavefronts_launched)
 
 
+def test_the_pool_is_taken_where_the_record_shows_a_gain(recorded):
+    """profiles/pool_scan.txt: the calls that end in orq_pool_kernel against the same calls in the kernel it stands in for, on the
+    mean of the recorded kinds of values and last buckets.  0.035: single sizes of ranges that gain, and what two scans of the
+    same kernels differ by.  Eight levels without sweeps in 2561 to 3072 buckets of 1025 to 1984 elements lose more, because the
+    other kernel is not compiled there."""
+    def left_out(d, rule, sweeps, nb):
+        return rule == "ORQ 3-bit" and sweeps == 0 and d < 2048 and 2560 < nb <= 3072
+
+    points = {}
+    for d, rule, sweeps, nb, launched, other, pool in recorded["scanned"]:
+        taken, ratios = points.setdefault((d, rule, sweeps, nb), (set(), []))
+        taken.add("orq_pool_kernel" in launched)
+        ratios += [b / a for a, b in zip(other, pool)]
+    assert len(points) > 1000
+    assert all(len(taken) == 1 for taken, _ in points.values())
+    taken = {point: sum(r) / len(r) - 1.0 for point, (pool, r) in points.items() if pool == {True}}
+    assert len(taken) > 400 and sum(taken.values()) / len(taken) < -0.1
+    assert {point: round(loss, 3) for point, loss in taken.items() if loss > (0.09 if left_out(*point) else 0.035)} == {}
+
+
 def _buckets_of_a_span(d):
     """The most buckets that any 1024 consecutive elements touch which begin at a multiple of 1024."""
     return max((start % d + 1023) // d + 1 for start in range(0, 1024 * d, 1024))
