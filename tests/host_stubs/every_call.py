@@ -1,15 +1,17 @@
 """Test infrastructure: makes the calls below on the built library, with record_launches.cpp preloaded in place of the HIP
 runtime, and prints what they launched.  Run as a child process by test_dispatch.py; argument: the stand-in's path.
 
-Every scheme and width, every bucket size, clipping on and off, every power of two of buckets and its neighbours (the limits
-of the dispatch are at or near powers of two, or listed), whole and ragged last buckets; the decoder with every number of
-workers at which it changes its form.  Also the benchmark's workloads at several lengths, with the kernels that the benchmark
-says they take, and the calls that profiles/pool_scan.txt holds times of."""
+Every scheme and width, every bucket size, clipping on and off, every power of two and every number of the dispatch in
+rounding_part.hip as number of buckets, with its neighbours, whole and ragged last buckets, sweeps where the dispatch looks at them,
+each with the kernel that the benchmark names for it; the decoder with every number of workers at which it changes its form.
+Also the benchmark's workloads at several lengths, with the kernels that the benchmark says they take, and the calls that
+profiles/pool_scan.txt holds times of."""
 import ctypes
 import json
 import os
 import re
 import sys
+import types
 
 import bench
 import paper_2002_11082_amd as ogq
@@ -18,10 +20,13 @@ from paper_2002_11082_amd import synth
 SCHEMES = ((ogq.BINGRAD_B, (1,)), (ogq.ORQ, (1, 2, 3)), (ogq.BINGRAD_PB, (1,)), (ogq.ORQ_PAPER, (2, 3, 4)), (ogq.SCALED_SIGN, (1,)),
            (ogq.EVEN, (2, 3, 4)), (ogq.LINEAR, (2, 3, 4)))
 SIZES = range(64, 32768 + 1, 64)
-BUCKETS = sorted({max(1, limit + step) for limit in [1 << k for k in range(17)] + [1280, 2560, 65536] for step in (-1, 0, 1)})
+ROOT = os.path.dirname(os.path.abspath(bench.__file__))
+DISPATCH = re.sub("//.*", "", open(os.path.join(ROOT, "paper_2002_11082_amd", "csrc", "rounding_part.hip")).read())
+LIMITS = {int(x) for x in re.findall(r"\b(\d+)u\b", DISPATCH)} | {1 << k for k in range(17)}
+BUCKETS = sorted({max(1, limit + step) for limit in LIMITS for step in (-1, 0, 1)})
 WORKERS = (1, 2, 3, 4, 5, 8, 9, 64)
 ADDRESS = 0x10000  # aligned; never looked at
-SCAN = os.path.join(os.path.dirname(os.path.abspath(bench.__file__)), "profiles", "pool_scan.txt")
+SCAN = os.path.join(ROOT, "profiles", "pool_scan.txt")
 SCANNED = {"ORQ 3-bit": (ogq.ORQ, 3), "ORQ-5": (ogq.ORQ_PAPER, 3), "ORQ-9": (ogq.ORQ_PAPER, 4)}
 
 
@@ -65,17 +70,25 @@ def main():
             wrong.append([what, status, now - seen])
         seen = now
 
-    calls = 0
+    bases = [re.search(r"3ogq\d+([a-z_]+)", stub.recorded_name(i).decode()).group(1) for i in range(stub.recorded_kernels())]
+    calls, misnamed = 0, []
     for scheme, widths in SCHEMES:
         for bits in widths:
             for d in SIZES:
-                for clip in (0.0, 2.5):
-                    p = ogq.make_params(d, bits, scheme, 0, 0, 0, clip)
+                for clip, sweeps in ((0.0, 0), (2.5, 0), (0.0, 1), (0.0, 2)):
+                    if sweeps and scheme not in (ogq.BINGRAD_B, ogq.ORQ, ogq.ORQ_PAPER):
+                        continue
+                    p = ogq.make_params(d, bits, scheme, sweeps, 0, 0, clip)
                     by = ctypes.byref(p)
+                    levels = ogq.ogq_levels_per_bucket(p)
+                    wl = types.SimpleNamespace(bucket_size=d, scheme=scheme, clip_factor=clip, level_iters=sweeps)
                     for nb in BUCKETS:
                         for n in (nb * d, nb * d - 1):
-                            once(f"quantize scheme {scheme} bits {bits} d {d} n {n} clip {clip}",
-                                 quantize(ADDRESS, n, by, ADDRESS, ADDRESS, None))
+                            what = f"quantize scheme {scheme} bits {bits} d {d} n {n} clip {clip} sweeps {sweeps}"
+                            once(what, quantize(ADDRESS, n, by, ADDRESS, ADDRESS, None))
+                            named = bench.quantize_kernel(synth, wl, n, levels)[0]
+                            if named != bases[stub.recorded_last()]:
+                                misnamed.append([what, named, bases[stub.recorded_last()]])
                             calls += 1
     pointers = (ctypes.c_void_p * 64)(*[ADDRESS] * 64)
     at = ctypes.addressof(pointers)
@@ -107,7 +120,7 @@ def main():
     once("probe_read", lib.ogq_probe_read(ADDRESS, 64, ADDRESS, None))
     once("probe_copy", lib.ogq_probe_copy(ADDRESS, ADDRESS, 64, None))
     names = [stub.recorded_name(i).decode() for i in range(stub.recorded_kernels())]
-    print(json.dumps({"calls": calls, "wrong": wrong[:20], "unknown": stub.recorded_unknown(),
+    print(json.dumps({"calls": calls, "wrong": wrong[:20], "misnamed": misnamed[:20], "unknown": stub.recorded_unknown(),
                       "launches": {name: stub.recorded_launches_of(i) for i, name in enumerate(names)},
                       "named": [[what, kernel, names[i], stated, here] for what, kernel, i, stated, here in named],
                       "scanned": [[d, rule, sweeps, nb, names[i], other, pool] for d, rule, sweeps, nb, i, other, pool in scanned],

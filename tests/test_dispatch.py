@@ -59,6 +59,11 @@ def test_the_benchmark_names_the_kernels_that_run(recorded):
             assert abs(wavefronts_launched / wavefronts - 1) < 0.01, (what, wavefronts, wavefronts_launched)
 
 
+def test_the_benchmark_repeats_the_dispatch(recorded):
+    """bench.py names the kernel of a call from limits of its own: the same as the library's, on both sides of each."""
+    assert recorded["misnamed"] == []
+
+
 def test_the_pool_is_taken_where_the_record_shows_a_gain(recorded):
     """profiles/pool_scan.txt: the calls that end in orq_pool_kernel against the same calls in the kernel it stands in for, on the
     mean of the recorded kinds of values and last buckets.  0.035: single sizes of ranges that gain, and what two scans of the
