@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 import sys
+import types
 
 import pytest
 
@@ -62,6 +63,25 @@ def test_the_benchmark_names_the_kernels_that_run(recorded):
 def test_the_benchmark_repeats_the_dispatch(recorded):
     """bench.py names the kernel of a call from limits of its own: the same as the library's, on both sides of each."""
     assert recorded["misnamed"] == []
+
+
+def test_the_listed_limits_are_those_of_the_dispatch():
+    """limits.py against the limits that bench.py repeats (which the test above holds against the library)."""
+    import bench
+    import paper_2002_11082_amd as ogq
+    from paper_2002_11082_amd import synth
+    from tests import limits
+    dispatch = re.sub("//.*", "", open(os.path.join(ROOT, "paper_2002_11082_amd", "csrc", "rounding_part.hip")).read())
+    numbers = sorted({max(1, int(x) + step) for x in re.findall(r"\b(\d+)u\b", dispatch) for step in (-1, 0)})
+    for d, stated in limits.CHANGES.items():
+        found = {}
+        for name, (scheme, bits, sweeps) in limits.RULES.items():
+            wl = types.SimpleNamespace(bucket_size=d, scheme=scheme, clip_factor=0.0, level_iters=sweeps)
+            levels = ogq.ogq_levels_per_bucket(ogq.make_params(d, bits, scheme))
+            for nb in numbers:
+                if bench.quantize_kernel(synth, wl, nb * d, levels) != bench.quantize_kernel(synth, wl, (nb + 1) * d, levels):
+                    found.setdefault(nb, []).append(name)
+        assert found == {limit: limits.rules(names) for limit, names in stated.items()}, d
 
 
 def test_the_pool_is_taken_where_the_record_shows_a_gain(recorded):

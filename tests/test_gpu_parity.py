@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2002_11082_amd as ogq
 from paper_2002_11082_amd import synth
-from tests import parity
+from tests import limits, parity
 
 pytestmark = pytest.mark.gpu
 
@@ -984,7 +984,7 @@ def test_three_levels_in_many_large_buckets(scheme, d):
                               clip_factor=clip, tag=f"gather-s{scheme}-d{d}-c{clip}")
 
 
-@pytest.mark.parametrize("d,limit", [(448, 2560), (512, 2560), (960, 512), (1024, 512), (2048, 1280), (1984, 1280), (4096, 4096),
+@pytest.mark.parametrize("d,limit", [(448, 4095), (512, 8191), (960, 512), (1024, 512), (2048, 1280), (1984, 1280), (4096, 4096),
                                      (8192, 256), (8128, 256), (16384, 0), (20480, 0)])
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0),
                                                 (ogq.ORQ_PAPER, 4, 0), (ogq.BINGRAD_PB, 1, 0), (ogq.LINEAR, 3, 0),
@@ -997,12 +997,30 @@ def test_few_and_many_buckets(scheme, bits, sweeps, d, limit):
                               tag=f"count-s{scheme}-b{bits}-d{d}-nb{nb}", clip_factor=2.5 if nb == limit else 0.0)
 
 
+@pytest.mark.parametrize("d,limit", [(d, limit) for d, changes in limits.CHANGES.items() for limit in changes])
+def test_both_sides_of_every_limit(d, limit):
+    """The last number of buckets that one kernel takes and the first of the next one, with every rule that changes there: unlike
+    neighbours at both ends of the gradient, a cut-off last bucket."""
+    rng = np.random.default_rng(d + limit)
+    kinds = ["heavy", "const", "ints", "normal", "zeros", "shifted"]
+    nb = limit + 1
+    g = _rng_bucket(rng, nb * d, "heavy")
+    buckets = g.reshape(nb, d)
+    for b in [*range(min(6, nb)), *range(max(0, nb - 8), nb)]:
+        buckets[b] = _rng_bucket(rng, d, kinds[b % len(kinds)])
+    for name in limits.rules(limits.CHANGES[d][limit]):
+        scheme, bits, sweeps = limits.RULES[name]
+        for count in (limit, limit + 1):
+            checked = sorted({*range(min(7, count)), *range(max(0, count - 9), count)})
+            parity.check_quantize(g[: count * d - 29], d, bits, scheme, sweeps, seed=41, buckets=checked, tag=f"limit-{name}-d{d}-nb{count}")
+
+
 @pytest.mark.parametrize("d,nb", [(448, 2600), (512, 2600), (704, 600), (1024, 600), (1472, 1400), (2048, 1400), (3008, 4200), (4096, 4200)])
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0), (ogq.ORQ_PAPER, 3, 1),
                                                 (ogq.ORQ_PAPER, 4, 0), (ogq.BINGRAD_PB, 1, 0), (ogq.LINEAR, 3, 0), (ogq.EVEN, 2, 0)])
 def test_unlike_buckets_of_long_gradients(scheme, bits, sweeps, d, nb):
     """The tests above with special values take a few buckets, which several wavefronts share; here there are enough that
-    each has one wavefront (two or four above 2048 elements): constant, crowded, sparse, sorted and tiny buckets, T exactly an
+    each has one wavefront (two or four above 2048 elements), or with many solves two share the one that solves: constant, crowded, sparse, sorted and tiny buckets, T exactly an
     integer, NaN and infinities in some, Philox blocks that pass 2^32, a cut-off last bucket."""
     rng = np.random.default_rng(d + 1000 * bits + scheme)
     g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
