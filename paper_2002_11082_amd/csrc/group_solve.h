@@ -1,5 +1,5 @@
 // Internal header of libogq: level solves of several buckets side by side in one wavefront, each by its own group of lanes.
-// Included by the kernels that group whole buckets in LDS (pool_kernels.h).  Compile with -ffp-contract=off.
+// Included by the kernels that hold several grouped buckets in LDS: row_kernels.h and pool_kernels.h.  Compile with -ffp-contract=off.
 #ifndef OGQ_GROUP_SOLVE_H
 #define OGQ_GROUP_SOLVE_H
 

@@ -9,9 +9,9 @@
 namespace ogq {
 
 // ----------------------------------------------------------------------------------------------
-// NB buckets per workgroup, W wavefronts each, wavefront w of a bucket holding its elements [256 C w, 256 C (w + 1)) in the register
+// Two buckets per workgroup, W wavefronts each, wavefront w of a bucket holding its elements [256 C w, 256 C (w + 1)) in the register
 // layout of orq_bucket.  The phases are those of orq_team_kernel: load, extremes, grouping in LDS, fp64 prefix, level solves,
-// encode; but one wavefront of the workgroup solves the levels of all NB buckets side by side, a row of 16 lanes for each of a
+// encode; but one wavefront of the workgroup solves the levels of both side by side, a row of 16 lanes for each of a
 // bucket's two chains of solves (group_solve.h).
 //
 // A solve is some 200 vector instructions on values that are the same for the whole bucket, in one chain of LDS reads and
@@ -24,8 +24,12 @@ namespace ogq {
 // The solving wavefront runs at a raised priority (its instructions go first on its SIMD): 30,000 -> 25,000 cycles of solves.
 // Four buckets per workgroup, in rows of 8 lanes, were slower (418 us): fewer workgroups overlap.
 // ----------------------------------------------------------------------------------------------
+constexpr int kPoolBuckets = 2;  // per workgroup
+constexpr int kPoolChains = 2;   // of solves per bucket, a row of 16 lanes each
+
 template <int W, int C, int S>
 struct alignas(16) PoolBucket {
+    static_assert(S > 4, "the two chains of solves begin with Algorithm 1's second level");
     static constexpr int D = 256 * C * W;                      // element capacity
     static constexpr int B = D / 4, HALF = B / 2;              // bins
     static constexpr int BLOCK = 4 * C;                        // positions per entry of the fp64 prefix: one lane's
@@ -46,8 +50,7 @@ struct alignas(16) PoolBucket {
 
 template <int W, int C, int S>
 struct PoolLds {
-    static constexpr int CHAINS = S > 4 ? 2 : 1, NB = 4 / CHAINS;
-    PoolBucket<W, C, S> bucket[NB];
+    PoolBucket<W, C, S> bucket[kPoolBuckets];
     unsigned long long exact_limb[kExactLimbs];
 };
 
@@ -59,7 +62,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     static_assert(W == 1 || W == 2, "the bin starts of a second wavefront follow from its own total");
     using Bucket = PoolBucket<W, C, S>;
     constexpr uint32_t PER_WAVE = 256u * C, B = Bucket::B, HALF = Bucket::HALF, BLOCK = Bucket::BLOCK;
-    constexpr int CHAINS = PoolLds<W, C, S>::CHAINS, NB = PoolLds<W, C, S>::NB;
+    constexpr int NB = kPoolBuckets;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = uniform_u32(threadIdx.x >> 6);
     const uint32_t slot_of = wave / (uint32_t)W, part = wave % (uint32_t)W;  // bucket of the workgroup, wavefront of the bucket
@@ -194,7 +197,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         char* grouped = reinterpret_cast<char*>(my.grouped);
         // (a start is half as wide as a counter)
         const uint32_t starts = (uint32_t)(uintptr_t)((LdsWord*)my.bin_start) - (uint32_t)(uintptr_t)((LdsWord*)my.bin_count) / 2u;
-        constexpr int GROUP = C < 4 ? C : 4;
+        constexpr int GROUP = 4;
         uint32_t here = lane;
         if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
 #pragma unroll
@@ -285,13 +288,13 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
             for (int b = 0; b < NB; ++b) lds.bucket[b].prefix[64u + lane] = before[b];
         }
         constexpr uint32_t G = 16;
-        static_assert(NB * CHAINS * G == 64, "one group per bucket and chain");
-        Bucket& b = lds.bucket[lane / (G * CHAINS)];
+        static_assert(NB * kPoolChains * G == 64, "one group per bucket and chain");
+        Bucket& b = lds.bucket[lane / (G * kPoolChains)];
         double total = b.wave_sum[0];
         if constexpr (W == 2) total += b.wave_sum[1];
         b.level[S - 1].sum_le = total;  // (the same from all lanes of the bucket)
         wave_lds_sync();
-        const uint32_t of_bucket = blockIdx.x * (uint32_t)NB + lane / (G * CHAINS);
+        const uint32_t of_bucket = blockIdx.x * (uint32_t)NB + lane / (G * kPoolChains);
         uint32_t its_len = (uint32_t)Bucket::D;
         if constexpr (!FULL) {
             const size_t at = (size_t)of_bucket * bucket_size;
@@ -309,7 +312,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                                its_len,
                                b.tiny != 0u ? sum_error_bound_of(largest, (uint32_t)Bucket::D) : 0.0,
                                its_len >= G + 4u && total == total};
-        group_solve_levels<(int)G, CHAINS, S, Bucket>(view, sweeps, lane);
+        group_solve_levels<(int)G, kPoolChains, S, Bucket>(view, sweeps, lane);
         __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();
@@ -330,14 +333,14 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 }
 
 template <int W, int C, int S, int BITS>
-__global__ __launch_bounds__((S > 4 ? 2 : 4) * W * kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 4 : 1))) void orq_pool_kernel(
+__global__ __launch_bounds__(kPoolBuckets* W* kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 4 : 1))) void orq_pool_kernel(
     const float* __restrict__ grad, size_t n, uint32_t bucket_size, uint32_t sweeps, float clip, uint32_t num_buckets, uint64_t seed,
     uint64_t index_offset, float* __restrict__ levels, uint32_t* __restrict__ codes32)
 {
     __shared__ __attribute__((aligned(16))) PoolLds<W, C, S> lds;
     static_assert(sizeof(lds) <= 65536, "an LDS address in 16 bits");
     constexpr uint32_t D = PoolBucket<W, C, S>::D;
-    if (bucket_size == D && ((size_t)blockIdx.x + 1u) * (PoolLds<W, C, S>::NB * D) <= n)
+    if (bucket_size == D && ((size_t)blockIdx.x + 1u) * (kPoolBuckets * D) <= n)
         orq_pool_group<W, C, S, BITS, true>(lds, grad, n, bucket_size, sweeps, clip, num_buckets, seed, index_offset, levels, codes32);
     else
         orq_pool_group<W, C, S, BITS, false>(lds, grad, n, bucket_size, sweeps, clip, num_buckets, seed, index_offset, levels, codes32);
@@ -349,7 +352,7 @@ __global__ __launch_bounds__((S > 4 ? 2 : 4) * W * kWave) __attribute__((amdgpu_
 template <int W, int C, int S, int BITS>
 void launch_orq_pool(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    constexpr int NB = PoolLds<W, C, S>::NB;
+    constexpr int NB = kPoolBuckets;
     launch_kernel((orq_pool_kernel<W, C, S, BITS>), dim3((nb + NB - 1) / NB), dim3(NB * W * kWave), st, g, n, p->bucket_size, p->level_iters,
                   p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
 }
