@@ -184,61 +184,87 @@ __device__ __forceinline__ GroupPicked group_pick_sorted(const char* at, uint32_
     return p;
 }
 
-// The same for a crowded bin (some group's bin holds more than fits the sort): the key is found by bisection over the bits in
-// which any group's smallest and largest key of the bin differ (none when all its values are equal).  HELD > 0: no bin holds
-// more than G * HELD elements, which are read once and kept: at eight levels one bucket of 512 in some 800 has a bin of 33 to 40 elements,
-// and its wavefront took 7 us longer with the elements read again for every bit.
-template <int G, bool SUMS, int HELD = 0>
-__device__ __forceinline__ GroupPicked group_pick_bisected(const char* at, uint32_t n, uint32_t index, uint32_t lane)
+// The same for a crowded bin (some group's bin holds more than fits the sort).  bin = the LDS address of its first element; n = 0: no
+// element is wanted.  What crowds a bin in earnest is one value that many elements share: zero in a sparse gradient, the threshold
+// in a clipped one.  So the pivots are elements: a pass over the bin counts what lies below and at the pivot, and ends the search
+// where the wanted index is among the equals, which the first pass does as often as the shared value is wanted.  Otherwise it
+// leaves a range of keys, and the next pivot is one of G elements drawn from the bin.  Where none of them lies in the range, and at every
+// fourth pass (which bounds the search whatever the elements), the range is narrowed to keys that elements have, and the pivot is its
+// middle.  Bisection over the bits of the key took some 20 passes (us, bisection -> this): eight levels, two sweeps, c = 2.5, 64 buckets of
+// 4096 of a mixture of scales 55 -> 17; half of the values zero, 25.6 M of them in buckets of 4096 2063 -> 148, in buckets of 256 (no
+// sweeps) 426 -> 118.
+template <int G, bool SUMS>
+__device__ __forceinline__ GroupPicked group_pick_crowded(uint32_t bin, uint32_t n, uint32_t index, uint32_t lane)
 {
     const uint32_t i = lane & (uint32_t)(G - 1);
-    uint32_t held[HELD > 0 ? HELD : 1];
-#pragma unroll
-    for (int k = 0; k < HELD; ++k)
-        held[k] = i + (uint32_t)(G * k) < n ? __float_as_uint(grouped_value(at + 4u * (i + (uint32_t)(G * k)))) : 0u;
-    auto each = [&](auto f) {
-        if constexpr (HELD > 0) {
-#pragma unroll
-            for (int k = 0; k < HELD; ++k)
-                if (i + (uint32_t)(G * k) < n) f(__uint_as_float(held[k]));
-        } else {
-            for (uint32_t p = i; p < n; p += (uint32_t)G) f(grouped_value(at + 4u * p));
-        }
-    };
-    uint32_t smallest = 0xFFFFFFFFu, largest = 0u;
-    each([&](float x) {
-        smallest = umin32(smallest, float_to_key(x));
-        largest = umax32(largest, float_to_key(x));
-    });
-    smallest = row_min_u32<G>(smallest, lane);
-    largest = row_max_u32<G>(largest, lane);
-    const uint32_t any = uniform_u32(wave_max_u32(smallest <= largest ? smallest ^ largest : 0u));
-    uint32_t key = smallest;
-    if (any != 0u) {
-        const int top = 31 - __builtin_clz(any);
-        key = top == 31 ? 0u : smallest & ~((2u << top) - 1u);
+    const LdsWord* at = (const LdsWord*)(uintptr_t)bin;
+    index = umin32(index, n - 1u);  // (a search beyond the bin would not end)
+    const uint32_t wanted = __float_as_uint(__uint_as_float(at[n != 0u ? index : 0u]) + 0.0f);
+    const uint32_t order = wanted >> 31 != 0u ? 0xFFFFFFFFu : 0x80000000u;  // float_to_key: a bin's elements have one sign
+    auto key_at = [&](uint32_t e) __attribute__((always_inline)) { return __float_as_uint(__uint_as_float(at[e]) + 0.0f) ^ order; };
+    auto each = [&](uint32_t end, auto f) __attribute__((always_inline)) {
+        uint32_t e = i;
 #pragma unroll 1
-        for (int bit = top; bit >= 0; --bit) {
-            const uint32_t candidate = key | (1u << bit);
-            uint32_t below = 0;
-            each([&](float x) { below += float_to_key(x) < candidate ? 1u : 0u; });
-            below = row_sum_u32<G>(below, lane);
-            if (below <= index) key = candidate;
+        for (; e + 3u * (uint32_t)G < end; e += 4u * (uint32_t)G) {
+            uint32_t key[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4u; ++k) key[k] = key_at(e + (uint32_t)G * k);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f(key[k]);
         }
-    }
-    GroupPicked p{key_to_float(key), 0u, 0u, 0.0};
-    if constexpr (SUMS) {
-        uint32_t counts = 0;
-        each([&](float x) {
-            const bool below = float_to_key(x) < key;
-            counts += (below ? 1u : 0u) + (float_to_key(x) <= key ? 0x10000u : 0u);
-            p.part += (double)(below ? x : 0.0f);
+#pragma unroll 1
+        for (; e < end; e += (uint32_t)G) f(key_at(e));
+    };
+    GroupPicked p{0.0f, 0u, 0u, 0.0};
+    uint32_t lo = 0u, hi = 0xFFFFFFFFu, pivot = wanted ^ order;
+    uint32_t rest = n;  // 0 once the element is found
+#pragma unroll 1
+    for (uint32_t step = 1;; ++step) {
+        uint32_t counts = 0u, not_above = 0u;
+        double part = 0.0;
+        each(rest, [&](uint32_t key) __attribute__((always_inline)) {
+            const bool lt = key < pivot;
+            counts += lt ? 1u : 0u;
+            not_above += key <= pivot ? 1u : 0u;
+            if constexpr (SUMS) part += (double)__uint_as_float(lt ? key ^ order : 0u);
         });
-        counts = row_sum_u32<G>(counts, lane);
-        p.count_lt = counts & 0xFFFFu;
-        p.count_le = counts >> 16;
+        counts = row_sum_u32<G>(counts | not_above << 16, lane);
+        const uint32_t below = counts & 0xFFFFu;
+        not_above = counts >> 16;
+        if (rest != 0u && below <= index && index < not_above) {
+            p = GroupPicked{__uint_as_float(pivot ^ order), below, not_above, part};
+            rest = 0u;
+        }
+        if (__ballot(rest != 0u) == 0) break;
+        if (index < below) hi = pivot - 1u;
+        else lo = pivot + 1u;
+        const uint32_t sample = key_at(__umulhi((i + (uint32_t)G * step) * 0x9E3779B1u, n));
+        const bool inside = lo <= sample && sample <= hi;
+        const uint32_t first = group_max<G>(inside ? (uint32_t)G - i : 0u);  // (the first lane whose element does)
+        const bool drawn = first != 0u && (step & 3u) != 0u;
+        pivot = group_max<G>((uint32_t)G - i == first ? sample : 0u);
+        if (__ballot(rest != 0u && !drawn) != 0) {
+            uint32_t smallest = 0xFFFFFFFFu, largest = 0u;
+            each(drawn ? 0u : rest, [&](uint32_t key) __attribute__((always_inline)) {
+                const bool in_range = lo <= key && key <= hi;
+                smallest = in_range ? umin32(smallest, key) : smallest;
+                largest = in_range ? umax32(largest, key) : largest;
+            });
+            smallest = row_min_u32<G>(smallest, lane);
+            largest = row_max_u32<G>(largest, lane);
+            lo = drawn ? lo : smallest;
+            hi = drawn ? hi : largest;
+            pivot = drawn ? pivot : lo + ((hi - lo) >> 1);
+        }
     }
     return p;
+}
+
+// Out of line for the level solves: inlined into their loops it cost solves that never need it 0.5 to 1 %.
+template <int G>
+static __device__ __attribute__((noinline)) GroupPicked group_pick_crowded_with_sums(uint32_t bin, uint32_t n, uint32_t index, uint32_t lane)
+{
+    return group_pick_crowded<G, true>(bin, n, index, lane);
 }
 
 // floor(T) of one group's bucket in exact arithmetic (see exact_floor_t), by the whole wavefront; elements = the LDS address of the
@@ -258,6 +284,14 @@ __device__ __forceinline__ uint32_t truncated_u32(double x)
     uint32_t r;
     asm("v_cvt_u32_f64_e32 %0, %1" : "=v"(r) : "v"(x));
     return r;
+}
+
+// The same value, of which the compiler does not know it: what a rare branch needs of the LDS it reads again, instead of registers
+// that hold it through the pick (the kernels have none to spare).
+__device__ __forceinline__ uint32_t read_again(uint32_t entry)
+{
+    asm("" : "+v"(entry));
+    return entry;
 }
 
 // One level solve per group of G lanes, run by a whole wavefront: level k between the levels l and r of the group's bucket (see
@@ -358,15 +392,35 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
             part += (double)(below ? own : 0.0f);
         }
     } else {
-        const uint32_t n = last - first;
+        const uint32_t n = same || !ordered ? 0u : last - first;  // (0: nothing is picked, and no other group waits for this one)
         const char* keys = b.grouped + 4u * first;
         GroupPicked p;
         if (!Shape::WINDOWED && __ballot(n > 8u) == 0) p = group_pick_sorted<G, 1, SUMS, 8>(keys, n, at - first, lane);
         else if (!Shape::WINDOWED && __ballot(n > LANES) == 0) p = group_pick_sorted<G, 1, SUMS>(keys, n, at - first, lane);
         else if (__ballot(n > 2u * LANES) == 0) p = group_pick_sorted<G, 2, SUMS>(keys, n, at - first, lane);
         else if (__ballot(n > 4u * LANES) == 0) p = group_pick_sorted<G, 4, SUMS>(keys, n, at - first, lane);
-        else if (G == 8 && __ballot(n > 6u * LANES) == 0) p = group_pick_bisected<G, SUMS, 6>(keys, n, at - first, lane);
-        else p = group_pick_bisected<G, SUMS>(keys, n, at - first, lane);
+        else {
+            // Is it one of the elements that this level, or a level beside it, has been found equal to?
+            bool equal = false;
+            if constexpr (SUMS) {
+                const uint32_t again = read_again(entry);
+#pragma unroll
+                for (uint32_t shift = 0; shift <= 8u; shift += 4u) {
+                    const uint32_t level = (again >> shift) & 15u;
+                    const GroupLevel x = b.level[level];
+                    const double rest = x.sum_lt - before;  // (not of infinities)
+                    if (b.rank[level] != 0u && x.count_lt < rank && rank <= x.count_le && rest == rest) {
+                        equal = true;
+                        p = GroupPicked{x.value, x.count_lt - (first - b.origin), x.count_le - (first - b.origin), 0.0};
+                        part = i == 0u ? rest : 0.0;
+                    }
+                }
+            }
+            const uint32_t elements = (uint32_t)(uintptr_t)(const LdsWord*)keys, search = equal ? 0u : n;
+            const GroupPicked found = SUMS ? group_pick_crowded_with_sums<G>(elements, search, at - first, lane)
+                                           : group_pick_crowded<G, false>(elements, search, at - first, lane);
+            if (!equal) p = found;
+        }
         value = p.value;
         count_lt = p.count_lt;
         count_le = p.count_le;
@@ -386,6 +440,8 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
         now.value = copy_left ? L : now.value;
         picked_at = copy_left ? 0u : picked_at;
         if constexpr (SUMS) {
+            const uint32_t again = read_again(entry);
+            const GroupLevel left = b.level[(again >> 4) & 15u], right = b.level[again >> 8];
             now.count_lt = copy_left ? left.count_lt : now.count_lt;
             now.count_le = copy_left ? (ordered ? left.count_le : right.count_le) : now.count_le;
             now.sum_lt = copy_left ? left.sum_lt : now.sum_lt;
@@ -399,9 +455,15 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
     wave_lds_sync();
 }
 
-// The element of 0-based index `index` of every group's sorted bucket (one chain).
+// What a crowded bin has shown of a group's bucket: the elements before index `end` of the sorted bucket are at most `value`.
+struct GroupTie {
+    float value;
+    uint32_t end;
+};
+
+// The element of 0-based index `index` of every group's sorted bucket (one chain), indexes in ascending order from call to call.
 template <int G, class Shape>
-__device__ __forceinline__ float group_element(const GroupBucket& b, uint32_t index, uint32_t lane)
+__device__ __forceinline__ float group_element(const GroupBucket& b, uint32_t index, GroupTie& tie, uint32_t lane)
 {
     const uint32_t at = b.origin + index;
     const int32_t bin = signed_bin<Shape::HALF>(grouped_value(b.grouped + 4u * at), b.bins);
@@ -413,7 +475,10 @@ __device__ __forceinline__ float group_element(const GroupBucket& b, uint32_t in
     if (__ballot(n > (uint32_t)G) == 0) return group_pick_sorted<G, 1, false>(keys, n, at - first, lane).value;
     if (__ballot(n > 2u * (uint32_t)G) == 0) return group_pick_sorted<G, 2, false>(keys, n, at - first, lane).value;
     if (__ballot(n > 4u * (uint32_t)G) == 0) return group_pick_sorted<G, 4, false>(keys, n, at - first, lane).value;
-    return group_pick_bisected<G, false>(keys, n, at - first, lane).value;
+    const bool known = index < tie.end;  // (no element before this one is larger than it)
+    const GroupPicked p = group_pick_crowded<G, false>((uint32_t)(uintptr_t)(const LdsWord*)keys, known ? 0u : n, at - first, lane);
+    if (!known) tie = GroupTie{p.value, first - b.origin + p.count_le};
+    return tie.value;
 }
 
 // The greedy steps of a chain, 12 bits each; head: with the first solves of the first sweep in the steps that have room for them.

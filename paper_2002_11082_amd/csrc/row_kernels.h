@@ -311,9 +311,10 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         const GroupBucket view{grouped,   lds.bin_start + row * B + HALF, lds.prefix, lds.level[row], lds.rank[row], lds.exact_limb, bins,
                                row * D,   len,                            bound,      true};
         if constexpr (RULE == kLinear) {
+            GroupTie tie{0.0f, 0u};
 #pragma unroll 1
             for (uint32_t k = 1; k + 1 < (uint32_t)S; ++k) {
-                const float value = group_element<LANES, Lds>(view, k * (len - 1u) / (uint32_t)(S - 1), lane);
+                const float value = group_element<LANES, Lds>(view, k * (len - 1u) / (uint32_t)(S - 1), tie, lane);
                 if (i == 0u) lds.level[row][k].value = value;
             }
             wave_lds_sync();

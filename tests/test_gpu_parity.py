@@ -1084,8 +1084,8 @@ def test_several_buckets_per_workgroup(scheme, bits, sweeps, d, nb):
 
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 4, 1), (ogq.ORQ_PAPER, 3, 2)])
 def test_levels_in_bins_beyond_the_sort(scheme, bits, sweeps):
-    """A level among 31 to 64 values of one bin, around the 32 that 8 lanes sort and the 48 that they keep in registers; distinct
-    values, equal ones, and neighbours in the wavefront with other counts."""
+    """A level among 31 to 64 values of one bin, around the 32 that 8 lanes sort and the 64 that 16 lanes do; distinct values,
+    equal ones, and neighbours in the wavefront with other counts."""
     d, nb = 512, 4100
     rng = np.random.default_rng(7 * bits + sweeps)
     g = rng.standard_normal(nb * d).astype(np.float32)
@@ -1100,6 +1100,84 @@ def test_levels_in_bins_beyond_the_sort(scheme, bits, sweeps):
             buckets[b, k:] = np.where(rng.random(d - k) < 0.5, -3.0, 3.0).astype(np.float32) + rng.standard_normal(d - k).astype(np.float32) * 0.1
     parity.check_quantize(g, d, bits, scheme, sweeps, seed=17, buckets=list(range(0, 92)) + _sample(nb, 8, nb),
                           tag=f"beyond-sort-s{scheme}-b{bits}")
+
+
+def _crowded_bucket(rng, d, kind):
+    """Buckets of which one bin holds most elements: a value that many share, or a range of neighbouring ones."""
+    g = (rng.standard_t(3, d) * 1e-3).astype(np.float32)
+    ulps = np.arange(d, dtype=np.float32) * np.float32(2.0 ** -23)
+    if kind in (0, 1, 2):                                              # zeros (of both signs), others on both sides
+        g[rng.random(d) < (0.5, 0.8, 0.95)[kind]] = 0.0
+        g[rng.random(d) < 0.1] = -0.0
+    elif kind == 3:                                                    # one positive value among zeros, or one negative
+        g[:] = 0.0
+        g[rng.integers(d)] = rng.choice(np.array([1.0, -1.0], np.float32))
+    elif kind == 4:                                                    # zeros and a few values too small to have a bin of their own
+        g[: d - d // 8] = 0.0
+        g[d // 2: d // 2 + 5] = np.float32([1e-30, 1e-30, 2e-30, 1e-38, 3e-30])
+    elif kind in (5, 6):                                               # two shared neighbours in one bin, among others
+        at = rng.random(d) < 0.7
+        g[at] = np.float32(1.0 if kind == 5 else -1.0) * (np.float32(1.0) + rng.integers(0, 2, d)[at].astype(np.float32) * np.float32(2.0 ** -23))
+    elif kind in (7, 8):                                               # distinct neighbours in ascending and descending order
+        g = (np.float32(1.0) + ulps) * np.float32(1.0 if kind == 7 else -1.0)
+    elif kind == 9:                                                    # the same, shuffled, one of them shared by a third
+        g = np.float32(1.0) + ulps[rng.permutation(d)]
+        g[rng.random(d) < 0.3] = g[0]
+    else:                                                              # both ends shared by many, as after clipping
+        g = np.clip(g, np.float32(-4e-4), np.float32(5e-4))
+    return g
+
+
+@pytest.mark.parametrize("d,nb", [(128, 8200), (128, 32800), (192, 3100), (256, 260), (512, 2060), (512, 8200), (576, 520), (1024, 520),
+                                  (2048, 400), (2048, 1300), (3008, 700), (4096, 20), (4096, 1300), (8192, 20), (8192, 300), (20480, 5),
+                                  (32768, 260)])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 2, 2), (ogq.ORQ, 3, 0), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0), (ogq.ORQ_PAPER, 3, 1),
+                                                (ogq.ORQ_PAPER, 4, 0), (ogq.LINEAR, 2, 0), (ogq.LINEAR, 4, 0)])
+def test_crowded_bins(scheme, bits, sweeps, d, nb):
+    """Levels inside bins that hold most of a bucket, of one sign and the other, at every place among the equal elements, beside
+    neighbours in the workgroup and wavefront that have none."""
+    rng = np.random.default_rng(d + 10 * bits + sweeps)
+    g = np.tile((rng.standard_t(3, 16 * d) * 1e-3).astype(np.float32), -(-nb // 16))[: nb * d]
+    buckets = g.reshape(nb, d)
+    crowded = min(nb - 1, 44 if d <= 4096 else 22)
+    for b in range(crowded):
+        buckets[b] = _crowded_bucket(rng, d, b % 11)
+    buckets[nb - 1] = _crowded_bucket(rng, d, 1)
+    checked = sorted({*range(min(crowded + 2, nb)), nb - 2, nb - 1})
+    for cut, clip in ((0, 0.0), (29, 2.5)):
+        parity.check_quantize(g[: nb * d - cut], d, bits, scheme, sweeps, seed=83, buckets=checked, clip_factor=clip,
+                              tag=f"crowded-s{scheme}-b{bits}-i{sweeps}-d{d}-nb{nb}-c{clip}")
+
+
+@pytest.mark.parametrize("scheme,bits,sweeps,d,nb,kind,clip,most", [
+    (ogq.ORQ, 3, 0, 256, 1024, "sparse", 0.0, 3.0),  # (with a bisection of every crowded bin 7 and more)
+    (ogq.ORQ, 3, 2, 512, 4096, "sparse", 0.0, 3.0),
+    (ogq.ORQ, 3, 2, 4096, 64, "mixture", 2.5, 2.0),  # (3.2)
+])
+def test_shared_values_are_found_without_a_search(scheme, bits, sweeps, d, nb, kind, clip, most):
+    """A gradient that is half zeros, or clipped at 2.5 sigma, against one of distinct values without clipping: the time of a call is
+    of the same order."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    n = nb * d
+    dense = torch.randn(n, generator=gen, device="cuda") * torch.where(torch.rand(n, generator=gen, device="cuda") < 0.9, 1e-4, 1e-2)
+    crowded = dense * (torch.rand(n, generator=gen, device="cuda") < 0.5) if kind == "sparse" else dense
+    levels = codes = None
+    fastest = []
+    for g, c in ((dense, 0.0), (crowded, clip)):
+        p = ogq.make_params(d, bits, scheme, sweeps, 1, 0, c)
+        times = []
+        for _ in range(7):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            levels, codes = ogq.ogq_quantize(g, p, levels, codes)
+            start.record()
+            for _ in range(20):
+                ogq.ogq_quantize(g, p, levels, codes)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        fastest.append(min(times))
+    assert fastest[1] < most * fastest[0], fastest
 
 
 @pytest.mark.parametrize("scheme,iters", [(ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 2), (ogq.SCALED_SIGN, 0)])
