@@ -202,14 +202,16 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
         }
         __syncthreads();
     }
-    const uint32_t bin = uniform_u32(lds.wanted[0]), in_front = uniform_u32(lds.wanted[1]), count = uniform_u32(lds.wanted[2]);
-    const uint32_t in_bin = rank - in_front;  // 1-based
+    const uint32_t bin = uniform_u32(lds.wanted[0]), in_front = uniform_u32(lds.wanted[1]);
+    uint32_t count = uniform_u32(lds.wanted[2]), in_bin = rank - in_front;  // in_bin: 1-based
 
     // ---- collect the bin's elements: those whose bit pattern lies in [from, from + range) -----------------
+    // Zeros, which sparse gradients have thousands of, are left out: they are the first elements of their bin, and as many as the
+    // list then lacks (half of the values zero, 300 buckets of 32768: 139 -> 43 us).
     const bool negative = bin < HALF;
     const uint32_t u = negative ? HALF - 1u - bin : bin - HALF;
     const uint32_t sign = negative ? 0x80000000u : 0u;
-    const uint32_t from = sign | (u == 0u ? 0u : (t_low + u) << SHIFT);
+    const uint32_t from = sign | (u == 0u ? 1u : (t_low + u) << SHIFT);
     const uint32_t range = (u == HALF - 1u ? sign + 0x80000000u : sign | ((t_low + u + 1u) << SHIFT)) - from;
     uint32_t smallest = 0xFFFFFFFFu, largest = 0u;
     // (another zero, here and in the bisection: what an earlier pass made of the elements is made again, not kept in registers)
@@ -228,7 +230,15 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
         }
     });
     uint32_t key;
-    if (count <= 64u) {
+    if (bin == HALF) {
+        __syncthreads();
+        const uint32_t others = uniform_u32(lds.list_count), zeros = count - others;
+        count = in_bin <= zeros ? 0u : others;
+        in_bin -= zeros;
+    }
+    if (count == 0u) {
+        key = float_to_key(0.0f);
+    } else if (count <= 64u) {
         __syncthreads();
         const uint32_t mine = lane < count ? float_to_key(__uint_as_float(lds.list[lane])) : 0xFFFFFFFFu;
         uint32_t not_above;

@@ -1153,6 +1153,7 @@ def test_crowded_bins(scheme, bits, sweeps, d, nb):
     (ogq.ORQ, 3, 0, 256, 1024, "sparse", 0.0, 3.0),  # (with a bisection of every crowded bin 7 and more)
     (ogq.ORQ, 3, 2, 512, 4096, "sparse", 0.0, 3.0),
     (ogq.ORQ, 3, 2, 4096, 64, "mixture", 2.5, 2.0),  # (3.2)
+    (ogq.ORQ_PAPER, 2, 0, 32768, 300, "sparse", 0.0, 3.0),  # (5)
 ])
 def test_shared_values_are_found_without_a_search(scheme, bits, sweeps, d, nb, kind, clip, most):
     """A gradient that is half zeros, or clipped at 2.5 sigma, against one of distinct values without clipping: the time of a call is
