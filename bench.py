@@ -61,9 +61,16 @@ def read_note(file_name: str, kernel_key: str):
     return None
 
 
-def pool_gains(d: int, levels: int, solves: int, nb: int) -> bool:
+def pool_gains(d: int, levels: int, solves: int, nb: int, clipped: bool) -> bool:
     """The rule of the same name in rounding_part.hip."""
     five = levels == 5
+    if clipped and solves < 18:
+        if d == 2048 and five and solves < 12 and 2560 < nb <= 3072:
+            return False
+        if 2048 < d < 4096 and (five or solves < 12 or nb <= 1024 or 2048 < nb <= 2432):
+            return False
+        if d == 4096 and nb <= (2432 if solves < 12 else 640):
+            return False
     if d <= 1024:
         return not five and nb >= 513
     if d < 2048:
@@ -117,7 +124,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
     if d in (64, 128):
         return "even_small_kernel" if even else "sorted_small_kernel", d / 256
     if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= 5:
-        if pool_gains(d, levels, (levels - 2) * (1 + wl.level_iters), nb):
+        if pool_gains(d, levels, (levels - 2) * (1 + wl.level_iters), nb, wl.clip_factor > 0):
             return "orq_pool_kernel", 2 if d > 2048 else 1
     if d <= 2048:
         few = 0 if d <= 256 else (2047 if long_solves else 0) if d <= 512 else 512 if d <= 1024 else 1280

@@ -56,9 +56,19 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 //                  behind 1792 there and behind 2048 here (1792: 17.3 -> 17.5, 2304: 21.5 -> 22.0)
 //   rest to 4032   the same rounds; what the pool does for elements that a bucket does not have shows up to some 2800 elements
 //                  (2304 of 2112: 7 solves 25.7 -> 26.3, 3 solves 19.8 -> 22.1; 12290 of 2112, 6 solves of five levels: 91.2 -> 94.0)
-static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb)
+// With clipping, values end at a few sigma, which crowds the other kernels' bins less: the pool gains less, and fewer calls take it
+// (profiles/pool_clip_scan.txt, held against the rule likewise).  Above 2048 elements it needs 18 solves (2304 of 2112, 7 solves: 29.4 -> 32.5), or 12
+// of eight levels outside the counts at which it begins a round too many (2060 of 2560: 37.8 -> 39.9), or whole 4096 in more than 2432
+// buckets (1792, 7 solves: 23.2 -> 24.4; 4096: 47.1 -> 43.7).  Eight and nine levels in 2561 to 3072 buckets of up to 1984 lose up to 17 % (2816 of 1344, 6
+// solves: 22.2 -> 25.9), 5120 to 6144 buckets of 768 up to 10 %: see above.
+static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb, bool clipped)
 {
     const bool five = levels == 5u;
+    if (clipped && solves < 18u) {
+        if (d == 2048u && five && solves < 12u && nb > 2560u && nb <= 3072u) return false;
+        if (d > 2048u && d < 4096u && (five || solves < 12u || nb <= 1024u || (nb > 2048u && nb <= 2432u))) return false;
+        if (d == 4096u && nb <= (solves < 12u ? 2432u : 640u)) return false;
+    }
     if (d <= 1024u) return !five && nb >= 513u;
     if (d <= 2048u) {
         if (d < 2048u) return !five && nb >= 1281u;
@@ -79,7 +89,8 @@ static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, ui
 {
     if (p->scheme != OGQ_ORQ && p->scheme != OGQ_ORQ_PAPER) return false;
     const uint32_t levels = levels_per_bucket(p->scheme, p->bits);
-    if (levels < 5u || !pool_gains(p->bucket_size, levels, (uint64_t)(levels - 2u) * (1u + (uint64_t)p->level_iters), nb)) return false;
+    const uint64_t solves = (uint64_t)(levels - 2u) * (1u + (uint64_t)p->level_iters);
+    if (levels < 5u || !pool_gains(p->bucket_size, levels, solves, nb, p->clip_factor > 0.0f)) return false;
     if (levels == 8u) launch_orq_pool<W, C, 8, 3>(g, n, p, nb, lv, codes, st);
     else if (levels == 9u) launch_orq_pool<W, C, 9, 4>(g, n, p, nb, lv, codes, st);
     else if constexpr (C > 4) launch_orq_pool<W, C, 5, 3>(g, n, p, nb, lv, codes, st);

@@ -5,7 +5,7 @@ Every scheme and width, every bucket size, clipping on and off, every power of t
 rounding_part.hip as number of buckets, with its neighbours, whole and ragged last buckets, sweeps where the dispatch looks at them,
 each with the kernel that the benchmark names for it; the decoder with every number of workers at which it changes its form.
 Also the benchmark's workloads at several lengths, with the kernels that the benchmark says they take, and the calls that
-profiles/pool_scan.txt holds times of."""
+profiles/pool_scan.txt and pool_clip_scan.txt hold times of."""
 import ctypes
 import json
 import os
@@ -26,14 +26,14 @@ LIMITS = {int(x) for x in re.findall(r"\b(\d+)u\b", DISPATCH)} | {1 << k for k i
 BUCKETS = sorted({max(1, limit + step) for limit in LIMITS for step in (-1, 0, 1)})
 WORKERS = (1, 2, 3, 4, 5, 8, 9, 64)
 ADDRESS = 0x10000  # aligned; never looked at
-SCAN = os.path.join(ROOT, "profiles", "pool_scan.txt")
+SCANS = (("pool_scan.txt", 0.0), ("pool_clip_scan.txt", 2.5))
 SCANNED = {"ORQ 3-bit": (ogq.ORQ, 3), "ORQ-5": (ogq.ORQ_PAPER, 3), "ORQ-9": (ogq.ORQ_PAPER, 4)}
 
 
-def pool_scan():
+def pool_scan(name):
     """(bucket size, rule, sweeps, buckets, elements cut off) -> times without the pool, times with it."""
     times, d, cut, numbers = {}, 0, 0, []
-    for line in open(SCAN):
+    for line in open(os.path.join(ROOT, "profiles", name)):
         head = re.match(r"(\d+) elements per bucket, last bucket (whole|cut)$", line)
         if head:
             d, cut = int(head.group(1)), 29 if head.group(2) == "cut" else 0
@@ -112,18 +112,20 @@ def main():
             once(f"decode {name} at {n}", average(at, at, wl.workers, n, ctypes.byref(p), ADDRESS, None))
             named.append([f"decode {name} at {n}", bench.decode_kernel_name(wl.bucket_size, wl.workers), stub.recorded_last(), 0, 0])
     scanned = []
-    for (d, rule, sweeps, nb, cut), (other, pool) in pool_scan().items():
-        scheme, bits = SCANNED[rule]
-        p = ogq.make_params(d, bits, scheme, sweeps)
-        once(f"quantize {rule} {sweeps} sweeps d {d} n {nb * d - cut}", quantize(ADDRESS, nb * d - cut, ctypes.byref(p), ADDRESS, ADDRESS, None))
-        scanned.append([d, rule, sweeps, nb, stub.recorded_last(), other, pool])
+    for name, clip in SCANS:
+        for (d, rule, sweeps, nb, cut), (other, pool) in pool_scan(name).items():
+            scheme, bits = SCANNED[rule]
+            p = ogq.make_params(d, bits, scheme, sweeps, 0, 0, clip)
+            once(f"quantize {rule} {sweeps} sweeps d {d} n {nb * d - cut} clip {clip}",
+                 quantize(ADDRESS, nb * d - cut, ctypes.byref(p), ADDRESS, ADDRESS, None))
+            scanned.append([d, rule, sweeps, nb, clip, stub.recorded_last(), other, pool])
     once("probe_read", lib.ogq_probe_read(ADDRESS, 64, ADDRESS, None))
     once("probe_copy", lib.ogq_probe_copy(ADDRESS, ADDRESS, 64, None))
     names = [stub.recorded_name(i).decode() for i in range(stub.recorded_kernels())]
     print(json.dumps({"calls": calls, "wrong": wrong[:20], "misnamed": misnamed[:20], "unknown": stub.recorded_unknown(),
                       "launches": {name: stub.recorded_launches_of(i) for i, name in enumerate(names)},
                       "named": [[what, kernel, names[i], stated, here] for what, kernel, i, stated, here in named],
-                      "scanned": [[d, rule, sweeps, nb, names[i], other, pool] for d, rule, sweeps, nb, i, other, pool in scanned],
+                      "scanned": [[d, rule, sweeps, nb, clip, names[i], other, pool] for d, rule, sweeps, nb, clip, i, other, pool in scanned],
                       "decoded_sizes": {names[i]: sorted(sizes) for i, sizes in decoders.items()}}))
 
 
