@@ -71,6 +71,9 @@ def pool_gains(d: int, levels: int, solves: int, nb: int, clipped: bool) -> bool
             return False
         if d == 4096 and nb <= (2432 if solves < 12 else 640):
             return False
+    if (levels == 8 and solves <= (12 if clipped else 6) and 1024 < d <= (2048 if clipped and solves == 6 else 1984) and nb > 2560
+            and (nb <= 3072 or (clipped and solves == 6 and d < 2048))):
+        return False
     if d <= 1024:
         return not five and nb >= 513
     if d < 2048:

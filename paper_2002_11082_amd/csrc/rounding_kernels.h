@@ -2743,7 +2743,7 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(RULE =
 template <int C>
 constexpr bool wave_serves(int S, int rule)
 {
-    return !(rule == kOptimal && S >= 8 && C >= 2 && C <= 8);
+    return !(rule == kOptimal && S >= 8 && C >= 2 && C <= 8) || (S == 8 && C == 8);  // (eight levels: where pool_gains says)
 }
 
 template <int C, int S, int BITS, int RULE = kOptimal>

@@ -42,15 +42,15 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 // Gaussian values, the pool's suit both.  So neither side is the faster one for all values at most sizes, and the rule takes the
 // pool where it gains on the mean of four kinds of values (mixture, Gaussian, Laplace, Student-t) and of a whole and a cut-off last
 // bucket; profiles/pool_scan.txt has both sides, and tests/test_dispatch.py holds the rule against it.  Over all the calls in that
-// file that take the pool it is 15 % faster, and no mean loses more than 3.5 %, but for six solves of eight levels in 2561 to 3072
-// buckets of up to 1984 (1344: 19.1 -> 20.3 us): one wavefront per bucket is compiled for no other call with eight levels there.
+// file that take the pool it is 15 % faster, and no mean loses more than 3.5 %.
 // Single kinds of values lose up to 8 %: 64 buckets of 4096 cut off at the end, 18 solves, mixture 16.0 -> 17.3 where Gaussian goes
 // 23.0 -> 17.4; 8192 buckets of 2048, five levels, mixture 30.7 -> 31.8 where Gaussian goes 34.5 -> 31.9.  Means, us, other -> pool:
 //   up to 1024     514 buckets of 1024, 7 solves 12.3 -> 9.9
 //   whole 2048     18 solves from 385 on (384: 19.5 -> 16.2), 12 from 1025 (1026: 18.8 -> 16.7), fewer from 1281 (7: 17.5 -> 12.9).
 //                  Five levels without sweeps: up to 3072 buckets one wavefront per bucket has three per SIMD in its only round
 //                  (2816: 15.6 -> 16.1)
-//   rest to 1984   from where a bucket has one wavefront in the other kernel; five levels never (16384 of 1344: 54.3 -> 55.5)
+//   rest to 1984   from where a bucket has one wavefront in the other kernel; five levels never (16384 of 1344: 54.3 -> 55.5), eight
+//                  without sweeps not in 2561 to 3072 buckets, for the reason above (2816 of 1344: 19.1 -> 20.3)
 //   whole 4096     18 solves from 16 on (17.9 -> 16.3), 12 from 385 (384: 17.4 -> 15.4), fewer from 1025 (1026, 7: 16.0 -> 15.5).
 //                  Five levels without sweeps: a CU holds 7 buckets in the other kernel and 8 in the pool, so a second round begins
 //                  behind 1792 there and behind 2048 here (1792: 17.3 -> 17.5, 2304: 21.5 -> 22.0)
@@ -59,8 +59,9 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 // With clipping, values end at a few sigma, which crowds the other kernels' bins less: the pool gains less, and fewer calls take it
 // (profiles/pool_clip_scan.txt, held against the rule likewise).  Above 2048 elements it needs 18 solves (2304 of 2112, 7 solves: 29.4 -> 32.5), or 12
 // of eight levels outside the counts at which it begins a round too many (2060 of 2560: 37.8 -> 39.9), or whole 4096 in more than 2432
-// buckets (1792, 7 solves: 23.2 -> 24.4; 4096: 47.1 -> 43.7).  Eight and nine levels in 2561 to 3072 buckets of up to 1984 lose up to 17 % (2816 of 1344, 6
-// solves: 22.2 -> 25.9), 5120 to 6144 buckets of 768 up to 10 %: see above.
+// buckets (1792, 7 solves: 23.2 -> 24.4; 4096: 47.1 -> 43.7).  Eight levels in 2561 to 3072 buckets of 1088 to 2048 stay out (2816 of
+// 1344, 6 solves: 22.2 -> 25.9; of up to 1984 also beyond, where neither side gains: 5120 of 1344 32.2 -> 34.7).  Up to 10 % is lost where one wavefront per bucket is compiled for no other call: nine levels in those
+// counts, and eight and nine in buckets of up to 1024 (5120 of 768, 6 solves: 22.2 -> 24.2).
 static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb, bool clipped)
 {
     const bool five = levels == 5u;
@@ -69,6 +70,9 @@ static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb
         if (d > 2048u && d < 4096u && (five || solves < 12u || nb <= 1024u || (nb > 2048u && nb <= 2432u))) return false;
         if (d == 4096u && nb <= (solves < 12u ? 2432u : 640u)) return false;
     }
+    if (levels == 8u && solves <= (clipped ? 12u : 6u) && d > 1024u && d <= (clipped && solves == 6u ? 2048u : 1984u) && nb > 2560u &&
+        (nb <= 3072u || (clipped && solves == 6u && d < 2048u)))
+        return false;
     if (d <= 1024u) return !five && nb >= 513u;
     if (d <= 2048u) {
         if (d < 2048u) return !five && nb >= 1281u;

@@ -77,7 +77,6 @@ int main()
     ask_wave<2, 9, 4>();
     ask_wave<4, 8, 3>();
     ask_wave<4, 9, 4>();
-    ask_wave<8, 8, 3>();
     ask_wave<8, 9, 4>();
     printf("%d combinations without a kernel\n", asked);
     return asked == 0 || silent != 0;

@@ -87,12 +87,10 @@ def test_the_listed_limits_are_those_of_the_dispatch():
 def test_the_pool_is_taken_where_the_record_shows_a_gain(recorded):
     """profiles/pool_scan.txt and pool_clip_scan.txt: the calls that end in orq_pool_kernel against the same calls in the kernel it
     stands in for, on the mean of the recorded kinds of values and last buckets.  0.035: single sizes of ranges that gain, and what
-    two scans of the same kernels differ by.  Eight and nine levels lose more in some counts of buckets of up to 2048 elements,
-    because the other kernel is not compiled there: without sweeps and clipping in 2561 to 3072 buckets, with clipping in those and more."""
+    two scans of the same kernels differ by.  With clipping, nine levels in 2561 to 3072 buckets and eight and nine in buckets of up
+    to 1024 lose more, because the other kernel is not compiled there."""
     def most(d, rule, sweeps, nb, clip):
-        if rule == "ORQ-5" or d > 2048 or nb <= 2560:
-            return 0.035
-        return 0.18 if clip else 0.09 if rule == "ORQ 3-bit" and sweeps == 0 and d < 2048 and nb <= 3072 else 0.035
+        return 0.11 if clip and nb > 2560 and (d <= 1024 or (rule == "ORQ-9" and d < 2048 and nb <= 3072)) else 0.035
 
     points = {}
     for d, rule, sweeps, nb, clip, launched, other, pool in recorded["scanned"]:
