@@ -114,12 +114,15 @@ def quantize_kernel(synth, wl, n: int, levels: int):
     long_solves = solves and not linear and levels >= 8
     if 64 < d <= 512 and not pb:
         several = solves and not linear and levels > 3
+        two_solves = several and levels == 4 and wl.level_iters == 0
         if d > 448:
-            enough = 8192 if not several else 4096 if levels < 8 else 2048
+            enough = (16384 if even or (linear and levels == 3) else 8192 if not several else 7168 if two_solves
+                      else 4096 if levels < 8 else 2049)
         elif d > 256:
-            enough = 4096 if not several or levels < 8 else 2048
+            enough = (8192 if even and d > 320 else 7168 if d > 384 and (two_solves or (not several and levels < 9))
+                      else 2048 if several and levels >= 8 else 4096)
         elif d > 128:
-            enough = 8192 if not solves else 3072 if not several or levels < 8 else 256
+            enough = 8192 if not solves else 256 if several and levels >= 8 else 3328 if d > 192 else 3072
         else:
             enough = 8192
         if nb >= enough:
@@ -130,7 +133,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         if pool_gains(d, levels, (levels - 2) * (1 + wl.level_iters), nb, wl.clip_factor > 0):
             return "orq_pool_kernel", 2 if d > 2048 else 1
     if d <= 2048:
-        few = 0 if d <= 256 else (2047 if long_solves else 0) if d <= 512 else 512 if d <= 1024 else 1280
+        few = 0 if d <= 256 else (2048 if long_solves else 0) if d <= 512 else 512 if d <= 1024 else 1280
         return ("orq_team_kernel", 2 if d <= 512 else 4) if nb <= few else ("orq_quantize_kernel", 1)
     if d <= 4096:
         return "orq_team_kernel", 2 if pb and nb > 4096 else 4

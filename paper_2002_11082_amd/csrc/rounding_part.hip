@@ -116,22 +116,29 @@ void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32
 #if OGQ_PART <= 2
 // Four buckets per wavefront, eight of 128 elements (row_kernels.h), where the gradient has enough of them: a wavefront takes
 // longer than one with a single bucket, so where it has a SIMD to itself it only adds latency, unless the solves are what takes long.
-// Measured crossover in buckets (profiles/row_kernels_scan.txt has both sides for a mixture of scales; here Gaussian values, us, other
-// kernels -> this one):
-//   eight and nine levels   of 256 and less elements always (512 buckets of 256: 9.2 -> 7.2 with nine levels), above some 2000 (4096 of
-//                           512: 16.2 -> 10.7; 1024: 8.6 -> 9.8), of 128 some 8000 (32768: 30.0 -> 18.8)
-//   four and five levels    of 256 some 3000, of 512 3000 to 4000 (8192: 17.1 -> 14.9), of 128 8000
-//   three levels, Linear-s  of 256 3000, of 320 3000 to 4000, of 512 4000 to 8000, of 128 6000 to 8000
-//   no solves               of 256 equal, of 320 4000 (8192: 5.9 -> 4.4), of 512 8000, of 128 equal up to 16000
+// Measured crossover in buckets, on the mean of four kinds of values (profiles/row_kernels_scan.txt; here us, other kernels -> this one):
+//   eight and nine levels   of 256 and less elements always (600 buckets of 256, nine levels: 10.3 -> 9.3), above 2048 (2500 of 512,
+//                           nine: 14.5 -> 13.0; 2048, where the other kernel's wavefronts just fill the chip: 11.5 -> 12.0), of 128 8192
+//   four and five levels    of 256 some 3300 (3500, five: 8.1 -> 6.3), above 4096; four without sweeps, two solves, of 448 and 512 7168 (5120 of
+//                           512: 9.2 -> 10.2, 8192: 12.4 -> 11.3), of 128 8192
+//   three levels, Linear-s  of 192 3072, of 256 3300 (3072, Linear-3: 4.0 -> 4.3), of 320 and 384 4096, of 448 7168 (5120, Linear-3: 7.1 -> 7.8),
+//                           of 512 8192, Linear-3 some 12000 to 16000 (9216: 8.9 -> 9.7), of 128 8192
+//   no solves               of 320 4096, of 384 and 448 8192 (5120 of 448, nine levels: 5.8 -> 6.9, 8192: 7.6 -> 7.4), of 512 12000 to 16000 (9216:
+//                           8.2 -> 8.8), below 8192
 static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     const uint32_t levels = levels_per_bucket(p->scheme, p->bits), d = p->bucket_size;
     const bool optimal = (p->scheme == OGQ_ORQ || p->scheme == OGQ_ORQ_PAPER) && levels > 3u;
-    const bool solves = p->scheme != OGQ_EVEN && levels > 2u;
-    const uint32_t enough = d > 448u   ? (!optimal ? 8192u : levels < 8u ? 4096u : 2048u)
-                            : d > 256u ? (!optimal || levels < 8u ? 4096u : 2048u)
-                            : d > 128u ? (!solves ? 8192u : !optimal || levels < 8u ? 3072u : 256u)
-                                       : 8192u;
+    const bool even = p->scheme == OGQ_EVEN, solves = !even && levels > 2u;
+    const bool two_solves = optimal && levels == 4u && p->level_iters == 0u;
+    const uint32_t above_448 = even || (p->scheme == OGQ_LINEAR && levels == 3u) ? 16384u
+                               : !optimal ? 8192u
+                                          : two_solves ? 7168u : levels < 8u ? 4096u : 2049u;
+    const uint32_t above_256 = even && d > 320u ? 8192u
+                               : d > 384u && (two_solves || (!optimal && levels < 9u)) ? 7168u
+                                                                                      : optimal && levels >= 8u ? 2048u : 4096u;
+    const uint32_t above_128 = !solves ? 8192u : optimal && levels >= 8u ? 256u : d > 192u ? 3328u : 3072u;
+    const uint32_t enough = d > 448u ? above_448 : d > 256u ? above_256 : d > 128u ? above_128 : 8192u;
     if (nb < enough) return false;
 #if OGQ_PART == 1
     switch (d) {
