@@ -17,11 +17,11 @@ namespace ogq {
 // A solve is some 200 vector instructions on values that are the same for the whole bucket, in one chain of LDS reads and
 // fp64 operations.  With a wavefront's 64 lanes on one solve (orq_team_kernel), eight levels and two sweeps took 1,080 of 2,819
 // vector instructions of each wavefront and as many scalar ones, 11 steps behind workgroup barriers; here the four rows work
-// for two buckets, the steps need no barrier, and the kernel has 2,265 vector and 213 scalar instructions per wavefront.
+// for two buckets, the steps need no barrier, and the kernel has 2,266 vector and 215 scalar instructions per wavefront.
 // 143.7 M values in buckets of 4096: 421 -> 368 us; 25.6 M values in buckets of 2048: 124 -> 80.
-// Bound by the solves' latency: of a workgroup's 46,000 cycles they take 21,000, during which its other wavefronts wait, and the
-// LDS (16 KB of values per bucket of 4096) holds the buckets of four workgroups; the vector units issue 74 % of the time.
-// The solving wavefront runs at a raised priority (its instructions go first on its SIMD): 30,000 -> 25,000 cycles of solves.
+// Bound by the solves' latency: of a workgroup's 45,000 cycles they take 22,000 (profiles/phase_cycles.txt), during which its other
+// wavefronts wait, and the LDS (16 KB of values per bucket of 4096) holds the buckets of four workgroups; the vector units issue 73 % of
+// the time.  The solving wavefront runs at a raised priority: its instructions go first on its SIMD.
 // Four buckets per workgroup, in rows of 8 lanes, were slower (418 us): fewer workgroups overlap.
 // ----------------------------------------------------------------------------------------------
 constexpr int kPoolBuckets = 2;  // per workgroup

@@ -24,9 +24,11 @@ namespace ogq {
 // Few buckets: where a gradient has at most a few of them per CU, the time of a call is that of one bucket, and several
 // wavefronts per bucket shorten it (64 buckets of 2048, one wavefront and four: eight levels 21.6 -> 14.4 us, three 6.0 ->
 // 4.8); beyond, the barriers and the registers of the idle wavefronts cost more than the shorter bucket gains (4096 buckets:
-// 39.2 -> 50.0, 13.6 -> 16.2).  profiles/few_buckets_scan.txt has both sides for all rules and sizes.  Each limit is a measured
-// number of buckets up to which no rule loses more than 3 %; one number serves all rules, so those with long solves
-// would gain somewhat further (1536 buckets of 1024: eight levels 22.8 -> 19.2, where BinGrad-pb loses, 7.4 -> 8.3).
+// 39.2 -> 50.0, 13.6 -> 16.2).  profiles/few_buckets_scan.txt has both sides for all rules and sizes.  Each limit up to 2048
+// elements, and that above 4096, is a measured number of buckets up to which no rule loses more than 3 %; one number serves all rules, so some
+// would gain further (768 buckets of 1024: BinGrad-pb 5.8 -> 6.3, five levels 7.1 -> 6.9).  From 2049 to 4096 elements the other form is two
+// wavefronts, and four lose to it around 2048 buckets, where they begin a second round (2048 of 2560: ORQ-4 17.9 -> 23.2, the most of
+// any rule; from 2560 on they gain again, 27.7 -> 26.1).
 template <int W, int C>
 bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes,
                 hipStream_t st)
