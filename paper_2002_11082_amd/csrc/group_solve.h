@@ -7,12 +7,14 @@
 
 namespace ogq {
 
-// Per level: what OrqLds keeps.
-struct GroupLevel {
+// Per level: what OrqLds keeps; rank = 0: not picked by rank.
+struct alignas(16) GroupLevel {
     double sum_lt, sum_le;
     float value;
     uint16_t count_lt, count_le;
+    uint32_t rank;
 };
+static_assert(sizeof(GroupLevel) == 32, "addressed by shifts");
 
 // Bins of a bucket, HALF per sign, monotone in the value: the bin of a magnitude grows like the logarithm of
 // y = (magnitude + unit) / (largest + unit), so the bins are linear below `unit` and logarithmic above, and end at the bucket's
@@ -58,12 +60,10 @@ struct GroupBucket {
     const uint16_t* bin_start;  // byte offset of every bin's first position in `grouped`; points at the middle bin's
     const double* prefix;       // sum of the bucket's elements before every BLOCK-th position of `grouped`
     GroupLevel* level;
-    uint16_t* rank;             // per level: the rank it was picked at (0 = not picked by rank)
     unsigned long long* limb;   // workspace of exact_floor_t, the same for all groups
     ScaledBins bins;
     uint32_t origin, len;       // the bucket's first position in `grouped`, its elements
     double bound;               // sum_error_bound (floor_t_from_sums)
-    bool ordinary;              // (windows of elements, see group_solve) at least 20 elements, none of them NaN
 };
 
 __device__ __forceinline__ float grouped_value(const char* at) { return __uint_as_float(*reinterpret_cast<const uint32_t*>(at)) + 0.0f; }
@@ -269,13 +269,19 @@ static __device__ __attribute__((noinline)) GroupPicked group_pick_crowded_with_
 
 // floor(T) of one group's bucket in exact arithmetic (see exact_floor_t), by the whole wavefront; elements = the LDS address of the
 // bucket's first one.
-static __device__ __attribute__((noinline)) uint32_t exact_floor_t_group(unsigned long long* limb, uint32_t elements, uint32_t len,
-                                                                         uint32_t lane, float L, float R, uint32_t count_in,
-                                                                         uint32_t guess)
+__device__ __forceinline__ uint32_t exact_floor_t_elements(unsigned long long* limb, uint32_t elements, uint32_t len, uint32_t lane, float L,
+                                                           float R, uint32_t count_in, uint32_t guess)
 {
     return exact_floor_t(limb, lane, L, R, count_in, guess, [&](auto add) {
         for (uint32_t i = lane; i < len; i += kWave) add(__uint_as_float(((const LdsWord*)(uintptr_t)elements)[i]) + 0.0f);
     });
+}
+
+static __device__ __attribute__((noinline)) uint32_t exact_floor_t_group(unsigned long long* limb, uint32_t elements, uint32_t len,
+                                                                         uint32_t lane, float L, float R, uint32_t count_in,
+                                                                         uint32_t guess)
+{
+    return exact_floor_t_elements(limb, elements, len, lane, L, R, count_in, guess);
 }
 
 // Truncation that takes negative values and NaN to 0 (v_cvt_u32_f64 saturates; the conversion of the language does not).
@@ -297,22 +303,19 @@ __device__ __forceinline__ uint32_t read_again(uint32_t entry)
 // One level solve per group of G lanes, run by a whole wavefront: level k between the levels l and r of the group's bucket (see
 // orq_solve_one), entry = k | l << 4 | r << 8, 0 for a group with nothing to do.  SUMS = false: one interior level,
 // whose solve reads the bucket's total alone.  Shape: HALF (signed_bin), BLOCK (positions per entry of the
-// prefix), END_OF_BUCKET (the entry behind a bucket's last bin is not its end) and WINDOWED.
+// prefix), END_OF_BUCKET (the entry behind a bucket's last bin is not its end) and LEAF (a function of its own, which calls none).
 //
 // The bin of a rank needs no search: the element at that position of the grouped bucket is in it.  The element of the rank is then
-// found by sorting the bin, or (WINDOWED, G = 16) by counting: every lane counts the elements smaller than its own among 20 that
-// begin at a multiple of 4; what they hold beside the bin changes nothing, it is smaller or larger than everything in it.  Counting
-// takes a few vector instructions more than the sort of 16 keys but a shorter chain: for a wavefront that others wait for.
+// found by sorting the bin.
 template <int G, bool SUMS, class Shape>
 __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry, uint32_t lane)
 {
     constexpr uint32_t BLOCK = Shape::BLOCK, LANES = (uint32_t)G;
     static_assert(!SUMS || BLOCK % LANES == 0, "the elements in front of a bin are read G at a time");
-    static_assert(!Shape::WINDOWED || G == 16, "one element per lane");
     const uint32_t i = lane & (LANES - 1u);
     const uint32_t k = entry & 15u;
     const GroupLevel left = b.level[(entry >> 4) & 15u], right = b.level[entry >> 8];
-    const uint32_t last_rank = b.rank[k];
+    const uint32_t last_rank = b.level[k].rank;
     const float L = left.value, R = right.value;
     const bool ordered = L < R;
     // S = sum_{L<=v<=R} (v - L),  T = S / (R - L),  level = element of rank #{v<=R} - floor(T)
@@ -329,8 +332,10 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
     for (uint64_t todo = __ballot(undecided && i == 0u); todo != 0; todo &= todo - 1u) {  // (rare) one group after the other
         const uint32_t of = (uint32_t)__builtin_ctzll(todo);
         const uint32_t elements = (uint32_t)(uintptr_t)((const LdsWord*)b.grouped) + 4u * b.origin;
-        const uint32_t exact = exact_floor_t_group(b.limb, __builtin_amdgcn_readlane(elements, of), __builtin_amdgcn_readlane(b.len, of), lane, readlane_f32(L, of), readlane_f32(R, of),
-                                                   __builtin_amdgcn_readlane(count_in, of), __builtin_amdgcn_readlane(m, of));
+        const uint32_t first = __builtin_amdgcn_readlane(elements, of), len = __builtin_amdgcn_readlane(b.len, of);
+        const uint32_t in = __builtin_amdgcn_readlane(count_in, of), guess = __builtin_amdgcn_readlane(m, of);
+        const uint32_t exact = Shape::LEAF ? exact_floor_t_elements(b.limb, first, len, lane, readlane_f32(L, of), readlane_f32(R, of), in, guess)
+                                           : exact_floor_t_group(b.limb, first, len, lane, readlane_f32(L, of), readlane_f32(R, of), in, guess);
         m = lane / LANES == of / LANES ? exact : m;
     }
     const uint32_t rank = umin32(umax32(__builtin_elementwise_sub_sat((uint32_t)right.count_le, m), 1u), b.len);
@@ -342,103 +347,59 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
     const uint32_t first = (uint32_t)b.bin_start[bin] >> 2;
     uint32_t last = (uint32_t)b.bin_start[bin + 1] >> 2;
     if constexpr (Shape::END_OF_BUCKET) last = umin32(last, b.origin + b.len);
-    uint32_t from = first, window = 0u;
-    bool windowed = false;
-    if constexpr (Shape::WINDOWED) {
-        // 20 elements that end inside the bucket (origin = 0), and the 16 of them that are the lanes' own
-        const uint32_t end = __builtin_elementwise_sub_sat(b.len, LANES + 4u) & ~3u;
-        const bool at_end = (first & ~3u) > end;
-        window = at_end ? end : first & ~3u;
-        const uint32_t own_first = at_end ? end + 4u : first;
-        windowed = __ballot(last > own_first + LANES || !b.ordinary) == 0;
-        from = windowed ? own_first : first;
-    }
     double before = 0.0, part = 0.0;
     if constexpr (SUMS) {
-        // the sum of everything before `from`: the prefix of its block, and the block's positions in front of it
-        before = b.prefix[from / BLOCK];
-        const uint32_t in_front = from & (BLOCK - 1u);
-        const char* block = b.grouped + 4u * (from - in_front + i);
+        // the sum of everything before the bin: the prefix of its block, and the block's positions in front of it
+        before = b.prefix[first / BLOCK];
+        const uint32_t in_front = first & (BLOCK - 1u);
+        const char* block = b.grouped + 4u * (first - in_front + i);
 #pragma unroll
         for (uint32_t c = 0; c < BLOCK / LANES; ++c) {
             const float x = __uint_as_float(*reinterpret_cast<const uint32_t*>(block + 4u * LANES * c));
             part += (double)(i + LANES * c < in_front ? x : 0.0f);
         }
     }
-    float value;
-    uint32_t count_lt = 0, count_le = 0;  // from `from` on
-    if (Shape::WINDOWED && windowed) {
-        const float4* around = reinterpret_cast<const float4*>(b.grouped + 4u * window);
-        const float own = grouped_value(b.grouped + 4u * (from + i));
-        uint32_t smaller = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < LANES / 4u + 1u; ++q) {
-            const float4 x = around[q];
-            smaller += x.x < own ? 1u : 0u;
-            smaller += x.y < own ? 1u : 0u;
-            smaller += x.z < own ? 1u : 0u;
-            smaller += x.w < own ? 1u : 0u;
-        }
-        // the wanted element is the largest one that has at most `at - window` smaller ones
-        value = smaller <= at - window ? own : -__builtin_inff();
-        value = fmaxf(value, dpp_f32<kDppXor1>(value));
-        value = fmaxf(value, dpp_f32<kDppXor2>(value));
-        value = fmaxf(value, dpp_f32<kDppHalfMirror>(value));
-        value = fmaxf(value, dpp_f32<kDppMirror>(value));
+    GroupPicked p;
+    const uint32_t n = same || !ordered ? 0u : last - first;  // (0: nothing is picked, and no other group waits for this one)
+    const char* keys = b.grouped + 4u * first;
+    if (__ballot(n > 8u) == 0) p = group_pick_sorted<G, 1, SUMS, 8>(keys, n, at - first, lane);
+    else if (__ballot(n > LANES) == 0) p = group_pick_sorted<G, 1, SUMS>(keys, n, at - first, lane);
+    else if (__ballot(n > 2u * LANES) == 0) p = group_pick_sorted<G, 2, SUMS>(keys, n, at - first, lane);
+    else if (__ballot(n > 4u * LANES) == 0) p = group_pick_sorted<G, 4, SUMS>(keys, n, at - first, lane);
+    else {
+        // Is it one of the elements that this level, or a level beside it, has been found equal to?
+        bool equal = false;
         if constexpr (SUMS) {
-            const bool below = own < value;
-            count_lt = group_count<G>(below, lane);
-            count_le = group_count<G>(own <= value, lane);
-            part += (double)(below ? own : 0.0f);
-        }
-    } else {
-        const uint32_t n = same || !ordered ? 0u : last - first;  // (0: nothing is picked, and no other group waits for this one)
-        const char* keys = b.grouped + 4u * first;
-        GroupPicked p;
-        if (!Shape::WINDOWED && __ballot(n > 8u) == 0) p = group_pick_sorted<G, 1, SUMS, 8>(keys, n, at - first, lane);
-        else if (!Shape::WINDOWED && __ballot(n > LANES) == 0) p = group_pick_sorted<G, 1, SUMS>(keys, n, at - first, lane);
-        else if (__ballot(n > 2u * LANES) == 0) p = group_pick_sorted<G, 2, SUMS>(keys, n, at - first, lane);
-        else if (__ballot(n > 4u * LANES) == 0) p = group_pick_sorted<G, 4, SUMS>(keys, n, at - first, lane);
-        else {
-            // Is it one of the elements that this level, or a level beside it, has been found equal to?
-            bool equal = false;
-            if constexpr (SUMS) {
-                const uint32_t again = read_again(entry);
+            const uint32_t again = read_again(entry);
 #pragma unroll
-                for (uint32_t shift = 0; shift <= 8u; shift += 4u) {
-                    const uint32_t level = (again >> shift) & 15u;
-                    const GroupLevel x = b.level[level];
-                    const double rest = x.sum_lt - before;  // (not of infinities)
-                    if (b.rank[level] != 0u && x.count_lt < rank && rank <= x.count_le && rest == rest) {
-                        equal = true;
-                        p = GroupPicked{x.value, x.count_lt - (first - b.origin), x.count_le - (first - b.origin), 0.0};
-                        part = i == 0u ? rest : 0.0;
-                    }
+            for (uint32_t shift = 0; shift <= 8u; shift += 4u) {
+                const uint32_t level = (again >> shift) & 15u;
+                const GroupLevel x = b.level[level];
+                const double rest = x.sum_lt - before;  // (not of infinities)
+                if (x.rank != 0u && x.count_lt < rank && rank <= x.count_le && rest == rest) {
+                    equal = true;
+                    p = GroupPicked{x.value, x.count_lt - (first - b.origin), x.count_le - (first - b.origin), 0.0};
+                    part = i == 0u ? rest : 0.0;
                 }
             }
-            const uint32_t elements = (uint32_t)(uintptr_t)(const LdsWord*)keys, search = equal ? 0u : n;
-            const GroupPicked found = SUMS ? group_pick_crowded_with_sums<G>(elements, search, at - first, lane)
-                                           : group_pick_crowded<G, false>(elements, search, at - first, lane);
-            if (!equal) p = found;
         }
-        value = p.value;
-        count_lt = p.count_lt;
-        count_le = p.count_le;
-        part += p.part;
+        const uint32_t elements = (uint32_t)(uintptr_t)(const LdsWord*)keys, search = equal ? 0u : n;
+        const GroupPicked found = SUMS && !Shape::LEAF ? group_pick_crowded_with_sums<G>(elements, search, at - first, lane)
+                                                       : group_pick_crowded<G, SUMS>(elements, search, at - first, lane);
+        if (!equal) p = found;
     }
-    GroupLevel now{0.0, 0.0, value, 0, 0};
-    uint32_t picked_at = rank;
+    GroupLevel now{0.0, 0.0, p.value, 0, 0, rank};
     if constexpr (SUMS) {
-        now.sum_lt = before + row_sum_f64<G>(part, lane);
-        now.sum_le = __builtin_fma((double)(count_le - count_lt), (double)value, now.sum_lt);
-        const uint32_t in_front = from - b.origin;
-        now.count_lt = (uint16_t)(in_front + count_lt);
-        now.count_le = (uint16_t)(in_front + count_le);
+        now.sum_lt = before + row_sum_f64<G>(part + p.part, lane);
+        now.sum_le = __builtin_fma((double)(p.count_le - p.count_lt), (double)p.value, now.sum_lt);
+        const uint32_t in_front = first - b.origin;
+        now.count_lt = (uint16_t)(in_front + p.count_lt);
+        now.count_le = (uint16_t)(in_front + p.count_le);
     }
-    const bool copy_left = !ordered || value < L;  // the level coincides with the left end
-    if (__ballot(copy_left) != 0) {                // (rare: nothing to select otherwise)
+    const bool copy_left = !ordered || p.value < L;  // the level coincides with the left end
+    if (__ballot(copy_left) != 0) {                  // (rare: nothing to select otherwise)
         now.value = copy_left ? L : now.value;
-        picked_at = copy_left ? 0u : picked_at;
+        now.rank = copy_left ? 0u : now.rank;
         if constexpr (SUMS) {
             const uint32_t again = read_again(entry);
             const GroupLevel left = b.level[(again >> 4) & 15u], right = b.level[again >> 8];
@@ -448,11 +409,156 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
             now.sum_le = copy_left ? (ordered ? left.sum_le : right.sum_le) : now.sum_le;
         }
     }
-    if (i == 0u && !same) {
-        b.level[k] = now;
-        b.rank[k] = (uint16_t)picked_at;
-    }
+    if (i == 0u && !same) b.level[k] = now;
     wave_lds_sync();
+}
+
+// ----------------------------------------------------------------------------------------------
+// The same solve as a straight line, by groups of 16 lanes, for a wavefront that others wait for.  What bounds it is the number of its
+// instructions (one wavefront issues one in four cycles) and its branches and trips to LDS (30 to 45 and 60 cycles each), so little is
+// tested before the end.  The element is found by counting: every lane takes one of the 16 elements from the bin's first on (two of 32
+// where a bin is larger) and counts those that are smaller than its own; what they hold beyond the bin is larger than everything in it.
+// Returns false, and leaves the level alone, where that does not do for some active group: floor(T) not settled by its first guess, a
+// bin of more than 32 elements, a value that several elements share, L == R, a bucket that is not `ordinary`; the general solve then takes the
+// step.  Eight levels, two sweeps, buckets of 4096 of Student-t values: one step in 7,000 does, and a step takes 1,150 cycles, the general
+// one 2,300; both kinds of picks in one line of branches (group_solve with windows) took 2,000.
+// ----------------------------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) const double LdsDouble;
+typedef __attribute__((address_space(3))) GroupLevel LdsLevel;
+
+// A bucket in LDS as one lane of its group sees it; LDS addresses.  The bucket's first position is 0.
+struct DirectBucket {
+    uint32_t grouped, own;     // first element; the one at the lane's place in the group
+    uint32_t bin_start, prefix;
+    ScaledBins bins;
+    uint32_t last, end;        // index of the last element; 4 times that of the last 16's first one
+    uint64_t ordinary;         // lanes whose bucket has at least 32 elements and a finite sum
+    double low, high;          // a rest above `low` and further than `high` from the width settles floor(T)
+};
+
+__device__ __forceinline__ DirectBucket direct_bucket(const GroupBucket& b, bool finite, uint32_t lane)
+{
+    DirectBucket d;
+    d.grouped = (uint32_t)(uintptr_t)(const LdsWord*)b.grouped;
+    d.own = d.grouped + 4u * (lane & 15u);
+    d.bin_start = (uint32_t)(uintptr_t)(const LdsHalf*)b.bin_start;
+    d.prefix = (uint32_t)(uintptr_t)(LdsDouble*)b.prefix;
+    d.bins = b.bins;
+    d.last = b.len > 0u ? b.len - 1u : 0u;
+    d.end = b.len >= 32u ? 4u * (b.len - 16u) : 64u;
+    d.ordinary = __ballot(finite && b.len >= 32u);
+    d.low = b.bound != 0.0 ? b.bound : -0x1p-1022;  // (exact sums: 0 settles it too)
+    d.high = b.bound;
+    return d;
+}
+
+// How many of the 16 elements `other` of the row are smaller than this lane's `own` (finite values, no -0): a move across the row with
+// a subtraction, and a shift that takes the sign, for each.  In assembly because the compiler puts a wait state into every pair.  Wait
+// states: two between whatever wrote `other` and the first move.  All lanes are active.
+__device__ __forceinline__ uint32_t smaller_in_row(float other, float own)
+{
+    uint32_t signs, d0, d1;
+#define OGQ_TURN(a, b) \
+    "v_sub_f32_dpp %[d0], %[other], %[own] row_ror:" a " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_sub_f32_dpp %[d1], %[other], %[own] row_ror:" b " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_alignbit_b32 %[signs], %[signs], %[d0], 31\n\t" \
+    "v_alignbit_b32 %[signs], %[signs], %[d1], 31\n\t"
+    asm("v_sub_f32_e32 %[signs], %[other], %[own]\n\t"
+        "v_lshrrev_b32_e32 %[signs], 31, %[signs]\n\t"
+        "v_sub_f32_dpp %[d0], %[other], %[own] row_ror:15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_alignbit_b32 %[signs], %[signs], %[d0], 31\n\t"
+        OGQ_TURN("1", "2") OGQ_TURN("3", "4") OGQ_TURN("5", "6") OGQ_TURN("7", "8") OGQ_TURN("9", "10") OGQ_TURN("11", "12") OGQ_TURN("13", "14")
+        "v_bcnt_u32_b32 %[signs], %[signs], 0"
+        : [signs] "=&v"(signs), [d0] "=&v"(d0), [d1] "=&v"(d1)
+        : [other] "v"(other), [own] "v"(own));
+#undef OGQ_TURN
+    return signs;
+}
+
+// The end of a direct solve, K elements per lane: picks element `at`, whose bin begins at `first` (times 4), writes the level's record.
+template <int K, class Shape>
+__device__ __forceinline__ bool direct_pick(const DirectBucket& b, uint32_t at, uint32_t first, uint32_t level, uint64_t settled,
+                                            uint64_t active, uint32_t lane)
+{
+    constexpr uint32_t BLOCK = Shape::BLOCK, G = 16;
+    static_assert(BLOCK % G == 0 && !Shape::END_OF_BUCKET, "the elements in front of a bin are read G at a time");
+    const uint32_t i4 = 4u * (lane & (G - 1u));
+    const uint32_t from = umin32(first, b.end - (K == 2 ? 4u * G : 0u));
+    const LdsWord* mine = (const LdsWord*)(uintptr_t)(b.own + from);
+    float own[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) own[k] = __uint_as_float(mine[G * k]) + 0.0f;
+    // the sum of everything before `from`: the prefix of its block, and the block's positions in front of it
+    const uint32_t in_front = from & (4u * BLOCK - 1u);
+    const LdsWord* block = (const LdsWord*)(uintptr_t)(b.own + (from - in_front));
+    const double before = *(LdsDouble*)(uintptr_t)(b.prefix + 8u * (from / (4u * BLOCK)));
+    float front[BLOCK / G];
+#pragma unroll
+    for (uint32_t c = 0; c < BLOCK / G; ++c) front[c] = __uint_as_float(block[G * c]);
+    uint32_t bits = 0;
+    uint64_t found = 0, twice = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        uint32_t smaller = smaller_in_row(own[0], own[k]);
+        if constexpr (K == 2) smaller += smaller_in_row(own[1], own[k]);
+        const bool is_it = smaller == at - from / 4u;
+        const uint64_t lanes = __ballot(is_it) & active;
+        twice |= found & lanes;
+        found |= lanes;
+        bits |= is_it ? __float_as_uint(own[k]) : 0u;
+    }
+    bits |= dpp_u32<kDppXor1>(bits);
+    bits |= dpp_u32<kDppXor2>(bits);
+    bits |= dpp_u32<kDppHalfMirror>(bits);
+    bits |= dpp_u32<kDppMirror>(bits);
+    const float value = __uint_as_float(bits);
+    double part = 0.0;
+#pragma unroll
+    for (uint32_t c = 0; c < BLOCK / G; ++c) part += (double)(i4 + 4u * G * c < in_front ? front[c] : 0.0f);
+#pragma unroll
+    for (int k = 0; k < K; ++k) part += (double)(own[k] < value ? own[k] : 0.0f);
+    const double sum_lt = before + row_sum_f64<16>(part, lane);
+    asm volatile("" ::"v"(sum_lt));  // (what it takes is read with the elements, not behind the branch)
+
+    // one lane of every active group has found it: where several elements share a value, none or several have
+    const uint64_t firsts = active & 0x0001000100010001ull;
+    const uint64_t amiss = twice | (found & (found - firsts)) | (active & ~settled);
+    if (__builtin_expect((amiss | (uint64_t)(uint32_t)(__popcll(found) - __popcll(firsts))) != 0, 0)) return false;
+
+    LdsLevel* out = (LdsLevel*)(uintptr_t)level;  // (the same from all lanes of the group)
+    out->sum_lt = sum_lt;
+    out->sum_le = sum_lt + (double)value;
+    out->value = value;
+    out->count_lt = (uint16_t)at;
+    out->count_le = (uint16_t)(at + 1u);
+    out->rank = at + 1u;
+    wave_lds_sync();
+    return true;
+}
+
+// left, right, level: LDS addresses of the records (level: of one that nothing reads for the other groups); active: the lanes (whole
+// groups) that solve.
+template <class Shape>
+__device__ __forceinline__ bool group_solve_direct(const DirectBucket& b, uint32_t left, uint32_t right, uint32_t level, uint64_t active,
+                                                   uint32_t lane)
+{
+    const floatx2 of_left = *(const LdsPair*)(uintptr_t)(left + 16u), of_right = *(const LdsPair*)(uintptr_t)(right + 16u);
+    const double sum_in = ((const LdsLevel*)(uintptr_t)right)->sum_le - ((const LdsLevel*)(uintptr_t)left)->sum_lt;
+    const uint32_t not_above = __float_as_uint(of_right.y) >> 16;
+    const double L = (double)of_left.x, width = (double)of_right.x - L;
+    const double Ssum = __builtin_fma(-L, (double)(not_above - (__float_as_uint(of_left.y) & 0xFFFFu)), sum_in);
+    const uint32_t m = truncated_u32(Ssum * __builtin_amdgcn_rcp(width));
+    const double rest = __builtin_fma(-(double)m, width, Ssum);
+    const uint64_t settled = __ballot(rest > b.low) & __ballot(width - rest > b.high) & b.ordinary;
+    const uint32_t at = umin32(not_above - m - 1u, b.last);  // (in range whatever m is)
+    const float element = __uint_as_float(*(const LdsWord*)(uintptr_t)(b.grouped + 4u * at)) + 0.0f;
+    const LdsHalf* bin = (const LdsHalf*)(uintptr_t)(b.bin_start + 2u * (uint32_t)signed_bin<Shape::HALF>(element, b.bins));
+    const uint32_t first = bin[0], size = bin[1] - first;
+    if (__builtin_expect((__ballot(size > 64u) & active) != 0, 0)) {
+        if ((__ballot(size > 128u) & active) != 0) return false;
+        return direct_pick<2, Shape>(b, at, first, level, settled, active, lane);
+    }
+    return direct_pick<1, Shape>(b, at, first, level, settled, active, lane);
 }
 
 // What a crowded bin has shown of a group's bucket: the elements before index `end` of the sorted bucket are at most `value`.
@@ -542,6 +648,55 @@ __device__ __forceinline__ void group_solve_levels(const GroupBucket& b, uint32_
             t = 0;
             left -= pair ? 2u : 1u;
         }
+    }
+}
+
+// The same by direct solves, CHAINS groups of 16 lanes per bucket; general(entry) takes a step that they leave.
+template <int CHAINS, int S, class Shape, class General>
+__device__ __forceinline__ void group_solve_levels_direct(const GroupBucket& b, bool finite, uint32_t sweeps, uint32_t lane, General general)
+{
+    static_assert(CHAINS == 2, "");
+    constexpr uint32_t INTERIOR = S - 2, RECORD = sizeof(GroupLevel);
+    constexpr uint64_t kChain[2] = {0x0000FFFF0000FFFFull, 0xFFFF0000FFFF0000ull};  // lanes
+    const DirectBucket direct = direct_bucket(b, finite, lane);
+    const uint32_t levels = (uint32_t)(uintptr_t)(LdsLevel*)b.level;
+    const bool second = (lane & 16u) != 0u;
+    uint32_t tries = 2;  // (values that many elements share would send every step both ways)
+    constexpr TeamGreedy greedy = team_greedy<S>();
+    static_assert(greedy.steps <= 5, "12 bits per step");
+    constexpr uint64_t second_entries = packed_entries(greedy, 1, false);
+    uint64_t first_ahead = sweeps > 0u ? packed_entries(greedy, 0, true) : packed_entries(greedy, 0, false), second_ahead = second_entries;
+#pragma unroll 1
+    for (int step = 0; step < greedy.steps; ++step) {
+        const uint32_t e0 = (uint32_t)first_ahead & 0xFFFu, e1 = (uint32_t)second_ahead & 0xFFFu;
+        const uint64_t active = (e0 != 0u ? kChain[0] : 0u) | (e1 != 0u ? kChain[1] : 0u);
+        const uint32_t entry = second ? e1 : e0;
+        if (tries == 0u || !group_solve_direct<Shape>(direct, levels + RECORD * ((entry >> 4) & 15u), levels + RECORD * (entry >> 8),
+                                                      levels + RECORD * (entry != 0u ? entry & 15u : (uint32_t)S), active, lane)) {
+            general(entry);
+            if (tries > 0u) --tries;
+        }
+        first_ahead >>= 12;
+        second_ahead >>= 12;
+    }
+    const uint32_t left_of_first = levels - (second ? 2u * RECORD : 0u);
+    uint32_t t = (uint32_t)greedy.head;  // (the first pair begins behind its head start)
+#pragma unroll 1
+    for (uint32_t left = sweeps; left > 0u;) {
+        const bool pair = left > 1u;
+        const uint32_t end = INTERIOR + (pair ? 2u : 0u);
+#pragma unroll 1
+        for (; t < end; ++t) {
+            const uint64_t active = (t < INTERIOR ? kChain[0] : 0u) | (pair && t >= 2u ? kChain[1] : 0u);
+            const uint32_t at = left_of_first + RECORD * t;
+            const uint32_t to = __builtin_amdgcn_inverse_ballot_w64(active) ? at + RECORD : levels + RECORD * (uint32_t)S;
+            if (tries == 0u || !group_solve_direct<Shape>(direct, at, at + 2u * RECORD, to, active, lane)) {
+                general(__builtin_amdgcn_inverse_ballot_w64(active) ? (second ? t - 2u : t) * 0x111u + 0x201u : 0u);
+                if (tries > 0u) --tries;
+            }
+        }
+        t = 0;
+        left -= pair ? 2u : 1u;
     }
 }
 

@@ -14,15 +14,15 @@ namespace ogq {
 // encode; but one wavefront of the workgroup solves the levels of both side by side, a row of 16 lanes for each of a
 // bucket's two chains of solves (group_solve.h).
 //
-// A solve is some 200 vector instructions on values that are the same for the whole bucket, in one chain of LDS reads and
-// fp64 operations.  With a wavefront's 64 lanes on one solve (orq_team_kernel), eight levels and two sweeps took 1,080 of 2,819
-// vector instructions of each wavefront and as many scalar ones, 11 steps behind workgroup barriers; here the four rows work
-// for two buckets, the steps need no barrier, and the kernel has 2,266 vector and 215 scalar instructions per wavefront.
-// 143.7 M values in buckets of 4096: 421 -> 368 us; 25.6 M values in buckets of 2048: 124 -> 80.
-// Bound by the solves' latency: of a workgroup's 45,000 cycles they take 22,000 (profiles/phase_cycles.txt), during which its other
-// wavefronts wait, and the LDS (16 KB of values per bucket of 4096) holds the buckets of four workgroups; the vector units issue 73 % of
-// the time.  The solving wavefront runs at a raised priority: its instructions go first on its SIMD.
-// Four buckets per workgroup, in rows of 8 lanes, were slower (418 us): fewer workgroups overlap.
+// A solve is some 120 vector instructions on values that are the same for the whole bucket, in one chain of LDS reads and
+// fp64 operations.  With a wavefront's 64 lanes on one solve (orq_team_kernel), eight levels and two sweeps took 11 steps behind workgroup
+// barriers and most of a wavefront's scalar instructions; here the four rows work for two buckets and the steps need no barrier.
+// 143.7 M values in buckets of 4096, eight levels, two sweeps: 421 -> 368 us, with direct solves (group_solve_direct) and 1280 instead of 1024
+// bins, so that hardly a bin is too large for them, 310; 25.6 M values in buckets of 2048 124 -> 80 -> 69.
+// Bound by the solves' latency, during which a workgroup's other wavefronts wait, and the LDS (16 KB of values per bucket of 4096), which
+// holds the buckets of four workgroups; the vector units are busy for some 230 of the 310 us.  The solving wavefront runs at a raised
+// priority: its instructions go first on its SIMD.  Four buckets per workgroup, in rows of 8 lanes, were slower (418 us when two took 368):
+// fewer workgroups overlap.
 // ----------------------------------------------------------------------------------------------
 constexpr int kPoolBuckets = 2;  // per workgroup
 constexpr int kPoolChains = 2;   // of solves per bucket, a row of 16 lanes each
@@ -31,21 +31,28 @@ template <int W, int C, int S>
 struct alignas(16) PoolBucket {
     static_assert(S > 4, "the two chains of solves begin with Algorithm 1's second level");
     static constexpr int D = 256 * C * W;                      // element capacity
-    static constexpr int B = D / 4, HALF = B / 2;              // bins
+    static constexpr int B = C == 8 ? (W == 2 ? 5 * D / 16 : D / 4) : D / 2, HALF = B / 2;  // bins: what the LDS leaves room for
     static constexpr int BLOCK = 4 * C;                        // positions per entry of the fp64 prefix: one lane's
-    static constexpr bool END_OF_BUCKET = false, WINDOWED = true;  // (group_solve)
+    static constexpr bool END_OF_BUCKET = false, LEAF = true;  // (group_solve)
     union {
         uint32_t bin_count[B];  // bytes: 4 per element
         uint32_t grouped[D];    // fp32 bit patterns by bin
     };
     double prefix[D / BLOCK];
-    GroupLevel level[S];
+    GroupLevel level[S + 1];    // (the last one takes what is of no use)
     double wave_sum[W];
     TeamSlot slots[2][W];
     uint16_t bin_start[B + 2];  // byte offset of each bin's first position in `grouped`; [B] = end of the last bin
-    uint16_t rank[S];
     ScaledBins bins;
     uint32_t tiny;              // set where an element is too small for exact sums
+
+    // What group_solve needs of a bucket of `len` elements.
+    __device__ __forceinline__ GroupBucket view(unsigned long long* limb, uint32_t len)
+    {
+        const uint32_t largest = umax32(__float_as_uint(level[0].value) & 0x7FFFFFFFu, __float_as_uint(level[S - 1].value) & 0x7FFFFFFFu);
+        return GroupBucket{reinterpret_cast<const char*>(grouped), bin_start + HALF, prefix, level, limb, bins, 0u, len,
+                           tiny != 0u ? sum_error_bound_of(largest, (uint32_t)D) : 0.0};
+    }
 };
 
 template <int W, int C, int S>
@@ -53,6 +60,14 @@ struct PoolLds {
     PoolBucket<W, C, S> bucket[kPoolBuckets];
     unsigned long long exact_limb[kExactLimbs];
 };
+
+// A step of solves that group_solve_direct leaves (bucket, limb: LDS addresses).  Out of line: few steps take it.
+template <class Bucket>
+static __device__ __attribute__((noinline)) void pool_solve_general(uint32_t bucket, uint32_t limb, uint32_t len, uint32_t entry, uint32_t lane)
+{
+    Bucket& b = *(Bucket*)(__attribute__((address_space(3))) Bucket*)(uintptr_t)bucket;
+    group_solve<16, true, Bucket>(b.view((unsigned long long*)(__attribute__((address_space(3))) unsigned long long*)(uintptr_t)limb, len), entry, lane);
+}
 
 template <int W, int C, int S, int BITS, bool FULL>
 __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const float* __restrict__ grad, size_t n,
@@ -86,10 +101,10 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     float v[C][4];
     load_range<C, FULL>(v, g, first, len, my_len, lane);
     {
-        constexpr uint32_t ZEROS = B / (64u * W) / 4u;
-        uint4* mine = reinterpret_cast<uint4*>(my.bin_count) + ZEROS * (64u * part + lane);
+        constexpr uint32_t ZEROS = B / (64u * W) / 2u;
+        uint2* mine = reinterpret_cast<uint2*>(my.bin_count) + ZEROS * (64u * part + lane);
 #pragma unroll
-        for (uint32_t i = 0; i < ZEROS; ++i) mine[i] = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t i = 0; i < ZEROS; ++i) mine[i] = make_uint2(0u, 0u);
         if (part == 0u && lane == 0u) my.tiny = 0u;
     }
     WaveTeam<W> team{my.slots, part, 0u};
@@ -167,13 +182,14 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 
     // ---- bin starts: wavefront `part` owns the bins [part B / W, (part + 1) B / W) ---------------------------
     {
-        constexpr uint32_t PER = B / (64u * W);  // bins per lane: 8
-        const uint4* mine = reinterpret_cast<const uint4*>(my.bin_count) + PER / 4u * (64u * part + lane);
+        constexpr uint32_t PER = B / (64u * W);  // bins per lane
+        static_assert(PER % 2u == 0u, "8-byte reads");
+        const uint2* mine = reinterpret_cast<const uint2*>(my.bin_count) + PER / 2u * (64u * part + lane);
         uint32_t count[PER], total = 0;
 #pragma unroll
-        for (uint32_t q = 0; q < PER / 4u; ++q) {
-            const uint4 x = mine[q];
-            count[4 * q] = x.x; count[4 * q + 1] = x.y; count[4 * q + 2] = x.z; count[4 * q + 3] = x.w;
+        for (uint32_t q = 0; q < PER / 2u; ++q) {
+            const uint2 x = mine[q];
+            count[2 * q] = x.x; count[2 * q + 1] = x.y;
         }
 #pragma unroll
         for (uint32_t t = 0; t < PER; ++t) total += count[t];
@@ -268,8 +284,8 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
             end.value = top ? high : low;
             end.count_lt = end.count_le = (uint16_t)(top ? len : 0u);
             end.sum_lt = end.sum_le = 0.0;  // (the top level's follows below)
+            end.rank = 0u;
             my.level[lane] = end;
-            my.rank[lane] = 0u;
             my.bins = bins_of;
         }
     }
@@ -300,19 +316,12 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
             const size_t at = (size_t)of_bucket * bucket_size;
             its_len = of_bucket >= num_buckets ? 0u : n - at < bucket_size ? (uint32_t)(n - at) : bucket_size;
         }
-        const uint32_t largest = umax32(__float_as_uint(b.level[0].value) & 0x7FFFFFFFu, __float_as_uint(b.level[S - 1].value) & 0x7FFFFFFFu);
-        const GroupBucket view{reinterpret_cast<const char*>(b.grouped),
-                               b.bin_start + HALF,
-                               b.prefix,
-                               b.level,
-                               b.rank,
-                               lds.exact_limb,
-                               b.bins,
-                               0u,
-                               its_len,
-                               b.tiny != 0u ? sum_error_bound_of(largest, (uint32_t)Bucket::D) : 0.0,
-                               its_len >= G + 4u && total == total};
-        group_solve_levels<(int)G, kPoolChains, S, Bucket>(view, sweeps, lane);
+        const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) Bucket*)&b;
+        const uint32_t limb = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned long long*)lds.exact_limb;
+        group_solve_levels_direct<kPoolChains, S, Bucket>(b.view(lds.exact_limb, its_len), __builtin_fabs(total) < __builtin_inf(), sweeps, lane,
+                                                          [&](uint32_t entry) __attribute__((always_inline)) {
+                                                              pool_solve_general<Bucket>(at, limb, its_len, entry, lane);
+                                                          });
         __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();
@@ -339,6 +348,7 @@ __global__ __launch_bounds__(kPoolBuckets* W* kWave) __attribute__((amdgpu_waves
 {
     __shared__ __attribute__((aligned(16))) PoolLds<W, C, S> lds;
     static_assert(sizeof(lds) <= 65536, "an LDS address in 16 bits");
+    static_assert(C != 8 || sizeof(lds) <= (size_t)W * 20480, "16 wavefronts in a CU");
     constexpr uint32_t D = PoolBucket<W, C, S>::D;
     if (bucket_size == D && ((size_t)blockIdx.x + 1u) * (kPoolBuckets * D) <= n)
         orq_pool_group<W, C, S, BITS, true>(lds, grad, n, bucket_size, sweeps, clip, num_buckets, seed, index_offset, levels, codes32);

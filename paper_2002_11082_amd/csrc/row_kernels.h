@@ -34,7 +34,7 @@ struct alignas(16) RowLds {
     static constexpr int GROUP = LANES / CHAINS;
     static constexpr int BLOCK = D >= 512 || GROUP > 8 ? 16 : 8;  // positions per entry of the fp64 prefix
     static constexpr bool SUMS = S > 3;  // (with one interior level the solve reads the bucket's total alone)
-    static constexpr bool END_OF_BUCKET = true, WINDOWED = false;  // (group_solve)
+    static constexpr bool END_OF_BUCKET = true, LEAF = false;  // (group_solve)
     union {
         uint32_t bin_count[ROWS * B];  // bytes: 4 per element
         uint32_t grouped[ROWS * D];    // fp32 bit patterns by bin, row after row
@@ -42,7 +42,6 @@ struct alignas(16) RowLds {
     uint16_t bin_start[ROWS * B + 2];  // byte offset of each bin's first position in `grouped`
     double prefix[SUMS ? ROWS * (D / BLOCK) : 1];
     GroupLevel level[ROWS][S];
-    uint16_t rank[ROWS][S];
     unsigned long long exact_limb[kExactLimbs];
 };
 
@@ -302,14 +301,13 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
             end.value = top ? high : low;
             end.count_lt = end.count_le = (uint16_t)(top ? len : 0u);
             end.sum_lt = end.sum_le = top ? total : 0.0;
+            end.rank = 0u;
             lds.level[row][k] = end;
-            lds.rank[row][k] = 0u;
         }
         wave_lds_sync();
 
         // ---- the levels ------------------------------------------------------------------------------------
-        const GroupBucket view{grouped,   lds.bin_start + row * B + HALF, lds.prefix, lds.level[row], lds.rank[row], lds.exact_limb, bins,
-                               row * D,   len,                            bound,      true};
+        const GroupBucket view{grouped, lds.bin_start + row * B + HALF, lds.prefix, lds.level[row], lds.exact_limb, bins, row * D, len, bound};
         if constexpr (RULE == kLinear) {
             GroupTie tie{0.0f, 0u};
 #pragma unroll 1

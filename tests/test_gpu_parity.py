@@ -1102,6 +1102,29 @@ def test_levels_in_bins_beyond_the_sort(scheme, bits, sweeps):
                           tag=f"beyond-sort-s{scheme}-b{bits}")
 
 
+@pytest.mark.parametrize("d,nb", [(640, 515), (1024, 515), (2048, 387), (3008, 643), (4096, 19), (4096, 1027)])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 4, 2), (ogq.ORQ, 3, 5)])
+def test_bins_that_a_group_counts(scheme, bits, sweeps, d, nb):
+    """A level among as many values of one bin as the lanes of a group take at once (16, then 32), one less and one more: distinct, in
+    pairs and all equal, at either end of the bucket and inside; last buckets around the shortest that is counted."""
+    rng = np.random.default_rng(11 * bits + sweeps + d)
+    g = rng.standard_normal(nb * d).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    counts = [2, 15, 16, 17, 18, 31, 32, 33, 34]
+    crowded = min(nb - 1, 54)
+    for b in range(crowded):
+        k = counts[b % len(counts)]
+        base = np.float32([0.25, -0.75, 4.0, -4.0, 1.25, 1e-3][(b // 9) % 6])
+        ulps = np.arange(k) // (1, 2, k)[(b // 3) % 3]
+        if b % 2:  # the rest far away, so that the cluster holds a level
+            buckets[b] = np.where(rng.random(d) < 0.5, -3.0, 3.0).astype(np.float32) + rng.standard_normal(d).astype(np.float32) * 0.1
+        buckets[b, rng.permutation(d)[:k]] = base * (np.float32(1.0) + ulps.astype(np.float32) * np.float32(2.0 ** -21))
+    checked = list(range(crowded)) + [nb - 2, nb - 1]
+    for last in (d, 15, 31, 32, 33, 47):
+        parity.check_quantize(g[: nb * d - d + last], d, bits, scheme, sweeps, seed=19, buckets=checked,
+                              tag=f"counted-s{scheme}-b{bits}-i{sweeps}-d{d}-last{last}")
+
+
 def _crowded_bucket(rng, d, kind):
     """Buckets of which one bin holds most elements: a value that many share, or a range of neighbouring ones."""
     g = (rng.standard_t(3, d) * 1e-3).astype(np.float32)
