@@ -106,8 +106,11 @@ def quantize_kernel(synth, wl, n: int, levels: int):
             if d > 16384:
                 return "bingrad_team_kernel", 16 if clip else 8
             return "bingrad_team_kernel", 8 if clip or nb <= 512 or (d == 16384 and once) else 4
-        if wl.clip_factor == 0 and 2048 % d == 0 and d < 2048 and n >= 2048 and (d <= 256 or n // 2048 >= 2048):
-            return "bingrad_chunk_kernel", d / 2048
+        clip = wl.clip_factor > 0
+        several = {64: 10240, 128: 12288 if clip else 8192, 192: 8192, 256: 12288 if clip else 8192, 512: 8192 if clip else 6144,
+                   1024: 8192 if clip else 4096}.get(d, 5120 if d < 512 else 3072)
+        if d <= 1024 and nb >= several:
+            return "bingrad_chunk_kernel", 1 / (2048 // d)
         return "bingrad_quantize_kernel", 1
     pb, even, linear = (wl.scheme == s for s in (synth.BINGRAD_PB, synth.EVEN, synth.LINEAR))
     solves = not even and levels > 2

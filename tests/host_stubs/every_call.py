@@ -2,7 +2,7 @@
 runtime, and prints what they launched.  Run as a child process by test_dispatch.py; argument: the stand-in's path.
 
 Every scheme and width, every bucket size, clipping on and off, every power of two and every number of the dispatch in
-rounding_part.hip as number of buckets, with its neighbours, whole and ragged last buckets, sweeps where the dispatch looks at them,
+rounding_part.hip and bingrad.hip as number of buckets, with its neighbours, whole and ragged last buckets, sweeps where the dispatch looks at them,
 each with the kernel that the benchmark names for it; the decoder with every number of workers at which it changes its form.
 Also the benchmark's workloads at several lengths, with the kernels that the benchmark says they take, and the calls that
 profiles/pool_scan.txt and pool_clip_scan.txt hold times of."""
@@ -21,7 +21,9 @@ SCHEMES = ((ogq.BINGRAD_B, (1,)), (ogq.ORQ, (1, 2, 3)), (ogq.BINGRAD_PB, (1,)), 
            (ogq.EVEN, (2, 3, 4)), (ogq.LINEAR, (2, 3, 4)))
 SIZES = range(64, 32768 + 1, 64)
 ROOT = os.path.dirname(os.path.abspath(bench.__file__))
-DISPATCH = re.sub("//.*", "", open(os.path.join(ROOT, "paper_2002_11082_amd", "csrc", "rounding_part.hip")).read())
+CSRC = os.path.join(ROOT, "paper_2002_11082_amd", "csrc")
+DISPATCH = re.sub("//.*", "", open(os.path.join(CSRC, "rounding_part.hip")).read() +
+                  open(os.path.join(CSRC, "bingrad.hip")).read().partition("uint32_t several_buckets_from")[2])
 LIMITS = {int(x) for x in re.findall(r"\b(\d+)u\b", DISPATCH)} | {1 << k for k in range(17)}
 BUCKETS = sorted({max(1, limit + step) for limit in LIMITS for step in (-1, 0, 1)})
 WORKERS = (1, 2, 3, 4, 5, 8, 9, 64)

@@ -71,6 +71,25 @@ def test_bingrad_unlike_buckets_in_one_wavefront(d):
         parity.check_quantize(g, d, 1, ogq.BINGRAD_B, iters, tag=f"bingrad-unlike-d{d}-it{iters}")
 
 
+@pytest.mark.parametrize("clip", [0.0, 2.5])
+@pytest.mark.parametrize("d", range(64, 1025, 64))
+def test_bingrad_every_size_with_several_buckets_per_wavefront(d, clip):
+    """Enough buckets that several share a wavefront, at every size that does so: neighbours with nothing in common, a cut-off last
+    bucket and none, wavefronts of whole buckets and what is left of the last one."""
+    rng = np.random.default_rng(d)
+    nb = {64: 10240, 128: 12288, 192: 8192, 256: 12288, 512: 8192, 1024: 8192}.get(d, 5120 if d < 512 else 3072)
+    for nb, cut in ((nb, 0), (nb + 2 * (2048 // d) - 1, d - 1)):
+        g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32).reshape(nb, d)
+        g[::5] += 1.0
+        g[1::7] = 0.25
+        g[3::7, d // 3] = -3000.0  # upper-side sum far below the largest magnitude
+        g[4::11] = 0.0
+        g = g.reshape(-1)[:nb * d - cut]
+        sample = sorted({*range(40), *range(nb - 40, nb), *map(int, rng.integers(0, nb, 200))})
+        for scheme, iters in ((ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 3), (ogq.SCALED_SIGN, 0)):
+            parity.check_quantize(g, d, 1, scheme, iters, clip_factor=clip, buckets=sample, tag=f"several-s{scheme}-d{d}-nb{nb}-it{iters}")
+
+
 @pytest.mark.parametrize("d", [512, 1024])
 def test_bingrad_several_buckets_per_wavefront_above_four_million_elements(d):
     """Buckets of 512 and 1024 elements are packed several to a wavefront only for long gradients."""
