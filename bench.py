@@ -63,34 +63,46 @@ def read_note(file_name: str, kernel_key: str):
 
 def pool_gains(d: int, levels: int, solves: int, nb: int, clipped: bool) -> bool:
     """The rule of the same name in rounding_part.hip."""
-    five = levels == 5
-    if clipped and solves < 18:
-        if d == 2048 and five and solves < 12 and 2560 < nb <= 3072:
+    second_round = 2560 < nb <= 3072
+    if levels >= 8:
+        if solves >= 12 or d <= 1024:
+            return True
+        if not clipped:
+            return nb >= 1025
+        if nb < 1281:
             return False
-        if 2048 < d < 4096 and (five or solves < 12 or nb <= 1024 or 2048 < nb <= 2432):
+        return not (levels == 8 and d < 2048 and second_round) if d <= 2048 else d >= 2816 or nb > 2816
+    if levels == 5:
+        if solves >= 12:
+            return d <= 1024 or d >= 2048 or (nb >= 256 and not (clipped and second_round))
+        if d <= 1024:
+            if clipped:
+                return 1024 < nb <= 2560
+            return nb > 512 and (nb <= 4096 or nb > 6144) and (solves >= 6 or not second_round)
+        if d < 2048:
+            return nb > 1280 and not second_round and (not clipped or nb <= 2560)
+        if d == 2048:
+            return nb > 1280 and not second_round if clipped else nb > 1024
+        if clipped:
+            return nb > (1792 if d == 4096 else 2816)
+        if solves >= 6:
+            return nb > 640
+        return nb > 1280 and (d == 4096 or not (1536 < nb <= 1792 or 2048 < nb <= 2432))
+    if d > 2048:
+        if clipped:
+            return d == 4096 and solves >= 6 and nb > 1792
+        if solves >= 6:
+            return nb > (384 if d == 4096 else 1024)
+        return nb > 1280 if solves >= 4 and d == 4096 else 1792 < nb <= 2048
+    if solves < 4:
+        if clipped:
             return False
-        if d == 4096 and nb <= (2432 if solves < 12 else 640):
-            return False
-    if (levels == 8 and solves <= (12 if clipped else 6) and 1024 < d <= (2048 if clipped and solves == 6 else 1984) and nb > 2560
-            and (nb <= 3072 or (clipped and solves == 6 and d < 2048))):
-        return False
+        return 1536 < nb <= 5120 if d <= 1024 else 1792 < nb <= (20480 if d == 2048 else 6144)
     if d <= 1024:
-        return not five and nb >= 513
-    if d < 2048:
-        return not five and nb >= 1281
-    if d == 2048:
-        return (nb >= (385 if solves >= 18 else 1025 if solves >= 12 else 1281) and not (solves == 3 and 2560 < nb <= 3072))
-    if d == 4096:
-        return (nb >= (16 if solves >= 18 else 385 if solves >= 12 else 1281 if five else 1025)
-                and not (solves == 3 and (1536 < nb <= 1792 or 2048 < nb <= 2432)))
-    if nb < (641 if solves >= 12 else 1281):
-        return False
-    fuller = d >= 2816
-    if solves == 3:
-        return 1792 < nb <= 2048 or (fuller and nb <= 1536)
-    if solves == 6 and nb > 6144 and (five or not fuller):
-        return False
-    return fuller or nb <= 2048 or nb > 2432 or (not five and solves >= 12)
+        return nb > 512
+    if clipped and solves < 6:
+        return nb > 1536 if d == 2048 else 1280 < nb <= 5120
+    return nb > 1280
 
 
 def quantize_kernel(synth, wl, n: int, levels: int):
@@ -132,7 +144,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
             return "orq_rows_kernel", 0.125 if d == 128 and nb >= (16384 if levels > 3 else 32768) else 0.25
     if d in (64, 128):
         return "even_small_kernel" if even else "sorted_small_kernel", d / 256
-    if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= 5:
+    if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= 4:
         if pool_gains(d, levels, (levels - 2) * (1 + wl.level_iters), nb, wl.clip_factor > 0):
             return "orq_pool_kernel", 2 if d > 2048 else 1
     if d <= 2048:

@@ -651,52 +651,67 @@ __device__ __forceinline__ void group_solve_levels(const GroupBucket& b, uint32_
     }
 }
 
-// The same by direct solves, CHAINS groups of 16 lanes per bucket; general(entry) takes a step that they leave.
+// The same by direct solves, by CHAINS groups of 16 lanes per bucket; general(entry) takes a step that they leave.  With one chain several
+// groups may share a bucket: they all do the same.  A bucket without elements (behind the gradient's last one) is in no step's way.
 template <int CHAINS, int S, class Shape, class General>
 __device__ __forceinline__ void group_solve_levels_direct(const GroupBucket& b, bool finite, uint32_t sweeps, uint32_t lane, General general)
 {
-    static_assert(CHAINS == 2, "");
     constexpr uint32_t INTERIOR = S - 2, RECORD = sizeof(GroupLevel);
-    constexpr uint64_t kChain[2] = {0x0000FFFF0000FFFFull, 0xFFFF0000FFFF0000ull};  // lanes
+    constexpr uint32_t kNext = 0x111u, kFirst = 0x201u;  // (as above)
     const DirectBucket direct = direct_bucket(b, finite, lane);
+    const uint64_t some = __ballot(b.len > 0u);
     const uint32_t levels = (uint32_t)(uintptr_t)(LdsLevel*)b.level;
-    const bool second = (lane & 16u) != 0u;
     uint32_t tries = 2;  // (values that many elements share would send every step both ways)
-    constexpr TeamGreedy greedy = team_greedy<S>();
-    static_assert(greedy.steps <= 5, "12 bits per step");
-    constexpr uint64_t second_entries = packed_entries(greedy, 1, false);
-    uint64_t first_ahead = sweeps > 0u ? packed_entries(greedy, 0, true) : packed_entries(greedy, 0, false), second_ahead = second_entries;
+    auto solve = [&](uint32_t left, uint32_t right, uint32_t level, uint64_t active, uint32_t entry) __attribute__((always_inline)) {
+        if (tries != 0u && group_solve_direct<Shape>(direct, left, right, level, active & some, lane)) return;
+        general(entry);
+        if (tries > 0u) --tries;
+    };
+    if constexpr (CHAINS == 1) {
+        constexpr GreedyOrder order = greedy_order<S>();
+        static_assert(order.count <= 5, "12 bits per step");
+        const uint32_t steps = (uint32_t)order.count + sweeps * INTERIOR;
+        uint32_t entry = 0;
 #pragma unroll 1
-    for (int step = 0; step < greedy.steps; ++step) {
-        const uint32_t e0 = (uint32_t)first_ahead & 0xFFFu, e1 = (uint32_t)second_ahead & 0xFFFu;
-        const uint64_t active = (e0 != 0u ? kChain[0] : 0u) | (e1 != 0u ? kChain[1] : 0u);
-        const uint32_t entry = second ? e1 : e0;
-        if (tries == 0u || !group_solve_direct<Shape>(direct, levels + RECORD * ((entry >> 4) & 15u), levels + RECORD * (entry >> 8),
-                                                      levels + RECORD * (entry != 0u ? entry & 15u : (uint32_t)S), active, lane)) {
-            general(entry);
-            if (tries > 0u) --tries;
+        for (uint32_t step = 0; step < steps; ++step) {
+            if (step < (uint32_t)order.count) entry = (uint32_t)(order.packed[0] >> (12 * step)) & 0xFFFu;
+            else entry = step == (uint32_t)order.count || (entry & 15u) == INTERIOR ? kFirst : entry + kNext;
+            solve(levels + RECORD * ((entry >> 4) & 15u), levels + RECORD * (entry >> 8), levels + RECORD * (entry & 15u), ~0ull, entry);
         }
-        first_ahead >>= 12;
-        second_ahead >>= 12;
-    }
-    const uint32_t left_of_first = levels - (second ? 2u * RECORD : 0u);
-    uint32_t t = (uint32_t)greedy.head;  // (the first pair begins behind its head start)
+    } else {
+        constexpr uint64_t kChain[2] = {0x0000FFFF0000FFFFull, 0xFFFF0000FFFF0000ull};  // lanes
+        const bool second = (lane & 16u) != 0u;
+        constexpr TeamGreedy greedy = team_greedy<S>();
+        static_assert(greedy.steps <= 5, "12 bits per step");
+        constexpr uint64_t second_entries = packed_entries(greedy, 1, false);
+        uint64_t first_ahead = sweeps > 0u ? packed_entries(greedy, 0, true) : packed_entries(greedy, 0, false), second_ahead = second_entries;
 #pragma unroll 1
-    for (uint32_t left = sweeps; left > 0u;) {
-        const bool pair = left > 1u;
-        const uint32_t end = INTERIOR + (pair ? 2u : 0u);
+        for (int step = 0; step < greedy.steps; ++step) {
+            const uint32_t e0 = (uint32_t)first_ahead & 0xFFFu, e1 = (uint32_t)second_ahead & 0xFFFu;
+            const uint64_t active = (e0 != 0u ? kChain[0] : 0u) | (e1 != 0u ? kChain[1] : 0u);
+            const uint32_t entry = second ? e1 : e0;
+            solve(levels + RECORD * ((entry >> 4) & 15u), levels + RECORD * (entry >> 8),
+                  levels + RECORD * (entry != 0u ? entry & 15u : (uint32_t)S), active, entry);
+            first_ahead >>= 12;
+            second_ahead >>= 12;
+        }
+        const uint32_t left_of_first = levels - (second ? 2u * RECORD : 0u);
+        uint32_t t = (uint32_t)greedy.head;  // (the first pair begins behind its head start)
 #pragma unroll 1
-        for (; t < end; ++t) {
-            const uint64_t active = (t < INTERIOR ? kChain[0] : 0u) | (pair && t >= 2u ? kChain[1] : 0u);
-            const uint32_t at = left_of_first + RECORD * t;
-            const uint32_t to = __builtin_amdgcn_inverse_ballot_w64(active) ? at + RECORD : levels + RECORD * (uint32_t)S;
-            if (tries == 0u || !group_solve_direct<Shape>(direct, at, at + 2u * RECORD, to, active, lane)) {
-                general(__builtin_amdgcn_inverse_ballot_w64(active) ? (second ? t - 2u : t) * 0x111u + 0x201u : 0u);
-                if (tries > 0u) --tries;
+        for (uint32_t left = sweeps; left > 0u;) {
+            const bool pair = left > 1u;
+            const uint32_t end = INTERIOR + (pair ? 2u : 0u);
+#pragma unroll 1
+            for (; t < end; ++t) {
+                const uint64_t active = (t < INTERIOR ? kChain[0] : 0u) | (pair && t >= 2u ? kChain[1] : 0u);
+                const bool mine = __builtin_amdgcn_inverse_ballot_w64(active);
+                const uint32_t at = left_of_first + RECORD * t;
+                solve(at, at + 2u * RECORD, mine ? at + RECORD : levels + RECORD * (uint32_t)S, active,
+                      mine ? (second ? t - 2u : t) * kNext + kFirst : 0u);
             }
+            t = 0;
+            left -= pair ? 2u : 1u;
         }
-        t = 0;
-        left -= pair ? 2u : 1u;
     }
 }
 

@@ -1,5 +1,5 @@
 // Internal header of libogq: the random-rounding quantize kernel for buckets of 513 to 4096 elements whose rule solves several
-// interior levels (ORQ with five levels and more), two buckets per workgroup.  Included by rounding_part.hip after
+// interior levels (ORQ with four levels and more), two or four buckets per workgroup.  Included by rounding_part.hip after
 // rounding_kernels.h, whose exact sums and encoder it uses.  Compile with -ffp-contract=off.
 #ifndef OGQ_POOL_KERNELS_H
 #define OGQ_POOL_KERNELS_H
@@ -9,10 +9,10 @@
 namespace ogq {
 
 // ----------------------------------------------------------------------------------------------
-// Two buckets per workgroup, W wavefronts each, wavefront w of a bucket holding its elements [256 C w, 256 C (w + 1)) in the register
-// layout of orq_bucket.  The phases are those of orq_team_kernel: load, extremes, grouping in LDS, fp64 prefix, level solves,
-// encode; but one wavefront of the workgroup solves the levels of both side by side, a row of 16 lanes for each of a
-// bucket's two chains of solves (group_solve.h).
+// Two or four buckets per workgroup, W wavefronts each, wavefront w of a bucket holding its elements [256 C w, 256 C (w + 1)) in the
+// register layout of orq_bucket.  The phases are those of orq_team_kernel: load, extremes, grouping in LDS, fp64 prefix, level solves,
+// encode; but one wavefront of the workgroup solves the levels of all side by side, a row of 16 lanes for each of a
+// bucket's two chains of solves (group_solve.h), which begin with Algorithm 1's second level; four levels are one chain.
 //
 // A solve is some 120 vector instructions on values that are the same for the whole bucket, in one chain of LDS reads and
 // fp64 operations.  With a wavefront's 64 lanes on one solve (orq_team_kernel), eight levels and two sweeps took 11 steps behind workgroup
@@ -23,13 +23,16 @@ namespace ogq {
 // holds the buckets of four workgroups; the vector units are busy for some 230 of the 310 us.  The solving wavefront runs at a raised
 // priority: its instructions go first on its SIMD.  Four buckets per workgroup, in rows of 8 lanes, were slower (418 us when two took 368):
 // fewer workgroups overlap.
+// Four levels: four buckets of up to 2048 elements, a row each, so that a workgroup spends no more instructions on solves than with more
+// levels (25.6 M values in buckets of 2048, two sweeps, mean of four kinds of values: one wavefront per bucket 54.4 us, two buckets in a
+// workgroup 50.9, four 50.7; 8192 buckets 38 / 37 / 32).  Above 2048 elements the LDS of a workgroup (an address in 16 bits) holds two, whose
+// two rows do the same work.
 // ----------------------------------------------------------------------------------------------
-constexpr int kPoolBuckets = 2;  // per workgroup
-constexpr int kPoolChains = 2;   // of solves per bucket, a row of 16 lanes each
+constexpr int pool_chains(int S) { return S > 4 ? 2 : 1; }                     // of solves per bucket, a row of 16 lanes each
+constexpr int pool_buckets(int W, int S) { return W == 1 && S == 4 ? 4 : 2; }  // per workgroup
 
 template <int W, int C, int S>
 struct alignas(16) PoolBucket {
-    static_assert(S > 4, "the two chains of solves begin with Algorithm 1's second level");
     static constexpr int D = 256 * C * W;                      // element capacity
     static constexpr int B = C == 8 ? (W == 2 ? 5 * D / 16 : D / 4) : D / 2, HALF = B / 2;  // bins: what the LDS leaves room for
     static constexpr int BLOCK = 4 * C;                        // positions per entry of the fp64 prefix: one lane's
@@ -57,7 +60,7 @@ struct alignas(16) PoolBucket {
 
 template <int W, int C, int S>
 struct PoolLds {
-    PoolBucket<W, C, S> bucket[kPoolBuckets];
+    PoolBucket<W, C, S> bucket[pool_buckets(W, S)];
     unsigned long long exact_limb[kExactLimbs];
 };
 
@@ -77,7 +80,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     static_assert(W == 1 || W == 2, "the bin starts of a second wavefront follow from its own total");
     using Bucket = PoolBucket<W, C, S>;
     constexpr uint32_t PER_WAVE = 256u * C, B = Bucket::B, HALF = Bucket::HALF, BLOCK = Bucket::BLOCK;
-    constexpr int NB = kPoolBuckets;
+    constexpr int NB = pool_buckets(W, S);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = uniform_u32(threadIdx.x >> 6);
     const uint32_t slot_of = wave / (uint32_t)W, part = wave % (uint32_t)W;  // bucket of the workgroup, wavefront of the bucket
@@ -304,13 +307,14 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
             for (int b = 0; b < NB; ++b) lds.bucket[b].prefix[64u + lane] = before[b];
         }
         constexpr uint32_t G = 16;
-        static_assert(NB * kPoolChains * G == 64, "one group per bucket and chain");
-        Bucket& b = lds.bucket[lane / (G * kPoolChains)];
+        constexpr uint32_t LANES = 64u / NB;  // of a bucket
+        static_assert(LANES >= pool_chains(S) * G, "a group per bucket and chain");
+        Bucket& b = lds.bucket[lane / LANES];
         double total = b.wave_sum[0];
         if constexpr (W == 2) total += b.wave_sum[1];
         b.level[S - 1].sum_le = total;  // (the same from all lanes of the bucket)
         wave_lds_sync();
-        const uint32_t of_bucket = blockIdx.x * (uint32_t)NB + lane / (G * kPoolChains);
+        const uint32_t of_bucket = blockIdx.x * (uint32_t)NB + lane / LANES;
         uint32_t its_len = (uint32_t)Bucket::D;
         if constexpr (!FULL) {
             const size_t at = (size_t)of_bucket * bucket_size;
@@ -318,7 +322,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         }
         const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) Bucket*)&b;
         const uint32_t limb = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned long long*)lds.exact_limb;
-        group_solve_levels_direct<kPoolChains, S, Bucket>(b.view(lds.exact_limb, its_len), __builtin_fabs(total) < __builtin_inf(), sweeps, lane,
+        group_solve_levels_direct<pool_chains(S), S, Bucket>(b.view(lds.exact_limb, its_len), __builtin_fabs(total) < __builtin_inf(), sweeps, lane,
                                                           [&](uint32_t entry) __attribute__((always_inline)) {
                                                               pool_solve_general<Bucket>(at, limb, its_len, entry, lane);
                                                           });
@@ -342,15 +346,15 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 }
 
 template <int W, int C, int S, int BITS>
-__global__ __launch_bounds__(kPoolBuckets* W* kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 4 : 1))) void orq_pool_kernel(
+__global__ __launch_bounds__(pool_buckets(W, S) * W * kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 4 : 1))) void orq_pool_kernel(
     const float* __restrict__ grad, size_t n, uint32_t bucket_size, uint32_t sweeps, float clip, uint32_t num_buckets, uint64_t seed,
     uint64_t index_offset, float* __restrict__ levels, uint32_t* __restrict__ codes32)
 {
     __shared__ __attribute__((aligned(16))) PoolLds<W, C, S> lds;
     static_assert(sizeof(lds) <= 65536, "an LDS address in 16 bits");
-    static_assert(C != 8 || sizeof(lds) <= (size_t)W * 20480, "16 wavefronts in a CU");
+    static_assert(C != 8 || sizeof(lds) <= (size_t)W * pool_buckets(W, S) * 10240, "16 wavefronts in a CU");
     constexpr uint32_t D = PoolBucket<W, C, S>::D;
-    if (bucket_size == D && ((size_t)blockIdx.x + 1u) * (kPoolBuckets * D) <= n)
+    if (bucket_size == D && ((size_t)blockIdx.x + 1u) * (pool_buckets(W, S) * D) <= n)
         orq_pool_group<W, C, S, BITS, true>(lds, grad, n, bucket_size, sweeps, clip, num_buckets, seed, index_offset, levels, codes32);
     else
         orq_pool_group<W, C, S, BITS, false>(lds, grad, n, bucket_size, sweeps, clip, num_buckets, seed, index_offset, levels, codes32);
@@ -362,7 +366,7 @@ __global__ __launch_bounds__(kPoolBuckets* W* kWave) __attribute__((amdgpu_waves
 template <int W, int C, int S, int BITS>
 void launch_orq_pool(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    constexpr int NB = kPoolBuckets;
+    constexpr int NB = pool_buckets(W, S);
     launch_kernel((orq_pool_kernel<W, C, S, BITS>), dim3((nb + NB - 1) / NB), dim3(NB * W * kWave), st, g, n, p->bucket_size, p->level_iters,
                   p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
 }

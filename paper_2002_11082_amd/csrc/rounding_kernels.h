@@ -2741,24 +2741,23 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(RULE =
 // W wavefronts.  The others are not compiled, and asking for one fails like a launch that the runtime refuses: a call must not
 // return success over outputs that nothing has written.
 template <int C>
-constexpr bool wave_serves(int S, int rule)
+constexpr bool wave_serves(int S, int rule, bool clip = false)
 {
-    return !(rule == kOptimal && S >= 8 && C >= 2 && C <= 8) || (S == 8 && C == 8);  // (eight levels: where pool_gains says)
+    return !(rule == kOptimal && S >= 8 && C >= 2 && C <= 8) || (S == 8 && C == 8 && clip);  // (eight levels: where pool_gains says)
 }
 
 template <int C, int S, int BITS, int RULE = kOptimal>
 void launch_orq(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    if constexpr (!wave_serves<C>(S, RULE))
-        launch_status() = hipErrorInvalidDeviceFunction;
-    else if (p->clip_factor > 0.0f)
-        launch_kernel((orq_quantize_kernel<C, S, BITS, true, RULE>), dim3(nb), dim3(kWave), st, g, n, p->bucket_size,
-                           p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv,
-                           static_cast<uint32_t*>(codes));
-    else
-        launch_kernel((orq_quantize_kernel<C, S, BITS, false, RULE>), dim3(nb), dim3(kWave), st, g, n, p->bucket_size,
-                           p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv,
-                           static_cast<uint32_t*>(codes));
+    auto launch = [&](auto clip) {
+        if constexpr (wave_serves<C>(S, RULE, clip.value))
+            launch_kernel((orq_quantize_kernel<C, S, BITS, clip.value, RULE>), dim3(nb), dim3(kWave), st, g, n, p->bucket_size,
+                          p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
+        else
+            launch_status() = hipErrorInvalidDeviceFunction;
+    };
+    if (p->clip_factor > 0.0f) launch(std::true_type{});
+    else launch(std::false_type{});
 }
 
 template <int S, int BITS>
@@ -2865,6 +2864,7 @@ constexpr bool team_serves(int S, int rule)
         return C == 16 && (S != 3 || rule == kPb);
     }
     if (W == 4 && C == 8) return S != 3 || rule == kEven;
+    if (W == 4 && C == 1) return S < 8 || rule != kOptimal;
     return true;
 }
 

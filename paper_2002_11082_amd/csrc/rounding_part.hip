@@ -39,55 +39,60 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 }
 
 #if OGQ_PART == 4 || OGQ_PART == 8 || OGQ_PART == 16
-// Two buckets per workgroup whose levels one wavefront solves side by side (pool_kernels.h), where the solves are what a bucket
+// Two or four buckets per workgroup whose levels one wavefront solves side by side (pool_kernels.h), where the solves are what a bucket
 // waits for.  What a solve takes in the other kernels depends on the values: their bins suit a mixture of scales and are crowded with
-// Gaussian values, the pool's suit both.  So neither side is the faster one for all values at most sizes, and the rule takes the
+// Gaussian values, the pool's suit both.  So neither side is the faster one for all values at every size, and the rule takes the
 // pool where it gains on the mean of four kinds of values (mixture, Gaussian, Laplace, Student-t) and of a whole and a cut-off last
-// bucket; profiles/pool_scan.txt has both sides, and tests/test_dispatch.py holds the rule against it.  Over all the calls in that
-// file that take the pool it is 15 % faster, and no mean loses more than 3.5 %.
-// Single kinds of values lose up to 8 %: 64 buckets of 4096 cut off at the end, 18 solves, mixture 16.0 -> 17.3 where Gaussian goes
-// 23.0 -> 17.4; 8192 buckets of 2048, five levels, mixture 30.7 -> 31.8 where Gaussian goes 34.5 -> 31.9.  Means, us, other -> pool:
-//   up to 1024     514 buckets of 1024, 7 solves 12.3 -> 9.9
-//   whole 2048     18 solves from 385 on (384: 19.5 -> 16.2), 12 from 1025 (1026: 18.8 -> 16.7), fewer from 1281 (7: 17.5 -> 12.9).
-//                  Five levels without sweeps: up to 3072 buckets one wavefront per bucket has three per SIMD in its only round
-//                  (2816: 15.6 -> 16.1)
-//   rest to 1984   from where a bucket has one wavefront in the other kernel; five levels never (16384 of 1344: 54.3 -> 55.5), eight
-//                  without sweeps not in 2561 to 3072 buckets, for the reason above (2816 of 1344: 19.1 -> 20.3)
-//   whole 4096     18 solves from 16 on (17.9 -> 16.3), 12 from 385 (384: 17.4 -> 15.4), fewer from 1025 (1026, 7: 16.0 -> 15.5).
-//                  Five levels without sweeps: a CU holds 7 buckets in the other kernel and 8 in the pool, so a second round begins
-//                  behind 1792 there and behind 2048 here (1792: 17.3 -> 17.5, 2304: 21.5 -> 22.0)
-//   rest to 4032   the same rounds; what the pool does for elements that a bucket does not have shows up to some 2800 elements
-//                  (2304 of 2112: 7 solves 25.7 -> 26.3, 3 solves 19.8 -> 22.1; 12290 of 2112, 6 solves of five levels: 91.2 -> 94.0)
-// With clipping, values end at a few sigma, which crowds the other kernels' bins less: the pool gains less, and fewer calls take it
-// (profiles/pool_clip_scan.txt, held against the rule likewise).  Above 2048 elements it needs 18 solves (2304 of 2112, 7 solves: 29.4 -> 32.5), or 12
-// of eight levels outside the counts at which it begins a round too many (2060 of 2560: 37.8 -> 39.9), or whole 4096 in more than 2432
-// buckets (1792, 7 solves: 23.2 -> 24.4; 4096: 47.1 -> 43.7).  Eight levels in 2561 to 3072 buckets of 1088 to 2048 stay out (2816 of
-// 1344, 6 solves: 22.2 -> 25.9; of up to 1984 also beyond, where neither side gains: 5120 of 1344 32.2 -> 34.7).  Up to 10 % is lost where one wavefront per bucket is compiled for no other call: nine levels in those
-// counts, and eight and nine in buckets of up to 1024 (5120 of 768, 6 solves: 22.2 -> 24.2).
+// bucket; profiles/pool_scan.txt and, with clipping, pool_clip_scan.txt have both sides, and tests/test_dispatch.py holds the rule against
+// them: no mean loses more than 3.5 %.  Clipped values end at a few sigma, which crowds the other kernels' bins less, so fewer calls take the
+// pool.  Means, us, other -> pool (solves: interior levels, once and for every sweep):
+//   eight, nine levels  12 solves and more at every size and number of buckets (18 solves: 64 buckets of 2112 16.8 -> 14.6, 2048 of 1024 25.0 ->
+//                       13.8; clipped, 12, 16 of 2048: 14.7 -> 14.2); fewer up to 1024 elements (6: 16 of 768 7.8 -> 7.3), above from 1025 buckets
+//                       on (514 of 1344: 11.1 -> 11.8, 1282 15.7 -> 13.0).  Clipped from 1281 on (1026 of 2112: 18.1 -> 19.2), but for
+//                       2561 to 3072 of 1088 to 1984 elements (second_round; eight levels, 2816 of 1344: 22.2 -> 23.5) and, of 2112 to 2752
+//                       elements, from 2817 on (2304 of 2112: 28.8 -> 30.1, 3072 35.7 -> 34.5)
+//   five levels         12 solves and more likewise (64 of 4096: 15.5 -> 12.6), of 1088 to 1984 elements from 256 buckets on.  Fewer where the other
+//                       kernel has one wavefront per bucket, without those two rounds (3 solves, 2816 of 1344: 14.7 -> 15.6), of up to 1024
+//                       elements without 4097 to 6144 buckets (5120 of 768: 14.6 -> 15.1); above 2048 elements 6 solves from 641 on, 3 from
+//                       1281, but for the numbers at which only the pool begins another round (2304 of 2112: 19.8 -> 20.8)
+//   four levels         where the other kernel has one wavefront per bucket (6 solves: 4096 of 2048 22.2 -> 17.4, 2048 of 1024 11.0 -> 9.1; 2, 4096
+//                       of 2048: 17.1 -> 16.2); two solves while that is less than two rounds, beyond which neither side gains (6144 of 1024:
+//                       13.8 -> 14.2).  Above 2048 elements with 6 solves (4096 of 4096: 38.8 -> 33.6), fewer in 1793 to 2048 buckets, where
+//                       only the other kernel needs a second round (2 solves of 2112: 2048 17.8 -> 15.3, 1792 13.9 -> 15.1)
 static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb, bool clipped)
 {
-    const bool five = levels == 5u;
-    if (clipped && solves < 18u) {
-        if (d == 2048u && five && solves < 12u && nb > 2560u && nb <= 3072u) return false;
-        if (d > 2048u && d < 4096u && (five || solves < 12u || nb <= 1024u || (nb > 2048u && nb <= 2432u))) return false;
-        if (d == 4096u && nb <= (solves < 12u ? 2432u : 640u)) return false;
+    const bool second_round = nb > 2560u && nb <= 3072u;  // of the pool up to 2048 elements, where one wavefront per bucket has its first
+    if (levels >= 8u) {
+        if (solves >= 12u || d <= 1024u) return true;
+        if (!clipped) return nb >= 1025u;
+        if (nb < 1281u) return false;
+        return d <= 2048u ? !(levels == 8u && d < 2048u && second_round) : d >= 2816u || nb > 2816u;
     }
-    if (levels == 8u && solves <= (clipped ? 12u : 6u) && d > 1024u && d <= (clipped && solves == 6u ? 2048u : 1984u) && nb > 2560u &&
-        (nb <= 3072u || (clipped && solves == 6u && d < 2048u)))
-        return false;
-    if (d <= 1024u) return !five && nb >= 513u;
-    if (d <= 2048u) {
-        if (d < 2048u) return !five && nb >= 1281u;
-        return nb >= (solves >= 18u ? 385u : solves >= 12u ? 1025u : 1281u) && !(solves == 3u && nb > 2560u && nb <= 3072u);
+    if (levels == 5u) {
+        if (solves >= 12u) return d <= 1024u || d >= 2048u || (nb >= 256u && !(clipped && second_round));
+        if (d <= 1024u) {
+            if (clipped) return nb > 1024u && nb <= 2560u;
+            return nb > 512u && (nb <= 4096u || nb > 6144u) && (solves >= 6u || !second_round);
+        }
+        if (d < 2048u) return nb > 1280u && !second_round && (!clipped || nb <= 2560u);
+        if (d == 2048u) return clipped ? nb > 1280u && !second_round : nb > 1024u;
+        if (clipped) return nb > (d == 4096u ? 1792u : 2816u);
+        if (solves >= 6u) return nb > 640u;
+        return nb > 1280u && (d == 4096u || !((nb > 1536u && nb <= 1792u) || (nb > 2048u && nb <= 2432u)));
     }
-    if (d == 4096u)
-        return nb >= (solves >= 18u ? 16u : solves >= 12u ? 385u : five ? 1281u : 1025u) &&
-               !(solves == 3u && ((nb > 1536u && nb <= 1792u) || (nb > 2048u && nb <= 2432u)));
-    if (nb < (solves >= 12u ? 641u : 1281u)) return false;
-    const bool fuller = d >= 2816u;
-    if (solves == 3u) return (nb > 1792u && nb <= 2048u) || (fuller && nb <= 1536u);
-    if (solves == 6u && nb > 6144u && (five || !fuller)) return false;
-    return fuller || nb <= 2048u || nb > 2432u || (!five && solves >= 12u);
+    if (d > 2048u) {
+        if (clipped) return d == 4096u && solves >= 6u && nb > 1792u;
+        if (solves >= 6u) return nb > (d == 4096u ? 384u : 1024u);
+        return solves >= 4u && d == 4096u ? nb > 1280u : nb > 1792u && nb <= 2048u;
+    }
+    if (solves < 4u) {
+        if (clipped) return false;
+        if (d <= 1024u) return nb > 1536u && nb <= 5120u;
+        return nb > 1792u && nb <= (d == 2048u ? 20480u : 6144u);
+    }
+    if (d <= 1024u) return nb > 512u;
+    if (clipped && solves < 6u) return d == 2048u ? nb > 1536u : nb > 1280u && nb <= 5120u;
+    return nb > 1280u;
 }
 
 template <int W, int C>
@@ -96,10 +101,11 @@ static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, ui
     if (p->scheme != OGQ_ORQ && p->scheme != OGQ_ORQ_PAPER) return false;
     const uint32_t levels = levels_per_bucket(p->scheme, p->bits);
     const uint64_t solves = (uint64_t)(levels - 2u) * (1u + (uint64_t)p->level_iters);
-    if (levels < 5u || !pool_gains(p->bucket_size, levels, solves, nb, p->clip_factor > 0.0f)) return false;
+    if (levels < 4u || !pool_gains(p->bucket_size, levels, solves, nb, p->clip_factor > 0.0f)) return false;
     if (levels == 8u) launch_orq_pool<W, C, 8, 3>(g, n, p, nb, lv, codes, st);
     else if (levels == 9u) launch_orq_pool<W, C, 9, 4>(g, n, p, nb, lv, codes, st);
-    else if constexpr (C > 4) launch_orq_pool<W, C, 5, 3>(g, n, p, nb, lv, codes, st);
+    else if (levels == 5u) launch_orq_pool<W, C, 5, 3>(g, n, p, nb, lv, codes, st);
+    else launch_orq_pool<W, C, 4, 2>(g, n, p, nb, lv, codes, st);
     return true;
 }
 #endif

@@ -29,7 +29,7 @@ BUCKETS = sorted({max(1, limit + step) for limit in LIMITS for step in (-1, 0, 1
 WORKERS = (1, 2, 3, 4, 5, 8, 9, 64)
 ADDRESS = 0x10000  # aligned; never looked at
 SCANS = (("pool_scan.txt", 0.0), ("pool_clip_scan.txt", 2.5))
-SCANNED = {"ORQ 3-bit": (ogq.ORQ, 3), "ORQ-5": (ogq.ORQ_PAPER, 3), "ORQ-9": (ogq.ORQ_PAPER, 4)}
+SCANNED = {"ORQ 2-bit": (ogq.ORQ, 2), "ORQ 3-bit": (ogq.ORQ, 3), "ORQ-5": (ogq.ORQ_PAPER, 3), "ORQ-9": (ogq.ORQ_PAPER, 4)}
 
 
 def pool_scan(name):

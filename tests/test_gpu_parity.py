@@ -1144,6 +1144,30 @@ def test_bins_that_a_group_counts(scheme, bits, sweeps, d, nb):
                               tag=f"counted-s{scheme}-b{bits}-i{sweeps}-d{d}-last{last}")
 
 
+@pytest.mark.parametrize("clip", [0.0, 2.5])
+@pytest.mark.parametrize("d,nb", [(576, 515), (1024, 513), (1088, 1283), (2048, 1281), (2048, 1538), (2112, 1030), (4096, 386), (4096, 1794)])
+@pytest.mark.parametrize("sweeps", [1, 2, 5])
+def test_four_levels_of_several_buckets_per_workgroup(sweeps, d, nb, clip):
+    """Four buckets of up to 2048 elements, or two above, in a workgroup whose last one is not full: neighbours with crowded bins, clusters of
+    as many values as a group counts, infinities, constant buckets, last buckets that are whole, cut off and of one element."""
+    rng = np.random.default_rng(sweeps + d)
+    g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    for b in range(44):
+        buckets[b] = _crowded_bucket(rng, d, b % 11)
+    for b, k in enumerate([2, 15, 16, 17, 31, 32, 33, 34], start=44):
+        buckets[b] = np.where(rng.random(d) < 0.5, -3.0, 3.0).astype(np.float32) + rng.standard_normal(d).astype(np.float32) * 0.1
+        buckets[b, rng.permutation(d)[:k]] = np.float32(0.25) * (np.float32(1.0) + np.arange(k, dtype=np.float32) * np.float32(2.0 ** -21))
+    buckets[53] = 1.5
+    if clip == 0.0:
+        buckets[55, 7] = np.inf
+        buckets[57, 9] = -np.inf
+    checked = [b for b in range(60) if b not in (55, 57)] + list(range(nb - 6, nb))
+    for last in (d, d - 29, 33, 31, 1):
+        parity.check_quantize(g[: nb * d - d + last], d, 2, ogq.ORQ, sweeps, seed=29, buckets=checked, clip_factor=clip,
+                              tag=f"four-levels-i{sweeps}-d{d}-nb{nb}-last{last}-c{clip}")
+
+
 def _crowded_bucket(rng, d, kind):
     """Buckets of which one bin holds most elements: a value that many share, or a range of neighbouring ones."""
     g = (rng.standard_t(3, d) * 1e-3).astype(np.float32)
