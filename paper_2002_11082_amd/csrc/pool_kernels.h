@@ -345,8 +345,9 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                                  encoder_table<S, true>(my.grouped, part));
 }
 
+// (Five wavefronts per SIMD with four levels up to 1024 elements: 12290 buckets of 768, two sweeps, four 36 us, five 30.)
 template <int W, int C, int S, int BITS>
-__global__ __launch_bounds__(pool_buckets(W, S) * W * kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 4 : 1))) void orq_pool_kernel(
+__global__ __launch_bounds__(pool_buckets(W, S) * W * kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 4 : S == 4 ? 5 : 1))) void orq_pool_kernel(
     const float* __restrict__ grad, size_t n, uint32_t bucket_size, uint32_t sweeps, float clip, uint32_t num_buckets, uint64_t seed,
     uint64_t index_offset, float* __restrict__ levels, uint32_t* __restrict__ codes32)
 {

@@ -1144,6 +1144,39 @@ def test_bins_that_a_group_counts(scheme, bits, sweeps, d, nb):
                               tag=f"counted-s{scheme}-b{bits}-i{sweeps}-d{d}-last{last}")
 
 
+@pytest.mark.parametrize("scheme,bits,d,nb", [(ogq.ORQ, 2, 1024, 515), (ogq.ORQ, 2, 4096, 1027), (ogq.ORQ_PAPER, 3, 4096, 400),
+                                              (ogq.ORQ, 3, 2048, 67), (ogq.ORQ, 3, 4096, 33), (ogq.ORQ_PAPER, 4, 768, 33)])
+def test_sweeps_end_where_no_level_moves(scheme, bits, d, nb):
+    """Sweeps behind the second, odd and even numbers of them, among neighbours that settle early, late and at once; and many more of
+    them once all levels have settled (the values below do within 40 sweeps) take no time: 30 times as many sweeps, less than 4 times
+    as long, where a step that solves again what it finds would take 30."""
+    rng = np.random.default_rng(bits + d)
+    g = (rng.standard_normal(nb * d) * np.where(rng.random(nb * d) < 0.9, 1e-4, 1e-2)).astype(np.float32).reshape(nb, d)
+    g[1], g[4] = 0.5, rng.integers(-3, 4, d)  # (equal values: the steps of their workgroups go to the general solve)
+    g[nb // 2:] = g[nb // 2]
+    checked = list(range(10)) + [nb // 2, nb - 1]
+    for last in (d, 40):
+        for sweeps in (3, 4, 7, 8, 300):
+            parity.check_quantize(g.reshape(-1)[: nb * d - d + last], d, bits, scheme, sweeps, seed=23, buckets=checked,
+                                  tag=f"settled-s{scheme}-b{bits}-d{d}-last{last}-i{sweeps}")
+    g[1], g[4] = g[0], g[0]
+    dg = torch.from_numpy(g.reshape(-1)).to(DEV)
+    shortest, levels = {}, {}
+    for sweeps in (300, 9000):
+        params = ogq.make_params(d, bits, scheme, sweeps)
+        times = []
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            levels[sweeps], _ = ogq.ogq_quantize(dg, params)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        shortest[sweeps] = min(times)
+    assert torch.equal(levels[300], levels[9000])
+    assert shortest[9000] < 4 * shortest[300], shortest
+
+
 @pytest.mark.parametrize("clip", [0.0, 2.5])
 @pytest.mark.parametrize("d,nb", [(576, 515), (1024, 513), (1088, 1283), (2048, 1281), (2048, 1538), (2112, 1030), (4096, 386), (4096, 1794)])
 @pytest.mark.parametrize("sweeps", [1, 2, 5])
