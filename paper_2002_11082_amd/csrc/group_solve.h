@@ -304,11 +304,12 @@ __device__ __forceinline__ uint32_t read_again(uint32_t entry)
 // orq_solve_one), entry = k | l << 4 | r << 8, 0 for a group with nothing to do.  SUMS = false: one interior level,
 // whose solve reads the bucket's total alone.  Shape: HALF (signed_bin), BLOCK (positions per entry of the
 // prefix), END_OF_BUCKET (the entry behind a bucket's last bin is not its end) and LEAF (a function of its own, which calls none).
+// Returns whether a level has moved (LEAF alone; else whether one was solved).
 //
 // The bin of a rank needs no search: the element at that position of the grouped bucket is in it.  The element of the rank is then
 // found by sorting the bin.
 template <int G, bool SUMS, class Shape>
-__device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry, uint32_t lane)
+__device__ __forceinline__ bool group_solve(const GroupBucket& b, uint32_t entry, uint32_t lane)
 {
     constexpr uint32_t BLOCK = Shape::BLOCK, LANES = (uint32_t)G;
     static_assert(!SUMS || BLOCK % LANES == 0, "the elements in front of a bin are read G at a time");
@@ -340,7 +341,7 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
     }
     const uint32_t rank = umin32(umax32(__builtin_elementwise_sub_sat((uint32_t)right.count_le, m), 1u), b.len);
     const bool same = entry == 0u || (ordered && rank == last_rank);  // same element as last time
-    if (__ballot(!same) == 0) return;
+    if (__ballot(!same) == 0) return false;
 
     const uint32_t at = b.origin + (rank > 0u ? rank - 1u : 0u);  // (rank 0: an empty bucket)
     const int32_t bin = signed_bin<Shape::HALF>(grouped_value(b.grouped + 4u * at), b.bins);
@@ -409,8 +410,11 @@ __device__ __forceinline__ void group_solve(const GroupBucket& b, uint32_t entry
             now.sum_le = copy_left ? (ordered ? left.sum_le : right.sum_le) : now.sum_le;
         }
     }
+    bool moved = true;
+    if constexpr (Shape::LEAF) moved = __ballot(!same && __float_as_uint(now.value) != __float_as_uint(b.level[read_again(entry) & 15u].value)) != 0;
     if (i == 0u && !same) b.level[k] = now;
     wave_lds_sync();
+    return moved;
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -657,8 +661,9 @@ __device__ __forceinline__ void group_solve_levels(const GroupBucket& b, uint32_
     }
 }
 
-// The same by direct solves, by CHAINS groups of 16 lanes per bucket; general(entry) takes a step that they leave.  With one chain several
-// groups may share a bucket: they all do the same.  A bucket without elements (behind the gradient's last one) is in no step's way.
+// The same by direct solves, by CHAINS groups of 16 lanes per bucket; general(entry) takes a step that they leave, and returns group_solve's
+// result.  With one chain several groups may share a bucket: they all do the same.  A bucket without elements (behind the gradient's last
+// one) is in no step's way.
 //
 // Sweeps behind the second find most levels where they are: such a step ends as soon as that shows, and a sweep that changes no level ends the
 // solves, as the next one would find the same neighbours (20 sweeps, mixture, every step to its end -> this: five levels, 4096 buckets of 2048
@@ -676,8 +681,8 @@ __device__ __forceinline__ void group_solve_levels_direct(const GroupBucket& b, 
     bool changed = false;
     auto solve = [&](auto skip, uint32_t left, uint32_t right, uint32_t level, uint64_t active, uint32_t entry) __attribute__((always_inline)) {
         if (tries != 0u && group_solve_direct<Shape, decltype(skip)::value>(direct, left, right, level, active & some, lane, changed)) return;
-        changed = true;
-        general(entry);
+        const bool moved = general(entry);
+        if constexpr (decltype(skip)::value) changed = changed || moved;
         if (tries > 0u) --tries;
     };
     const uint32_t first_sweeps = umin32(sweeps, 2u);

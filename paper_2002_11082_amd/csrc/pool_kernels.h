@@ -66,10 +66,10 @@ struct PoolLds {
 
 // A step of solves that group_solve_direct leaves (bucket, limb: LDS addresses).  Out of line: few steps take it.
 template <class Bucket>
-static __device__ __attribute__((noinline)) void pool_solve_general(uint32_t bucket, uint32_t limb, uint32_t len, uint32_t entry, uint32_t lane)
+static __device__ __attribute__((noinline)) uint32_t pool_solve_general(uint32_t bucket, uint32_t limb, uint32_t len, uint32_t entry, uint32_t lane)
 {
     Bucket& b = *(Bucket*)(__attribute__((address_space(3))) Bucket*)(uintptr_t)bucket;
-    group_solve<16, true, Bucket>(b.view((unsigned long long*)(__attribute__((address_space(3))) unsigned long long*)(uintptr_t)limb, len), entry, lane);
+    return group_solve<16, true, Bucket>(b.view((unsigned long long*)(__attribute__((address_space(3))) unsigned long long*)(uintptr_t)limb, len), entry, lane);
 }
 
 template <int W, int C, int S, int BITS, bool FULL>
@@ -324,7 +324,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         const uint32_t limb = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned long long*)lds.exact_limb;
         group_solve_levels_direct<pool_chains(S), S, Bucket>(b.view(lds.exact_limb, its_len), __builtin_fabs(total) < __builtin_inf(), sweeps, lane,
                                                           [&](uint32_t entry) __attribute__((always_inline)) {
-                                                              pool_solve_general<Bucket>(at, limb, its_len, entry, lane);
+                                                              return uniform_u32(pool_solve_general<Bucket>(at, limb, its_len, entry, lane)) != 0u;
                                                           });
         __builtin_amdgcn_s_setprio(0);
     }
