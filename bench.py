@@ -94,8 +94,6 @@ def pool_gains(d: int, levels: int, solves: int, nb: int, clipped: bool) -> bool
         if solves >= 6:
             return nb > (384 if d == 4096 else 1024)
         return nb > 1280 if solves >= 4 and d == 4096 else 1792 < nb <= 2048
-    if 1024 < d and 4096 < nb <= 20480 and (nb - 1) % 4096 < 512:
-        return False
     if solves < 4:
         if clipped:
             return False

@@ -57,8 +57,8 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 //                       1281, but for the numbers at which only the pool begins another round (2304 of 2112: 19.8 -> 20.8)
 //   four levels         where the other kernel has one wavefront per bucket (6 solves: 4096 of 2048 22.2 -> 17.4, 2048 of 1024 11.0 -> 9.1; 2, 4096
 //                       of 2048: 17.1 -> 16.2); two solves while that is less than two rounds, beyond which neither side gains (6144 of 1024:
-//                       13.8 -> 14.2).  A round of the pool is 4096 buckets of 1088 to 2048 elements; where the last one has few, mixtures
-//                       lose (12500 of 2048: 50.8 -> 51.8) what the others gain.  Above 2048 elements with 6 solves (4096 of 4096: 38.8 -> 33.6), fewer in 1793 to 2048 buckets, where
+//                       13.8 -> 14.2).  A round of the pool is 4096 buckets of 1088 to 2048 elements; one with few buckets takes some of the
+//                       gain (6 solves, 12290 of 2048: 52.4 -> 50.4, 12500 53.9 -> 50.8).  Above 2048 elements with 6 solves (4096 of 4096: 38.8 -> 33.6), fewer in 1793 to 2048 buckets, where
 //                       only the other kernel needs a second round (2 solves of 2112: 2048 17.8 -> 15.3, 1792 13.9 -> 15.1)
 static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb, bool clipped)
 {
@@ -86,7 +86,6 @@ static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb
         if (solves >= 6u) return nb > (d == 4096u ? 384u : 1024u);
         return solves >= 4u && d == 4096u ? nb > 1280u : nb > 1792u && nb <= 2048u;
     }
-    if (d > 1024u && nb > 4096u && nb <= 20480u && (nb - 1u) % 4096u < 512u) return false;  // (a last round of few buckets)
     if (solves < 4u) {
         if (clipped) return false;
         if (d <= 1024u) return nb > 1536u && nb <= 5120u;

@@ -3,7 +3,7 @@ runtime, and prints what they launched.  Run as a child process by test_dispatch
 
 Every scheme and width, every bucket size, clipping on and off, every power of two and every number of the dispatch in
 rounding_part.hip and bingrad.hip as number of buckets, with its neighbours, whole and ragged last buckets, sweeps where the dispatch looks at them,
-each with the kernel that the benchmark names for it; the decoder with every number of workers at which it changes its form.
+each with the kernel that the benchmark names for it, and every 64th number of buckets up to 40000 at the sizes of limits.py; the decoder with every number of workers at which it changes its form.
 Also the benchmark's workloads at several lengths, with the kernels that the benchmark says they take, and the calls that
 profiles/pool_scan.txt and pool_clip_scan.txt hold times of."""
 import ctypes
@@ -16,6 +16,7 @@ import types
 import bench
 import paper_2002_11082_amd as ogq
 from paper_2002_11082_amd import synth
+from tests import limits
 
 SCHEMES = ((ogq.BINGRAD_B, (1,)), (ogq.ORQ, (1, 2, 3)), (ogq.BINGRAD_PB, (1,)), (ogq.ORQ_PAPER, (2, 3, 4)), (ogq.SCALED_SIGN, (1,)),
            (ogq.EVEN, (2, 3, 4)), (ogq.LINEAR, (2, 3, 4)))
@@ -92,6 +93,19 @@ def main():
                             if named != bases[stub.recorded_last()]:
                                 misnamed.append([what, named, bases[stub.recorded_last()]])
                             calls += 1
+    for d in limits.CHANGES:
+        for scheme, bits, sweeps in limits.RULES.values():
+            for clip in (0.0, 2.5):
+                p = ogq.make_params(d, bits, scheme, sweeps, 0, 0, clip)
+                by, levels = ctypes.byref(p), ogq.ogq_levels_per_bucket(p)
+                wl = types.SimpleNamespace(bucket_size=d, scheme=scheme, clip_factor=clip, level_iters=sweeps)
+                for nb in range(32, 40000, 64):
+                    what = f"quantize scheme {scheme} bits {bits} d {d} n {nb * d} clip {clip} sweeps {sweeps}"
+                    once(what, quantize(ADDRESS, nb * d, by, ADDRESS, ADDRESS, None))
+                    named = bench.quantize_kernel(synth, wl, nb * d, levels)[0]
+                    if named != bases[stub.recorded_last()]:
+                        misnamed.append([what, named, bases[stub.recorded_last()]])
+                    calls += 1
     pointers = (ctypes.c_void_p * 64)(*[ADDRESS] * 64)
     at = ctypes.addressof(pointers)
     for scheme, bits in ((ogq.ORQ, 1), (ogq.ORQ, 2), (ogq.ORQ, 3), (ogq.ORQ_PAPER, 2), (ogq.ORQ_PAPER, 3), (ogq.ORQ_PAPER, 4)):

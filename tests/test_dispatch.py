@@ -66,20 +66,26 @@ def test_the_benchmark_repeats_the_dispatch(recorded):
 
 
 def test_the_listed_limits_are_those_of_the_dispatch():
-    """limits.py against the limits that bench.py repeats (which the test above holds against the library)."""
+    """limits.py against the limits that bench.py repeats (which the test above holds against the library): every number of buckets up to
+    40000 where the kernel changes, whatever the form of the rule, but for ranges of fewer than 16."""
     import bench
     import paper_2002_11082_amd as ogq
     from paper_2002_11082_amd import synth
     from tests import limits
-    dispatch = re.sub("//.*", "", open(os.path.join(ROOT, "paper_2002_11082_amd", "csrc", "rounding_part.hip")).read())
-    numbers = sorted({max(1, int(x) + step) for x in re.findall(r"\b(\d+)u\b", dispatch) for step in (-1, 0)})
+
+    def changes(kernel, low, high):
+        if kernel(low) == kernel(high):
+            return []
+        middle = (low + high) // 2
+        return [low] if middle == low else changes(kernel, low, middle) + changes(kernel, middle, high)
+
     for d, stated in limits.CHANGES.items():
         found = {}
         for name, (scheme, bits, sweeps) in limits.RULES.items():
             wl = types.SimpleNamespace(bucket_size=d, scheme=scheme, clip_factor=0.0, level_iters=sweeps)
             levels = ogq.ogq_levels_per_bucket(ogq.make_params(d, bits, scheme))
-            for nb in numbers:
-                if bench.quantize_kernel(synth, wl, nb * d, levels) != bench.quantize_kernel(synth, wl, (nb + 1) * d, levels):
+            for low in range(0, 40000, 16):
+                for nb in changes(lambda nb: bench.quantize_kernel(synth, wl, nb * d, levels), max(low, 1), low + 16):
                     found.setdefault(nb, []).append(name)
         assert found == {limit: limits.rules(names) for limit, names in stated.items()}, d
 
