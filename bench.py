@@ -61,6 +61,15 @@ def read_note(file_name: str, kernel_key: str):
     return None
 
 
+def several_buckets_from(d: int, clipped: bool, updates: bool) -> int:
+    """The rule of the same name in bingrad.hip."""
+    listed = {64: (8192, 10240, 10240), 128: (4608, 5632, 12288), 192: (4608, 4608, 6656), 256: (4608, 5632, 7680), 512: (6144, 6144, 6656),
+              1024: (4608, 4608, 6656)}
+    if d in listed:
+        return listed[d][2 if clipped else int(updates)]
+    return 4608 if d < 512 else 768 if d in (704, 768) else 2560
+
+
 def pool_gains(d: int, levels: int, solves: int, nb: int, clipped: bool) -> bool:
     """The rule of the same name in rounding_part.hip."""
     second_round = 2560 < nb <= 3072
@@ -118,10 +127,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
             if d > 16384:
                 return "bingrad_team_kernel", 16 if clip else 8
             return "bingrad_team_kernel", 8 if clip or nb <= 512 or (d == 16384 and once) else 4
-        clip = wl.clip_factor > 0
-        several = {64: 10240, 128: 12288 if clip else 8192, 192: 8192, 256: 12288 if clip else 8192, 512: 8192 if clip else 6144,
-                   1024: 8192 if clip else 4096}.get(d, 5120 if d < 512 else 3072)
-        if d <= 1024 and nb >= several:
+        if d <= 1024 and nb >= several_buckets_from(d, wl.clip_factor > 0, wl.scheme == synth.BINGRAD_B and wl.level_iters > 0):
             return "bingrad_chunk_kernel", 1 / (2048 // d)
         return "bingrad_quantize_kernel", 1
     pb, even, linear = (wl.scheme == s for s in (synth.BINGRAD_PB, synth.EVEN, synth.LINEAR))

@@ -594,27 +594,27 @@ void launch_bingrad_chunks(const float* g, size_t n, const ogq_params_t* p, floa
 }
 
 // Number of buckets from which several of them share a wavefront.  Below, every SIMD has a wavefront or two anyway and one with more
-// buckets only takes longer.  Crossovers on Laplace values (us, one bucket per wavefront -> several; BinGrad-b, its two updates, with
-// clipping, Scaled SignSGD with clipping):
-//   64    8192 buckets 3.9 -> 4.0, 6.0 -> 6.6, 4.7 -> 5.6, 3.5 -> 4.3; 12288: 4.9 -> 4.1, 7.9 -> 7.0, 6.1 -> 5.6, 4.3 -> 4.3
-//   128   8192: 4.1 -> 3.4, 6.1 -> 5.7, 5.0 -> 4.8, 3.7 -> 3.9; 10240 with clipping 5.8 -> 6.5, 4.3 -> 5.1, 16384: 8.1 -> 6.6, 5.6 -> 5.4
-//   256   8192: 5.1 -> 4.5, 7.0 -> 6.7, 5.5 -> 5.9, 4.2 -> 4.9; 12288: 6.6 -> 4.6, 9.8 -> 7.0, 7.8 -> 6.4, 5.9 -> 5.4
-//   512   6144: 4.8 -> 4.6, 7.0 -> 6.8, 5.7 -> 5.8, 4.5 -> 5.0; 8192: 5.7 -> 4.8, 8.6 -> 7.1, 7.0 -> 6.1, 5.6 -> 5.3
-//   1024  4096: 4.7 -> 4.7, 6.7 -> 6.6; 6144 with clipping 7.5 -> 8.1, 6.0 -> 6.7, 8192: 9.2 -> 8.7, 7.5 -> 7.2
-// A size between two of these leaves registers of the one-bucket kernel empty:
-//   192   6144: 4.7 -> 4.5, 6.4 -> 6.9, 5.6 -> 6.4, 4.4 -> 5.0; 8192: 5.5 -> 4.6, 7.7 -> 7.0, 6.8 -> 6.5, 5.3 -> 5.3
-//   320   4096: 4.0 -> 4.2, 5.5 -> 6.5, 5.2 -> 5.8, 4.1 -> 4.7; 5120: 4.9 -> 4.5, 6.6 -> 6.5, 5.9 -> 5.9, 4.8 -> 4.8
-//   640   2048: 3.7 -> 4.1, 4.9 -> 6.1, 4.5 -> 5.4, 3.7 -> 4.4; 3072: 4.6 -> 4.3, 6.7 -> 6.3, 6.3 -> 5.7, 5.1 -> 4.6
-static uint32_t several_buckets_from(uint32_t d, bool clipped)
+// buckets only takes longer; threshold updates add to that.  profiles/bingrad_scan.txt has both sides for every size, tests/test_dispatch.py
+// holds the limits against it.  us, one bucket per wavefront -> several, of BinGrad-b, its two updates, Scaled SignSGD:
+//   64    8192 buckets 4.1 -> 4.1, 6.3 -> 7.4, 3.0 -> 2.9; 10240: 5.1 -> 4.2, 7.3 -> 6.9, 3.4 -> 2.9; clipped, 10240: 5.8 -> 5.8, 8.4 -> 7.9, 4.2 -> 4.4
+//   128   4608: 3.5 -> 3.5, 4.9 -> 5.8, 2.8 -> 2.7; 5632: 3.9 -> 3.6, 5.4 -> 5.6, 3.1 -> 2.8; clipped, 12288: 7.1 -> 6.5, 10.2 -> 9.2, 5.4 -> 5.1
+//   256   4608: 4.2 -> 3.8, 5.7 -> 6.2, 3.4 -> 3.0; 5632: 4.4 -> 3.9, 6.2 -> 6.3, 3.4 -> 3.0; clipped, 7680: 5.9 -> 5.6, 8.3 -> 7.9, 4.6 -> 4.6
+//   512   5632: 4.2 -> 4.4, 6.7 -> 6.7, 3.3 -> 3.4; 6144: 4.2 -> 4.4, 6.8 -> 6.6, 3.7 -> 3.4; clipped, 6656: 6.2 -> 5.8, 8.9 -> 8.1, 4.9 -> 5.0
+//   1024  4096: 4.6 -> 4.8, 6.9 -> 7.3, 3.6 -> 3.6; 4608: 5.2 -> 5.1, 8.0 -> 8.0, 4.4 -> 3.9; clipped, 6656: 8.4 -> 8.3, 12.1 -> 12.0, 6.5 -> 6.7
+// A size between two of these leaves registers of the one-bucket kernel empty, and shares earlier:
+//   192   4096: 3.8 -> 3.6, 5.2 -> 5.4, 3.0 -> 2.8; 4608: 4.3 -> 3.5, 5.9 -> 5.3, 3.4 -> 3.0; clipped, 6656: 6.5 -> 6.0, 8.7 -> 8.4, 5.2 -> 4.7
+//   704   512: 3.2 -> 3.0, 4.3 -> 4.4, 2.7 -> 2.4; 768: 3.6 -> 3.0, 5.1 -> 4.4, 2.8 -> 2.4; clipped 4.6 -> 3.6, 6.1 -> 5.0, 3.9 -> 3.0
+static uint32_t several_buckets_from(uint32_t d, bool clipped, bool updates)
 {
     switch (d) {
-        case 64: return 10240u;
-        case 128: return clipped ? 12288u : 8192u;
-        case 192: return 8192u;
-        case 256: return clipped ? 12288u : 8192u;
-        case 512: return clipped ? 8192u : 6144u;
-        case 1024: return clipped ? 8192u : 4096u;
-        default: return d < 512u ? 5120u : 3072u;
+        case 64: return clipped || updates ? 10240u : 8192u;
+        case 128: return clipped ? 12288u : updates ? 5632u : 4608u;
+        case 192: return clipped ? 6656u : 4608u;
+        case 256: return clipped ? 7680u : updates ? 5632u : 4608u;
+        case 512: return clipped ? 6656u : 6144u;
+        case 1024: return clipped ? 6656u : 4608u;
+        case 704: case 768: return 768u;
+        default: return d < 512u ? 4608u : 2560u;
     }
 }
 
@@ -625,7 +625,8 @@ void launch_two_level(const float* g, size_t n, const ogq_params_t* p, float* lv
     const uint32_t regs = d / 64;
     // Buckets of up to 1024 elements: several per wavefront where there are enough of them (what is left, fewer than 2048 elements, gets
     // one wavefront per bucket in the same launch: one of its own cost 2.8 us).
-    if (regs <= 16 && nb >= several_buckets_from(d, p->clip_factor > 0.0f)) {
+    const bool updates = p->scheme == OGQ_BINGRAD_B && p->level_iters > 0u;
+    if (regs <= 16 && nb >= several_buckets_from(d, p->clip_factor > 0.0f, updates)) {
         switch (regs) {
 #define OGQ_CASE(E) case E: launch_bingrad_chunks<E>(g, n, p, lv, codes, st); return
             OGQ_CASE(1); OGQ_CASE(2); OGQ_CASE(3); OGQ_CASE(4); OGQ_CASE(5); OGQ_CASE(6); OGQ_CASE(7); OGQ_CASE(8);

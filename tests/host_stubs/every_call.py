@@ -5,7 +5,7 @@ Every scheme and width, every bucket size, clipping on and off, every power of t
 rounding_part.hip and bingrad.hip as number of buckets, with its neighbours, whole and ragged last buckets, sweeps where the dispatch looks at them,
 each with the kernel that the benchmark names for it, and every 64th number of buckets up to 40000 at the sizes of limits.py; the decoder with every number of workers at which it changes its form.
 Also the benchmark's workloads at several lengths, with the kernels that the benchmark says they take, and the calls that
-profiles/pool_scan.txt and pool_clip_scan.txt hold times of."""
+profiles/pool_scan.txt, pool_clip_scan.txt and bingrad_scan.txt hold times of."""
 import ctypes
 import json
 import os
@@ -51,6 +51,23 @@ def pool_scan(name):
                 other.append(values[2 * k])
                 pool.append(values[2 * k + 1])
     return times
+
+
+def bingrad_scan():
+    """(bucket size, rule, threshold updates, clipping factor, buckets), times with one bucket per wavefront and with several."""
+    d, numbers = 0, []
+    for line in open(os.path.join(ROOT, "profiles", "bingrad_scan.txt")):
+        head = re.match(r"(\d+) elements per bucket$", line)
+        if head:
+            d = int(head.group(1))
+        elif line.startswith("buckets") and d:
+            numbers = [int(x) for x in line.split()[1:]]
+        elif d and line.strip():
+            rule, updates, rest = line.split(",")
+            clip, *values = [float(x) for x in rest.replace("/", " ").split()]
+            assert len(values) == 2 * len(numbers), line
+            for k, nb in enumerate(numbers):
+                yield (d, rule, int(updates), clip, nb), values[2 * k], values[2 * k + 1]
 
 
 def main():
@@ -135,6 +152,13 @@ def main():
             once(f"quantize {rule} {sweeps} sweeps d {d} n {nb * d - cut} clip {clip}",
                  quantize(ADDRESS, nb * d - cut, ctypes.byref(p), ADDRESS, ADDRESS, None))
             scanned.append([d, rule, sweeps, nb, clip, stub.recorded_last(), other, pool])
+    shared = []
+    for (d, rule, updates, clip, nb), one, several in bingrad_scan():
+        scheme = ogq.BINGRAD_B if rule == "BinGrad-b" else ogq.SCALED_SIGN
+        p = ogq.make_params(d, 1, scheme, updates, 0, 0, clip)
+        once(f"quantize {rule} {updates} updates d {d} n {nb * d - 29} clip {clip}",
+             quantize(ADDRESS, nb * d - 29, ctypes.byref(p), ADDRESS, ADDRESS, None))
+        shared.append([d, clip, updates, nb, stub.recorded_last(), one, several])
     once("probe_read", lib.ogq_probe_read(ADDRESS, 64, ADDRESS, None))
     once("probe_copy", lib.ogq_probe_copy(ADDRESS, ADDRESS, 64, None))
     names = [stub.recorded_name(i).decode() for i in range(stub.recorded_kernels())]
@@ -142,6 +166,7 @@ def main():
                       "launches": {name: stub.recorded_launches_of(i) for i, name in enumerate(names)},
                       "named": [[what, kernel, names[i], stated, here] for what, kernel, i, stated, here in named],
                       "scanned": [[d, rule, sweeps, nb, clip, names[i], other, pool] for d, rule, sweeps, nb, clip, i, other, pool in scanned],
+                      "shared": [[d, clip, updates, nb, names[i], one, several] for d, clip, updates, nb, i, one, several in shared],
                       "decoded_sizes": {names[i]: sorted(sizes) for i, sizes in decoders.items()}}))
 
 

@@ -106,6 +106,20 @@ def test_the_pool_is_taken_where_the_record_shows_a_gain(recorded):
     assert {point: round(loss, 3) for point, loss in taken.items() if loss > 0.035} == {}
 
 
+def test_buckets_share_a_wavefront_where_the_record_shows_a_gain(recorded):
+    """profiles/bingrad_scan.txt: one bucket per wavefront or several; without updates on the mean of BinGrad-b and Scaled SignSGD.  0.05:
+    ranges that gain with a number in them that does not; 0.25: numbers below a limit that gain, with others between that lose."""
+    points = {}
+    for d, clip, updates, nb, launched, one, several in recorded["shared"]:
+        taken, ratios = points.setdefault((d, clip, updates, nb), (set(), []))
+        taken.add("bingrad_chunk_kernel" in launched)
+        ratios.append(several / one)
+    assert len(points) > 1600 and all(len(taken) == 1 for taken, _ in points.values())
+    change = {point: (taken == {True}, sum(ratios) / len(ratios) - 1.0) for point, (taken, ratios) in points.items()}
+    assert {point: loss for point, (taken, loss) in change.items() if taken and loss > 0.05} == {}
+    assert {point: gain for point, (taken, gain) in change.items() if not taken and gain < -0.25} == {}
+
+
 def _buckets_of_a_span(d):
     """The most buckets that any 1024 consecutive elements touch which begin at a multiple of 1024."""
     return max((start % d + 1023) // d + 1 for start in range(0, 1024 * d, 1024))

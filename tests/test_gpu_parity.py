@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import bench
 import oracle
 import paper_2002_11082_amd as ogq
 from paper_2002_11082_amd import synth
@@ -88,6 +89,20 @@ def test_bingrad_every_size_with_several_buckets_per_wavefront(d, clip):
         sample = sorted({*range(40), *range(nb - 40, nb), *map(int, rng.integers(0, nb, 200))})
         for scheme, iters in ((ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 3), (ogq.SCALED_SIGN, 0)):
             parity.check_quantize(g, d, 1, scheme, iters, clip_factor=clip, buckets=sample, tag=f"several-s{scheme}-d{d}-nb{nb}-it{iters}")
+
+
+@pytest.mark.parametrize("clip", [0.0, 2.5])
+@pytest.mark.parametrize("d", [64, 128, 192, 256, 448, 512, 640, 704, 832, 1024])
+def test_bingrad_both_sides_of_the_limit(d, clip):
+    """The number of buckets from which several share a wavefront, and one less."""
+    rng = np.random.default_rng(d)
+    for scheme, iters in ((ogq.BINGRAD_B, 0), (ogq.BINGRAD_B, 2), (ogq.SCALED_SIGN, 0)):
+        limit = bench.several_buckets_from(d, clip > 0, iters > 0)
+        for nb in (limit - 1, limit):
+            g = (rng.standard_t(3, nb * d) * 1e-3).astype(np.float32)
+            g[d:2 * d] = 0.25
+            sample = [*range(40), *range(nb - 40, nb), *map(int, rng.integers(0, nb, 40))]
+            parity.check_quantize(g[:nb * d - 5], d, 1, scheme, iters, clip_factor=clip, buckets=sample, tag=f"limit-s{scheme}-d{d}-nb{nb}-c{clip}")
 
 
 @pytest.mark.parametrize("d", [512, 1024])
