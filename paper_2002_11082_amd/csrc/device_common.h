@@ -122,8 +122,7 @@ __device__ __forceinline__ float wave_max(float x)
     return fmaxf(fmaxf(readlane_f32(x, 0), readlane_f32(x, 16)), fmaxf(readlane_f32(x, 32), readlane_f32(x, 48)));
 }
 
-constexpr int kDppRor0 = 0x120;   // + n: rotate by n = 1 .. 15 inside a row of 16 lanes
-constexpr int kDppRor8 = kDppRor0 + 8;  // partner lane ^ 8
+constexpr int kDppRor8 = 0x128;   // rotate by 8 inside a row of 16 lanes: partner lane ^ 8
 constexpr int kDppRowShl4 = 0x104;  // lane i takes lane i + 4 of its row
 constexpr int kDppRowShr4 = 0x114;  // lane i takes lane i - 4 of its row
 

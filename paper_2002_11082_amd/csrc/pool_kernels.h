@@ -19,10 +19,10 @@ namespace ogq {
 // barriers and most of a wavefront's scalar instructions; here the four rows work for two buckets and the steps need no barrier.
 // 143.7 M values in buckets of 4096, eight levels, two sweeps: 421 -> 368 us, with direct solves (group_solve_direct) and 1280 instead of 1024
 // bins, so that hardly a bin is too large for them, 310; 25.6 M values in buckets of 2048 124 -> 80 -> 69.
-// Bound by the solves' latency, during which a workgroup's other wavefronts wait, and the LDS (16 KB of values per bucket of 4096), which
-// holds the buckets of four workgroups; the vector units are busy for some 230 of the 310 us.  The solving wavefront runs at a raised
-// priority: its instructions go first on its SIMD.  Four buckets per workgroup, in rows of 8 lanes, were slower (418 us when two took 368):
-// fewer workgroups overlap.
+// Bound by the solves' latency (37 % of a workgroup's cycles, profiles/phase_cycles.txt), during which a workgroup's other wavefronts wait, and
+// the LDS (16 KB of values per bucket of 4096), which holds the buckets of four workgroups; the vector units are busy 0.81 of the time
+// (profiles/orq_cfg4_issue_counters_pmc.txt).  The solving wavefront runs at a raised priority: its instructions go first on its SIMD.  Four
+// buckets per workgroup, in rows of 8 lanes, were slower (418 us when two took 368): fewer workgroups overlap.
 // Four levels: four buckets of up to 2048 elements, a row each, so that a workgroup spends no more instructions on solves than with more
 // levels (25.6 M values in buckets of 2048, two sweeps, mean of four kinds of values: one wavefront per bucket 54.4 us, two buckets in a
 // workgroup 50.9, four 50.7; 8192 buckets 38 / 37 / 32).  Above 2048 elements the LDS of a workgroup (an address in 16 bits) holds two, whose
