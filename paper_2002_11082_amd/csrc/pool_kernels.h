@@ -296,7 +296,18 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 
     // ---- the levels of all buckets, on one wavefront (another one from workgroup to workgroup: a CU's wavefronts are dealt
     //      to its SIMDs in order) -----------------------------------------------------------------------------------------
-    if (wave == (blockIdx.x * 0x9E3779B1u >> 16) % (uint32_t)(NB * W)) {
+    // The random numbers, a third of the encoder, do not depend on the levels: the wavefronts that wait make theirs meanwhile, and most or
+    // all of those of the one that solves, which takes them through LDS.  Eight levels, two sweeps, 143.7 M values in buckets of 4096 310 -> 292 us
+    // (each its own, the solving wavefront behind the others: 300); four levels, 25.6 M in buckets of 2048 51.5 -> 45.8 (49.1).
+    const EncodeRange range = one_range<BITS>(my_len, begin + first, seed, index_offset, codes32);
+    constexpr uint32_t HELPERS = (uint32_t)(NB * W) - 1u;
+    constexpr int SHARE = HELPERS == 3u ? (C + 2) / 3 : C / 2;                        // chunks helper, helper + HELPERS, ... of them
+    constexpr int HANDED = (int)HELPERS * SHARE < C ? (int)HELPERS * SHARE : C;       // it makes the others itself
+    DrawsAhead<C> draws;
+    DrawsAhead<SHARE> share;
+    const uint32_t solver = (blockIdx.x * 0x9E3779B1u >> 16) % (HELPERS + 1u), helper = (wave - solver - 1u) & HELPERS;
+    const bool solves = wave == solver;
+    if (solves) {
         __builtin_amdgcn_s_setprio(3);
         if constexpr (W == 2) {
             // the second wavefronts' prefixes count from their own first position
@@ -327,8 +338,34 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                                                               return uniform_u32(pool_solve_general<Bucket>(at, limb, its_len, entry, lane)) != 0u;
                                                           });
         __builtin_amdgcn_s_setprio(0);
+    } else {
+        draws.template make<OneRange>(range);
+        const uint32_t its_bucket = blockIdx.x * (uint32_t)NB + solver / (uint32_t)W;
+        const size_t at = (size_t)its_bucket * bucket_size + PER_WAVE * (solver % (uint32_t)W);
+        share.template make<OneRange, (int)HELPERS>(one_range<BITS>(PER_WAVE, at, seed, index_offset, codes32), helper);
     }
     __syncthreads();
+    {
+        // (the grouped values are no longer read; the encoder's tables lie at their beginning)
+        static_assert(Bucket::D >= 256 * HANDED && (S <= kScaledWidthLevels || Bucket::D > 256 * HANDED), "place for both");
+        floatx4* place = reinterpret_cast<floatx4*>(lds.bucket[0].grouped + (Bucket::D - 256 * HANDED)) + lane;
+        if (!solves) {
+#pragma unroll
+            for (int t = 0; t < SHARE; ++t) {
+                const uint32_t c = helper + HELPERS * (uint32_t)t;
+                if (c < (uint32_t)HANDED) place[64u * c] = floatx4{share.draw[t][0], share.draw[t][1], share.draw[t][2], share.draw[t][3]};
+            }
+        }
+        __syncthreads();
+        if (solves) {
+            draws.template make<OneRange, 1, HANDED>(range);
+#pragma unroll
+            for (int c = 0; c < HANDED; ++c) {
+                const floatx4 x = place[64 * c];
+                draws.draw[c][0] = x.x; draws.draw[c][1] = x.y; draws.draw[c][2] = x.z; draws.draw[c][3] = x.w;
+            }
+        }
+    }
 
     float lv[S];
     lv[0] = low;
@@ -341,8 +378,8 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         for (int k = 1; k < S; ++k) mine = lane == (uint32_t)k ? lv[k] : mine;
         if (lane < (uint32_t)S) levels[(size_t)bucket * S + lane] = mine;
     }
-    orq_encode<C, S, BITS, FULL>(v, lv, my_len, begin + first, seed, index_offset, codes32, ReloadFromMemory{g + first, my_len, limit},
-                                 encoder_table<S, true>(my.grouped, part));
+    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged>(v, lv, range, ReloadFromMemory{g + first, my_len, limit},
+                                                                        encoder_table<S, true>(my.grouped, part), draws);
 }
 
 // (Five wavefronts per SIMD with four levels up to 1024 elements: 12290 buckets of 768, two sweeps, four 36 us, five 30.)

@@ -871,6 +871,12 @@ struct NoPairs {
 // exist in a chunk that does are NaN: no comparison with NaN holds, so their bits come out as 0.
 enum class Fill { kAll, kRagged, kWholeChunks };
 
+// The encoder's random numbers: made where an element is encoded, or before (DrawsAhead::make), where a wavefront waits anyway:
+// draw[c][k] = the draw of v[c][k], its upper 24 bits as a number.
+struct DrawsInPlace {
+    static constexpr bool kAhead = false;
+};
+
 // What the encoder needs to know about the elements a wavefront encodes.
 struct EncodeRange {
     uint32_t len;         // valid elements
@@ -879,6 +885,28 @@ struct EncodeRange {
     uint32_t row_groups;  // 64-element groups from row to row
     uint32_t k0, k1;      // Philox key
     uint32_t* words;      // the first element's packed words
+};
+
+template <int C>
+struct DrawsAhead {
+    static constexpr bool kAhead = true;
+    float draw[C][4];
+    // Chunks first + STRIDE c of the range into draw[c], c = BEGIN .. C - 1.  (In the lean form: a range that encode_is_plain() refuses has
+    // its draws made chunk by chunk.)
+    template <class Layout, int STRIDE = 1, int BEGIN = 0>
+    __device__ __forceinline__ void make(const EncodeRange& range, uint32_t first = 0)
+    {
+        if constexpr (BEGIN >= C) return;
+        const PhiloxWords words = philox_words((uint32_t)(range.block >> 32), range.k0, range.k1);
+#pragma unroll
+        for (int c = BEGIN; c < C; ++c) {
+            uint32_t r[4];
+            philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * (first + (uint32_t)(STRIDE * c)), words, r);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) draw[c][k] = (float)(r[k] >> 8);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
 };
 
 // Levels up to which the rounding test takes its width already multiplied by 2^-24 (above, the width is a difference of
@@ -924,10 +952,11 @@ __device__ __forceinline__ void transpose_codes(const uint32_t (&a)[4], uint32_t
 
 // Encodes and packs chunks c0 .. c0 + GROUP - 1 (256 elements each).  CAREFUL: valid for every width and Philox block;
 // otherwise encode_is_plain() holds.
-template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL, class Pairs>
+template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL, bool AHEAD, class Pairs>
 __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (&lv)[S], const float (&width)[S - 1], uint32_t c0,
                                               const EncodeRange& range, const PhiloxWords& words,
-                                              const NibbleTranspose& transpose, uint32_t lane, Pairs pairs)
+                                              const NibbleTranspose& transpose, uint32_t lane, Pairs pairs,
+                                              const float (*ahead)[4] = nullptr)
 {
     constexpr bool SCALED = !CAREFUL && S <= kScaledWidthLevels;
     constexpr bool LOOKUP = !CAREFUL && Pairs::kUsed;
@@ -944,7 +973,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
         if constexpr (FILL != Fill::kAll) {
             if (256u * c >= len) continue;
         }
-        uint32_t r[4];
+        float draws[4];  // upper 24 bits
         [[maybe_unused]] uint32_t index[4];
         [[maybe_unused]] floatx2 level[4];
         if constexpr (LOOKUP) {  // the looks into LDS go ahead of the random numbers
@@ -954,24 +983,32 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
                 level[k] = *(const LdsPair*)(uintptr_t)(pairs.table + 8u * index[k]);
             }
         }
-        if constexpr (CAREFUL) {
-            const uint64_t block = range.block + Layout::kBlocks * c + range.lane_block;
-            philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), range.k0, range.k1, r);
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) draws[k] = ahead[i][k];
         } else {
-            philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * c, words, r);
+            uint32_t r[4];
+            if constexpr (CAREFUL) {
+                const uint64_t block = range.block + Layout::kBlocks * c + range.lane_block;
+                philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), range.k0, range.k1, r);
+            } else {
+                philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * c, words, r);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) draws[k] = (float)(r[k] >> 8);
         }
 #pragma unroll
         for (int k = 3; k >= 0; --k) {
             const float x = v[i][k];
             if constexpr (LOOKUP) {
-                const bool up = (float)(r[k] >> 8) * level[k].y < x - level[k].x;
+                const bool up = draws[k] * level[k].y < x - level[k].x;
                 code[k] = code[k] << 4 | (index[k] + (up ? 1u : 0u));
                 continue;
             }
             const Interval<S> in = find_interval<S>(x, lv, width);
             const float delta = x - in.base;
             // u * width in fp32, u = the draw's upper 24 bits times 2^-24 (the factor is in the width where that is exact)
-            const float draw = SCALED ? (float)(r[k] >> 8) : (float)(r[k] >> 8) * 0x1p-24f;
+            const float draw = SCALED ? draws[k] : draws[k] * 0x1p-24f;
             const float scaled = draw * in.width;
             uint64_t carry = __ballot(scaled < delta);  // rounded up
 #pragma unroll
@@ -1046,9 +1083,9 @@ __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], con
 // (PairsInLds): three or two compares give the interval's index, one look-up its level and width, and the index plus the carry is
 // the code: 17.5 instead of 23 vector instructions per element beside Philox at eight levels (nine levels, buckets of 512, clipping,
 // 25.6 M values 66.0 -> 63.3 us; eight levels, 32768 172.9 -> 167.1).  The rare range that encode_is_plain() refuses is encoded chunk by chunk in a loop.
-template <class Layout, int C, int S, int BITS, Fill FILL, class ReloadFn, class Pairs = NoPairs>
+template <class Layout, int C, int S, int BITS, Fill FILL, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
 __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (&lv)[S], const EncodeRange& range, ReloadFn reload,
-                                           Pairs pairs = Pairs{})
+                                           Pairs pairs = Pairs{}, const Draws& draws = Draws{})
 {
     constexpr bool SCALED = S <= kScaledWidthLevels || Pairs::kUsed;
     const uint32_t lane = threadIdx.x & 63u;
@@ -1061,7 +1098,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         for (uint32_t c = 0; 256u * c < range.len; ++c) {
             float y[1][4];
             reload(c, y[0]);
-            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true>(y, lv, width, c, range, PhiloxWords{}, transpose, lane, NoPairs{});
+            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true, false>(y, lv, width, c, range, PhiloxWords{}, transpose, lane, NoPairs{});
         }
         return;
     }
@@ -1076,25 +1113,35 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         }
         wave_lds_sync();
     }
-    const PhiloxWords words = philox_words((uint32_t)(range.block >> 32), range.k0, range.k1);
+    PhiloxWords words{};
+    if constexpr (!Draws::kAhead) words = philox_words((uint32_t)(range.block >> 32), range.k0, range.k1);
     constexpr int GROUP = C < 8 ? C : 8;
 #pragma unroll
     for (int c0 = C - GROUP; c0 >= 0; c0 -= GROUP) {
         if constexpr (FILL != Fill::kAll) {
             if (256u * (uint32_t)c0 >= range.len) continue;  // nothing in these chunks: no words to write
         }
-        encode_chunks<Layout, GROUP, S, BITS, FILL, false>(&v[c0], lv, width, (uint32_t)c0, range, words, transpose, lane, pairs);
+        const float(*ahead)[4] = nullptr;
+        if constexpr (Draws::kAhead) ahead = &draws.draw[c0];
+        encode_chunks<Layout, GROUP, S, BITS, FILL, false, Draws::kAhead>(&v[c0], lv, width, (uint32_t)c0, range, words, transpose, lane, pairs, ahead);
     }
 }
 
-template <int C, int S, int BITS, bool FULL, class ReloadFn, class Pairs = NoPairs>
+// The `len` elements from global element `begin` on, as orq_encode takes them.
+template <int BITS>
+__device__ __forceinline__ EncodeRange one_range(uint32_t len, size_t begin, uint64_t seed, uint64_t index_offset, uint32_t* codes32)
+{
+    return EncodeRange{uniform_u32(len), (index_offset + begin) >> 2, threadIdx.x & 63u, 1u, (uint32_t)seed, (uint32_t)(seed >> 32),
+                       codes32 + begin / 64 * (2 * BITS)};
+}
+
+template <int C, int S, int BITS, bool FULL, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
 __device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
                                            uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32, ReloadFn reload,
-                                           Pairs pairs = Pairs{})
+                                           Pairs pairs = Pairs{}, const Draws& draws = Draws{})
 {
-    const EncodeRange range{uniform_u32(len), (index_offset + begin) >> 2, threadIdx.x & 63u, 1u, (uint32_t)seed, (uint32_t)(seed >> 32),
-                            codes32 + begin / 64 * (2 * BITS)};
-    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged>(v, lv, range, reload, pairs);
+    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged>(v, lv, one_range<BITS>(len, begin, seed, index_offset, codes32), reload,
+                                                                        pairs, draws);
 }
 
 // The table of levels of wavefront `wave` in the place of a grouped bucket, once the levels are solved (five and more of them).

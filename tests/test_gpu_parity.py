@@ -1116,6 +1116,20 @@ def test_several_buckets_per_workgroup(scheme, bits, sweeps, d, nb):
                               clip_factor=clip, tag=f"pool-s{scheme}-b{bits}-i{sweeps}-d{d}-nb{nb}-cut{cut}")
 
 
+@pytest.mark.parametrize("scheme,bits,d,nb", [(ogq.ORQ, 3, 640, 514), (ogq.ORQ, 3, 2048, 385), (ogq.ORQ_PAPER, 4, 3904, 1282), (ogq.ORQ, 3, 4096, 386),
+                                              (ogq.ORQ, 2, 704, 515), (ogq.ORQ, 2, 2048, 1283), (ogq.ORQ, 2, 4096, 387)])
+def test_random_numbers_of_the_solving_wavefront(scheme, bits, d, nb):
+    """The wavefronts of a workgroup make the random numbers of the one that solves its levels, another one from workgroup to workgroup: the upper
+    counter word turns in each of the first ones in turn, so that it differs between the wavefront that makes and the one that uses."""
+    rng = np.random.default_rng(d + bits)
+    g = (rng.standard_normal(nb * d) * 1e-3).astype(np.float32)
+    checked = list(range(18)) + [nb - 2, nb - 1]
+    for turn in (1, 2, 3, 5, 6, 9, 11, 12):
+        for cut in (0, d - 321):
+            parity.check_quantize(g[: nb * d - cut], d, bits, scheme, 2, seed=(7 << 32) + turn, index_offset=(1 << 34) - turn * d - 64 * (turn % 5),
+                                  buckets=checked, tag=f"ahead-s{scheme}-b{bits}-d{d}-turn{turn}-cut{cut}")
+
+
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 4, 1), (ogq.ORQ_PAPER, 3, 2)])
 def test_levels_in_bins_beyond_the_sort(scheme, bits, sweeps):
     """A level among 31 to 64 values of one bin, around the 32 that 8 lanes sort and the 64 that 16 lanes do; distinct values,
