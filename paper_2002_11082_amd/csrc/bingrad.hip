@@ -53,11 +53,13 @@ __device__ __forceinline__ void bingrad_bucket(Team team, uint32_t first_element
     const uint32_t padding = 64u * E * Team::kSize - len;
     if constexpr (CLIP) {
         uint32_t here = first;
-        const auto bucket_sum = [&](double x) {
+        const auto bucket_sums = [&](double& x, double& y) {
             if constexpr (!FULL && E > 16) asm volatile("" : "+v"(here));  // (the first pass's lane masks would not fit the scalar registers)
-            return team.sum(wave_sum(x));
+            x = wave_sum(x);
+            y = wave_sum(y);
+            team.sums(x, y);
         };
-        clip_in_registers<E>(v, len, clip, [&](int j) { return FULL || here + 64u * j < len; }, bucket_sum);
+        clip_in_registers<E>(v, len, clip, [&](int j) { return FULL || here + 64u * j < len; }, bucket_sums);
     }
 
     double part = 0.0;
@@ -387,37 +389,54 @@ __global__ __launch_bounds__(kWave* kBinGradWaves) __attribute__((amdgpu_waves_p
     const auto add = [](double a, double b) { return a + b; };
     const auto larger = [](float a, float b) { return fmaxf(a, b); };
     if constexpr (CLIP) {  // clip_in_registers, NB buckets at once
-        const double mean = reduce_buckets<NB, double>(
-                                lane,
-                                [&](auto q) {
-                                    double s = 0.0;
+        const double sum = reduce_buckets<NB, double>(
+            lane,
+            [&](auto q) {
+                double s = 0.0;
 #pragma unroll
-                                    for (int j = 0; j < E; ++j) s += (double)v[decltype(q)::value * E + j];
-                                    return s;
-                                },
-                                add) /
-                            (double)D;
+                for (int j = 0; j < E; ++j) s += (double)v[decltype(q)::value * E + j];
+                return s;
+            },
+            add);
         const double squares = reduce_buckets<NB, double>(
             lane,
             [&](auto q) {
-                constexpr int kQ = decltype(q)::value;
-                const double middle = readlane_f64(mean, (int)reverse6(kQ));
                 double s = 0.0;
 #pragma unroll
                 for (int j = 0; j < E; ++j) {
                     // (converted again: the fp64 copies of the first pass would not fit the registers)
-                    const double dv = (double)reread(v[kQ * E + j]) - middle;
-                    s += dv * dv;
+                    const double x = (double)reread(v[decltype(q)::value * E + j]);
+                    s = __builtin_fma(x, x, s);
                 }
                 return s;
             },
             add);
-        const float limit_of_mine = (float)((double)clip * sqrt(squares / (double)D));
+        bool cancels;
+        double about_mean = squares_about_mean(sum, squares, (double)D, cancels);
+        if (__builtin_expect(__ballot(cancels) != 0, 0)) {
+            const double mean = sum / (double)D;
+            const double again = reduce_buckets<NB, double>(
+                lane,
+                [&](auto q) {
+                    constexpr int kQ = decltype(q)::value;
+                    const double middle = readlane_f64(mean, (int)reverse6(kQ));
+                    double s = 0.0;
+#pragma unroll
+                    for (int j = 0; j < E; ++j) {
+                        const double dv = (double)reread(v[kQ * E + j]) - middle;
+                        s += dv * dv;
+                    }
+                    return s;
+                },
+                add);
+            about_mean = cancels ? again : about_mean;
+        }
+        const float limit_of_mine = (float)((double)clip * sqrt(about_mean / (double)D));
         for_each_bucket<NB>([&](auto q) {
             constexpr int kQ = decltype(q)::value;
             const float limit = readlane_f32(limit_of_mine, (int)reverse6(kQ));
 #pragma unroll
-            for (int j = 0; j < E; ++j) v[kQ * E + j] = fminf(fmaxf(v[kQ * E + j], -limit), limit);
+            for (int j = 0; j < E; ++j) v[kQ * E + j] = clipped(v[kQ * E + j], limit);
         });
     }
     // From here on lane l works for bucket q(l); the lane with the free bits clear ("home") and the one

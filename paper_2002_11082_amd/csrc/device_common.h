@@ -180,36 +180,64 @@ __device__ __forceinline__ uint32_t nibble_transpose(uint32_t x, const NibbleTra
     return __builtin_amdgcn_bitop3_b32(t.take, __builtin_amdgcn_alignbit(y, y, t.turn), x, 0xCA);
 }
 
-// Gradient clipping of a register-resident bucket (Section 5): v <- sign(v) * min(|v|, c * sigma) with
-// sigma^2 the population variance about the bucket mean, both in fp64.  valid(j) tells whether
-// register j of this lane holds a bucket element; bucket_sum(x) adds x over all lanes that hold the bucket.  Returns
-// the threshold.
-template <int N, class ValidFn, class SumFn>
-__device__ __forceinline__ float clip_in_registers(float (&v)[N], uint32_t len, float c, ValidFn valid, SumFn bucket_sum)
+// v within [-limit, limit], in one instruction (v_med3_f32).  limit = NaN (a bucket that is not finite): v as it is.
+__device__ __forceinline__ float clipped(float v, float limit) { return __builtin_amdgcn_fmed3f(v, -limit, limit); }
+
+// Variance times length of a bucket from its sum and its sum of squares, which fp64 fma adds without rounding a product (48 bits).
+// `cancels`: the square of the bucket's mean is more than an eighth of the mean of its squares, so that the difference would lose more than a part
+// of a bit; such a bucket, and one that is not finite, takes the sum of the squares about its mean.
+__device__ __forceinline__ double squares_about_mean(double sum, double squares, double len, bool& cancels)
 {
-    double part = 0.0;
-#pragma unroll
-    for (int j = 0; j < N; ++j) part += valid(j) ? (double)v[j] : 0.0;
-    const double mean = bucket_sum(part) / (double)len;
-    part = 0.0;
+    const double mean = sum / len;
+    cancels = !(sum * mean <= 0.125 * squares);
+    return __builtin_fma(-sum, mean, squares);
+}
+
+// Gradient clipping of a register-resident bucket (Section 5): v <- sign(v) * min(|v|, c * sigma) with
+// sigma^2 the population variance about the bucket mean, in fp64.  valid(j) tells whether
+// register j of this lane holds a bucket element; bucket_sums(x, y) adds x and y over all lanes that hold the bucket.  MEET: it has
+// barriers at which wavefronts of other buckets wait too, so that all call it equally often.  Returns the threshold.  (One pass and one reduction in place of two, and v_med3 in place of three instructions: nine levels, buckets of 512,
+// @@.)
+template <int N, bool MEET = false, class ValidFn, class SumsFn>
+__device__ __forceinline__ float clip_in_registers(float (&v)[N], uint32_t len, float c, ValidFn valid, SumsFn bucket_sums)
+{
+    double sum = 0.0, squares = 0.0;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        // converted again: fp64 copies of 32 values kept from the first pass would not fit the registers
-        if constexpr (N >= 32) asm volatile("" : "+v"(v[j]));
-        const double dv = (double)v[j] - mean;
-        part += valid(j) ? dv * dv : 0.0;
+        const double x = valid(j) ? (double)v[j] : 0.0;
+        sum += x;
+        squares = __builtin_fma(x, x, squares);
     }
-    const double sigma = sqrt(bucket_sum(part) / (double)len);
-    const float limit = (float)((double)c * sigma);
+    bucket_sums(sum, squares);
+    bool cancels;
+    double about_mean = squares_about_mean(sum, squares, (double)len, cancels);
+    double part = 0.0, unused = 0.0;
+    const bool again = __ballot(cancels) != 0;  // (every wavefront of a bucket, or none: they hold the same sums)
+    if (__builtin_expect(again, 0)) {
+        const double mean = sum / (double)len;
 #pragma unroll
-    for (int j = 0; j < N; ++j) v[j] = fminf(fmaxf(v[j], -limit), limit);
+        for (int j = 0; j < N; ++j) {
+            // converted again: fp64 copies of 32 values kept from the first pass would not fit the registers
+            asm volatile("" : "+v"(v[j]));
+            const double dv = (double)v[j] - mean;
+            part += valid(j) ? dv * dv : 0.0;
+        }
+    }
+    if (MEET || again) bucket_sums(part, unused);
+    about_mean = cancels ? part : about_mean;
+    const float limit = (float)((double)c * sqrt(about_mean / (double)len));
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] = clipped(v[j], limit);
     return limit;
 }
 
 template <int N, class ValidFn>
 __device__ __forceinline__ float clip_in_registers(float (&v)[N], uint32_t len, float c, ValidFn valid)
 {
-    return clip_in_registers<N>(v, len, c, valid, [](double x) { return wave_sum(x); });
+    return clip_in_registers<N>(v, len, c, valid, [](double& x, double& y) {
+        x = wave_sum(x);
+        y = wave_sum(y);
+    });
 }
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -234,6 +262,7 @@ __device__ __forceinline__ double uniform_f64(double x)
 struct OneWave {
     static constexpr int kSize = 1;
     __device__ __forceinline__ double sum(double x) { return x; }
+    __device__ __forceinline__ void sums(double&, double&) {}
     __device__ __forceinline__ void sum_and_max(double&, float&) {}
     __device__ __forceinline__ void sum_and_count(double&, uint32_t&) {}
 };
@@ -271,6 +300,19 @@ struct WaveTeam {
 #pragma unroll
         for (int w = 1; w < W; ++w) r += s[w].sum;
         return r;
+    }
+    __device__ __forceinline__ void sums(double& x, double& y)
+    {
+        const uint64_t u = (uint64_t)__double_as_longlong(y);
+        const TeamSlot* s = exchange(x, (uint32_t)u, (uint32_t)(u >> 32));
+        auto other = [](const TeamSlot& t) { return __longlong_as_double((long long)((uint64_t)t.b << 32 | t.a)); };
+        x = s[0].sum;
+        y = other(s[0]);
+#pragma unroll
+        for (int w = 1; w < W; ++w) {
+            x += s[w].sum;
+            y += other(s[w]);
+        }
     }
     __device__ __forceinline__ void sum_and_max(double& x, float& m)
     {

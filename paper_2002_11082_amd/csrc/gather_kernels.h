@@ -54,7 +54,7 @@ __device__ __forceinline__ uint32_t exact_floor_t_team(unsigned long long* limb,
     __syncthreads();
     if (tid < (uint32_t)kExactLimbs) limb[tid] = 0ull;
     __syncthreads();
-    for (uint32_t i = tid; i < len; i += threads) exact_add_shared(limb, fminf(fmaxf(g[i], -limit), limit) + 0.0f);
+    for (uint32_t i = tid; i < len; i += threads) exact_add_shared(limb, clipped(g[i], limit) + 0.0f);
     __syncthreads();
     uint32_t lo = 0u, hi = len;  // m = 0 fits
     uint32_t probe = guess < len ? guess : len;
@@ -94,9 +94,11 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
         uint32_t here = lane;
         limit = clip_in_registers<4 * C>(
             flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * here + (j & 3) < my_len); },
-            [&](double x) __attribute__((always_inline)) {
+            [&](double& x, double& y) __attribute__((always_inline)) {
                 if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
-                return team.sum(wave_sum(x));
+                x = wave_sum(x);
+                y = wave_sum(y);
+                team.sums(x, y);
             });
         if constexpr (!FULL) set_padding<C>(v, my_len, lane);
     }

@@ -116,12 +116,13 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     if (clip > 0.0f) {  // the same for every thread of the grid
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
         uint32_t here = lane;
-        limit = clip_in_registers<4 * C>(
+        limit = clip_in_registers<4 * C, (W > 1)>(
             flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * here + (j & 3) < my_len); },
-            [&](double x) __attribute__((always_inline)) {
+            [&](double& x, double& y) __attribute__((always_inline)) {
                 if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
-                if constexpr (W == 1) return wave_sum(x);
-                else return team.sum(wave_sum(x));
+                x = wave_sum(x);
+                y = wave_sum(y);
+                if constexpr (W > 1) team.sums(x, y);
             });
         if constexpr (!FULL) set_padding<C>(v, my_len, lane);
     }

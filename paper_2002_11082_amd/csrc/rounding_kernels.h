@@ -1341,7 +1341,7 @@ struct ReloadFromMemory {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint32_t e = 256u * c + 4u * (threadIdx.x & 63u) + (uint32_t)k;
-            y[k] = e < len ? fminf(fmaxf(g[e], -limit), limit) : kNoElement;
+            y[k] = e < len ? clipped(g[e], limit) : kNoElement;
         }
     }
 };
@@ -2059,17 +2059,21 @@ __device__ __forceinline__ void clip_small_buckets(float (&v)[4], uint32_t len, 
     if constexpr (!FULL) count = q * D < len ? (len - q * D < D ? len - q * D : D) : 1u;  // (no element: nothing is stored)
     clip_in_registers<4>(
         v, count, clip, [&](int j) { return FULL || 4u * lane + j < len; },
-        [&](double x) __attribute__((always_inline)) {
-            x += dpp_f64<kDppXor1>(x);
-            x += dpp_f64<kDppXor2>(x);
-            x += dpp_f64<kDppHalfMirror>(x);
-            x += dpp_f64<kDppMirror>(x);
-            if constexpr (G == 32u) {
-                const uint64_t u = (uint64_t)__double_as_longlong(x);
-                const uint32_t lo = lane_xor<16>((uint32_t)u, lane), hi = lane_xor<16>((uint32_t)(u >> 32), lane);
-                x += __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-            }
-            return x;
+        [&](double& sum, double& squares) __attribute__((always_inline)) {
+            auto over_group = [&](double x) __attribute__((always_inline)) {
+                x += dpp_f64<kDppXor1>(x);
+                x += dpp_f64<kDppXor2>(x);
+                x += dpp_f64<kDppHalfMirror>(x);
+                x += dpp_f64<kDppMirror>(x);
+                if constexpr (G == 32u) {
+                    const uint64_t u = (uint64_t)__double_as_longlong(x);
+                    const uint32_t lo = lane_xor<16>((uint32_t)u, lane), hi = lane_xor<16>((uint32_t)(u >> 32), lane);
+                    x += __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+                }
+                return x;
+            };
+            sum = over_group(sum);
+            squares = over_group(squares);
         });
 }
 
@@ -2596,9 +2600,11 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
         uint32_t here = lane;
         limit = clip_in_registers<4 * C>(
             flat, len, clip, [&](int j) { return FULL || (64u * (j & ~3) + 4u * here + (j & 3) < my_len); },
-            [&](double x) __attribute__((always_inline)) {
+            [&](double& x, double& y) __attribute__((always_inline)) {
                 if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
-                return team.sum(wave_sum(x));
+                x = wave_sum(x);
+                y = wave_sum(y);
+                team.sums(x, y);
             });
         if constexpr (!FULL) set_padding<C>(v, my_len, lane);
     }

@@ -98,7 +98,7 @@ struct ReloadRow {
     {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            y[k] = fminf(fmaxf(g[4u * LANES * c + 4u * (threadIdx.x & (uint32_t)(LANES - 1)) + (uint32_t)k], -limit), limit);
+            y[k] = clipped(g[4u * LANES * c + 4u * (threadIdx.x & (uint32_t)(LANES - 1)) + (uint32_t)k], limit);
     }
 };
 
@@ -146,7 +146,10 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         float(&flat)[4 * C] = reinterpret_cast<float(&)[4 * C]>(v);
         limit = clip_in_registers<4 * C>(
             flat, len, clip, [&](int j) { return EXACT || (uint32_t)(j >> 2) < chunks; },
-            [&](double x) { return row_sum_f64<LANES>(x, lane); });
+            [&](double& x, double& y) {
+                x = row_sum_f64<LANES>(x, lane);
+                y = row_sum_f64<LANES>(y, lane);
+            });
     }
 
     // ---- extremes of every row ---------------------------------------------------------------------
