@@ -25,6 +25,7 @@ static_assert(sizeof(GroupLevel) == 32, "addressed by shifts");
 struct ScaledBins {
     float scale, offset;  // y = magnitude * scale + offset
     uint32_t factor;      // bins per unit in the last place of y, times 2^32
+    uint64_t origin;      // what `offset` times `factor` is taken off with
 };
 
 template <int HALF>
@@ -37,6 +38,8 @@ __device__ __forceinline__ ScaledBins scaled_bins(float mean_magnitude, uint32_t
     b.offset = fminf(unit * b.scale, 1.0f);  // (infinities: 1)
     const uint32_t range = 0x3F800000u - __float_as_uint(b.offset);
     b.factor = (uint32_t)fminf((float)HALF * 0x1p32f * __builtin_amdgcn_rcpf((float)range + 1.0f), 0x1.fffffep31f);
+    b.origin = 0u - (uint64_t)__float_as_uint(b.offset) * b.factor;
+    asm("" : "+v"(b.origin));  // (known, it is turned back into a subtraction and a wider product)
     return b;
 }
 
@@ -44,7 +47,8 @@ template <int HALF>
 __device__ __forceinline__ uint32_t magnitude_bin(float value, const ScaledBins& b)
 {
     const uint32_t y = __float_as_uint(__builtin_fmaf(__builtin_fabsf(value), b.scale, b.offset));
-    return umin32(__umulhi(y - __float_as_uint(b.offset), b.factor), (uint32_t)(HALF - 1));  // (rounding near the largest; NaN)
+    // (y's bits - offset's bits) * factor, one multiply-add; the minimum: rounding near the largest, NaN
+    return umin32((uint32_t)(((uint64_t)y * b.factor + b.origin) >> 32), (uint32_t)(HALF - 1));
 }
 
 // Bin of a value (with -0 already turned into +0) counted from the middle: -HALF .. HALF - 1.
@@ -52,6 +56,21 @@ template <int HALF>
 __device__ __forceinline__ int32_t signed_bin(float canonical, const ScaledBins& b)
 {
     return (int32_t)magnitude_bin<HALF>(canonical, b) ^ ((int32_t)__float_as_uint(canonical) >> 31);
+}
+
+// Grouping.  A bin's counter begins as the LDS address of its entry of `bin_start` in the upper half and that of the grouped values in the
+// lower one, and counts in bytes.  So what the returning add hands an element holds both addresses that the scatter needs, already added up: a
+// shift for the start, a 16-bit addition for the place: two vector instructions per element where packing position and counter, and two additions
+// to each half, took five (25.6 M values in buckets of 2048, four levels, 45.9 -> 44.4 us; 143.7 M in buckets of 4096, eight, 293 -> 289).
+__device__ __forceinline__ uint32_t counter_start(uint32_t starts, uint32_t grouped, uint32_t bin) { return (starts << 16 | grouped) + (bin << 17); }
+
+// Two starts of 16 bits, whatever lies above.
+__device__ __forceinline__ uint32_t two_starts(uint32_t start, uint32_t next) { return __builtin_amdgcn_perm(next, start, 0x05040100u); }
+
+// LDS address of the element's place in the grouped values, from what its counter returned.
+__device__ __forceinline__ uint32_t place_in_bin(uint32_t slot)
+{
+    return (uint16_t)(*(const LdsHalf*)(uintptr_t)(slot >> 16) + (uint16_t)slot);
 }
 
 // A bucket in LDS as one lane of its group sees it.

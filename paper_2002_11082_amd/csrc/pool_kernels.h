@@ -103,11 +103,14 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 
     float v[C][4];
     load_range<C, FULL>(v, g, first, len, my_len, lane);
+    uint32_t grouped_at = (uint32_t)(uintptr_t)((LdsWord*)my.grouped);
+    asm("" : "+s"(grouped_at));
     {
         constexpr uint32_t ZEROS = B / (64u * W) / 2u;
         uint2* mine = reinterpret_cast<uint2*>(my.bin_count) + ZEROS * (64u * part + lane);
+        const uint32_t count = counter_start((uint32_t)(uintptr_t)((LdsHalf*)my.bin_start), grouped_at, 2u * ZEROS * (64u * part + lane));
 #pragma unroll
-        for (uint32_t i = 0; i < ZEROS; ++i) mine[i] = make_uint2(0u, 0u);
+        for (uint32_t i = 0; i < ZEROS; ++i) mine[i] = make_uint2(count + (i << 18), count + (i << 18) + (1u << 17));
         if (part == 0u && lane == 0u) my.tiny = 0u;
     }
     WaveTeam<W> team{my.slots, part, 0u};
@@ -157,7 +160,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     bins_of.factor = uniform_u32(bins_of.factor);
 
     // ---- histogram: the returning LDS add hands every element its position inside its bin ------------------
-    uint32_t slot[C][4];  // LDS address of the bin's counter | 4 * position inside the bin << 16
+    uint32_t slot[C][4];  // what the bin's counter returned (counter_start)
     {
         const float zero = opaque_zero();
         uint32_t middle = (uint32_t)(uintptr_t)((LdsWord*)my.bin_count + HALF);
@@ -172,9 +175,8 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                     const bool valid = FULL || 256u * c + 4u * here + k < my_len;
                     // (padding adds 0 to one bin per lane: no branch)
                     const uint32_t counter = middle + 4u * (uint32_t)(valid ? signed_bin<(int)HALF>(v[c][k] + zero, bins_of) : (int32_t)here);
-                    const uint32_t position = __hip_atomic_fetch_add((LdsWord*)(uintptr_t)counter, valid ? 4u : 0u, __ATOMIC_RELAXED,
-                                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-                    slot[c][k] = __builtin_amdgcn_perm(position, counter, 0x05040100u);
+                    slot[c][k] = __hip_atomic_fetch_add((LdsWord*)(uintptr_t)counter, valid ? 4u : 0u, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             } else {
 #pragma unroll
@@ -197,6 +199,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         }
 #pragma unroll
         for (uint32_t t = 0; t < PER; ++t) total += count[t];
+        total -= PER * grouped_at;  // (the lower 16 bits are what counts)
         const uint32_t incl = wave_inclusive_scan_u32(total);
         uint32_t start = incl - total;
         if constexpr (W == 2)  // all counts together make the bucket
@@ -204,9 +207,9 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         uint32_t* pairs = reinterpret_cast<uint32_t*>(my.bin_start) + PER / 2u * (64u * part + lane);
 #pragma unroll
         for (uint32_t t = 0; t < PER / 2u; ++t) {
-            const uint32_t next = start + count[2 * t];
-            pairs[t] = start | next << 16;
-            start = next + count[2 * t + 1];
+            const uint32_t next = start + count[2 * t] - grouped_at;
+            pairs[t] = two_starts(start, next);
+            start = next + count[2 * t + 1] - grouped_at;
         }
         if (part == (uint32_t)W - 1u && lane == 63u) my.bin_start[B] = (uint16_t)start;  // = 4 len
     }
@@ -214,9 +217,6 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 
     // ---- scatter the values into their bins (bin starts of a group of chunks read before its writes) ----------
     {
-        char* grouped = reinterpret_cast<char*>(my.grouped);
-        // (a start is half as wide as a counter)
-        const uint32_t starts = (uint32_t)(uintptr_t)((LdsWord*)my.bin_start) - (uint32_t)(uintptr_t)((LdsWord*)my.bin_count) / 2u;
         constexpr int GROUP = 4;
         uint32_t here = lane;
         if constexpr (!FULL) asm volatile("" : "+v"(here));  // (see set_padding)
@@ -227,7 +227,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
             for (int c = c0; c < c0 + GROUP; ++c)
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    slot[c][k] = *(const LdsHalf*)(uintptr_t)(starts + __builtin_amdgcn_ubfe(slot[c][k], 1u, 15u)) + (slot[c][k] >> 16);
+                    slot[c][k] = place_in_bin(slot[c][k]);
 #pragma unroll
             for (int c = c0; c < c0 + GROUP; ++c)
 #pragma unroll
@@ -237,10 +237,10 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                         // padding goes where it lies in the bucket, behind all elements, as zeros that the prefix may add
                         const uint32_t e = 256u * c + 4u * here + k;
                         const bool valid = e < my_len;
-                        at = valid ? at : 4u * (first + e);
+                        at = valid ? at : grouped_at + 4u * (first + e);
                         bits = valid ? bits : 0u;
                     }
-                    *reinterpret_cast<uint32_t*>(grouped + at) = bits;
+                    *(LdsWord*)(uintptr_t)at = bits;
                 }
         }
     }

@@ -29,7 +29,10 @@ template <int LANES, int C, int S>
 struct alignas(16) RowLds {
     static constexpr int ROWS = 64 / LANES;
     static constexpr int D = 4 * LANES * C;  // element capacity of a row
-    static constexpr int B = 128, HALF = B / 2;  // bins
+    // Bins.  Eight rows of three levels: 80, so that 25 wavefronts of 6240 bytes fit a CU's LDS (128 bins: 21), and a lane's ten counters are read
+    // without bank conflicts; with counter_start and the sum of compares, 25.6 M values in buckets of 128 38.4 -> 34.4 us on one card, 38.6 -> 37.5 on
+    // another.
+    static constexpr int B = LANES == 8 && S <= 3 ? 80 : 128, HALF = B / 2;
     static constexpr int CHAINS = S > 4 && LANES == 16 ? 2 : 1;  // groups of lanes that solve a bucket's levels
     static constexpr int GROUP = LANES / CHAINS;
     static constexpr int BLOCK = D >= 512 || GROUP > 8 ? 16 : 8;  // positions per entry of the fp64 prefix
@@ -121,6 +124,10 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
     using Lds = RowLds<LANES, C, S>;
     constexpr uint32_t B = Lds::B, HALF = B / 2, D = Lds::D;
     constexpr uint32_t PER = B / LANES;  // bins per lane
+    constexpr uint32_t PIECE = PER % 4u == 0u ? 4u : 2u;  // counters read or written at once
+    struct alignas(4 * PIECE) CounterPiece {
+        uint32_t at[PIECE];
+    };
     constexpr bool GROUPED = S > 2 && RULE != kEven;
     constexpr bool SUMS = RULE == kOptimal && Lds::SUMS;
     const uint32_t lane = threadIdx.x & 63u, row = lane / LANES, i = lane & (uint32_t)(LANES - 1);
@@ -136,10 +143,16 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + 4 * LANES * c + 4 * i));
         v[c][0] = q.x; v[c][1] = q.y; v[c][2] = q.z; v[c][3] = q.w;
     });
+    const uint32_t grouped_at = (uint32_t)(uintptr_t)((LdsWord*)lds.grouped);
     if constexpr (GROUPED) {
-        uint4* mine = reinterpret_cast<uint4*>(lds.bin_count) + PER / 4u * lane;
+        const uint32_t count = counter_start((uint32_t)(uintptr_t)((LdsHalf*)lds.bin_start), grouped_at, PIECE * lane);
 #pragma unroll
-        for (uint32_t q = 0; q < PER / 4u; ++q) mine[q] = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t q = 0; q < PER / PIECE; ++q) {  // (neighbours write neighbouring counters: no bank conflicts)
+            CounterPiece x;
+#pragma unroll
+            for (uint32_t t = 0; t < PIECE; ++t) x.at[t] = count + ((64u * PIECE * q + t) << 17);
+            reinterpret_cast<CounterPiece*>(lds.bin_count)[64u * q + lane] = x;
+        }
     }
     float limit = __uint_as_float(0x7F800000u);  // clipping threshold
     if (clip > 0.0f) {  // the same for every thread of the grid
@@ -172,7 +185,7 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         const ScaledBins bins = scaled_bins<(int)HALF>(mean, mag_max);
 
         // ---- histogram: the returning LDS add hands every element its position inside its bin --------
-        uint32_t slot[C][4];  // LDS address of the bin's counter | 4 * position inside the bin << 16
+        uint32_t slot[C][4];  // what the bin's counter returned (counter_start)
         {
             wave_lds_sync();
             const float zero = opaque_zero();
@@ -181,9 +194,7 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const uint32_t counter = middle + 4u * (uint32_t)signed_bin<(int)HALF>(v[c][k] + zero, bins);
-                    const uint32_t position =
-                        __hip_atomic_fetch_add((LdsWord*)(uintptr_t)counter, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    slot[c][k] = __builtin_amdgcn_perm(position, counter, 0x05040100u);
+                    slot[c][k] = __hip_atomic_fetch_add((LdsWord*)(uintptr_t)counter, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             });
             wave_lds_sync();
@@ -191,22 +202,25 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
 
         // ---- bin starts: exclusive prefix over the row's counts (lane i owns PER bins) ----------------
         {
-            const uint4* mine = reinterpret_cast<const uint4*>(lds.bin_count) + PER / 4u * lane;
+            const CounterPiece* mine = reinterpret_cast<const CounterPiece*>(lds.bin_count) + PER / PIECE * lane;
             uint32_t count[PER], total = 0;
 #pragma unroll
-            for (uint32_t q = 0; q < PER / 4u; ++q) {
-                const uint4 x = mine[q];
-                count[4 * q] = x.x; count[4 * q + 1] = x.y; count[4 * q + 2] = x.z; count[4 * q + 3] = x.w;
+            for (uint32_t q = 0; q < PER / PIECE; ++q) {
+                const CounterPiece x = mine[q];
+#pragma unroll
+                for (uint32_t t = 0; t < PIECE; ++t) count[PIECE * q + t] = x.at[t];
             }
 #pragma unroll
             for (uint32_t t = 0; t < PER; ++t) total += count[t];
+            // (the lower 16 bits are what counts)
+            total -= PER * grouped_at;
             uint32_t start = 4u * D * row + row_scan_u32<LANES>(total, i) - total;
             uint32_t* pairs = reinterpret_cast<uint32_t*>(lds.bin_start) + PER / 2u * lane;
 #pragma unroll
             for (uint32_t t = 0; t < PER / 2u; ++t) {
-                const uint32_t next = start + count[2 * t];
-                pairs[t] = start | next << 16;
-                start = next + count[2 * t + 1];
+                const uint32_t next = start + count[2 * t] - grouped_at;
+                pairs[t] = two_starts(start, next);
+                start = next + count[2 * t + 1] - grouped_at;
             }
             if (lane == 63u) lds.bin_start[Lds::ROWS * B] = (uint16_t)start;
         }
@@ -215,8 +229,6 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         // ---- scatter the values into their bins (bin starts of a group of chunks read before its writes) ----
         char* grouped = reinterpret_cast<char*>(lds.grouped);
         {
-            // (a start is half as wide as a counter)
-            const uint32_t starts = (uint32_t)(uintptr_t)((LdsWord*)lds.bin_start) - (uint32_t)(uintptr_t)((LdsWord*)lds.bin_count) / 2u;
             constexpr int BATCH = C < 4 ? C : 4;
 #pragma unroll
             for (int c0 = 0; c0 < C; c0 += BATCH) {
@@ -225,14 +237,14 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
                     if (EXACT || (uint32_t)c < chunks) {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            slot[c][k] = *(const LdsHalf*)(uintptr_t)(starts + __builtin_amdgcn_ubfe(slot[c][k], 1u, 15u)) + (slot[c][k] >> 16);
+                            slot[c][k] = place_in_bin(slot[c][k]);
                     }
 #pragma unroll
                 for (int c = c0; c < c0 + BATCH; ++c)
                     if (EXACT || (uint32_t)c < chunks) {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            *reinterpret_cast<uint32_t*>(grouped + slot[c][k]) = __float_as_uint(v[c][k]);
+                            *(LdsWord*)(uintptr_t)slot[c][k] = __float_as_uint(v[c][k]);
                     }
             }
             wave_lds_sync();
@@ -353,10 +365,11 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         encode_all<Rows<LANES>, C, S, BITS, FILL>(v, lv, range, ReloadRow<LANES>{g, limit});
 }
 
+// (Eight rows of three levels: 80 registers, six wavefronts per SIMD, which their LDS allows.)
 // Blocks 0 .. singles - 1 take the buckets behind the last whole span (a few whole ones and a cut-off one), one each as in
 // orq_quantize_kernel and first so that they do not end the launch alone; the others take a span each.
 template <int LANES, int C, int S, int BITS, bool EXACT, int RULE>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? (EXACT ? 4 : 3) : 1))) void orq_rows_kernel(const float* __restrict__ grad, size_t n, uint32_t bucket_size,
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? (EXACT ? 4 : 3) : LANES == 8 && S <= 3 ? 6 : 1))) void orq_rows_kernel(const float* __restrict__ grad, size_t n, uint32_t bucket_size,
                                                          uint32_t sweeps, float clip, uint32_t num_buckets, uint32_t spans,
                                                          uint64_t seed, uint64_t index_offset, float* __restrict__ levels,
                                                          uint32_t* __restrict__ codes32)
