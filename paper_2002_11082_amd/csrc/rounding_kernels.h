@@ -38,7 +38,10 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 
 // The same where c1 is wave-uniform: the first two rounds are then partly scalar (one product and one exclusive or of
 // each; written out because the compiler takes the scalar product for a vector one).  What depends on c1 and the key alone
-// is made once and held in scalar registers: the compiler would make it again behind every branch.
+// is made once and held in registers: the compiler would make it again behind every branch.  VECTOR: in vector registers.  An exclusive or with a
+// scalar operand issues in four cycles, one of vector registers alone in little more than half of that where other wavefronts fill in, and a Philox
+// block has 17 of them; but 19 moves come first, which pay from some eight blocks on (25.6 M values in buckets of 2048, TernGrad 21.3 -> 20.7 us;
+// 143.7 M in buckets of 4096, eight levels, 293 -> 287; buckets of 128, four blocks: no gain).
 struct PhiloxWords {
     uint32_t first;       // k1
     uint32_t second[2];   // of round 2: what x0 and x2 are combined with
@@ -46,6 +49,7 @@ struct PhiloxWords {
     uint32_t k0[8], k1[7];  // the keys of rounds 3 .. 10 and 4 .. 10
 };
 
+template <bool VECTOR>
 __device__ __forceinline__ PhiloxWords philox_words(uint32_t c1, uint32_t k0, uint32_t k1)
 {
     constexpr uint32_t kMulA = 0xD2511F53u, kWeylA = 0x9E3779B9u, kWeylB = 0xBB67AE85u;
@@ -60,8 +64,12 @@ __device__ __forceinline__ PhiloxWords philox_words(uint32_t c1, uint32_t k0, ui
 #pragma unroll
     for (uint32_t r = 0; r < 7; ++r) w.k1[r] = k1 + (r + 3u) * kWeylB;
     auto hold = [](uint32_t& x) {
-        x = uniform_u32(x);
-        asm("" : "+s"(x));
+        if constexpr (VECTOR) {
+            asm("" : "+v"(x));
+        } else {
+            x = uniform_u32(x);
+            asm("" : "+s"(x));
+        }
     };
     hold(w.first); hold(w.second[0]); hold(w.second[1]); hold(w.third);
 #pragma unroll
@@ -828,6 +836,30 @@ __device__ __forceinline__ uint32_t push_bit(uint32_t x, uint64_t mask)
     return r;
 }
 
+// 2 x + (1 in the lanes where a < b): a compare and an add with carry, two wait states between them (the compiler does not look into the
+// asm).  Of two such pairs one's instructions are most of the other's wait.
+__device__ __forceinline__ void push_less(uint32_t& x, float a, float b)
+{
+    asm("v_cmp_lt_f32_e32 vcc, %1, %2\n\ts_nop 1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(x) : "v"(a), "v"(b) : "vcc");
+}
+
+__device__ __forceinline__ void push_less(uint32_t& x, float a, float b, uint32_t& y, float c, float d)
+{
+    uint64_t first, second;
+    asm("v_cmp_lt_f32_e64 %2, %4, %5\n\tv_cmp_lt_f32_e64 %3, %6, %7\n\ts_nop 0\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\tv_addc_co_u32_e64 %1, vcc, %1, %1, %3"
+        : "+v"(x), "+v"(y), "=&s"(first), "=&s"(second)
+        : "v"(a), "v"(b), "v"(c), "v"(d)
+        : "vcc");
+}
+
+// The largest number below x (x finite).
+__device__ __forceinline__ float next_below(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    return __uint_as_float((u << 1) == 0u ? 0x80000001u : (u >> 31) != 0u ? u + 1u : u - 1u);
+}
+
 // How the elements a wavefront encodes lie in its registers.  kBlocks: Philox blocks from chunk to chunk.  group, half:
 // which half of which 64-element group the lanes 8 h .. 8 h + 7 hold of chunk c; row_groups =
 // 64-element groups from row to row.
@@ -897,7 +929,7 @@ struct DrawsAhead {
     __device__ __forceinline__ void make(const EncodeRange& range, uint32_t first = 0)
     {
         if constexpr (BEGIN >= C) return;
-        const PhiloxWords words = philox_words((uint32_t)(range.block >> 32), range.k0, range.k1);
+        const PhiloxWords words = philox_words<(C - BEGIN > 4)>((uint32_t)(range.block >> 32), range.k0, range.k1);
 #pragma unroll
         for (int c = BEGIN; c < C; ++c) {
             uint32_t r[4];
@@ -912,6 +944,14 @@ struct DrawsAhead {
 // Levels up to which the rounding test takes its width already multiplied by 2^-24 (above, the width is a difference of
 // two selected levels, see find_interval).
 constexpr int kScaledWidthLevels = 4;
+// Levels up to which the code is a sum of compares (LADDER in encode_chunks).  An element's code is the number of rungs k, 0 .. S - 2, with
+// u * width_k < x - level_k: below its interval that never holds, as the right side is negative, and above it always, as x - level_k is then at
+// least width_k, in fp32 too, and u * width_k at most the number below width_k.  That leaves intervals of width 0.  One that is not the last counts for
+// every element from its level on: there the number below the level stands in its place.  The last one never counts.  No selects, and the products and
+// compares of the rungs do not wait for each other: 25.6 M values in buckets of 32768, ORQ-3, 45.5 -> 44.3 us; with evenly spaced levels, whose
+// two products are one and whose middle level is 0, TernGrad 21.8 -> 21.3.  Four levels take 14 instructions that way where the selects take
+// 13, and were slower (44.0 -> 44.8).
+constexpr int kLadderLevels = 3;
 
 // Index of an element's interval (see find_interval; five, eight or nine levels).
 template <int S>
@@ -951,14 +991,15 @@ __device__ __forceinline__ void transpose_codes(const uint32_t (&a)[4], uint32_t
 }
 
 // Encodes and packs chunks c0 .. c0 + GROUP - 1 (256 elements each).  CAREFUL: valid for every width and Philox block;
-// otherwise encode_is_plain() holds.
-template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL, bool AHEAD, class Pairs>
+// otherwise encode_is_plain() holds.  EVEN: three levels -M, 0, M.
+template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL, bool AHEAD, bool EVEN, class Pairs>
 __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (&lv)[S], const float (&width)[S - 1], uint32_t c0,
                                               const EncodeRange& range, const PhiloxWords& words,
                                               const NibbleTranspose& transpose, uint32_t lane, Pairs pairs,
                                               const float (*ahead)[4] = nullptr)
 {
     constexpr bool SCALED = !CAREFUL && S <= kScaledWidthLevels;
+    constexpr bool LADDER = !CAREFUL && S <= kLadderLevels;
     constexpr bool LOOKUP = !CAREFUL && Pairs::kUsed;
     constexpr int PLANES = 8 / GROUP;                // planes that share a register for the transpose
     constexpr int REGS = (BITS + PLANES - 1) / PLANES;
@@ -967,6 +1008,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
 #pragma unroll
     for (int p = 0; p < BITS; ++p) plane[p] = 0;
     [[maybe_unused]] uint32_t code[4] = {0u, 0u, 0u, 0u};  // (LOOKUP) a nibble per chunk
+    [[maybe_unused]] uint32_t rung[2] = {0u, 0u};          // (LADDER) a bit per element: past rung t
 #pragma unroll
     for (int i = GROUP - 1; i >= 0; --i) {
         const uint32_t c = c0 + (uint32_t)i;
@@ -1005,6 +1047,13 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
                 code[k] = code[k] << 4 | (index[k] + (up ? 1u : 0u));
                 continue;
             }
+            if constexpr (LADDER) {
+                if constexpr (S == 3)
+                    push_less(rung[0], draws[k] * width[0], x - lv[0], rung[1], draws[k] * width[EVEN ? 0 : 1], EVEN ? x : x - lv[1]);
+                else
+                    push_less(rung[0], draws[k] * width[0], x - lv[0]);
+                continue;
+            }
             const Interval<S> in = find_interval<S>(x, lv, width);
             const float delta = x - in.base;
             // u * width in fp32, u = the draw's upper 24 bits times 2^-24 (the factor is in the width where that is exact)
@@ -1021,6 +1070,10 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
         __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (LOOKUP) transpose_codes<BITS>(code, plane);
+    if constexpr (LADDER) {
+        plane[0] = rung[0] ^ rung[1];
+        if constexpr (S > 2) plane[1] = rung[1];
+    }
     if constexpr (GROUP == 1) {
         // a single chunk: the 8 lanes of a half word or their nibbles together, and lane p of them stores plane p
         const uint32_t j = lane & 7u, h = lane >> 3;
@@ -1056,7 +1109,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
 
 // Whether the lean form of encode_chunks may be used: all of the range's Philox blocks share the upper counter word, and
 // (where the widths are scaled) no width is so small that width * 2^-24 rounds.  Both hold for all but a few buckets
-// that one meets in earnest.
+// that one meets in earnest.  The rungs of up to three levels also want finite widths.
 template <int CHUNKS, int S, bool SCALED>
 __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], const EncodeRange& range)
 {
@@ -1066,6 +1119,12 @@ __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], con
 #pragma unroll
         for (int k = 0; k < S - 1; ++k) smallest = umin32(smallest, __float_as_uint(width[k]) - 1u);
         plain = plain && __ballot(smallest < __float_as_uint(0x1p-102f) - 1u) == 0;
+    }
+    if constexpr (S <= kLadderLevels) {
+        bool finite = true;
+#pragma unroll
+        for (int k = 0; k < S - 1; ++k) finite = finite && __builtin_fabsf(width[k]) < __builtin_inff();
+        plain = plain && __ballot(!finite) == 0;
     }
     return plain;
 }
@@ -1083,7 +1142,7 @@ __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], con
 // (PairsInLds): three or two compares give the interval's index, one look-up its level and width, and the index plus the carry is
 // the code: 17.5 instead of 23 vector instructions per element beside Philox at eight levels (nine levels, buckets of 512, clipping,
 // 25.6 M values 66.0 -> 63.3 us; eight levels, 32768 172.9 -> 167.1).  The rare range that encode_is_plain() refuses is encoded chunk by chunk in a loop.
-template <class Layout, int C, int S, int BITS, Fill FILL, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
+template <class Layout, int C, int S, int BITS, Fill FILL, bool EVEN = false, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
 __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (&lv)[S], const EncodeRange& range, ReloadFn reload,
                                            Pairs pairs = Pairs{}, const Draws& draws = Draws{})
 {
@@ -1098,13 +1157,23 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         for (uint32_t c = 0; 256u * c < range.len; ++c) {
             float y[1][4];
             reload(c, y[0]);
-            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true, false>(y, lv, width, c, range, PhiloxWords{}, transpose, lane, NoPairs{});
+            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true, false, EVEN>(y, lv, width, c, range, PhiloxWords{}, transpose, lane, NoPairs{});
         }
         return;
     }
     if constexpr (SCALED) {
 #pragma unroll
         for (int k = 0; k < S - 1; ++k) width[k] *= 0x1p-24f;
+    }
+    float base[S];  // (see kLadderLevels)
+#pragma unroll
+    for (int k = 0; k < S; ++k) base[k] = lv[k];
+    if constexpr (S <= kLadderLevels) {
+#pragma unroll
+        for (int k = 0; k < S - 1; ++k) {
+            if (k < S - 2) base[k] = width[k] == 0.0f ? next_below(lv[k]) : lv[k];
+            asm("" : "+v"(base[k]), "+v"(width[k]));
+        }
     }
     if constexpr (Pairs::kUsed) {
         if (pairs.writer) {
@@ -1114,7 +1183,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         wave_lds_sync();
     }
     PhiloxWords words{};
-    if constexpr (!Draws::kAhead) words = philox_words((uint32_t)(range.block >> 32), range.k0, range.k1);
+    if constexpr (!Draws::kAhead) words = philox_words<(C >= 8)>((uint32_t)(range.block >> 32), range.k0, range.k1);
     constexpr int GROUP = C < 8 ? C : 8;
 #pragma unroll
     for (int c0 = C - GROUP; c0 >= 0; c0 -= GROUP) {
@@ -1123,7 +1192,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         }
         const float(*ahead)[4] = nullptr;
         if constexpr (Draws::kAhead) ahead = &draws.draw[c0];
-        encode_chunks<Layout, GROUP, S, BITS, FILL, false, Draws::kAhead>(&v[c0], lv, width, (uint32_t)c0, range, words, transpose, lane, pairs, ahead);
+        encode_chunks<Layout, GROUP, S, BITS, FILL, false, Draws::kAhead, EVEN>(&v[c0], base, width, (uint32_t)c0, range, words, transpose, lane, pairs, ahead);
     }
 }
 
@@ -1135,12 +1204,12 @@ __device__ __forceinline__ EncodeRange one_range(uint32_t len, size_t begin, uin
                        codes32 + begin / 64 * (2 * BITS)};
 }
 
-template <int C, int S, int BITS, bool FULL, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
+template <int C, int S, int BITS, bool FULL, bool EVEN = false, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
 __device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
                                            uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32, ReloadFn reload,
                                            Pairs pairs = Pairs{}, const Draws& draws = Draws{})
 {
-    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged>(v, lv, one_range<BITS>(len, begin, seed, index_offset, codes32), reload,
+    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged, EVEN>(v, lv, one_range<BITS>(len, begin, seed, index_offset, codes32), reload,
                                                                         pairs, draws);
 }
 
@@ -2023,7 +2092,7 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
         for (int k = 0; k < S; ++k) levels[(size_t)bucket * S + k] = lv[k];
     }
 
-    orq_encode<C, S, BITS, FULL>(v, lv, len, begin, seed, index_offset, codes32, ReloadFromMemory{g, len, limit},
+    orq_encode<C, S, BITS, FULL, RULE == kEven && S == 3>(v, lv, len, begin, seed, index_offset, codes32, ReloadFromMemory{g, len, limit},
                                  encoder_table<S, RULE != kEven>(lds.grouped, 0u));
 }
 
@@ -2762,7 +2831,7 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
         for (int k = 0; k < S; ++k) levels[(size_t)bucket * S + k] = lv[k];
     }
 
-    orq_encode<C, S, BITS, FULL>(v, lv, my_len, begin + first, seed, index_offset, codes32, ReloadFromMemory{g + first, my_len, limit},
+    orq_encode<C, S, BITS, FULL, RULE == kEven && S == 3>(v, lv, my_len, begin + first, seed, index_offset, codes32, ReloadFromMemory{g + first, my_len, limit},
                                  encoder_table<S, RULE != kEven>(lds.grouped, wave));
 }
 

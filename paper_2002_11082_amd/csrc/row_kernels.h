@@ -362,7 +362,7 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         encode_all<Rows<LANES>, C, S, BITS, FILL>(v, lv, range, ReloadRow<LANES>{g, limit},
                                                   PairsInLds{(uint32_t)(uintptr_t)((LdsWord*)lds.grouped) + 72u * row, i == 0u});
     else
-        encode_all<Rows<LANES>, C, S, BITS, FILL>(v, lv, range, ReloadRow<LANES>{g, limit});
+        encode_all<Rows<LANES>, C, S, BITS, FILL, RULE == kEven && S == 3>(v, lv, range, ReloadRow<LANES>{g, limit});
 }
 
 // (Eight rows of three levels: 80 registers, six wavefronts per SIMD, which their LDS allows.)

@@ -437,6 +437,30 @@ def test_clipping_threshold_where_the_mean_outweighs_the_spread(scheme, bits, sw
     parity.check_quantize(g, d, bits, scheme, sweeps, seed=5, buckets=buckets, clip_factor=1.7, tag=f"threshold-s{scheme}-b{bits}-d{d}")
 
 
+@pytest.mark.parametrize("d,nb", [(64, 30), (128, 30), (128, 33000), (192, 3300), (256, 3400), (512, 20), (512, 17000), (1024, 14), (2048, 1400),
+                                  (4096, 13), (8192, 13), (16384, 12), (32768, 13)])
+@pytest.mark.parametrize("scheme,bits", [(ogq.ORQ_PAPER, 2), (ogq.LINEAR, 2), (ogq.EVEN, 2), (ogq.ORQ, 1), (ogq.BINGRAD_PB, 1)])
+def test_two_and_three_levels_that_coincide(scheme, bits, d, nb):
+    """The encoder's sum of compares: intervals of width 0 at either end and at both, zeros of either sign, values on the levels, widths too
+    small for the scaled form (some of them subnormal) and beyond the largest number."""
+    rng = np.random.default_rng(d + bits)
+    g = (rng.standard_normal(nb * d) * 1e-3).astype(np.float32)
+    b = g.reshape(nb, d)
+    b[0] = np.float32(0.25)
+    b[1] = np.where(rng.random(d) < 0.5, np.float32(0.0), np.float32(-0.0))
+    b[2] = np.where(rng.random(d) < 0.9, np.float32(-1.5), np.float32(2.0))   # the middle level is the lowest
+    b[3] = np.where(rng.random(d) < 0.9, np.float32(1.5), np.float32(-2.0))   # ... the highest
+    b[4] = np.where(rng.random(d) < 0.9, np.float32(-0.0), b[4])              # ... zero
+    b[5] = np.where(rng.random(d) < 0.9, np.float32(0.0), np.abs(b[5]))       # the lowest zero
+    b[6] = rng.integers(-1, 2, d).astype(np.float32)                          # every value on a level
+    b[7] *= np.float32(1e-30)
+    b[8] *= np.float32(1e-37)
+    b[9] = (rng.uniform(-1.0, 1.0, d) * 3.3e38).astype(np.float32)
+    b[10] = np.float32(-0.75)
+    g = g[: nb * d - d // 3]
+    parity.check_quantize(g, d, bits, scheme, 0, seed=11, buckets=sorted(set(list(range(12)) + [nb - 2, nb - 1])), tag=f"coincide-s{scheme}-d{d}")
+
+
 def test_random_shapes_and_parameters():
     # many small random problems: sizes, bucket sizes (every multiple of 64 is legal), schemes, widths, iterations,
     # clipping, value distributions, including buckets dominated by repeated values
