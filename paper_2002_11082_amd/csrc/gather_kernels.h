@@ -115,8 +115,7 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
                 part += (double)(decltype(all)::value || 256u * c + 4u * lane + k < my_len ? v[c][k] : 0.0f);
         });
     }
-    low = wave_min(low);
-    high = wave_max(high);
+    wave_extremes(low, high);
     double total = 0.0;
     {
         const TeamSlot* s = team.exchange(RULE == kOptimal ? wave_sum(part) : 0.0, __float_as_uint(low), __float_as_uint(high));
@@ -177,10 +176,11 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
     {
         constexpr uint32_t PER = B / THREADS;
         static_assert(PER >= 4 && PER % 4 == 0, "16-byte reads");
-        uint32_t mine = 0;
+        uint32_t count[PER], mine = 0;
 #pragma unroll
         for (uint32_t q = 0; q < PER / 4u; ++q) {
             const uint4 x = reinterpret_cast<const uint4*>(lds.bin_count)[tid * (PER / 4u) + q];
+            count[4 * q] = x.x; count[4 * q + 1] = x.y; count[4 * q + 2] = x.z; count[4 * q + 3] = x.w;
             mine += (x.x + x.y) + (x.z + x.w);
         }
         const uint32_t incl = wave_inclusive_scan_u32(mine);
@@ -190,17 +190,19 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
 #pragma unroll
         for (int w = 0; w < W; ++w) before += (uint32_t)w < wave ? lds.wave_total[w] : 0u;
         if (before < rank && rank <= before + mine) {  // one thread of the workgroup
-#pragma unroll 1
-            for (uint32_t i = 0; i < PER; ++i) {
-                const uint32_t count = lds.bin_count[tid * PER + i];
-                if (rank <= before + count) {
-                    lds.wanted[0] = tid * PER + i;
-                    lds.wanted[1] = before;
-                    lds.wanted[2] = count;
-                    break;
-                }
-                before += count;
+            // (in a straight line: read again bin by bin, every wavefront waits for up to PER trips to LDS)
+            uint32_t at = 0, front = before, in_it = count[0];
+#pragma unroll
+            for (uint32_t i = 1; i < PER; ++i) {
+                before += count[i - 1];
+                const bool further = before < rank;
+                at = further ? i : at;
+                front = further ? before : front;
+                in_it = further ? count[i] : in_it;
             }
+            lds.wanted[0] = tid * PER + at;
+            lds.wanted[1] = front;
+            lds.wanted[2] = in_it;
         }
         __syncthreads();
     }
@@ -216,18 +218,26 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
     const uint32_t from = sign | (u == 0u ? 1u : (t_low + u) << SHIFT);
     const uint32_t range = (u == HALF - 1u ? sign + 0x80000000u : sign | ((t_low + u + 1u) << SHIFT)) - from;
     uint32_t smallest = 0xFFFFFFFFu, largest = 0u;
-    // (another zero, here and in the bisection: what an earlier pass made of the elements is made again, not kept in registers)
-    const float again = opaque_zero();
+    // (-0 need not be turned into +0 first: neither is in any range.  One branch for four elements, of which few are wanted,
+    // and the bin of the rank in a straight line: 25.6 M values in buckets of 32768 43.6 -> 42.4 us)
     for_each_chunk<C, FULL>(my_len, [&](int c, auto all) __attribute__((always_inline)) {
+        bool wanted[4], some = false;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bool valid = decltype(all)::value || (256u * c + 4u * lane + k < my_len);
-            const float x = v[c][k] + again;
-            if (valid && __float_as_uint(x) - from < range) {
-                const uint32_t at = atomicAdd(&lds.list_count, 1u);
-                if (at < Lds::LIST) lds.list[at] = __float_as_uint(x);
-                smallest = umin32(smallest, float_to_key(x));
-                largest = umax32(largest, float_to_key(x));
+            wanted[k] = valid && __float_as_uint(v[c][k]) - from < range;
+            some = some || wanted[k];
+        }
+        if (__ballot(some) != 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (wanted[k]) {
+                    const float x = v[c][k];
+                    const uint32_t at = atomicAdd(&lds.list_count, 1u);
+                    if (at < Lds::LIST) lds.list[at] = __float_as_uint(x);
+                    smallest = umin32(smallest, float_to_key(x));
+                    largest = umax32(largest, float_to_key(x));
+                }
             }
         }
     });

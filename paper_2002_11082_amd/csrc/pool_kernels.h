@@ -134,8 +134,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     float low, high;
     uint32_t unused_zeros;
     lane_extremes<C, false>(v, low, high, unused_zeros);
-    low = wave_min(low);
-    high = wave_max(high);
+    wave_extremes(low, high);
     // mean magnitude of every fourth element (padding is NaN)
     float sample = 0.0f;
 #pragma unroll

@@ -1973,8 +1973,8 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
     float lane_min, lane_max;
     uint32_t lane_zeros;
     lane_extremes<C, PB>(v, lane_min, lane_max, lane_zeros);
-    const float bucket_min = wave_min(lane_min) + 0.0f;  // -0 -> +0
-    const float bucket_max = wave_max(lane_max) + 0.0f;
+    wave_extremes(lane_min, lane_max);
+    const float bucket_min = lane_min + 0.0f, bucket_max = lane_max + 0.0f;  // -0 -> +0
     const uint32_t key_min = float_to_key(bucket_min), key_max = float_to_key(bucket_max);
     const uint32_t mag_max = umax32(__float_as_uint(bucket_min) & 0x7FFFFFFFu, __float_as_uint(bucket_max) & 0x7FFFFFFFu);
     const uint32_t t_max = mag_max >> SHIFT;
@@ -2682,7 +2682,8 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
     float lane_min, lane_max;
     uint32_t lane_zeros;
     lane_extremes<C, PB>(v, lane_min, lane_max, lane_zeros);
-    float bucket_min = wave_min(lane_min), bucket_max = wave_max(lane_max);
+    wave_extremes(lane_min, lane_max);
+    float bucket_min = lane_min, bucket_max = lane_max;
     uint32_t zeros = PB ? wave_sum_u32(lane_zeros) : 0u;
     {
         const TeamSlot* s = team.exchange((double)zeros, __float_as_uint(bucket_min), __float_as_uint(bucket_max));
