@@ -67,6 +67,46 @@ __device__ __forceinline__ uint32_t exact_floor_t_team(unsigned long long* limb,
     return lo;
 }
 
+// The element of 1-based rank `rank` among the first `count` (more than 64 (K - 1), at most 64 K) of the list, as its key: quickselect by a wavefront that
+// holds K keys per lane.  A pivot is an element that is still open; it leaves at least itself out of the next round, and only a rank beyond
+// the list, which there is none of, leaves none open.
+template <int K>
+__device__ __forceinline__ uint32_t select_in_list(const uint32_t* list, uint32_t count, uint32_t rank, uint32_t lane)
+{
+    uint32_t mine[K];
+    uint64_t open[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t i = lane + 64u * (uint32_t)k;
+        mine[k] = i < count ? float_to_key(__uint_as_float(list[i])) : 0xFFFFFFFFu;
+        open[k] = __ballot(i < count);
+    }
+    for (;;) {
+        uint32_t pivot = 0;
+        bool found = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (!found && open[k] != 0) {
+                pivot = __builtin_amdgcn_readlane(mine[k], (uint32_t)__builtin_ctzll(open[k]));
+                found = true;
+            }
+        }
+        uint64_t below[K], not_above[K];
+        uint32_t count_below = 0, count_not_above = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            below[k] = __ballot(mine[k] < pivot);
+            not_above[k] = __ballot(mine[k] <= pivot);
+            count_below += (uint32_t)__popcll(below[k]);
+            count_not_above += (uint32_t)__popcll(not_above[k]);
+        }
+        if (!found || (count_below < rank && rank <= count_not_above)) return pivot;
+        const bool lower = rank <= count_below;
+#pragma unroll
+        for (int k = 0; k < K; ++k) open[k] &= lower ? below[k] : ~not_above[k];
+    }
+}
+
 template <int W, int C, int BITS, bool FULL, int RULE>
 __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const float* __restrict__ g, uint32_t len, size_t begin,
                                                   uint32_t bucket, float clip, uint64_t seed, uint64_t index_offset,
@@ -255,8 +295,14 @@ __device__ __forceinline__ void orq_gather_bucket(GatherLds<W, C>& lds, const fl
         const uint32_t mine = lane < count ? float_to_key(__uint_as_float(lds.list[lane])) : 0xFFFFFFFFu;
         uint32_t not_above;
         select_rank(mine, count, in_bin, ~0ull >> (64u - count), key, not_above);
+    } else if (count <= 256u) {
+        // The bins next to zero hold all that is more than 16 binades below the largest magnitude, some 70 elements of a mixture of scales at
+        // 32768, and the level is often found there.  25.6 M such values in buckets of 32768 46.6 us with the bisection below, 41.4 with this
+        // (one card; 256 buckets 23.9 and 17.8).
+        __syncthreads();
+        key = count <= 128u ? select_in_list<2>(lds.list, count, in_bin, lane) : select_in_list<4>(lds.list, count, in_bin, lane);
     } else {
-        // A crowded bin: bisection over the bits in which its smallest and largest key differ (none when all its values
+        // A more crowded bin: bisection over the bits in which its smallest and largest key differ (none when all its values
         // are equal), on the list, or where that is too short on the registers of all wavefronts.
         smallest = wave_min_u32(smallest);
         largest = wave_max_u32(largest);

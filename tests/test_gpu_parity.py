@@ -461,6 +461,27 @@ def test_two_and_three_levels_that_coincide(scheme, bits, d, nb):
     parity.check_quantize(g, d, bits, scheme, 0, seed=11, buckets=sorted(set(list(range(12)) + [nb - 2, nb - 1])), tag=f"coincide-s{scheme}-d{d}")
 
 
+@pytest.mark.parametrize("d", [8192, 10240, 16384, 32768])
+@pytest.mark.parametrize("scheme", [ogq.ORQ_PAPER, ogq.LINEAR])
+def test_three_levels_in_large_buckets_with_the_level_in_a_crowded_bin(scheme, d):
+    """Small elements beside large ones of both signs share the bin next to zero, which holds the level: numbers of them on both sides of each limit
+    of the search (64, 128, 256 and the list's 1024), distinct ones and few values shared by many."""
+    rng = np.random.default_rng(d + scheme)
+    sizes = [63, 64, 65, 66, 127, 128, 129, 255, 256, 257, 1023, 1024, 1025, 1500]
+    rows = []
+    for m in sizes:
+        for values in (0, 3):
+            x = rng.uniform(0.5, 1.0, d) * np.where(np.arange(d) % 2 == 0, 1.0, -1.0)
+            small = rng.uniform(1e-9, 1e-7, m)
+            if values:
+                small = rng.choice(small[:values], m)
+            x[:m] = small * (1.0 if m % 3 else -1.0)
+            rows.append(rng.permutation(x).astype(np.float32))
+    for nb in (len(rows), 300):  # (above 16384 elements another form from 257 buckets on)
+        g = np.concatenate([rows[i % len(rows)] for i in range(nb)])
+        parity.check_quantize(g, d, 2, scheme, 0, seed=3, buckets=range(len(rows)), tag=f"crowded-s{scheme}-d{d}-nb{nb}")
+
+
 def test_random_shapes_and_parameters():
     # many small random problems: sizes, bucket sizes (every multiple of 64 is legal), schemes, widths, iterations,
     # clipping, value distributions, including buckets dominated by repeated values
