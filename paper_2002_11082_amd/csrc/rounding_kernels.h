@@ -2983,8 +2983,8 @@ constexpr bool team_serves(int S, int rule)
 {
     if (W == 2) return C == 8 ? rule == kPb : S >= 8 && rule == kOptimal;
     if (W * C == 64 || W * C == 128) {
-        if (rule == kEven) return C == 8;
-        return C == 16 && (S != 3 || rule == kPb);
+        if (C == 8) return rule == kEven || (S != 3 && rule != kPb);
+        return rule == kPb || (W == 8 && S != 3 && rule != kEven);
     }
     if (W == 4 && C == 8) return S != 3 || rule == kEven;
     if (W == 4 && C == 1) return S < 8 || rule != kOptimal;

@@ -3,7 +3,7 @@
 // wavefront per bucket of at most 256 * OGQ_PART elements (for 2048 elements one wavefront is the faster choice unless
 // there are few buckets); 16: four or two wavefronts per bucket of at most 4096 elements; 102: four wavefronts of 2048
 // elements per bucket of at most 8192 (22-37 % faster than two wavefronts of 4096: half the registers, twice the resident
-// wavefronts); 104, 108: 4, 8 wavefronts of 4096 elements per bucket of at most 16384, 32768.  ORQ-3 and Linear-3 above
+// wavefronts); 104, 108: 8, 16 wavefronts of 2048 elements, or 4, 8 of 4096, per bucket of at most 16384, 32768.  ORQ-3 and Linear-3 above
 // 4096 elements have a kernel of their own (gather_kernels.h).
 #include "rounding_kernels.h"
 #include "row_kernels.h"
@@ -209,11 +209,10 @@ void launch_rounding_w2(const float* g, size_t n, const ogq_params_t* p, uint32_
 void launch_rounding_w4(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     if (launch_gather<8, 8>(g, n, p, nb, lv, codes, st)) return;
-    if (p->scheme == OGQ_EVEN) {  // no grouping in LDS: half the registers, twice the wavefronts (28 -> 25 us at 25.6 M)
-        launch_orq_team_levels<8, 8>(g, n, p, nb, lv, codes, st);
-        return;
-    }
-    launch_orq_team_levels<4, 16>(g, n, p, nb, lv, codes, st);
+    // Eight wavefronts of 2048 elements in 128 registers, so that two workgroups put 16 on a CU, where four of 4096 made 8 (four levels, two sweeps, 1562
+    // buckets of 16384 72.4 -> 68.3 us, nine 75.0 -> 72.8, Linear-5 52.7 -> 51.1, evenly spaced 28 -> 25); BinGrad-pb would spill (56.7 -> 80.9).
+    if (p->scheme == OGQ_BINGRAD_PB) launch_orq_team<4, 16, 2, 1, kPb>(g, n, p, nb, lv, codes, st);
+    else launch_orq_team_levels<8, 8>(g, n, p, nb, lv, codes, st);
 }
 #elif OGQ_PART == 108
 void launch_rounding_w8(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
@@ -222,11 +221,10 @@ void launch_rounding_w8(const float* g, size_t n, const ogq_params_t* p, uint32_
     // and barriers overlap the other's work (ORQ-3: 512 buckets of 32768 43.6 -> 30.9 us, 782 58.6 -> 44.8, 1562 of 20480 97 -> 75; 256 of
     // 20480 15.2 -> 18.8).
     if (nb <= 256u ? launch_gather<16, 8>(g, n, p, nb, lv, codes, st) : launch_gather<8, 16>(g, n, p, nb, lv, codes, st)) return;
-    if (p->scheme == OGQ_EVEN) {
-        launch_orq_team_levels<16, 8>(g, n, p, nb, lv, codes, st);
-        return;
-    }
-    launch_orq_team_levels<8, 16>(g, n, p, nb, lv, codes, st);
+    // Likewise 16 of 2048 where a fourth of 8 of 4096 would hold nothing, and always where the rule has no passes over LDS: four levels, two sweeps, 1040
+    // buckets of 24576 117.7 -> 111.3, 1550 of 16448 132.6 -> 127.2, Linear-9 119.9 -> 106.9; but 900 of 28672 112.5 -> 114.7, five levels 88.2 -> 91.5.
+    if (p->scheme == OGQ_EVEN || (p->scheme != OGQ_BINGRAD_PB && p->bucket_size <= 24576u)) launch_orq_team_levels<16, 8>(g, n, p, nb, lv, codes, st);
+    else launch_orq_team_levels<8, 16>(g, n, p, nb, lv, codes, st);
 }
 #else
 #error "unknown OGQ_PART"
