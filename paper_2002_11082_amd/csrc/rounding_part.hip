@@ -211,6 +211,7 @@ void launch_rounding_w4(const float* g, size_t n, const ogq_params_t* p, uint32_
     if (launch_gather<8, 8>(g, n, p, nb, lv, codes, st)) return;
     // Eight wavefronts of 2048 elements in 128 registers, so that two workgroups put 16 on a CU, where four of 4096 made 8 (four levels, two sweeps, 1562
     // buckets of 16384 72.4 -> 68.3 us, nine 75.0 -> 72.8, Linear-5 52.7 -> 51.1, evenly spaced 28 -> 25); BinGrad-pb would spill (56.7 -> 80.9).
+    // Linear-5 at 12288, without clipping, is the one rule that loses (1628 buckets 54.0 -> 57.0; with it 68.4 -> 63.6).
     if (p->scheme == OGQ_BINGRAD_PB) launch_orq_team<4, 16, 2, 1, kPb>(g, n, p, nb, lv, codes, st);
     else launch_orq_team_levels<8, 8>(g, n, p, nb, lv, codes, st);
 }
