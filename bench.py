@@ -169,7 +169,7 @@ def quantize_kernel(synth, wl, n: int, levels: int):
     wavefronts = 4 if d <= 8192 else 8 if d <= 16384 else 16
     if levels == 3 and not even:
         return "orq_gather_kernel", 8 if d > 16384 and nb > 256 else wavefronts
-    return "orq_team_kernel", wavefronts if even or d <= 8192 or (not pb and d <= 24576) else wavefronts // 2
+    return "orq_team_kernel", wavefronts if even or d <= 8192 or (not pb and d <= 25600) else wavefronts // 2
 
 
 def decode_kernel_name(d: int, workers: int) -> str:

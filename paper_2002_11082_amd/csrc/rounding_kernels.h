@@ -2714,8 +2714,31 @@ __device__ __forceinline__ void orq_team_bucket(OrqTeamLds<W, C>& lds, const flo
         count_into_bins<C, FULL, HALF, SHIFT>(slot, v, lds.bin_start, t_low, my_len, lane);
         __syncthreads();
 
-        // ---- exclusive prefix over the bin counts (wavefront 0; lane l owns bins l*PER .. l*PER+PER-1) ------
-        if (wave == 0u) {
+        // ---- exclusive prefix over the bin counts --------------------------------------------------------
+        // Wavefront 0, lane l owning bins l*PER .. l*PER+PER-1; 2048 bins: all wavefronts, thread t owning bins t*PER .. likewise.  32 bins to a lane
+        // are 32 registers on top of the values and their slots, which eight wavefronts of 2048 elements do not have: 76 to 80 bytes per lane went to
+        // scratch memory, and Linear-5 in 1628 buckets of 12288 took 60.1 us where it takes 51.8 now (four levels, two sweeps, 1000 of 24576 102.3 -> 98.9).
+        // Linear-s with 4096 elements per wavefront, which has the registers, is 1.5 to 2 % faster with one (700 buckets of 28672 66.9 and 68.0).
+        if constexpr (B >= 2048 && (C == 8 || RULE != kLinear)) {
+            constexpr uint32_t PER = B / THREADS;
+            uint32_t count[PER], tot = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < PER; ++i) {
+                count[i] = lds.bin_start[tid * PER + i];
+                tot += count[i];
+            }
+            const uint32_t incl = wave_inclusive_scan_u32(tot);
+            const TeamSlot* s = team.exchange(0.0, __builtin_amdgcn_readlane(incl, 63), 0u);
+            uint32_t run = incl - tot;
+#pragma unroll
+            for (int w = 0; w < W; ++w) run += (uint32_t)w < wave ? s[w].a : 0u;
+#pragma unroll
+            for (uint32_t i = 0; i < PER; ++i) {
+                lds.bin_start[tid * PER + i] = run;
+                run += count[i];
+            }
+            if (tid == THREADS - 1u) lds.bin_start[B] = run;  // = len
+        } else if (wave == 0u) {
             constexpr uint32_t PER = B / 64;
             uint32_t tot = 0;
             for (uint32_t i = 0; i < PER; ++i) tot += lds.bin_start[lane * PER + i];

@@ -209,9 +209,9 @@ void launch_rounding_w2(const float* g, size_t n, const ogq_params_t* p, uint32_
 void launch_rounding_w4(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     if (launch_gather<8, 8>(g, n, p, nb, lv, codes, st)) return;
-    // Eight wavefronts of 2048 elements in 128 registers, so that two workgroups put 16 on a CU, where four of 4096 made 8 (four levels, two sweeps, 1562
-    // buckets of 16384 72.4 -> 68.3 us, nine 75.0 -> 72.8, Linear-5 52.7 -> 51.1, evenly spaced 28 -> 25); BinGrad-pb would spill (56.7 -> 80.9).
-    // Linear-5 at 12288, without clipping, is the one rule that loses (1628 buckets 54.0 -> 57.0; with it 68.4 -> 63.6).
+    // Eight wavefronts of 2048 elements in 128 registers, so that two workgroups put 16 on a CU, where four of 4096 made 8 (1300 buckets of 16384: four
+    // levels, two sweeps, 62.8 -> 60.5 us, nine 64.9 -> 62.6, Linear-5 47.2 -> 45.8; 1628 of 12288, Linear-5, 58.0 -> 51.8; but 300 of 16384, five
+    // levels, 21.8 -> 22.4).  BinGrad-pb would spill (56.7 -> 80.9).
     if (p->scheme == OGQ_BINGRAD_PB) launch_orq_team<4, 16, 2, 1, kPb>(g, n, p, nb, lv, codes, st);
     else launch_orq_team_levels<8, 8>(g, n, p, nb, lv, codes, st);
 }
@@ -222,9 +222,10 @@ void launch_rounding_w8(const float* g, size_t n, const ogq_params_t* p, uint32_
     // and barriers overlap the other's work (ORQ-3: 512 buckets of 32768 43.6 -> 30.9 us, 782 58.6 -> 44.8, 1562 of 20480 97 -> 75; 256 of
     // 20480 15.2 -> 18.8).
     if (nb <= 256u ? launch_gather<16, 8>(g, n, p, nb, lv, codes, st) : launch_gather<8, 16>(g, n, p, nb, lv, codes, st)) return;
-    // Likewise 16 of 2048 where a fourth of 8 of 4096 would hold nothing, and always where the rule has no passes over LDS: four levels, two sweeps, 1040
-    // buckets of 24576 117.7 -> 111.3, 1550 of 16448 132.6 -> 127.2, Linear-9 119.9 -> 106.9; but 900 of 28672 112.5 -> 114.7, five levels 88.2 -> 91.5.
-    if (p->scheme == OGQ_EVEN || (p->scheme != OGQ_BINGRAD_PB && p->bucket_size <= 24576u)) launch_orq_team_levels<16, 8>(g, n, p, nb, lv, codes, st);
+    // Likewise 16 of 2048 where a fifth of 8 of 4096 would hold nothing, and always where the rule has no passes over LDS (8 of 4096 -> 16 of 2048: four
+    // levels, two sweeps, 1550 buckets of 16448 132.7 -> 123.3 us, 1000 of 24640 103.6 -> 97.0, clipped 115.8 -> 111.8; Linear-9 107.0 -> 98.1).
+    // Above, the gain falls until the buckets fill both (790 of 28672: 106.8 -> 105.8; five levels, clipped, 95.4 -> 97.2).
+    if (p->scheme == OGQ_EVEN || (p->scheme != OGQ_BINGRAD_PB && p->bucket_size <= 25600u)) launch_orq_team_levels<16, 8>(g, n, p, nb, lv, codes, st);
     else launch_orq_team_levels<8, 16>(g, n, p, nb, lv, codes, st);
 }
 #else

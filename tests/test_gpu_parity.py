@@ -346,6 +346,19 @@ def test_buckets_above_4096(scheme, bits, d):
     parity.check_quantize(g, d, bits, scheme, 1, seed=3, clip_factor=2.5, tag=f"large-clip-s{scheme}b{bits}-d{d}")
 
 
+@pytest.mark.parametrize("scheme,bits,iters", [(ogq.ORQ, 2, 2), (ogq.ORQ, 3, 1), (ogq.ORQ_PAPER, 3, 0), (ogq.ORQ_PAPER, 4, 0), (ogq.LINEAR, 3, 0),
+                                               (ogq.LINEAR, 4, 0), (ogq.BINGRAD_PB, 1, 0), (ogq.EVEN, 3, 0)])
+@pytest.mark.parametrize("d", [8256, 16384, 16448, 24576, 24640, 25600, 25664, 32704])
+def test_wavefronts_of_2048_and_4096_elements(scheme, bits, iters, d):
+    """Buckets that 8 or 16 wavefronts hold, on both sides of each limit between the forms, full and cut off, with and without clipping: bin starts
+    that all wavefronts make, or one."""
+    rng = np.random.default_rng(d + 31 * scheme + bits)
+    for kind, n in (("heavy", 2 * d), ("shifted", 2 * d - 29), ("ints", d + 70)):
+        g = _rng_bucket(rng, n, kind)
+        for clip in (0.0, 2.5):
+            parity.check_quantize(g, d, bits, scheme, iters, seed=n, clip_factor=clip, tag=f"forms-s{scheme}b{bits}-{kind}-d{d}-n{n}")
+
+
 def test_bucket_size_sweep_of_the_paper_at_resnet50_size():
     """ORQ-3 and TernGrad-noclip over the bucket sizes of the paper's CIFAR-10 sweep (128 .. 32768), every
     bucket against the oracle; the expected rounding error per element must grow with the bucket size for
