@@ -19,8 +19,8 @@ namespace ogq {
 // barriers and most of a wavefront's scalar instructions; here the four rows work for two buckets and the steps need no barrier.
 // 143.7 M values in buckets of 4096, eight levels, two sweeps: 421 -> 368 us, with direct solves (group_solve_direct) and 1280 instead of 1024
 // bins, so that hardly a bin is too large for them, 310; 25.6 M values in buckets of 2048 124 -> 80 -> 69.
-// Bound by the solves' latency (37 % of a workgroup's cycles, profiles/phase_cycles.txt), during which a workgroup's other wavefronts wait, and
-// the LDS (16 KB of values per bucket of 4096), which holds the buckets of four workgroups; the vector units are busy 0.81 of the time
+// Bound by the solves' latency (profiles/phase_cycles.txt), of which the random numbers that a workgroup's other wavefronts make meanwhile are the
+// smaller part, and the LDS (16 KB of values per bucket of 4096), which holds the buckets of four workgroups; the vector units are busy 0.83 of the time
 // (profiles/orq_cfg4_issue_counters_pmc.txt).  The solving wavefront runs at a raised priority: its instructions go first on its SIMD.  Four
 // buckets per workgroup, in rows of 8 lanes, were slower (418 us when two took 368): fewer workgroups overlap.
 // Four levels: four buckets of up to 2048 elements, a row each, so that a workgroup spends no more instructions on solves than with more
@@ -296,9 +296,11 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
 
     // ---- the levels of all buckets, on one wavefront (another one from workgroup to workgroup: a CU's wavefronts are dealt
     //      to its SIMDs in order) -----------------------------------------------------------------------------------------
-    // The random numbers, a third of the encoder, do not depend on the levels: the wavefronts that wait make theirs meanwhile, and most or
-    // all of those of the one that solves, which takes them through LDS.  Eight levels, two sweeps, 143.7 M values in buckets of 4096 310 -> 292 us
-    // (each its own, the solving wavefront behind the others: 300); four levels, 25.6 M in buckets of 2048 51.5 -> 45.8 (49.1).
+    // The random numbers, a third of the encoder, do not depend on the levels: the wavefronts that wait make theirs meanwhile, and all (with two
+    // wavefronts in the workgroup: half) of those of the one that solves, which takes them through LDS.  Eight levels, two sweeps, 143.7 M values in buckets
+    // of 4096 310 -> 292 us (each its own, the solving wavefront behind the others: 300); four levels, 25.6 M in buckets of 2048 51.5 -> 45.8 (49.1).
+    // None are made for chunks without elements: with them four levels, two sweeps, 1628 buckets of 3072, whose second wavefronts hold half, took 20.4 us, each
+    // its own 19.1, now 19.7.
     const EncodeRange range = one_range<BITS>(my_len, begin + first, seed, index_offset, codes32);
     constexpr uint32_t HELPERS = (uint32_t)(NB * W) - 1u;
     constexpr int SHARE = HELPERS == 3u ? (C + 2) / 3 : C / 2;                        // chunks helper, helper + HELPERS, ... of them
@@ -339,10 +341,13 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                                                           });
         __builtin_amdgcn_s_setprio(0);
     } else {
-        draws.template make<OneRange>(range);
-        const uint32_t its_bucket = blockIdx.x * (uint32_t)NB + solver / (uint32_t)W;
-        const size_t at = (size_t)its_bucket * bucket_size + PER_WAVE * (solver % (uint32_t)W);
-        share.template make<OneRange, (int)HELPERS>(one_range<BITS>(PER_WAVE, at, seed, index_offset, codes32), helper);
+        draws.template make<OneRange, !FULL>(range);
+        const uint32_t its_bucket = blockIdx.x * (uint32_t)NB + solver / (uint32_t)W, its_first = PER_WAVE * (solver % (uint32_t)W);
+        // (as many as a whole bucket has, and none behind those that are handed over)
+        const uint32_t its_len = FULL ? 256u * HANDED : __builtin_elementwise_sub_sat(bucket_size, its_first);
+        share.template make<OneRange, (!FULL || HANDED < (int)HELPERS * SHARE), (int)HELPERS>(
+            one_range<BITS>(its_len < 256u * HANDED ? its_len : 256u * HANDED, (size_t)its_bucket * bucket_size + its_first, seed, index_offset, codes32),
+            helper);
     }
     __syncthreads();
     {
@@ -358,7 +363,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         }
         __syncthreads();
         if (solves) {
-            draws.template make<OneRange, 1, HANDED>(range);
+            draws.template make<OneRange, !FULL, 1, HANDED>(range);
 #pragma unroll
             for (int c = 0; c < HANDED; ++c) {
                 const floatx4 x = place[64 * c];

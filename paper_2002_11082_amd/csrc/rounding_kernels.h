@@ -925,17 +925,19 @@ template <int C>
 struct DrawsAhead {
     static constexpr bool kAhead = true;
     float draw[C][4];
-    // Chunks first + STRIDE c of the range into draw[c], c = BEGIN .. C - 1.  (In the lean form: a range that encode_is_plain() refuses has
-    // its draws made chunk by chunk.)
-    template <class Layout, int STRIDE = 1, int BEGIN = 0>
+    // Chunks first + STRIDE c of the range into draw[c], c = BEGIN .. C - 1; LIMITED: those of them that begin below range.len.  (In the lean form: a
+    // range that encode_is_plain() refuses has its draws made chunk by chunk.)
+    template <class Layout, bool LIMITED, int STRIDE = 1, int BEGIN = 0>
     __device__ __forceinline__ void make(const EncodeRange& range, uint32_t first = 0)
     {
         if constexpr (BEGIN >= C) return;
         const PhiloxWords words = philox_words<(C - BEGIN > 4)>((uint32_t)(range.block >> 32), range.k0, range.k1);
 #pragma unroll
         for (int c = BEGIN; c < C; ++c) {
+            const uint32_t chunk = first + (uint32_t)(STRIDE * c);
+            if (LIMITED && 256u * chunk >= range.len) continue;
             uint32_t r[4];
-            philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * (first + (uint32_t)(STRIDE * c)), words, r);
+            philox4x32_10_uniform_c1((uint32_t)range.block + range.lane_block + Layout::kBlocks * chunk, words, r);
 #pragma unroll
             for (int k = 0; k < 4; ++k) draw[c][k] = (float)(r[k] >> 8);
             __builtin_amdgcn_sched_barrier(0);

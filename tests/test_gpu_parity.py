@@ -1207,6 +1207,19 @@ def test_random_numbers_of_the_solving_wavefront(scheme, bits, d, nb):
                                   buckets=checked, tag=f"ahead-s{scheme}-b{bits}-d{d}-turn{turn}-cut{cut}")
 
 
+@pytest.mark.parametrize("scheme,bits", [(ogq.ORQ, 2), (ogq.ORQ, 3), (ogq.ORQ_PAPER, 3)])
+@pytest.mark.parametrize("d,nb", [(576, 514), (832, 1283), (1088, 1282), (1280, 1283), (1792, 1027), (2112, 514), (2304, 515), (3072, 1027), (3328, 514)])
+def test_random_numbers_of_the_chunks_that_hold_elements(scheme, bits, d, nb):
+    """None are made for the others: the last chunk of a bucket full, partly filled and alone in its second wavefront, the last bucket shorter than its
+    neighbour, whose numbers the same wavefront may make."""
+    rng = np.random.default_rng(d + bits)
+    g = (rng.standard_normal(nb * d) * 1e-3).astype(np.float32)
+    for cut in (0, 29, d - 257, d - 1):
+        for clip in (0.0, 2.5):
+            parity.check_quantize(g[: nb * d - cut], d, bits, scheme, 2, seed=9, index_offset=64 * 5, buckets=list(range(8)) + list(range(nb - 5, nb)),
+                                  clip_factor=clip, tag=f"chunks-s{scheme}-b{bits}-d{d}-cut{cut}")
+
+
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 4, 1), (ogq.ORQ_PAPER, 3, 2)])
 def test_levels_in_bins_beyond_the_sort(scheme, bits, sweeps):
     """A level among 31 to 64 values of one bin, around the 32 that 8 lanes sort and the 64 that 16 lanes do; distinct values,
