@@ -28,6 +28,13 @@ namespace ogq {
 // workgroup 50.9, four 50.7; 8192 buckets 38 / 37 / 32).  Above 2048 elements the LDS of a workgroup (an address in 16 bits) holds two, whose
 // two rows do the same work.
 // ----------------------------------------------------------------------------------------------
+// Priorities of a wavefront.  The random numbers that a waiting wavefront makes are work for what the others leave: at the priority of all but the
+// solves they held up the histograms and scatters of the CU's workgroups whose loads had come late, which end the call (1920 buckets of
+// 4096, eight levels, two sweeps: bin starts 2,800 cycles in the slowest tenth of the workgroups, where they had taken 1,200).  us, no numbers ahead -> ahead, at
+// work's priority -> below it: four levels, two sweeps, 1920 buckets of 2112 18.2 -> 19.0 -> 16.8, 1628 of 3072 19.1 -> 19.7 -> 17.5; eight levels, 1920 of
+// 4096 23.5 -> 22.8 -> 21.6, 143.7 M values in buckets of 4096 313 -> 286 -> 273.
+constexpr int kAhead = 0, kAtWork = 1, kSolving = 3;
+
 constexpr int pool_chains(int S) { return S > 4 ? 2 : 1; }                     // of solves per bucket, a row of 16 lanes each
 constexpr int pool_buckets(int W, int S) { return W == 1 && S == 4 ? 4 : 2; }  // per workgroup
 
@@ -101,6 +108,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         else __syncthreads();
     };
 
+    __builtin_amdgcn_s_setprio(kAtWork);
     float v[C][4];
     load_range<C, FULL>(v, g, first, len, my_len, lane);
     uint32_t grouped_at = (uint32_t)(uintptr_t)((LdsWord*)my.grouped);
@@ -310,7 +318,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     const uint32_t solver = (blockIdx.x * 0x9E3779B1u >> 16) % (HELPERS + 1u), helper = (wave - solver - 1u) & HELPERS;
     const bool solves = wave == solver;
     if (solves) {
-        __builtin_amdgcn_s_setprio(3);
+        __builtin_amdgcn_s_setprio(kSolving);
         if constexpr (W == 2) {
             // the second wavefronts' prefixes count from their own first position
             double before[NB];
@@ -339,8 +347,9 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                                                           [&](uint32_t entry) __attribute__((always_inline)) {
                                                               return uniform_u32(pool_solve_general<Bucket>(at, limb, its_len, entry, lane)) != 0u;
                                                           });
-        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_s_setprio(kAtWork);
     } else {
+        __builtin_amdgcn_s_setprio(kAhead);
         draws.template make<OneRange, !FULL>(range);
         const uint32_t its_bucket = blockIdx.x * (uint32_t)NB + solver / (uint32_t)W, its_first = PER_WAVE * (solver % (uint32_t)W);
         // (as many as a whole bucket has, and none behind those that are handed over)
@@ -348,6 +357,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
         share.template make<OneRange, (!FULL || HANDED < (int)HELPERS * SHARE), (int)HELPERS>(
             one_range<BITS>(its_len < 256u * HANDED ? its_len : 256u * HANDED, (size_t)its_bucket * bucket_size + its_first, seed, index_offset, codes32),
             helper);
+        __builtin_amdgcn_s_setprio(kAtWork);
     }
     __syncthreads();
     {
