@@ -383,10 +383,12 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     }
 
     float lv[S];
-    lv[0] = low;
-    lv[S - 1] = high;
 #pragma unroll
-    for (int k = 1; k < S - 1; ++k) lv[k] = my.level[k].value;
+    for (int k = 0; k < S; ++k) lv[k] = my.level[k].value;
+    if constexpr (!(C < 8 && S == 4)) {  // (kept through the solves but for the kernel that has 96 registers: three would go to scratch memory)
+        lv[0] = low;
+        lv[S - 1] = high;
+    }
     if (part == 0u && exists) {
         float mine = lv[0];
 #pragma unroll

@@ -42,7 +42,7 @@ def kernels():
     return found
 
 
-@pytest.mark.parametrize("kernel", ["orq_team_kernel"])
+@pytest.mark.parametrize("kernel", ["orq_team_kernel", "orq_pool_kernel", "orq_rows_kernel", "orq_gather_kernel", "orq_quantize_kernel"])
 def test_no_scratch_memory(kernels, kernel):
     """Registers that spill cost a trip to memory in every bucket."""
     mine = {name: k[".private_segment_fixed_size"] for name, k in kernels.items() if kernel in name}
