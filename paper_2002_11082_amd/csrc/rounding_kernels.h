@@ -838,13 +838,8 @@ __device__ __forceinline__ uint32_t push_bit(uint32_t x, uint64_t mask)
     return r;
 }
 
-// 2 x + (1 in the lanes where a < b): a compare and an add with carry, two wait states between them (the compiler does not look into the
-// asm).  Of two such pairs one's instructions are most of the other's wait.
-__device__ __forceinline__ void push_less(uint32_t& x, float a, float b)
-{
-    asm("v_cmp_lt_f32_e32 vcc, %1, %2\n\ts_nop 1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(x) : "v"(a), "v"(b) : "vcc");
-}
-
+// x = 2 x + (1 in the lanes where a < b), y likewise: two compares, two wait states (the compiler does not look into the asm), two adds with carry; one
+// pair's instructions are most of the other's wait.
 __device__ __forceinline__ void push_less(uint32_t& x, float a, float b, uint32_t& y, float c, float d)
 {
     uint64_t first, second;
@@ -948,14 +943,17 @@ struct DrawsAhead {
 // Levels up to which the rounding test takes its width already multiplied by 2^-24 (above, the width is a difference of
 // two selected levels, see find_interval).
 constexpr int kScaledWidthLevels = 4;
-// Levels up to which the code is a sum of compares (LADDER in encode_chunks).  An element's code is the number of rungs k, 0 .. S - 2, with
+// Where the code is a sum of compares (LADDER in encode_chunks): three levels.  An element's code is the number of rungs k, 0 .. S - 2, with
 // u * width_k < x - level_k: below its interval that never holds, as the right side is negative, and above it always, as x - level_k is then at
 // least width_k, in fp32 too, and u * width_k at most the number below width_k.  That leaves intervals of width 0.  One that is not the last counts for
 // every element from its level on: there the number below the level stands in its place.  The last one never counts.  No selects, and the products and
 // compares of the rungs do not wait for each other: 25.6 M values in buckets of 32768, ORQ-3, 45.5 -> 44.3 us; with evenly spaced levels, whose
 // two products are one and whose middle level is 0, TernGrad 21.8 -> 21.3.  Four levels take 14 instructions that way where the selects take
-// 13, and were slower (44.0 -> 44.8).
-constexpr int kLadderLevels = 3;
+// 13, and were slower (44.0 -> 44.8).  Two levels have no selects to save (ORQ in buckets of 64 to 512 was 1 to 2 % slower; two elements side by side, which
+// fill the wait, gained nothing); a single chunk does not earn back the numbers below the levels, which differ from lane to lane there (ORQ-3, 20 M values in
+// buckets of 64: selects 48.8, sums 50.0).
+template <int S, int C>
+constexpr bool kLadder = S == 3 && C > 1;
 
 // Index of an element's interval (see find_interval; five, eight or nine levels).
 template <int S>
@@ -995,15 +993,15 @@ __device__ __forceinline__ void transpose_codes(const uint32_t (&a)[4], uint32_t
 }
 
 // Encodes and packs chunks c0 .. c0 + GROUP - 1 (256 elements each).  CAREFUL: valid for every width and Philox block;
-// otherwise encode_is_plain() holds.  EVEN: three levels -M, 0, M.
-template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL, bool AHEAD, bool EVEN, class Pairs>
+// otherwise encode_is_plain() holds.  EVEN: three levels -M, 0, M.  LADDER: see kLadder.
+template <class Layout, int GROUP, int S, int BITS, Fill FILL, bool CAREFUL, bool AHEAD, bool EVEN, bool LADDER, class Pairs>
 __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (&lv)[S], const float (&width)[S - 1], uint32_t c0,
                                               const EncodeRange& range, const PhiloxWords& words,
                                               const NibbleTranspose& transpose, uint32_t lane, Pairs pairs,
                                               const float (*ahead)[4] = nullptr)
 {
     constexpr bool SCALED = !CAREFUL && S <= kScaledWidthLevels;
-    constexpr bool LADDER = !CAREFUL && S <= kLadderLevels;
+    static_assert(!LADDER || (S == 3 && !CAREFUL), "two rungs, finite widths");
     constexpr bool LOOKUP = !CAREFUL && Pairs::kUsed;
     constexpr int PLANES = 8 / GROUP;                // planes that share a register for the transpose
     constexpr int REGS = (BITS + PLANES - 1) / PLANES;
@@ -1052,10 +1050,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
                 continue;
             }
             if constexpr (LADDER) {
-                if constexpr (S == 3)
-                    push_less(rung[0], draws[k] * width[0], x - lv[0], rung[1], draws[k] * width[EVEN ? 0 : 1], EVEN ? x : x - lv[1]);
-                else
-                    push_less(rung[0], draws[k] * width[0], x - lv[0]);
+                push_less(rung[0], draws[k] * width[0], x - lv[0], rung[1], draws[k] * width[EVEN ? 0 : 1], EVEN ? x : x - lv[1]);
                 continue;
             }
             const Interval<S> in = find_interval<S>(x, lv, width);
@@ -1076,7 +1071,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
     if constexpr (LOOKUP) transpose_codes<BITS>(code, plane);
     if constexpr (LADDER) {
         plane[0] = rung[0] ^ rung[1];
-        if constexpr (S > 2) plane[1] = rung[1];
+        plane[BITS - 1] = rung[1];
     }
     if constexpr (GROUP == 1) {
         // a single chunk: the 8 lanes of a half word or their nibbles together, and lane p of them stores plane p
@@ -1113,7 +1108,7 @@ __device__ __forceinline__ void encode_chunks(const float (*v)[4], const float (
 
 // Whether the lean form of encode_chunks may be used: all of the range's Philox blocks share the upper counter word, and
 // (where the widths are scaled) no width is so small that width * 2^-24 rounds.  Both hold for all but a few buckets
-// that one meets in earnest.  The rungs of up to three levels also want finite widths.
+// that one meets in earnest.  The rungs of three levels also want finite widths.
 template <int CHUNKS, int S, bool SCALED>
 __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], const EncodeRange& range)
 {
@@ -1124,7 +1119,7 @@ __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], con
         for (int k = 0; k < S - 1; ++k) smallest = umin32(smallest, __float_as_uint(width[k]) - 1u);
         plain = plain && __ballot(smallest < __float_as_uint(0x1p-102f) - 1u) == 0;
     }
-    if constexpr (S <= kLadderLevels) {
+    if constexpr (kLadder<S, CHUNKS>) {
         bool finite = true;
 #pragma unroll
         for (int k = 0; k < S - 1; ++k) finite = finite && __builtin_fabsf(width[k]) < __builtin_inff();
@@ -1138,7 +1133,8 @@ __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], con
 // reload(c, y) fetches the lane's four elements of chunk c once more.
 //
 // Bound by vector-instruction issue: Philox takes 9.5 instructions per element, the rounding test 5 or 6, the interval
-// 0 .. 14 (find_interval).  The level index is assembled from the compare masks on the scalar unit.  Every bit plane keeps
+// 0 .. 14 (find_interval).  The level index is assembled from the compare masks on the scalar unit, with three levels it is a sum of
+// compares (kLadder).  Every bit plane keeps
 // one register for up to 8 chunks: the elements are taken in descending order and each shifts its bit in (one
 // instruction), so nibble c of lane l ends up holding the bits of this lane's four elements of chunk c.  One nibble
 // transpose among 8 lanes then leaves 32 consecutive bits of a packed word in every lane, stored with one instruction
@@ -1161,7 +1157,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         for (uint32_t c = 0; 256u * c < range.len; ++c) {
             float y[1][4];
             reload(c, y[0]);
-            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true, false, EVEN>(y, lv, width, c, range, PhiloxWords{}, transpose, lane, NoPairs{});
+            encode_chunks<Layout, 1, S, BITS, FILL == Fill::kAll ? Fill::kRagged : FILL, true, false, EVEN, false>(y, lv, width, c, range, PhiloxWords{}, transpose, lane, NoPairs{});
         }
         return;
     }
@@ -1169,10 +1165,10 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
 #pragma unroll
         for (int k = 0; k < S - 1; ++k) width[k] *= 0x1p-24f;
     }
-    float base[S];  // (see kLadderLevels)
+    float base[S];  // (see kLadder)
 #pragma unroll
     for (int k = 0; k < S; ++k) base[k] = lv[k];
-    if constexpr (S <= kLadderLevels) {
+    if constexpr (kLadder<S, C>) {
 #pragma unroll
         for (int k = 0; k < S - 1; ++k) {
             if (k < S - 2) base[k] = width[k] == 0.0f ? next_below(lv[k]) : lv[k];
@@ -1196,7 +1192,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         }
         const float(*ahead)[4] = nullptr;
         if constexpr (Draws::kAhead) ahead = &draws.draw[c0];
-        encode_chunks<Layout, GROUP, S, BITS, FILL, false, Draws::kAhead, EVEN>(&v[c0], base, width, (uint32_t)c0, range, words, transpose, lane, pairs, ahead);
+        encode_chunks<Layout, GROUP, S, BITS, FILL, false, Draws::kAhead, EVEN, kLadder<S, C>>(&v[c0], base, width, (uint32_t)c0, range, words, transpose, lane, pairs, ahead);
     }
 }
 
