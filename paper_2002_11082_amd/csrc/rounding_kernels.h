@@ -40,10 +40,10 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // each; written out because the compiler takes the scalar product for a vector one).  What depends on c1 and the key alone
 // is made once and held in registers: the compiler would make it again behind every branch.  VECTOR: in vector registers.  An exclusive or with a
 // scalar operand issues in four cycles, one of vector registers alone in little more than half of that where other wavefronts fill in, and a Philox
-// block has 17 of them; but 19 moves come first, which pay
-// from some eight blocks on, and 19 registers must cost no wavefronts: three evenly spaced levels (25.6 M values in buckets of 2048, TernGrad 21.3 -> 20.7 us)
-// and the pool's draws (143.7 M in buckets of 4096, eight levels, 293 -> 287).  Buckets of 128, four blocks: no gain; three levels in buckets of 16384,
-// whose kernel then has five wavefronts per SIMD in place of eight: 28.0 -> 29.4.
+// block has 17 of them; but 19 moves come first, and 19 registers must cost no wavefronts, as they don't in the pool's draws (143.7 M values in buckets of
+// 4096, eight levels, 293 -> 287 us).  Everywhere else the keys are scalar: three evenly spaced levels, 25.6 M values in buckets of 2048, would have six
+// wavefronts per SIMD in place of eight, in buckets of 512 five in place of seven (vector 24.2 us, scalar 23.6; 24.0 both), three
+// levels in buckets of 16384 five in place of seven (29.4 and 28.0).
 struct PhiloxWords {
     uint32_t first;       // k1
     uint32_t second[2];   // of round 2: what x0 and x2 are combined with
@@ -1183,7 +1183,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         wave_lds_sync();
     }
     PhiloxWords words{};
-    if constexpr (!Draws::kAhead) words = philox_words<(EVEN && C >= 8)>((uint32_t)(range.block >> 32), range.k0, range.k1);
+    if constexpr (!Draws::kAhead) words = philox_words<false>((uint32_t)(range.block >> 32), range.k0, range.k1);
     constexpr int GROUP = C < 8 ? C : 8;
 #pragma unroll
     for (int c0 = C - GROUP; c0 >= 0; c0 -= GROUP) {
