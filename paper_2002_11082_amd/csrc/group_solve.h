@@ -25,7 +25,6 @@ static_assert(sizeof(GroupLevel) == 32, "addressed by shifts");
 struct ScaledBins {
     float scale, offset;  // y = magnitude * scale + offset
     uint32_t factor;      // bins per unit in the last place of y, times 2^32
-    uint64_t origin;      // what `offset` times `factor` is taken off with
 };
 
 template <int HALF>
@@ -38,17 +37,15 @@ __device__ __forceinline__ ScaledBins scaled_bins(float mean_magnitude, uint32_t
     b.offset = fminf(unit * b.scale, 1.0f);  // (infinities: 1)
     const uint32_t range = 0x3F800000u - __float_as_uint(b.offset);
     b.factor = (uint32_t)fminf((float)HALF * 0x1p32f * __builtin_amdgcn_rcpf((float)range + 1.0f), 0x1.fffffep31f);
-    b.origin = 0u - (uint64_t)__float_as_uint(b.offset) * b.factor;
-    asm("" : "+v"(b.origin));  // (known, it is turned back into a subtraction and a wider product)
     return b;
 }
 
+// (y's bits - offset's bits) * factor; the minimum: rounding near the largest, NaN.
 template <int HALF>
 __device__ __forceinline__ uint32_t magnitude_bin(float value, const ScaledBins& b)
 {
     const uint32_t y = __float_as_uint(__builtin_fmaf(__builtin_fabsf(value), b.scale, b.offset));
-    // (y's bits - offset's bits) * factor, one multiply-add; the minimum: rounding near the largest, NaN
-    return umin32((uint32_t)(((uint64_t)y * b.factor + b.origin) >> 32), (uint32_t)(HALF - 1));
+    return umin32(__umulhi(y - __float_as_uint(b.offset), b.factor), (uint32_t)(HALF - 1));
 }
 
 // Bin of a value (with -0 already turned into +0) counted from the middle: -HALF .. HALF - 1.
@@ -56,6 +53,23 @@ template <int HALF>
 __device__ __forceinline__ int32_t signed_bin(float canonical, const ScaledBins& b)
 {
     return (int32_t)magnitude_bin<HALF>(canonical, b) ^ ((int32_t)__float_as_uint(canonical) >> 31);
+}
+
+// The same for many values: the subtraction goes into the product, one multiply-add, with two registers more; they must not live through the solves
+// (orq_rows_kernel<16, 2> would have 97 registers where five wavefronts per SIMD allow 96: four levels, two sweeps, 16383 buckets of 128 14.2 and 15.6 us).
+__device__ __forceinline__ uint64_t bin_origin(const ScaledBins& b)
+{
+    uint64_t origin = 0u - (uint64_t)__float_as_uint(b.offset) * b.factor;
+    asm("" : "+v"(origin));  // (known, it is turned back into a subtraction and a wider product)
+    return origin;
+}
+
+template <int HALF>
+__device__ __forceinline__ int32_t signed_bin(float canonical, const ScaledBins& b, uint64_t origin)
+{
+    const uint32_t y = __float_as_uint(__builtin_fmaf(__builtin_fabsf(canonical), b.scale, b.offset));
+    const uint32_t bin = umin32((uint32_t)(((uint64_t)y * b.factor + origin) >> 32), (uint32_t)(HALF - 1));
+    return (int32_t)bin ^ ((int32_t)__float_as_uint(canonical) >> 31);
 }
 
 // Grouping.  A bin's counter begins as the LDS address of its entry of `bin_start` in the upper half and that of the grouped values in the

@@ -170,6 +170,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
     uint32_t slot[C][4];  // what the bin's counter returned (counter_start)
     {
         const float zero = opaque_zero();
+        const uint64_t origin = bin_origin(bins_of);
         uint32_t middle = (uint32_t)(uintptr_t)((LdsWord*)my.bin_count + HALF);
         asm("" : "+s"(middle));  // (one addition with the bin, not two)
         uint32_t here = lane;
@@ -181,7 +182,7 @@ __device__ __forceinline__ void orq_pool_group(PoolLds<W, C, S>& lds, const floa
                 for (int k = 0; k < 4; ++k) {
                     const bool valid = FULL || 256u * c + 4u * here + k < my_len;
                     // (padding adds 0 to one bin per lane: no branch)
-                    const uint32_t counter = middle + 4u * (uint32_t)(valid ? signed_bin<(int)HALF>(v[c][k] + zero, bins_of) : (int32_t)here);
+                    const uint32_t counter = middle + 4u * (uint32_t)(valid ? signed_bin<(int)HALF>(v[c][k] + zero, bins_of, origin) : (int32_t)here);
                     slot[c][k] = __hip_atomic_fetch_add((LdsWord*)(uintptr_t)counter, valid ? 4u : 0u, __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_WORKGROUP);
                 }

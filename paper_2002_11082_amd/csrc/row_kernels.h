@@ -189,11 +189,12 @@ __device__ __forceinline__ void orq_rows_span(RowLds<LANES, C, S>& lds, const fl
         {
             wave_lds_sync();
             const float zero = opaque_zero();
+            const uint64_t origin = bin_origin(bins);
             const uint32_t middle = (uint32_t)(uintptr_t)((LdsWord*)lds.bin_count) + 4u * (B * row + HALF);
             for_row_chunks<C, EXACT>(chunks, [&](int c) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const uint32_t counter = middle + 4u * (uint32_t)signed_bin<(int)HALF>(v[c][k] + zero, bins);
+                    const uint32_t counter = middle + 4u * (uint32_t)signed_bin<(int)HALF>(v[c][k] + zero, bins, origin);
                     slot[c][k] = __hip_atomic_fetch_add((LdsWord*)(uintptr_t)counter, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             });
