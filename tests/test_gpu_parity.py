@@ -432,9 +432,28 @@ def test_clipping_before_quantization(clip):
 
 
 @pytest.mark.parametrize("d,nb", [(64, 200), (128, 200), (128, 16400), (192, 3100), (512, 2100), (512, 300), (1024, 600), (2048, 60), (2048, 1300),
-                                  (4096, 400), (8192, 30), (16384, 17), (32768, 17)])
+                                  (4096, 400), (8192, 30), (32768, 9)])
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.BINGRAD_B, 1, 0), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0), (ogq.EVEN, 2, 0)])
 def test_clipping_threshold_where_the_mean_outweighs_the_spread(scheme, bits, sweeps, d, nb):
+    """The threshold comes from one pass over sums and squares, or from a second one about the mean where the difference cancels (mean above the
+    standard deviation): both sides of that limit beside each other, far beyond it, constant buckets and zeros, a cut-off last bucket."""
+    rng = np.random.default_rng(d + 7 * bits)
+    g = (rng.standard_normal(nb * d) * 1e-3).astype(np.float32)
+    buckets = g.reshape(nb, d)
+    for b, shift in enumerate([0.9, 1.1, 0.0, 1.0, -0.98, 30.0, -3e3, 0.5, 1.05]):
+        buckets[b] += np.float32(shift * 1e-3)
+    buckets[4] *= np.float32(1e-30)
+    buckets[6] = np.float32(0.1)
+    buckets[7] = 0.0
+    g = g[: nb * d - d // 3]
+    buckets = sorted(set(list(range(9)) + [nb // 2, nb - 2, nb - 1]))
+    parity.check_quantize(g, d, bits, scheme, sweeps, seed=5, buckets=buckets, clip_factor=1.7, tag=f"threshold-s{scheme}-b{bits}-d{d}")
+
+
+@pytest.mark.parametrize("d,nb", [(64, 200), (128, 200), (128, 16400), (192, 3100), (512, 2100), (512, 300), (1024, 600), (2048, 60), (2048, 1300),
+                                  (4096, 400), (8192, 30), (16384, 17), (32768, 17)])
+@pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.BINGRAD_B, 1, 0), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0), (ogq.EVEN, 2, 0)])
+def test_clipping_threshold_on_both_sides_of_its_limit(scheme, bits, sweeps, d, nb):
     """The threshold comes from one pass over sums and squares, or from a second one about the mean where the square of a bucket's mean is more than an
     eighth of the mean of its squares: buckets on both sides of that limit and right at it in turn, so that they share wavefronts and workgroups, then
     far beyond it, constant buckets and zeros, a cut-off last bucket."""
