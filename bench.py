@@ -72,52 +72,21 @@ def several_buckets_from(d: int, clipped: bool, updates: bool) -> int:
 
 def pool_gains(d: int, levels: int, solves: int, nb: int, clipped: bool) -> bool:
     """The rule of the same name in rounding_part.hip."""
-    second_round = 2560 < nb <= 3072
-    full_chip = 1792 < nb <= 2048
-    if levels >= 8:
-        if solves >= 12 or d <= 1024:
-            return True
-        if not clipped:
-            return nb >= (384 if d > 2048 else 1025)
-        if nb < 1281:
-            return False
-        return not (levels == 8 and d < 2048 and second_round) if d <= 2048 else d >= 2816 or nb > 2816 or full_chip
-    if levels == 5:
-        if solves >= 12:
-            return solves >= 18 or d <= 1024 or d >= 2048 or (nb >= 256 and not (clipped and second_round))
-        if d <= 1024:
-            if clipped:
-                return 1024 < nb <= 4096 and not second_round
-            return (nb <= 4096 or nb > 6144) and (solves >= 6 or (nb > 512 and not second_round))
-        if d < 2048:
-            return nb > 1280 and not second_round and (not clipped or nb <= 2560)
-        if d == 2048:
-            return nb > 1280 and not second_round if clipped else nb > 1024
-        if clipped:
-            return full_chip or nb > (1792 if d == 4096 else 2816)
-        if solves >= 6:
-            return nb >= 384
-        return nb > 1280 and (d == 4096 or not (1536 < nb <= 1792 or 2048 < nb <= 2432))
-    if d > 2048:
-        fuller = d >= 3584
-        if solves >= 12:
-            return nb >= (256 if fuller else 384)
-        if clipped:
-            return solves >= 6 and (full_chip or (d == 4096 and nb > 1792))
-        if solves >= 6:
-            return nb >= (384 if fuller else 1025)
-        return nb > 1280 if solves >= 4 and fuller else full_chip
-    if solves < 4:
-        return not clipped and (1536 < nb <= 5120 if d <= 1024 else 1792 < nb <= (20480 if d == 2048 else 4096))
-    if d <= 1024:
-        return solves >= 12 or nb >= (384 if solves >= 6 else 513)
-    if d == 2048 and solves >= 6:
-        return nb > (384 if solves >= 12 else 640)
     if solves >= 12:
-        return nb > 640
-    if clipped and solves < 6:
-        return nb > 1536 if d == 2048 else 1280 < nb <= 5120
-    return nb > 1280
+        return levels > 4 or d <= 1024 or d > 2048 or nb >= 256
+    if d <= 1024:
+        return solves >= 6 or nb >= (513 if solves == 2 else 384)
+    if levels >= 8:
+        return nb >= (384 if d > 2048 else 1025)
+    if d > 2048:
+        if solves == 2:
+            return nb > 3072 or 1792 < nb <= 2048
+        return nb >= (384 if solves >= 6 else 1025 if solves == 3 else 1281)
+    if levels == 4:
+        return nb >= ((384 if d == 2048 else 513) if solves >= 6 else 1025 if solves == 4 else 1281)
+    if clipped and d < 2048 and 2560 < nb <= 3072:
+        return False
+    return nb >= (1281 if solves < 6 else 384 if d == 2048 and not clipped else 1025)
 
 
 def quantize_kernel(synth, wl, n: int, levels: int):

@@ -2893,7 +2893,7 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(RULE =
 template <int C>
 constexpr bool wave_serves(int S, int rule, bool clip = false)
 {
-    return !(rule == kOptimal && S >= 8 && C >= 2 && C <= 8) || (S == 8 && C == 8 && clip);  // (eight levels: where pool_gains says)
+    return !(rule == kOptimal && S >= (C == 2 ? 8 : 4) && C >= 2 && C <= 8) || (S == 5 && C == 8 && clip);  // (five levels: where pool_gains says)
 }
 
 template <int C, int S, int BITS, int RULE = kOptimal>

@@ -40,73 +40,38 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 
 #if OGQ_PART == 4 || OGQ_PART == 8 || OGQ_PART == 16
 // Two or four buckets per workgroup whose levels one wavefront solves side by side (pool_kernels.h), where the solves are what a bucket
-// waits for.  What a solve takes in the other kernels depends on the values: their bins suit a mixture of scales and are crowded with
-// Gaussian values, the pool's suit both.  So neither side is the faster one for all values at every size, and the rule takes the
-// pool where it gains on the mean of four kinds of values (mixture, Gaussian, Laplace, Student-t) and of a whole and a cut-off last
-// bucket; profiles/pool_scan.txt and, with clipping, pool_clip_scan.txt have both sides, and tests/test_dispatch.py holds the rule against
-// them: no mean loses more than 3.5 %, no kind of values more than 13 % (mixtures in few buckets: five levels, three sweeps, 64 buckets of 2048
-// 10.6 -> 11.1 where Gaussian values go 20.4 -> 12.3), and the other kernel is kept nowhere that the mean would gain more than 13 %.
-// Clipped values end at a few sigma, which crowds the other kernels' bins less, so fewer calls take the pool.  Means, us, other -> pool
-// (solves: interior levels, once and for every sweep):
-//   eight, nine levels  12 solves and more at every size and number of buckets (18 solves: 64 buckets of 2112 16.8 -> 14.5, 2048 of 1024 24.7 ->
-//                       13.2; clipped, 12, 16 of 2048: 15.9 -> 14.1); fewer up to 1024 elements (6: 16 of 768 7.8 -> 7.3), to 2048 from 1025 buckets
-//                       on (514 of 1344: 10.1 -> 10.8, 1282 16.8 -> 13.8), above from 384 on (256 of 4096: 10.7 -> 10.6, 384 12.1 -> 10.7).
-//                       Clipped from 1281 on (1026 of 2112: 18.1 -> 19.1), but for
-//                       2561 to 3072 of 1088 to 1984 elements (second_round; eight levels, 2816 of 1344: 22.2 -> 23.6) and, of 2112 to 2752
-//                       elements, from 2817 on (2304 of 2112: 28.8 -> 30.1, 3072 35.8 -> 34.6) and in full_chip (2048 of 2112: 26.6 -> 25.0)
-//   five levels         12 solves and more likewise (64 of 4096: 15.8 -> 12.6), of 1088 to 1984 elements from 256 buckets on.  Fewer where the other
-//                       kernel has one wavefront per bucket, without those two rounds (3 solves, 2816 of 1344: 14.6 -> 15.6), of up to 1024
-//                       elements without 4097 to 6144 buckets (5120 of 768: 14.6 -> 15.1), 6 solves there also in fewer (16 of 768: 7.9 -> 7.5);
-//                       above 2048 elements 6 solves from 384 on (256 of 2112: 10.0 -> 11.1, 384 11.2 -> 11.1), 3 from
-//                       1281, but for the numbers at which only the pool begins another round (2304 of 2112: 19.8 -> 20.8).  Clipped, up to
-//                       1024 elements 1025 to 4096 buckets (3584 of 1024, 6 solves: 15.5 -> 13.6), above 2048 full_chip (2048 of 3008: 27.6 ->
-//                       25.6, 1792 23.7 -> 25.5) and many
-//   four levels         where the other kernel has one wavefront per bucket (6 solves: 4096 of 2048 22.5 -> 17.6), and some below (384 of 1024: 8.8 ->
-//                       8.1, 768 of 2048 12.4 -> 10.9, 514 11.4 -> 11.1); two solves while that is one round of it, beyond which neither side
-//                       gains (4352 of 1344: 19.1 -> 19.3; whole 2048, 8192: 28.9 -> 27.8, 12290 40.7 -> 41.0).  A round of the pool is 4096 buckets of
-//                       1088 to 2048 elements; one with few buckets takes some of the gain (6 solves, 12290 of 2048: 52.6 -> 50.4).  Above 2048
-//                       elements with 6 solves (4096 of 4096: 38.9 -> 33.8, 384 12.5 -> 11.2; 384 of 2112 11.6 -> 11.9), fewer in full_chip, where
-//                       only the other kernel needs a second round (2 solves of 2112: 2048 17.7 -> 15.2, 1792 13.9 -> 15.1).  12 solves and
-//                       more mostly repeat what they find, which the pool ends early: 16 of 768 11.1 -> 10.4, 384 of 2112 15.2 -> 14.5
+// waits for: but for few buckets with few solves nearly everywhere.  What a solve takes in the other kernels depends on the values: their bins suit a
+// mixture of scales and are crowded with Gaussian values, the pool's suit both.  The rule takes the pool where it gains on the mean of four kinds of values
+// (mixture, Gaussian, Laplace, Student-t) and of a whole and a cut-off last bucket; profiles/pool_scan.txt and, with clipping, pool_clip_scan.txt have both sides, and
+// tests/test_dispatch.py holds the rule against them.  On the recorded sizes no mean loses more than 2.7 %, no kind of values more than 10 % (mixtures in
+// few buckets: four levels, five sweeps, 256 of 1664), and the other kernel is kept nowhere that the mean would gain more than 12 %.  Means, us,
+// other -> pool (solves: interior levels, once and for every sweep):
+//   12 solves and more  at every number of buckets (eight levels, 18: 64 of 2112 16.5 -> 14.0, 2048 of 1024 24.4 -> 12.6, 12290 of 4096 160 -> 103;
+//                       five, 64 of 2112 13.7 -> 12.3), four levels of 1088 to 2048 elements from 256 on: repeated sweeps end early with a mixture in
+//                       either kernel (256 of 2048 15.8 -> 12.8, but mixtures in 16 of 1984 14 % slower)
+//   up to 1024 elements from six solves on always (16 of 768, eight levels 7.7 -> 7.2, four 8.1 -> 7.8), below from 384 (256, five levels: 6.0 -> 6.2, 384
+//                       6.6 -> 6.2; four, one sweep, 7.0 -> 7.0 and 7.5 -> 7.1), with two solves where the other kernel has one wavefront per bucket
+//   eight, nine levels  of up to 2048 elements from 1025 on (768 of 1344: 10.7 -> 11.0, 1026 11.6 -> 11.0), above from 384 (256 of 2112: 10.2 -> 10.9,
+//                       384 11.1 -> 10.9)
+//   five levels         of up to 2048 six solves from 1025 (of whole 2048, whose values are not clipped, from 384: 11.1 -> 9.4; clipped, 768, 12.1 -> 12.2), three from
+//                       1281 (1026 of 1344: 9.2 -> 9.5, 1282 11.2 -> 9.9); clipped not in the pool's second round, where one wavefront per bucket has its first
+//                       (2816 of 1344: 16.1 -> 16.9, 18.4 -> 19.3).  Above, six from 384 and three from 1025 (768 of 2112: 10.1 -> 10.1, 1026 11.3 -> 11.1)
+//   four levels         of up to 2048 six solves from 513 (514 of 1664: 10.6 -> 10.7), of whole 2048 from 384 (11.4 -> 10.1), four from 1025 (768 of
+//                       1664: 9.4 -> 9.8, 1026 10.4 -> 10.1), two from 1281 (1026: 8.6 -> 9.2, 1282 10.9 -> 10.1).  Above, six from 384 (256 of 2112: 10.5 ->
+//                       10.9, 384 11.4 -> 11.0), four from 1281 (clipped, 1026: 14.8 -> 15.5, 1282 16.1 -> 16.0), two where only the other kernel needs a second
+//                       round (2048: 16.9 -> 13.2) and from 3073 on (2304: 17.7 -> 18.9, 3584 23.6 -> 23.6, 4096 26.9 -> 24.5)
 static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb, bool clipped)
 {
-    const bool second_round = nb > 2560u && nb <= 3072u;  // of the pool up to 2048 elements, where one wavefront per bucket has its first
-    const bool full_chip = nb > 1792u && nb <= 2048u;     // above 2048 elements: the pool's first round, the other kernel's second
-    if (levels >= 8u) {
-        if (solves >= 12u || d <= 1024u) return true;
-        if (!clipped) return nb >= (d > 2048u ? 384u : 1025u);
-        if (nb < 1281u) return false;
-        return d <= 2048u ? !(levels == 8u && d < 2048u && second_round) : d >= 2816u || nb > 2816u || full_chip;
-    }
-    if (levels == 5u) {
-        if (solves >= 12u) return solves >= 18u || d <= 1024u || d >= 2048u || (nb >= 256u && !(clipped && second_round));
-        if (d <= 1024u) {
-            if (clipped) return nb > 1024u && nb <= 4096u && !second_round;
-            return (nb <= 4096u || nb > 6144u) && (solves >= 6u || (nb > 512u && !second_round));
-        }
-        if (d < 2048u) return nb > 1280u && !second_round && (!clipped || nb <= 2560u);
-        if (d == 2048u) return clipped ? nb > 1280u && !second_round : nb > 1024u;
-        if (clipped) return full_chip || nb > (d == 4096u ? 1792u : 2816u);
-        if (solves >= 6u) return nb >= 384u;
-        return nb > 1280u && (d == 4096u || !((nb > 1536u && nb <= 1792u) || (nb > 2048u && nb <= 2432u)));
-    }
+    if (solves >= 12u) return levels > 4u || d <= 1024u || d > 2048u || nb >= 256u;
+    if (d <= 1024u) return solves >= 6u || nb >= (solves == 2u ? 513u : 384u);
+    if (levels >= 8u) return nb >= (d > 2048u ? 384u : 1025u);
     if (d > 2048u) {
-        const bool fuller = d >= 3584u;
-        if (solves >= 12u) return nb >= (fuller ? 256u : 384u);
-        if (clipped) return solves >= 6u && (full_chip || (d == 4096u && nb > 1792u));
-        if (solves >= 6u) return nb >= (fuller ? 384u : 1025u);
-        return solves >= 4u && fuller ? nb > 1280u : full_chip;
+        if (solves == 2u) return nb > 3072u || (nb > 1792u && nb <= 2048u);
+        return nb >= (solves >= 6u ? 384u : solves == 3u ? 1025u : 1281u);
     }
-    if (solves < 4u) {
-        if (clipped) return false;
-        if (d <= 1024u) return nb > 1536u && nb <= 5120u;
-        return nb > 1792u && nb <= (d == 2048u ? 20480u : 4096u);
-    }
-    if (d <= 1024u) return solves >= 12u || nb >= (solves >= 6u ? 384u : 513u);
-    if (d == 2048u && solves >= 6u) return nb > (solves >= 12u ? 384u : 640u);
-    if (solves >= 12u) return nb > 640u;
-    if (clipped && solves < 6u) return d == 2048u ? nb > 1536u : nb > 1280u && nb <= 5120u;
-    return nb > 1280u;
+    if (levels == 4u) return nb >= (solves >= 6u ? (d == 2048u ? 384u : 513u) : solves == 4u ? 1025u : 1281u);
+    if (clipped && d < 2048u && nb > 2560u && nb <= 3072u) return false;
+    return nb >= (solves < 6u ? 1281u : d == 2048u && !clipped ? 384u : 1025u);
 }
 
 template <int W, int C>

@@ -1154,6 +1154,23 @@ def test_both_sides_of_every_limit(d, limit):
             parity.check_quantize(g[: count * d - 29], d, bits, scheme, sweeps, seed=41, buckets=checked, tag=f"limit-{name}-d{d}-nb{count}")
 
 
+@pytest.mark.parametrize("d,number", [(d, number) for d, numbers in limits.INSIDE.items() for number in numbers])
+def test_numbers_of_buckets_between_the_limits(d, number):
+    """The same between two limits, with clipping too."""
+    rng = np.random.default_rng(d + number)
+    kinds = ["heavy", "const", "ints", "normal", "zeros", "shifted"]
+    g = _rng_bucket(rng, (number + 1) * d, "heavy")
+    buckets = g.reshape(number + 1, d)
+    for b in [*range(6), *range(number - 7, number + 1)]:
+        buckets[b] = _rng_bucket(rng, d, kinds[b % len(kinds)])
+    for name in limits.rules(limits.INSIDE[d][number]):
+        scheme, bits, sweeps = limits.RULES[name]
+        for count, clip in ((number, 0.0), (number + 1, 0.0), (number + 1, 2.5)):
+            checked = [*range(7), *range(count - 9, count)]
+            parity.check_quantize(g[: count * d - 29], d, bits, scheme, sweeps, seed=41, buckets=checked, clip_factor=clip,
+                                  tag=f"inside-{name}-d{d}-nb{count}-c{clip}")
+
+
 @pytest.mark.parametrize("d,nb", [(448, 2600), (512, 2600), (704, 600), (1024, 600), (1472, 1400), (2048, 1400), (3008, 4200), (4096, 4200)])
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 1, 0), (ogq.ORQ, 2, 2), (ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 2, 0), (ogq.ORQ_PAPER, 3, 1),
                                                 (ogq.ORQ_PAPER, 4, 0), (ogq.BINGRAD_PB, 1, 0), (ogq.LINEAR, 3, 0), (ogq.EVEN, 2, 0)])
