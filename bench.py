@@ -63,10 +63,11 @@ def read_note(file_name: str, kernel_key: str):
 
 def several_buckets_from(d: int, clipped: bool, updates: bool) -> int:
     """The rule of the same name in bingrad.hip."""
-    listed = {64: (8192, 10240, 10240), 128: (4608, 5632, 12288), 192: (4608, 4608, 6656), 256: (4608, 5632, 7680), 512: (6144, 6144, 6656),
-              1024: (4608, 4608, 6656)}
+    # without threshold updates, with them, clipped, clipped with updates
+    listed = {64: (8192, 10240, 12288, 10240), 128: (4608, 6656, 12288, 12288), 192: (4608, 4608, 6656, 6656), 256: (4608, 6656, 7680, 7680),
+              512: (6656, 6656, 6656, 6656), 1024: (4608, 6656, 6656, 6656)}
     if d in listed:
-        return listed[d][2 if clipped else int(updates)]
+        return listed[d][2 * int(clipped) + int(updates)]
     return 4608 if d < 512 else 768 if d in (704, 768) else 2560
 
 

@@ -615,23 +615,25 @@ void launch_bingrad_chunks(const float* g, size_t n, const ogq_params_t* p, floa
 // Number of buckets from which several of them share a wavefront.  Below, every SIMD has a wavefront or two anyway and one with more
 // buckets only takes longer; threshold updates add to that.  profiles/bingrad_scan.txt has both sides for every size, tests/test_dispatch.py
 // holds the limits against it.  us, one bucket per wavefront -> several, of BinGrad-b, its two updates, Scaled SignSGD:
-//   64    8192 buckets 4.1 -> 4.1, 6.3 -> 7.4, 3.0 -> 2.9; 10240: 5.1 -> 4.2, 7.3 -> 6.9, 3.4 -> 2.9; clipped, 10240: 5.8 -> 5.8, 8.4 -> 7.9, 4.2 -> 4.4
-//   128   4608: 3.5 -> 3.5, 4.9 -> 5.8, 2.8 -> 2.7; 5632: 3.9 -> 3.6, 5.4 -> 5.6, 3.1 -> 2.8; clipped, 12288: 7.1 -> 6.5, 10.2 -> 9.2, 5.4 -> 5.1
-//   256   4608: 4.2 -> 3.8, 5.7 -> 6.2, 3.4 -> 3.0; 5632: 4.4 -> 3.9, 6.2 -> 6.3, 3.4 -> 3.0; clipped, 7680: 5.9 -> 5.6, 8.3 -> 7.9, 4.6 -> 4.6
-//   512   5632: 4.2 -> 4.4, 6.7 -> 6.7, 3.3 -> 3.4; 6144: 4.2 -> 4.4, 6.8 -> 6.6, 3.7 -> 3.4; clipped, 6656: 6.2 -> 5.8, 8.9 -> 8.1, 4.9 -> 5.0
-//   1024  4096: 4.6 -> 4.8, 6.9 -> 7.3, 3.6 -> 3.6; 4608: 5.2 -> 5.1, 8.0 -> 8.0, 4.4 -> 3.9; clipped, 6656: 8.4 -> 8.3, 12.1 -> 12.0, 6.5 -> 6.7
+//   64    8192 buckets 4.4 -> 4.2, 6.3 -> 6.8, 3.3 -> 2.9; 10240: 4.6 -> 4.2, 7.2 -> 6.8, 3.3 -> 2.9; clipped, 10240: 5.7 -> 6.1, 8.4 -> 8.3, 4.1 -> 4.8;
+//         12288: 6.4 -> 6.1, 9.6 -> 8.3, 4.6 -> 4.8
+//   128   4608: 3.4 -> 3.6, 4.9 -> 5.8, 2.7 -> 2.8; 6656: 3.9 -> 3.6, 5.8 -> 5.8, 2.9 -> 2.8; clipped, 12288: 6.8 -> 5.9, 9.9 -> 8.5, 4.7 -> 4.4
+//   256   4608: 3.8 -> 3.8, 5.4 -> 6.2, 3.0 -> 2.9; 6656: 4.3 -> 4.1, 6.4 -> 6.4, 3.3 -> 3.2; clipped, 7680: 5.6 -> 5.1, 8.1 -> 7.4, 4.1 -> 3.9
+//   512   6144: 4.3 -> 4.4, 6.7 -> 6.7, 3.1 -> 3.4; 6656: 4.6 -> 4.5, 7.3 -> 6.8, 3.3 -> 3.5; clipped 5.8 -> 5.5, 8.8 -> 7.8, 4.3 -> 4.4
+//   1024  4096: 4.7 -> 4.7, 7.0 -> 7.3, 3.7 -> 3.7; 4608: 5.3 -> 5.2, 8.1 -> 8.2, 4.5 -> 3.9; 5632: 5.8 -> 5.9, 9.0 -> 9.5, 4.9 -> 4.4; 6656: 6.7 -> 6.1, 10.1 -> 9.8,
+//         5.4 -> 4.8; clipped 7.9 -> 8.0, 11.6 -> 11.6, 6.3 -> 6.1
 // A size between two of these leaves registers of the one-bucket kernel empty, and shares earlier:
-//   192   4096: 3.8 -> 3.6, 5.2 -> 5.4, 3.0 -> 2.8; 4608: 4.3 -> 3.5, 5.9 -> 5.3, 3.4 -> 3.0; clipped, 6656: 6.5 -> 6.0, 8.7 -> 8.4, 5.2 -> 4.7
-//   704   512: 3.2 -> 3.0, 4.3 -> 4.4, 2.7 -> 2.4; 768: 3.6 -> 3.0, 5.1 -> 4.4, 2.8 -> 2.4; clipped 4.6 -> 3.6, 6.1 -> 5.0, 3.9 -> 3.0
+//   192   4096: 3.7 -> 3.5, 5.0 -> 5.4, 2.9 -> 2.8; 4608: 4.1 -> 3.5, 5.8 -> 5.4, 3.2 -> 2.8; clipped, 6656: 6.0 -> 5.5, 8.4 -> 8.0, 4.7 -> 4.3
+//   704   512: 3.2 -> 3.1, 4.3 -> 4.5, 2.7 -> 2.5; 768: 3.6 -> 3.1, 5.1 -> 4.5, 2.9 -> 2.5; clipped 4.2 -> 3.6, 5.8 -> 5.0, 3.6 -> 3.0
 static uint32_t several_buckets_from(uint32_t d, bool clipped, bool updates)
 {
     switch (d) {
-        case 64: return clipped || updates ? 10240u : 8192u;
-        case 128: return clipped ? 12288u : updates ? 5632u : 4608u;
+        case 64: return updates ? 10240u : clipped ? 12288u : 8192u;
+        case 128: return clipped ? 12288u : updates ? 6656u : 4608u;
         case 192: return clipped ? 6656u : 4608u;
-        case 256: return clipped ? 7680u : updates ? 5632u : 4608u;
-        case 512: return clipped ? 6656u : 6144u;
-        case 1024: return clipped ? 6656u : 4608u;
+        case 256: return clipped ? 7680u : updates ? 6656u : 4608u;
+        case 512: return 6656u;
+        case 1024: return clipped || updates ? 6656u : 4608u;
         case 704: case 768: return 768u;
         default: return d < 512u ? 4608u : 2560u;
     }
