@@ -20,8 +20,8 @@ namespace ogq {
 // levels, buckets of 128 69 -> 43.7 -> 38.7; eight levels, two sweeps, 512: 137.6 -> 93.4 (the last two).
 // The phases are those of orq_bucket: extremes, grouping in LDS by value bins (ScaledBins), fp64 prefix, level solves, encode.
 //
-// Positions and bin counts are kept in bytes (times 4), bin starts as offsets into the wavefront's values, so that the scatter
-// needs one addition per element.  Buckets of 256 in rows of 8 lanes were slower (1 to 27 %: half the wavefronts, twice the registers).
+// Positions and bin counts are kept in bytes (times 4), bin starts as offsets into the wavefront's values; what a bin's counter hands an element
+// leaves the scatter two vector instructions (counter_start).  Buckets of 256 in rows of 8 lanes were slower (1 to 27 %: half the wavefronts, twice the registers).
 // ----------------------------------------------------------------------------------------------
 // LDS of a wavefront.  At 512 elements per bucket it decides how many wavefronts a CU holds (14 with 11.5 KB), so the bin counts lie
 // where the values are grouped afterwards, and bin starts take 16 bits.
@@ -397,13 +397,25 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(C == 8 ? 
 // ----------------------------------------------------------------------------------------------
 // host side
 // ----------------------------------------------------------------------------------------------
+// Which rules and level counts the dispatch in rounding_part.hip gives to rows of LANES; the others are not compiled, and asking for one fails
+// (see wave_serves).
+template <int LANES, int C>
+constexpr bool rows_serve(int S, int rule)
+{
+    return !(LANES == 16 && C == 2 && S >= 5 && rule == kLinear);  // (buckets of 128: rows of 8 lanes or sorted_small_kernel)
+}
+
 template <int LANES, int C, int S, int BITS, bool EXACT, int RULE>
 void launch_rows(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
-    constexpr uint32_t ROWS = RowLds<LANES, C, S>::ROWS;
-    const uint32_t spans = (uint32_t)(n / p->bucket_size / ROWS);
-    launch_kernel((orq_rows_kernel<LANES, C, S, BITS, EXACT, RULE>), dim3(nb - ROWS * spans + spans), dim3(kWave), st, g, n, p->bucket_size,
-                  p->level_iters, p->clip_factor, nb, spans, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
+    if constexpr (rows_serve<LANES, C>(S, RULE)) {
+        constexpr uint32_t ROWS = RowLds<LANES, C, S>::ROWS;
+        const uint32_t spans = (uint32_t)(n / p->bucket_size / ROWS);
+        launch_kernel((orq_rows_kernel<LANES, C, S, BITS, EXACT, RULE>), dim3(nb - ROWS * spans + spans), dim3(kWave), st, g, n, p->bucket_size,
+                      p->level_iters, p->clip_factor, nb, spans, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
+    } else {
+        launch_status() = hipErrorInvalidDeviceFunction;
+    }
 }
 
 template <int LANES, int C, bool EXACT>

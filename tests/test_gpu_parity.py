@@ -1265,6 +1265,20 @@ def test_random_numbers_of_the_chunks_that_hold_elements(scheme, bits, d, nb):
                                   clip_factor=clip, tag=f"chunks-s{scheme}-b{bits}-d{d}-cut{cut}")
 
 
+@pytest.mark.parametrize("bits,limit", [(3, 16384), (4, 65536)])
+@pytest.mark.parametrize("clip", [0.0, 2.5])
+def test_equal_mass_levels_in_buckets_of_128(bits, limit, clip):
+    """Sorted in registers up to the limit, eight buckets per wavefront from there on: one bucket less, the limit, and a last wavefront that is not full."""
+    rng = np.random.default_rng(bits)
+    for nb, cut in ((limit - 1, 0), (limit, 0), (limit + 3, 29)):
+        g = (rng.standard_t(3, nb * 128) * 1e-3).astype(np.float32)
+        g[128:256] = 0.25
+        g[3 * 128::7 * 128] = 0.0
+        sample = [*range(40), *range(nb - 40, nb), *map(int, rng.integers(0, nb, 40))]
+        parity.check_quantize(g[:nb * 128 - cut], 128, bits, ogq.LINEAR, 0, seed=3, index_offset=64 * 5, clip_factor=clip, buckets=sample,
+                              tag=f"linear128-b{bits}-nb{nb}-c{clip}")
+
+
 @pytest.mark.parametrize("scheme,bits,sweeps", [(ogq.ORQ, 3, 2), (ogq.ORQ_PAPER, 4, 1), (ogq.ORQ_PAPER, 3, 2)])
 def test_levels_in_bins_beyond_the_sort(scheme, bits, sweeps):
     """A level among 31 to 64 values of one bin, around the 32 that 8 lanes sort and the 64 that 16 lanes do; distinct values,
