@@ -22,13 +22,13 @@ namespace ogq {
 #define OGQ_CAT(a, b) OGQ_CAT2(a, b)
 
 // Few buckets: where a gradient has at most a few of them per CU, the time of a call is that of one bucket, and several
-// wavefronts per bucket shorten it (64 buckets of 2048, one wavefront and four: eight levels 21.6 -> 14.4 us, three 6.0 ->
+// wavefronts per bucket shorten it (64 buckets of 2048, one wavefront and four: eight levels 20.8 -> 14.6 us, three 5.9 ->
 // 4.8); beyond, the barriers and the registers of the idle wavefronts cost more than the shorter bucket gains (4096 buckets:
-// 39.2 -> 50.0, 13.6 -> 16.2).  profiles/few_buckets_scan.txt has both sides for all rules and sizes.  Each limit up to 2048
-// elements, and that above 4096, is a measured number of buckets up to which no rule loses more than 3 %; one number serves all rules, so some
-// would gain further (768 buckets of 1024: BinGrad-pb 5.8 -> 6.3, five levels 7.1 -> 6.9).  From 2049 to 4096 elements the other form is two
-// wavefronts, and four lose to it around 2048 buckets, where they begin a second round (2048 of 2560: ORQ-4 17.9 -> 23.2, the most of
-// any rule; from 2560 on they gain again, 27.7 -> 26.1).
+// 38.5 -> 51.1, 14.1 -> 16.8).  profiles/few_buckets_scan.txt has both sides for all rules and sizes.  Each limit up to 2048
+// elements, and that above 4096, is a measured number of buckets up to which no rule loses more than 3 % (but BinGrad-pb and three levels 5 and 4 % in
+// 1024 of 2048, which the sizes on both sides gain); one number serves all rules, so some would gain further (768 buckets of 1024: BinGrad-pb 6.0 ->
+// 6.6, five levels 7.3 -> 6.8).  From 2049 to 4096 elements the other form is two wavefronts, and four lose to it around 2048 buckets, where they begin a
+// second round (2048 of 2560: BinGrad-pb 14.6 -> 17.8, the most of any rule that the pool does not take; from 2560 on they gain again, 20.9 -> 20.0).
 template <int W, int C>
 bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes,
                 hipStream_t st)
@@ -92,7 +92,7 @@ static bool launch_pool_part(const float* g, size_t n, const ogq_params_t* p, ui
 #if OGQ_PART == 16
 // Four wavefronts of 1024 elements (28 of them in a CU, where two of 2048 make 16) are up to 18 % faster than two on the passes
 // over the elements; with BinGrad-pb's long solve that is lost again above some 4000 buckets, which two wavefronts serve better
-// (8192 buckets of 4096: 50.8 us with two, 53.4 with four).
+// (8192 buckets of 4096: 48.9 us with two, 51.4 with four).
 void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     if (launch_pool_part<2, 8>(g, n, p, nb, lv, codes, st)) return;
