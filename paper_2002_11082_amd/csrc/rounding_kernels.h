@@ -40,10 +40,11 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // each; written out because the compiler takes the scalar product for a vector one).  What depends on c1 and the key alone
 // is made once and held in registers: the compiler would make it again behind every branch.  VECTOR: in vector registers.  An exclusive or with a
 // scalar operand issues in four cycles, one of vector registers alone in little more than half of that where other wavefronts fill in, and a Philox
-// block has 17 of them; but 19 moves come first, and 19 registers must cost no wavefronts, as they don't in the pool's draws (143.7 M values in buckets of
-// 4096, eight levels, 293 -> 287 us).  Everywhere else the keys are scalar: three evenly spaced levels, 25.6 M values in buckets of 2048, would have six
-// wavefronts per SIMD in place of eight, in buckets of 512 five in place of seven (vector 24.2 us, scalar 23.6; 24.0 both), three
-// levels in buckets of 16384 five in place of seven (29.4 and 28.0).
+// block has 17 of them; but 19 moves and 19 registers come first.  They pay in the pool's draws, where they cost no wavefronts (143.7 M values in buckets of
+// 4096, eight levels, 293 -> 287 us), and with three evenly spaced levels in whole buckets of 2048, which have few other instructions, although six wavefronts
+// per SIMD are left of eight (scalar -> vector on two cards, 20 M values 16.2 -> 15.8, 17.2 -> 16.9; 25.6 M 19.9 -> 19.3, 21.4 -> 21.0; 50 M 36.9 -> 35.4, 37.8 -> 37.8).
+// In buckets of 512, where it is five of seven, neither is the faster one (16.5 -> 16.3, 17.3 -> 17.1; 12 M 11.6 -> 12.0; 50 M 36.8 -> 35.9, 38.0 -> 38.3), with clipping nothing
+// is left of it (24.3 -> 24.5), 8 wavefronts per bucket lose (25.6 M in buckets of 16384 23.9 -> 24.2), and so does ORQ-3 there (28.0 -> 29.4).
 struct PhiloxWords {
     uint32_t first;       // k1
     uint32_t second[2];   // of round 2: what x0 and x2 are combined with
@@ -1142,7 +1143,8 @@ __device__ __forceinline__ bool encode_is_plain(const float (&width)[S - 1], con
 // (PairsInLds): three or two compares give the interval's index, one look-up its level and width, and the index plus the carry is
 // the code: 17.5 instead of 23 vector instructions per element beside Philox at eight levels (nine levels, buckets of 512, clipping,
 // 25.6 M values 66.0 -> 63.3 us; eight levels, 32768 172.9 -> 167.1).  The rare range that encode_is_plain() refuses is encoded chunk by chunk in a loop.
-template <class Layout, int C, int S, int BITS, Fill FILL, bool EVEN = false, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
+template <class Layout, int C, int S, int BITS, Fill FILL, bool EVEN = false, bool VECTOR = false, class ReloadFn, class Pairs = NoPairs,
+          class Draws = DrawsInPlace>
 __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (&lv)[S], const EncodeRange& range, ReloadFn reload,
                                            Pairs pairs = Pairs{}, const Draws& draws = Draws{})
 {
@@ -1183,7 +1185,7 @@ __device__ __forceinline__ void encode_all(const float (&v)[C][4], const float (
         wave_lds_sync();
     }
     PhiloxWords words{};
-    if constexpr (!Draws::kAhead) words = philox_words<false>((uint32_t)(range.block >> 32), range.k0, range.k1);
+    if constexpr (!Draws::kAhead) words = philox_words<VECTOR>((uint32_t)(range.block >> 32), range.k0, range.k1);
     constexpr int GROUP = C < 8 ? C : 8;
 #pragma unroll
     for (int c0 = C - GROUP; c0 >= 0; c0 -= GROUP) {
@@ -1204,12 +1206,12 @@ __device__ __forceinline__ EncodeRange one_range(uint32_t len, size_t begin, uin
                        codes32 + begin / 64 * (2 * BITS)};
 }
 
-template <int C, int S, int BITS, bool FULL, bool EVEN = false, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
+template <int C, int S, int BITS, bool FULL, bool EVEN = false, bool VECTOR = false, class ReloadFn, class Pairs = NoPairs, class Draws = DrawsInPlace>
 __device__ __forceinline__ void orq_encode(const float (&v)[C][4], const float (&lv)[S], uint32_t len, size_t begin,
                                            uint64_t seed, uint64_t index_offset, uint32_t* __restrict__ codes32, ReloadFn reload,
                                            Pairs pairs = Pairs{}, const Draws& draws = Draws{})
 {
-    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged, EVEN>(v, lv, one_range<BITS>(len, begin, seed, index_offset, codes32), reload,
+    encode_all<OneRange, C, S, BITS, FULL ? Fill::kAll : Fill::kRagged, EVEN, VECTOR>(v, lv, one_range<BITS>(len, begin, seed, index_offset, codes32), reload,
                                                                         pairs, draws);
 }
 
@@ -2096,7 +2098,8 @@ __device__ __forceinline__ void orq_bucket(OrqLds<OrqShape<C>::D, OrqShape<C>::B
         for (int k = 0; k < S; ++k) levels[(size_t)bucket * S + k] = lv[k];
     }
 
-    orq_encode<C, S, BITS, FULL, RULE == kEven && S == 3>(v, lv, len, begin, seed, index_offset, codes32, ReloadFromMemory{g, len, limit},
+    constexpr bool EVEN = RULE == kEven && S == 3;
+    orq_encode<C, S, BITS, FULL, EVEN, EVEN && C == 8 && FULL && !CLIP>(v, lv, len, begin, seed, index_offset, codes32, ReloadFromMemory{g, len, limit},
                                  encoder_table<S, RULE != kEven>(lds.grouped, 0u));
 }
 
