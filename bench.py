@@ -121,9 +121,10 @@ def quantize_kernel(synth, wl, n: int, levels: int):
         elif d > 128:
             enough = 8192 if not solves else 256 if several and levels >= 8 else 3328 if d > 192 else 3072
         else:
-            enough = 8192 if not linear or levels == 3 else 16384 if levels == 5 else 65536
+            clipped = wl.clip_factor > 0
+            enough = 8192 if not linear or levels == 3 else (12288 if clipped else 16384) if levels == 5 else 16384 if clipped else 65536
         if nb >= enough:
-            return "orq_rows_kernel", 0.125 if d == 128 and nb >= (16384 if levels > 3 else 32768) else 0.25
+            return "orq_rows_kernel", 0.125 if d == 128 and (nb >= (16384 if levels > 3 else 32768) or (linear and levels > 3)) else 0.25
     if d in (64, 128):
         return "even_small_kernel" if even else "sorted_small_kernel", d / 256
     if 512 < d <= 4096 and wl.scheme in (synth.ORQ, synth.ORQ_PAPER) and levels >= 4:

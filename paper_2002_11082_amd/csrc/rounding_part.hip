@@ -109,8 +109,9 @@ void launch_rounding_c16(const float* g, size_t n, const ogq_params_t* p, uint32
 //   four and five levels    of 256 some 3300 (3500, five: 8.3 -> 6.4), above 4096; four without sweeps, two solves, of 448 and 512 7168 (5120 of
 //                           512: 9.4 -> 10.0, 8192: 12.5 -> 11.2), of 128 8192
 //   three levels, Linear-s  of 192 3072, of 256 3300 (3072, Linear-3: 4.1 -> 4.2), of 320 and 384 4096, of 448 7168 (5120, Linear-3: 7.0 -> 7.1),
-//                           of 512 8192, Linear-3 some 12000 to 16000 (9216: 9.0 -> 9.3), of 128 8192, Linear-5 16384 (12288: 6.4 -> 6.8, 16384: 7.5 -> 7.5)
-//                           and Linear-9 65536 (8192: 5.6 -> 7.6, 50000: 20.1 -> 20.4, 65536: 25.6 -> 24.2): what the sorted buckets need no search for
+//                           of 512 8192, Linear-3 some 12000 to 16000 (9216: 9.0 -> 9.3), of 128 8192, Linear-5 16384 (12288: 6.3 -> 6.7, 16384: 7.5 -> 7.4)
+//                           and Linear-9 65536 (8192: 5.6 -> 7.5, 50000: 19.4 -> 19.8, 65536: 24.3 -> 23.3), as sorted buckets need no search for their
+//                           levels; with clipping, which takes the other kernel longer, 12288 (7.3 -> 7.1) and 16384 (9.5 -> 9.4, 12288: 7.9 -> 8.7)
 //   no solves               of 320 4096, of 384 and 448 8192 (5120 of 448, nine levels: 5.8 -> 6.7, 8192: 7.7 -> 7.4), of 512 12000 to 16000 (9216:
 //                           8.1 -> 9.2), below 8192
 static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
@@ -126,7 +127,8 @@ static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uin
                                : d > 384u && (two_solves || (!optimal && levels < 9u)) ? 7168u
                                                                                       : optimal && levels >= 8u ? 2048u : 4096u;
     const uint32_t above_128 = !solves ? 8192u : optimal && levels >= 8u ? 256u : d > 192u ? 3328u : 3072u;
-    const uint32_t of_128 = p->scheme != OGQ_LINEAR || levels == 3u ? 8192u : levels == 5u ? 16384u : 65536u;
+    const bool clipped = p->clip_factor > 0.0f, more_masses = p->scheme == OGQ_LINEAR && levels > 3u;
+    const uint32_t of_128 = !more_masses ? 8192u : levels == 5u ? (clipped ? 12288u : 16384u) : clipped ? 16384u : 65536u;
     const uint32_t enough = d > 448u ? above_448 : d > 256u ? above_256 : d > 128u ? above_128 : of_128;
     if (nb < enough) return false;
 #if OGQ_PART == 1
@@ -134,7 +136,7 @@ static bool launch_row_part(const float* g, size_t n, const ogq_params_t* p, uin
         case 64: return false;  // (four buckets per wavefront already: sorted_small_kernel, even_small_kernel)
         case 128:  // eight buckets per wavefront where that leaves two wavefronts per SIMD, with three levels four (four buckets per
                    // wavefront -> eight, us: ORQ-3 9216 buckets 5.3 -> 5.5, 20480 7.3 -> 7.0, 32768 10.1 -> 8.9; ORQ-4 10240 6.9 -> 7.0, 16384 8.6 -> 8.0)
-            return nb < (levels > 3u ? 16384u : 32768u) ? launch_rows_levels<16, 2, true>(g, n, p, nb, lv, codes, st) : launch_rows_levels<8, 4, true>(g, n, p, nb, lv, codes, st);
+            return nb < (levels > 3u ? 16384u : 32768u) && !more_masses ? launch_rows_levels<16, 2, true>(g, n, p, nb, lv, codes, st) : launch_rows_levels<8, 4, true>(g, n, p, nb, lv, codes, st);
         case 192: return launch_rows_levels<16, 4, false>(g, n, p, nb, lv, codes, st);
         default: return launch_rows_levels<16, 4, true>(g, n, p, nb, lv, codes, st);
     }

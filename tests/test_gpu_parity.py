@@ -1265,9 +1265,8 @@ def test_random_numbers_of_the_chunks_that_hold_elements(scheme, bits, d, nb):
                                   clip_factor=clip, tag=f"chunks-s{scheme}-b{bits}-d{d}-cut{cut}")
 
 
-@pytest.mark.parametrize("bits,limit", [(3, 16384), (4, 65536)])
-@pytest.mark.parametrize("clip", [0.0, 2.5])
-def test_equal_mass_levels_in_buckets_of_128(bits, limit, clip):
+@pytest.mark.parametrize("bits,clip,limit", [(3, 0.0, 16384), (3, 2.5, 12288), (4, 0.0, 65536), (4, 2.5, 16384)])
+def test_equal_mass_levels_in_buckets_of_128(bits, clip, limit):
     """Sorted in registers up to the limit, eight buckets per wavefront from there on: one bucket less, the limit, and a last wavefront that is not full."""
     rng = np.random.default_rng(bits)
     for nb, cut in ((limit - 1, 0), (limit, 0), (limit + 3, 29)):
