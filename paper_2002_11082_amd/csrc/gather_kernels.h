@@ -35,7 +35,7 @@ struct GatherLds {
     static constexpr int SHIFT = D >= 32768 ? 16 : D >= 16384 ? 17 : 18;  // magnitude bits dropped
     static constexpr uint32_t LIST = 1024;
     uint32_t bin_count[B];
-    uint32_t list[LIST];  // the wanted bin's elements (bit patterns, -0 as +0), in any order
+    uint32_t list[LIST];  // the wanted bin's elements but zeros (bit patterns), in any order
     uint32_t list_count;
     uint32_t wave_total[W];
     uint32_t wanted[3];  // bin that holds the rank, elements in front of it, elements in it

@@ -457,7 +457,7 @@ __device__ __forceinline__ bool group_solve(const GroupBucket& b, uint32_t entry
 // where a bin is larger) and counts those that are smaller than its own; what they hold beyond the bin is larger than everything in it.
 // Returns false, and leaves the level alone, where that does not do for some active group: floor(T) not settled by its first guess, a
 // bin of more than 32 elements, a value that several elements share, L == R, a bucket that is not `ordinary`; the general solve then takes the
-// step.  Eight levels, two sweeps, buckets of 4096 of Student-t values: one step in 4,100 does, and a step takes 1,280 cycles; both kinds of
+// step.  Eight levels, two sweeps, buckets of 4096 of Student-t values: one step in 4,100 does, and a step takes 1,300 cycles; both kinds of
 // picks in one line of branches took 2,000 (profiles/phase_cycles.txt).
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) const double LdsDouble;

@@ -20,7 +20,7 @@ namespace ogq {
 // 143.7 M values in buckets of 4096, eight levels, two sweeps: 421 -> 368 us, with direct solves (group_solve_direct) and 1280 instead of 1024
 // bins, so that hardly a bin is too large for them, 310; 25.6 M values in buckets of 2048 124 -> 80 -> 69.
 // Bound by the solves' latency (profiles/phase_cycles.txt), of which the random numbers that a workgroup's other wavefronts make meanwhile are the
-// smaller part, and the LDS (16 KB of values per bucket of 4096), which holds the buckets of four workgroups; the vector units are busy 0.83 of the time
+// smaller part, and the LDS (16 KB of values per bucket of 4096), which holds the buckets of four workgroups; the vector units are busy 0.88 of the time
 // (profiles/orq_cfg4_issue_counters_pmc.txt).  The solving wavefront runs at a raised priority: its instructions go first on its SIMD.  Four
 // buckets per workgroup, in rows of 8 lanes, were slower (418 us when two took 368): fewer workgroups overlap.
 // Four levels: four buckets of up to 2048 elements, a row each, so that a workgroup spends no more instructions on solves than with more
