@@ -73,21 +73,36 @@ def several_buckets_from(d: int, clipped: bool, updates: bool) -> int:
 
 def pool_gains(d: int, levels: int, solves: int, nb: int, clipped: bool) -> bool:
     """The rule of the same name in rounding_part.hip."""
-    if solves >= 12:
-        return levels > 4 or d <= 1024 or d > 2048 or nb >= 256
-    if d <= 1024:
-        return solves >= 6 or nb >= (513 if solves == 2 else 384)
+    second_round = 2560 < nb <= 3072
+    full_chip = 1792 < nb <= 2048
+    fuller = d >= 3584
     if levels >= 8:
-        return nb >= (384 if d > 2048 else 1025)
+        return solves >= 12 or d <= 1024 or nb >= (1281 if clipped else 384 if d > 2048 else 1025)
+    if levels == 5:
+        if solves >= 12:
+            return solves >= 18 or d <= 1024 or d >= 2048 or nb >= 256
+        if d <= 1024:
+            return 1024 < nb <= 4096 if clipped else (nb <= 4096 or nb > 6144) and (solves >= 6 or nb > 512)
+        if d < 2048:
+            return nb > 1280 and not second_round
+        return nb >= (384 if solves >= 6 and (fuller or (d > 2048 and not clipped)) else 1025 if d == 2048 and not clipped else 1281)
     if d > 2048:
+        if solves >= 12:
+            return fuller or nb >= 384
+        if full_chip:
+            return True
         if solves == 2:
-            return nb > 3072 or 1792 < nb <= 2048
-        return nb >= (384 if solves >= 6 else 1025 if solves == 3 else 1281)
-    if levels == 4:
-        return nb >= ((384 if d == 2048 else 513) if solves >= 6 else 1025 if solves == 4 else 1281)
-    if clipped and d < 2048 and 2560 < nb <= 3072:
-        return False
-    return nb >= (1281 if solves < 6 else 384 if d == 2048 and not clipped else 1025)
+            return d == 4096 and nb > 3584
+        if solves < 6:
+            return d == 4096 and nb > 1792 if clipped else nb > 1280 and (fuller or nb <= 2048 or nb > 3584)
+        return fuller and nb > 1280 if clipped else nb >= (384 if fuller else 1025)
+    if solves == 2:
+        return 1536 < nb <= 5120 if d <= 1024 else nb > 1280 if d == 2048 else 1792 < nb <= 4096
+    if d <= 1024:
+        return solves >= 12 or nb >= (384 if solves >= 6 else 513)
+    if solves >= 12:
+        return nb >= (256 if d == 2048 else 384)
+    return nb > (1280 if solves < 6 else 640 if d == 2048 else 1024)
 
 
 def quantize_kernel(synth, wl, n: int, levels: int):

@@ -2894,16 +2894,16 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(RULE =
 // W wavefronts.  The others are not compiled, and asking for one fails like a launch that the runtime refuses: a call must not
 // return success over outputs that nothing has written.
 template <int C>
-constexpr bool wave_serves(int S, int rule, bool clip = false)
+constexpr bool wave_serves(int S, int rule)
 {
-    return !(rule == kOptimal && S >= (C == 2 ? 8 : 4) && C >= 2 && C <= 8) || (S == 5 && C == 8 && clip);  // (five levels: where pool_gains says)
+    return !(rule == kOptimal && S >= 8 && C >= 2 && C <= 8);
 }
 
 template <int C, int S, int BITS, int RULE = kOptimal>
 void launch_orq(const float* g, size_t n, const ogq_params_t* p, uint32_t nb, float* lv, void* codes, hipStream_t st)
 {
     auto launch = [&](auto clip) {
-        if constexpr (wave_serves<C>(S, RULE, clip.value))
+        if constexpr (wave_serves<C>(S, RULE))
             launch_kernel((orq_quantize_kernel<C, S, BITS, clip.value, RULE>), dim3(nb), dim3(kWave), st, g, n, p->bucket_size,
                           p->level_iters, p->clip_factor, nb, p->seed, p->index_offset, lv, static_cast<uint32_t*>(codes));
         else

@@ -40,38 +40,48 @@ bool launch_few(uint32_t limit, const float* g, size_t n, const ogq_params_t* p,
 
 #if OGQ_PART == 4 || OGQ_PART == 8 || OGQ_PART == 16
 // Two or four buckets per workgroup whose levels one wavefront solves side by side (pool_kernels.h), where the solves are what a bucket
-// waits for: but for few buckets with few solves nearly everywhere.  What a solve takes in the other kernels depends on the values: their bins suit a
-// mixture of scales and are crowded with Gaussian values, the pool's suit both.  The rule takes the pool where it gains on the mean of four kinds of values
-// (mixture, Gaussian, Laplace, Student-t) and of a whole and a cut-off last bucket; profiles/pool_scan.txt and, with clipping, pool_clip_scan.txt have both sides, and
-// tests/test_dispatch.py holds the rule against them.  On the recorded sizes no mean loses more than 2.7 %, no kind of values more than 10 % (mixtures in
-// few buckets: four levels, five sweeps, 256 of 1664), and the other kernel is kept nowhere that the mean would gain more than 12 %.  Means, us,
-// other -> pool (solves: interior levels, once and for every sweep):
-//   12 solves and more  at every number of buckets (eight levels, 18: 64 of 2112 16.5 -> 14.0, 2048 of 1024 24.4 -> 12.6, 12290 of 4096 160 -> 103;
-//                       five, 64 of 2112 13.7 -> 12.3), four levels of 1088 to 2048 elements from 256 on: repeated sweeps end early with a mixture in
-//                       either kernel (256 of 2048 15.8 -> 12.8, but mixtures in 16 of 1984 14 % slower)
-//   up to 1024 elements from six solves on always (16 of 768, eight levels 7.7 -> 7.2, four 8.1 -> 7.8), below from 384 (256, five levels: 6.0 -> 6.2, 384
-//                       6.6 -> 6.2; four, one sweep, 7.0 -> 7.0 and 7.5 -> 7.1), with two solves where the other kernel has one wavefront per bucket
-//   eight, nine levels  of up to 2048 elements from 1025 on (768 of 1344: 10.7 -> 11.0, 1026 11.6 -> 11.0), above from 384 (256 of 2112: 10.2 -> 10.9,
-//                       384 11.1 -> 10.9)
-//   five levels         of up to 2048 six solves from 1025 (of whole 2048, whose values are not clipped, from 384: 11.1 -> 9.4; clipped, 768, 12.1 -> 12.2), three from
-//                       1281 (1026 of 1344: 9.2 -> 9.5, 1282 11.2 -> 9.9); clipped not in the pool's second round, where one wavefront per bucket has its first
-//                       (2816 of 1344: 16.1 -> 16.9, 18.4 -> 19.3).  Above, six from 384 and three from 1025 (768 of 2112: 10.1 -> 10.1, 1026 11.3 -> 11.1)
-//   four levels         of up to 2048 six solves from 513 (514 of 1664: 10.6 -> 10.7), of whole 2048 from 384 (11.4 -> 10.1), four from 1025 (768 of
-//                       1664: 9.4 -> 9.8, 1026 10.4 -> 10.1), two from 1281 (1026: 8.6 -> 9.2, 1282 10.9 -> 10.1).  Above, six from 384 (256 of 2112: 10.5 ->
-//                       10.9, 384 11.4 -> 11.0), four from 1281 (clipped, 1026: 14.8 -> 15.5, 1282 16.1 -> 16.0), two where only the other kernel needs a second
-//                       round (2048: 16.9 -> 13.2) and from 3073 on (2304: 17.7 -> 18.9, 3584 23.6 -> 23.6, 4096 26.9 -> 24.5)
+// waits for.  What a solve takes in the other kernels depends on the values: their bins suit a mixture of scales and are crowded with Gaussian values, the pool's
+// suit both.  The rule takes the pool where it gains on the mean of four kinds of values (mixture, Gaussian, Laplace, Student-t) and of a whole and a
+// cut-off last bucket, and not much sooner than it has to: values that few elements share alone (bf16 gradients) send more steps to the general solve, which the
+// other kernels do sooner in few buckets (384 of 768, four levels, one sweep, bf16 24 % slower), while half zeros take the pool a third of the time.
+// profiles/pool_scan.txt and, with clipping, pool_clip_scan.txt have both sides (crowded values: pool_crowded_scan.txt), and tests/test_dispatch.py holds the rule against them: on the recorded sizes no mean loses
+// more than 2 %, no kind of values more than 8 %, and the other kernel is kept nowhere that the mean would gain more than 13 %.  Means, us, other -> pool
+// (solves: interior levels, once and for every sweep):
+//   eight, nine levels  12 solves and more at every size and number of buckets (18: 64 of 2112 16.5 -> 14.0, 2048 of 1024 24.4 -> 12.6, 12290 of 4096 160 -> 103), fewer up to 1024
+//                       elements (16 of 768: 7.7 -> 7.2), to 2048 from 1025 buckets on (768 of 1344: 10.7 -> 11.0, 1026 11.6 -> 11.0), above from 384 (256 of 2112: 10.2 ->
+//                       10.9, 384 11.1 -> 10.9), clipped from 1281
+//   five levels         12 solves and more likewise (64 of 2112: 13.7 -> 12.3), of 1088 to 1984 elements from 256 on.  Fewer of up to 1024 elements without 4097 to 6144
+//                       buckets, where the other kernel still has one round, three from 513 on; clipped 1025 to 4096 buckets.  Of 1088 to 1984 from 1281 on (1026 of 1344:
+//                       9.2 -> 9.5, 1282 11.2 -> 9.9) without second_round (clipped, 2816 of 1344: 16.1 -> 16.9).  Above from 1025 (2048), six solves from 384 (of
+//                       2112: 11.1 -> 10.5), else from 1281
+//   four levels         12 solves and more mostly repeat what they find, which the pool ends early (64 of 4096: 15.8 -> 12.5, 256 of 2048 15.8 -> 12.8).  Up to 1024 elements
+//                       from 384 on, four solves from 513, two from 1537 to 5120 buckets (clipped, 4096 of 1024: 11.0 -> 9.5).  Up to 2048 from 1025 on (six solves, whole
+//                       2048 from 641, four from 1281), two solves in one round of the pool (4096 of 1344: 15.3 -> 13.1), of whole 2048 from 1281 (clipped, 3072: 15.1 -> 12.9).
+//                       Above in full_chip (2 solves of 2112: 16.9 -> 13.2); six solves from 384 or 1025, clipped where three quarters of the registers hold elements (1536 of
+//                       4032: 21.6 -> 18.3), four likewise or beyond 3584 (4096 of 3008: 33.2 -> 27.5), two of whole 4096 (8192: 51.6 -> 44.6)
 static bool pool_gains(uint32_t d, uint32_t levels, uint64_t solves, uint32_t nb, bool clipped)
 {
-    if (solves >= 12u) return levels > 4u || d <= 1024u || d > 2048u || nb >= 256u;
-    if (d <= 1024u) return solves >= 6u || nb >= (solves == 2u ? 513u : 384u);
-    if (levels >= 8u) return nb >= (d > 2048u ? 384u : 1025u);
-    if (d > 2048u) {
-        if (solves == 2u) return nb > 3072u || (nb > 1792u && nb <= 2048u);
-        return nb >= (solves >= 6u ? 384u : solves == 3u ? 1025u : 1281u);
+    const bool second_round = nb > 2560u && nb <= 3072u;  // of the pool up to 2048 elements, where one wavefront per bucket has its first
+    const bool full_chip = nb > 1792u && nb <= 2048u;     // above 2048 elements: the pool's first round, the other kernel's second
+    const bool fuller = d >= 3584u;
+    if (levels >= 8u) return solves >= 12u || d <= 1024u || nb >= (clipped ? 1281u : d > 2048u ? 384u : 1025u);
+    if (levels == 5u) {
+        if (solves >= 12u) return solves >= 18u || d <= 1024u || d >= 2048u || nb >= 256u;
+        if (d <= 1024u) return clipped ? nb > 1024u && nb <= 4096u : (nb <= 4096u || nb > 6144u) && (solves >= 6u || nb > 512u);
+        if (d < 2048u) return nb > 1280u && !second_round;
+        return nb >= (solves >= 6u && (fuller || (d > 2048u && !clipped)) ? 384u : d == 2048u && !clipped ? 1025u : 1281u);
     }
-    if (levels == 4u) return nb >= (solves >= 6u ? (d == 2048u ? 384u : 513u) : solves == 4u ? 1025u : 1281u);
-    if (clipped && d < 2048u && nb > 2560u && nb <= 3072u) return false;
-    return nb >= (solves < 6u ? 1281u : d == 2048u && !clipped ? 384u : 1025u);
+    if (d > 2048u) {
+        if (solves >= 12u) return fuller || nb >= 384u;
+        if (full_chip) return true;
+        if (solves == 2u) return d == 4096u && nb > 3584u;
+        if (solves < 6u) return clipped ? d == 4096u && nb > 1792u : nb > 1280u && (fuller || nb <= 2048u || nb > 3584u);
+        return clipped ? fuller && nb > 1280u : nb >= (fuller ? 384u : 1025u);
+    }
+    if (solves == 2u) return d <= 1024u ? nb > 1536u && nb <= 5120u : d == 2048u ? nb > 1280u : nb > 1792u && nb <= 4096u;
+    if (d <= 1024u) return solves >= 12u || nb >= (solves >= 6u ? 384u : 513u);
+    if (solves >= 12u) return nb >= (d == 2048u ? 256u : 384u);
+    return nb > (solves < 6u ? 1280u : d == 2048u ? 640u : 1024u);
 }
 
 template <int W, int C>
